@@ -136,8 +136,8 @@ lcd_status lcd_build_lut(const uint16_t *codebook /*DEVICE*/, int N, int bits,
  *               columns.  The smoothing is fused into the kernel, except on the dequantising
  *               route with K >= 16384, where a small kernel ahead of the product leaves the
  *               smoothed activations in the workspace (same rounding, same result).
- * lcd_lut_gemm: prefill path, any M >= 1 (tuned for M >= 64): a smoothing kernel into the
- *               workspace, then register dequantisation into fp16 MFMA operands.
+ * lcd_lut_gemm: prefill path, any M >= 1: up to 64 tokens the kernels of lcd_lut_gemv; beyond, a
+ *               smoothing kernel into the workspace, then register dequantisation into fp16 MFMA operands.
  * Both give bit-identical results from run to run (fixed reduction order).
  */
 lcd_status lcd_lut_gemv(const void *packed, const void *lut, const uint16_t *x, const float *s,

@@ -459,9 +459,14 @@ __global__ void __launch_bounds__(kGemmWaves * 64, 1) gemm_group_kernel(const Ge
                     pb.out_scale);
 }
 
+// Up to kDecodeTokens tokens the tokens kernel takes the call: a 256 x 128 output tile would leave most compute
+// units without work (16 workgroups on a 4096-row layer) and half of every tile to tokens that are not there.
+static bool decode_takes(int M, int K) { return M <= kDecodeTokens && (long long)M * K * 2 < (1ll << 32); }
+
 int launch_gemm(const void *packed, const void *lut, const uint16_t *x, const float *s, uint16_t *y,
                 int M, int N, int K, int bits, float act_scale, void *workspace, const GemmPlan &plan, void *stream_)
 {
+    if (decode_takes(M, K)) return launch_gemv(packed, lut, x, s, y, M, N, K, bits, act_scale, workspace, stream_);
     hipStream_t stream = (hipStream_t)stream_;
     const int Mpad = plan.m_pad;
     if (int e = launch_smooth(x, s, workspace, M, Mpad, K, act_scale, stream)) return e;
@@ -487,6 +492,9 @@ int launch_gemm(const void *packed, const void *lut, const uint16_t *x, const fl
 
 int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream_)
 {
+    bool decode = true;
+    for (int i = 0; i < count; ++i) decode = decode && decode_takes(M, items[i].K);
+    if (decode) return launch_decode_group(items, count, M, bits, workspace, stream_);
     hipStream_t stream = (hipStream_t)stream_;
     const int Mpad = plan_gemm(M, items[0].N, items[0].K, bits).m_pad;
     // layers with the longest tiles (largest K) first in every XCD's queue

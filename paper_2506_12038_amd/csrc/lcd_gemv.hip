@@ -27,29 +27,11 @@
 #include <type_traits>
 #include <algorithm>
 #include <mutex>
-#include "lcd_internal.h"
-#include "lcd_device.h"
+#include <climits>
+#include "lcd_decode.h"
 #include "lcd_launch.h"
 
-
 namespace lcd {
-
-// Cache policy of the packed-index loads: non-temporal.  Every index byte is read exactly once per
-// launch, and without the hint the stream pushes the small reused data (activations, smoothing
-// factors, codebook tables) out of the caches: measured +4 % (7B set, 3 bits) to +8 % (70B MLP, 2
-// bits) on the single-token kernel, +3.5 % on the tokens kernel.  (Bit 1 of the buffer
-// instructions' cache-policy operand is "nt" on gfx950.)
-constexpr int kStreamPolicy = 2;
-
-
-
-// Buffer resources give branch-free predication: a lane whose offset is past the end of the
-// buffer reads zeros and touches no memory.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
-}
-constexpr uint32_t kOob = 0xFFFFFFF0u;
 
 // ---- single-token bucket kernel: persistent workgroups over a group of layers ---------------
 //
@@ -67,74 +49,31 @@ constexpr uint32_t kOob = 0xFFFFFFF0u;
 // Loads of packed indices run kSets-1 steps ahead of the arithmetic, across segment and visit
 // boundaries.  Matrix and vector instructions of one SIMD do not overlap in time (measured), so
 // the instruction count per byte is what matters, not the number of waves.
-constexpr int kBW = 8;            // waves per workgroup
 constexpr int kBCH = 2;           // chunks per wave per segment (their activations stay in registers)
 constexpr int kBSeg = kBW * kBCH; // chunks per segment (one pass of the workgroup over K)
 // chunk `ch` of wave `wave` in segment `sg`: chunks go round the waves, so that a short last segment
 // spreads over as many waves (and SIMDs) as it has chunks
-template <int CH = 2>
-__device__ __forceinline__ int wave_chunk(int sg, int wave, int ch) { return sg * (kBW * CH) + ch * kBW + wave; }
+__device__ __forceinline__ int wave_chunk(int sg, int wave, int ch) { return sg * kBSeg + ch * kBW + wave; }
 constexpr int kSets = 4;          // register sets in rotation (loads run kSets-1 steps ahead)
 constexpr int kVisitTiles = 32;   // row tiles per visit
 
-struct BucketProblem {
-    const uint8_t *packed;
-    const float *lutA;
-    const uint16_t *x;
-    const float *s;
-    uint16_t *y;
-    int nt, kc;
-    int tiles_base, tiles_extra;  // workgroup i of this layer owns tiles_base (+1 if i < tiles_extra) row tiles
-    float act_scale;              // 0: fp16 activations x/s; s_q > 0: INT8 codes of Sec. 4.1, output scaled by s_q
-    int x_ready;                  // tokens kernel: x already holds the smoothed activations / the codes (transform_kernel)
-    int wg_first;                 // first workgroup of this layer
-};
-// The table of first workgroups (wg_begin[1..16], 16 bits each) also travels as eight leading scalar
-// kernel arguments: those are preloaded into scalar registers when a wave starts, so a workgroup
-// knows its layer without a load and the problem record is the only load between the kernel's
-// entry and its first index loads.  Number of table entries <= b, for b < 2^15 - 1:
-struct WgTable { uint32_t t[kMaxGroup / 2]; };
-__device__ __forceinline__ int layer_of_workgroup(uint32_t b, uint32_t t0, uint32_t t1, uint32_t t2, uint32_t t3,
-                                                  uint32_t t4, uint32_t t5, uint32_t t6, uint32_t t7)
-{
-    // per 16-bit field f: bit 15 of (0x8000 + f) - (b + 1) is clear exactly when f <= b (no borrow crosses a field)
-    const uint32_t bb = (b + 1u) * 0x00010001u, top = 0x80008000u;
-    const uint32_t t[8] = {t0, t1, t2, t3, t4, t5, t6, t7};
-    int n = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) n += __builtin_popcount(~((t[i] | top) - bb) & top);
-    return n;
-}
-struct BucketBatch {
-    BucketProblem p[kMaxGroup];
-    int count;
-};
-
 // Walks the (visit, segment, tile) sequence of one workgroup.  Everything is wave-uniform.
-// Padded (the tokens kernel): each (visit, segment) run is padded to a multiple of kSets steps so
-// that the register-set rotation is static; padding steps load nothing and compute nothing.
-// Unpadded (the bucket kernel): the sequence has real steps only and the kernel keeps track of the
-// set a run starts with.
 struct Cursor {
     int v0, v1, range_end, sg, i, steps;
-    bool done, padded;
+    bool done;
 };
 
-__device__ __forceinline__ int run_steps(const Cursor &c) { return c.padded ? (c.v1 - c.v0 + kSets - 1) / kSets * kSets : c.v1 - c.v0; }
-
-template <bool PADDED>
 __device__ __forceinline__ void cursor_begin(Cursor &c, int ta, int tb)
 {
-    c.padded = PADDED;
     c.v0 = ta; c.range_end = tb; c.v1 = min(tb, ta + kVisitTiles);
-    c.sg = 0; c.i = 0; c.steps = run_steps(c); c.done = ta >= tb;
+    c.sg = 0; c.i = 0; c.steps = c.v1 - c.v0; c.done = ta >= tb;
 }
 
 __device__ __forceinline__ void cursor_next_visit(Cursor &c)
 {
     c.sg = 0; c.i = 0;
     if (c.v1 < c.range_end) {
-        c.v0 = c.v1; c.v1 = min(c.range_end, c.v0 + kVisitTiles); c.steps = run_steps(c);
+        c.v0 = c.v1; c.v1 = min(c.range_end, c.v0 + kVisitTiles); c.steps = c.v1 - c.v0;
     } else {
         c.done = true;
     }
@@ -253,7 +192,7 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_bucket_kernel(const uint32_t
     const __amdgpu_buffer_rsrc_t rs_lut = make_rsrc(pb.lutA, (uint32_t)pb.nt * 16 * NB * 4);
 
     Cursor pf{}, cur{};
-    cursor_begin<false>(pf, ta, tb);
+    cursor_begin(pf, ta, tb);
     cur = pf;
 
     // Activations.  A segment is kBSeg*256 = 8 * (threads of the workgroup) columns, and thread t of
@@ -623,259 +562,6 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_bucket_kernel(const uint32_t
 }
 
 
-// ---- batched decode kernel (2 <= M <= 16): persistent workgroups over a group of layers -------
-//
-// Same walk as the bucket kernel (layer -> run of row tiles -> visits -> K segments -> steps, loads
-// kSets-1 steps ahead), but the 16 columns of the matrix core's output tile are the tokens: the
-// packed indices are dequantised in registers (v_perm_b32 through per-row byte-split codebook
-// tables) into the A operand of v_mfma_f32_16x16x32_f16, and the smoothed activations of the
-// wave's CH chunks, all tokens, stay in registers as B operands for a whole segment.
-//   segment start  every wave smooths its own 512 columns of every token (Sec. 3.4: x / s) and
-//                  fans them out to the B-operand layout through its own LDS stage: no workgroup
-//                  synchronisation;
-//   step           one row tile: 16 MFMAs per wave; after every second step the 8 waves' 16x16
-//                  partial tiles of both meet in LDS (double-buffered, one s_barrier, no wait on
-//                  outstanding loads) and the 512 threads add them in a fixed order.  With one segment the sum is rounded
-//                  and stored; with several it accumulates in LDS until the last segment.
-constexpr int kStageStride = kTileCols + 8;   // halfs per token row of a wave's stage (+16 B: no bank conflicts)
-
-template <int BITS, int CH>
-struct TokStepRegs {
-    uint4v lo[CH];
-    uint2v hi[CH];     // 3 bits: the third-bit words
-    uint4v hi4[CH];    // 4 bits: the second plane
-    uint4v tb;         // the lane's row of byte-split codebook tables (4 bits: the low bytes)
-    uint4v tb2;        // 4 bits: the high bytes
-};
-
-template <int BITS, int CH>
-__device__ __forceinline__ void issue_tok_loads(TokStepRegs<BITS, CH> &r, const Cursor &c, __amdgpu_buffer_rsrc_t rs,
-                                                __amdgpu_buffer_rsrc_t rs_tb, int kc, int wave, int lane)
-{
-    constexpr uint32_t TB = kTileRows * kTileCols * BITS / 8;
-    const int tile = c.v0 + c.i;
-    const bool tv = !c.done && tile < c.v1;
-#pragma unroll
-    for (int ch = 0; ch < CH; ++ch) {
-        const int chunk = wave_chunk<CH>(c.sg, wave, ch);
-        const bool v = tv && chunk < kc;
-        const uint32_t o = ((uint32_t)tile * (uint32_t)kc + (uint32_t)chunk) * TB;
-        r.lo[ch] = __builtin_amdgcn_raw_buffer_load_b128(rs, v ? o + 16 * lane : kOob, 0, kStreamPolicy);
-        if (BITS == 3) r.hi[ch] = __builtin_amdgcn_raw_buffer_load_b64(rs, v ? o + 1024 + 8 * lane : kOob, 0, kStreamPolicy);
-        if (BITS == 4) r.hi4[ch] = __builtin_amdgcn_raw_buffer_load_b128(rs, v ? o + 1024 + 16 * lane : kOob, 0, kStreamPolicy);
-    }
-    const uint32_t row = (uint32_t)tile * kTileRows + (lane & 15);
-    if (BITS == 2) {
-        const uint2v t = __builtin_amdgcn_raw_buffer_load_b64(rs_tb, tv ? row * 8 : kOob, 0, 0);
-        r.tb = uint4v{t[0], t[1], 0u, 0u};
-    } else if (BITS == 3) {
-        r.tb = __builtin_amdgcn_raw_buffer_load_b128(rs_tb, tv ? row * 16 : kOob, 0, 0);
-    } else {
-        r.tb = __builtin_amdgcn_raw_buffer_load_b128(rs_tb, tv ? row * 32 : kOob, 0, 0);
-        r.tb2 = __builtin_amdgcn_raw_buffer_load_b128(rs_tb, tv ? row * 32 + 16 : kOob, 0, 0);
-    }
-}
-
-template <int BITS, int CH>
-__global__ void __launch_bounds__(kBW * 64, 1) gemv_tokens_kernel(const uint32_t t0, const uint32_t t1, const uint32_t t2, const uint32_t t3,
-                                                                   const uint32_t t4, const uint32_t t5, const uint32_t t6, const uint32_t t7,
-                                                                   const BucketBatch batch, const int M)
-{
-    constexpr int NC = BITS == 2 ? 4 : 8;
-    constexpr uint32_t TB = kTileRows * kTileCols * BITS / 8;
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    // LDS: [ stage: kBW x 16 tokens x kStageStride halfs ][ red: 2 x 2 x kBW x 256 floats ][ sums: kVisitTiles x 256 floats ]
-    _Float16 *stage = reinterpret_cast<_Float16 *>(smem) ;
-    float *red = reinterpret_cast<float *>(smem + (size_t)kBW * 16 * kStageStride * 2);
-    float *sums = red + 2 * 2 * kBW * 256;
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int q = lane >> 4, j = lane & 15, bq = lane >> 4;
-
-    const int pi = layer_of_workgroup(blockIdx.x, t0, t1, t2, t3, t4, t5, t6, t7);
-    const BucketProblem pb = batch.p[pi];
-    const int li = (int)blockIdx.x - pb.wg_first;
-    const int ta = li * pb.tiles_base + min(li, pb.tiles_extra);
-    const int tb_end = ta + pb.tiles_base + (li < pb.tiles_extra ? 1 : 0);
-    const int kc = pb.kc, nseg = (kc + kBW * CH - 1) / (kBW * CH), K = kc * kTileCols, N = pb.nt * kTileRows;
-    const bool x_ready = pb.x_ready != 0;                       // wave-uniform
-    const float out_scale = pb.act_scale != 0.0f ? pb.act_scale : 1.0f;
-    const __amdgpu_buffer_rsrc_t rs_packed = make_rsrc(pb.packed, (uint32_t)pb.nt * (uint32_t)kc * TB);
-    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(pb.x, (uint32_t)M * (uint32_t)K * 2);
-    const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(pb.s, (uint32_t)K * 4);
-    // byte-split tables: behind the bucket multipliers (2 and 3 bits), the whole table (4 bits)
-    const __amdgpu_buffer_rsrc_t rs_tb = make_rsrc(reinterpret_cast<const uint8_t *>(pb.lutA) + (BITS == 4 ? 0 : (size_t)N * NC * 4),
-                                                   (uint32_t)N * (BITS == 2 ? 8 : BITS == 3 ? 16 : 32));
-
-    Cursor pf{}, cur{};
-    cursor_begin<true>(pf, ta, tb_end);
-    cur = pf;
-
-    TokStepRegs<BITS, CH> r0, r1, r2, r3;
-    uint4v Bx[CH][8];                      // B operands: lane (q, token j) holds 8 activations per MFMA
-    bool chunk_in_k[CH] = {};                // wave-uniform: a short last segment leaves some chunks empty
-    _Float16 *my_stage = stage + wave * (16 * kStageStride);
-
-    // Smooth the wave's CH chunks of segment sg for all tokens and load them as B operands.
-    // Lane l covers the 8 columns [8*(l&31), +8) of a chunk for the tokens 8*(l>>5) .. +7.
-    uint4v xr[CH][8];
-    float4v sa[CH], sb[CH];
-    auto issue_activation_loads = [&](int sg) {
-        const int kg = lane & 31, th = lane >> 5;
-#pragma unroll
-        for (int ch = 0; ch < CH; ++ch) {
-            const int chunk = wave_chunk<CH>(sg, wave, ch);
-            const uint32_t k0 = (uint32_t)chunk * kTileCols + 8 * kg;
-            const bool cv = chunk < kc;
-            sa[ch] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs_s, cv ? k0 * 4 : kOob, 0, 0));
-            sb[ch] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs_s, cv ? k0 * 4 + 16 : kOob, 0, 0));
-#pragma unroll
-            for (int mm = 0; mm < 8; ++mm) {
-                const int m = th * 8 + mm;
-                xr[ch][mm] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, (cv && m < M) ? ((uint32_t)m * (uint32_t)K + k0) * 2 : kOob, 0, 0);
-            }
-        }
-    };
-    auto finish_activations = [&](int sg) {
-        const int kg = lane & 31, th = lane >> 5;
-#pragma unroll
-        for (int ch = 0; ch < CH; ++ch) {
-            const bool cv = wave_chunk<CH>(sg, wave, ch) < kc;
-            chunk_in_k[ch] = cv;
-            // operand slot order 0,4,1,5,2,6,3,7 (the dequantiser pairs weight v with weight 4+v)
-            if (!x_ready) {
-                float rs[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) rs[e] = cv ? __builtin_amdgcn_rcpf(e < 4 ? sa[ch][e] : sb[ch][e - 4]) : 0.0f;
-#pragma unroll
-                for (int mm = 0; mm < 8; ++mm) {
-                    const uint4v v = xr[ch][mm];   // register i: columns 2i, 2i+1; result register j: columns j, 4+j
-                    uint4v o;
-                    o[0] = smooth_pair<0, 0>(v[0], rs[0], v[2], rs[4]);
-                    o[1] = smooth_pair<1, 1>(v[0], rs[1], v[2], rs[5]);
-                    o[2] = smooth_pair<0, 0>(v[1], rs[2], v[3], rs[6]);
-                    o[3] = smooth_pair<1, 1>(v[1], rs[3], v[3], rs[7]);
-                    *reinterpret_cast<uint4v *>(&my_stage[(th * 8 + mm) * kStageStride + 8 * kg]) = o;
-                }
-            } else {   // wave-uniform branch: x already holds the operands, only the slot order is left
-#pragma unroll
-                for (int mm = 0; mm < 8; ++mm) {
-                    const uint4v v = xr[ch][mm];   // OOB loads returned zero
-                    uint4v o;
-                    o[0] = __builtin_amdgcn_perm(v[2], v[0], 0x05040100u); o[1] = __builtin_amdgcn_perm(v[2], v[0], 0x07060302u);
-                    o[2] = __builtin_amdgcn_perm(v[3], v[1], 0x05040100u); o[3] = __builtin_amdgcn_perm(v[3], v[1], 0x07060302u);
-                    *reinterpret_cast<uint4v *>(&my_stage[(th * 8 + mm) * kStageStride + 8 * kg]) = o;
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < 8; ++g)   // written by this wave only: LDS operations of a wave stay in order
-                Bx[ch][g] = *reinterpret_cast<const uint4v *>(&my_stage[j * kStageStride + 64 * q + 8 * g]);
-        }
-    };
-
-    auto tile_product = [&](const TokStepRegs<BITS, CH> &r) -> float4v {
-        float4v acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-        RowTables t;
-        if (BITS == 2) { t.lo[0] = r.tb[0]; t.hi[0] = r.tb[1]; t.lo[1] = 0; t.hi[1] = 0; }
-        else if (BITS == 4) { t.lo[0] = t.lo[1] = t.hi[0] = t.hi[1] = 0; }
-        else { t.lo[0] = r.tb[0]; t.lo[1] = r.tb[1]; t.hi[0] = r.tb[2]; t.hi[1] = r.tb[3]; }
-#pragma unroll
-        for (int ch = 0; ch < CH; ++ch) {
-            if (!chunk_in_k[ch]) continue;
-            uint4v op0, op1;
-            if (BITS == 4) {
-                const RowTables4 t4{{r.tb[0], r.tb[1], r.tb[2], r.tb[3]}, {r.tb2[0], r.tb2[1], r.tb2[2], r.tb2[3]}};
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    decode_word4(r.lo[ch][d], r.hi4[ch][d], t4, op0, op1);
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op0), as_half8(Bx[ch][2 * d]), acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op1), as_half8(Bx[ch][2 * d + 1]), acc1, 0, 0, 0);
-                }
-                continue;
-            }
-            HighBits hb{0u, 0u};
-            if (BITS == 3) hb = regroup_high(r.hi[ch]);
-            decode_word<BITS, 0>(r.lo[ch][0], hb, t, op0, op1);
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op0), as_half8(Bx[ch][0]), acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op1), as_half8(Bx[ch][1]), acc1, 0, 0, 0);
-            decode_word<BITS, 1>(r.lo[ch][1], hb, t, op0, op1);
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op0), as_half8(Bx[ch][2]), acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op1), as_half8(Bx[ch][3]), acc1, 0, 0, 0);
-            decode_word<BITS, 2>(r.lo[ch][2], hb, t, op0, op1);
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op0), as_half8(Bx[ch][4]), acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op1), as_half8(Bx[ch][5]), acc1, 0, 0, 0);
-            decode_word<BITS, 3>(r.lo[ch][3], hb, t, op0, op1);
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op0), as_half8(Bx[ch][6]), acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op1), as_half8(Bx[ch][7]), acc1, 0, 0, 0);
-        }
-        return acc0 + acc1;   // lane (bq, j): rows 4bq..4bq+3 of token j
-    };
-
-    // two steps: this wave's two partial tiles -> LDS; one barrier; every thread adds one output of
-    // one of the two tiles over the waves, in a fixed order
-    int phase = 0;
-    auto finish_pair = [&](float4v p0, float4v p1, int tl, bool second) {
-        float *buf = red + phase * (2 * kBW * 256);
-        *reinterpret_cast<float4v *>(&buf[wave * 256 + j * 16 + 4 * bq]) = p0;
-        *reinterpret_cast<float4v *>(&buf[(kBW + wave) * 256 + j * 16 + 4 * bq]) = p1;
-        // LDS writes done, then the barrier; outstanding global loads keep flying
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        const int which = threadIdx.x >> 8, o = threadIdx.x & 255;   // waves 0-3: first tile, waves 4-7: second
-        if (which == 0 || second) {
-            const int m = o >> 4, row = o & 15;
-            float sum = 0.f;
-#pragma unroll
-            for (int w = 0; w < kBW; ++w) sum += buf[(which * kBW + w) * 256 + o];
-            if (nseg > 1) {
-                float *slot = &sums[(tl + which) * 256 + o];
-                if (cur.sg > 0) sum += *slot;
-                if (cur.sg + 1 < nseg) *slot = sum;
-            }
-            if (cur.sg + 1 == nseg && m < M)
-                pb.y[(size_t)m * N + (size_t)(cur.v0 + tl + which) * kTileRows + row] = __builtin_bit_cast(uint16_t, (_Float16)(sum * out_scale));
-        }
-        phase ^= 1;
-    };
-
-    auto four_steps = [&]() {
-        const int left = (cur.v1 - cur.v0) - cur.i;   // tiles left in this run; padding steps skip their work
-        const float4v zero = {0.f, 0.f, 0.f, 0.f};
-        float4v p0, p1 = zero;
-        issue_tok_loads<BITS, CH>(r3, pf, rs_packed, rs_tb, kc, wave, lane); cursor_advance(pf, nseg);
-        p0 = tile_product(r0);
-        issue_tok_loads<BITS, CH>(r0, pf, rs_packed, rs_tb, kc, wave, lane); cursor_advance(pf, nseg);
-        if (left > 1) p1 = tile_product(r1);
-        finish_pair(p0, p1, cur.i, left > 1);
-        issue_tok_loads<BITS, CH>(r1, pf, rs_packed, rs_tb, kc, wave, lane); cursor_advance(pf, nseg);
-        p1 = zero;
-        if (left > 2) p0 = tile_product(r2);
-        issue_tok_loads<BITS, CH>(r2, pf, rs_packed, rs_tb, kc, wave, lane); cursor_advance(pf, nseg);
-        if (left > 3) p1 = tile_product(r3);
-        if (left > 2) finish_pair(p0, p1, cur.i + 2, left > 3);
-        cur.i += 4;
-    };
-
-    issue_activation_loads(0);   // they start the longest dependency chain: ahead of the tile loads
-    issue_tok_loads<BITS, CH>(r0, pf, rs_packed, rs_tb, kc, wave, lane); cursor_advance(pf, nseg);
-    issue_tok_loads<BITS, CH>(r1, pf, rs_packed, rs_tb, kc, wave, lane); cursor_advance(pf, nseg);
-    issue_tok_loads<BITS, CH>(r2, pf, rs_packed, rs_tb, kc, wave, lane); cursor_advance(pf, nseg);
-    if (cur.done) return;   // no row tiles (the host never launches such a workgroup); the loads above moved nothing
-    finish_activations(0);
-    bool primed = true;   // the first segment's activations are in place
-    while (!cur.done) {
-        for (cur.sg = 0; cur.sg < nseg; ++cur.sg) {
-            if (!primed) {
-                issue_activation_loads(cur.sg);
-                finish_activations(cur.sg);
-            }
-            primed = false;
-            for (cur.i = 0; cur.i < cur.steps;) four_steps();
-        }
-        cursor_next_visit(cur);
-    }
-}
-
 // ---- activation transformation ahead of the tokens kernel (Sec. 4.1) -----------------------------
 // On the tokens kernel's route (2..16 tokens, and 4 bits) every workgroup of a layer stages the whole activation matrix, so whatever is
 // done to an activation is repeated by each of them.  This small kernel does it once per layer
@@ -1003,24 +689,26 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     if (grid < count) grid = count;
     // 2 bits on the sparse matrix core with quantised activations: the codes go in as int8 numbers
     const bool int8_codes = !tokens_path && bits != 4 && all_quantised;   // (3 bits: one token, the plain pass only)
-    const bool light_steps = !tokens_path && bits == 2 && M == 1;   // one sparse pass per tile: a step is short next to the fixed costs
-    // the several-token kernel, measured per workgroup (unit: the time of two chunks of one row tile, about 1 us):
-    // smoothing inside the kernel, a segment switch re-stages 16 tokens x 512 columns per wave (2.3); with the
-    // activations transformed ahead it only permutes them (1.5)
+    const bool light_steps = bits == 2 && M == 1;   // one sparse pass per tile: a step is short next to the fixed costs
     const bool staged_ahead = tokens_path && codes[0] != nullptr;
-    const double startup_steps = tokens_path ? (staged_ahead ? 0.5 : 0.7) : light_steps ? 3.5 : 2.0;
-    const double segment_steps = tokens_path ? (staged_ahead ? 1.5 : 2.3) : light_steps ? 1.8 : 0.4;
-    const double step_overhead = tokens_path ? (staged_ahead ? 0.22 : 0.3) : 0.1;   // per tile and segment: barrier / bookkeeping
-    auto layer_time_with = [&](int ch, int i, int n) {
-        const int seg = kBW * ch;
-        const int kc = batch.p[i].kc, segs = (kc + seg - 1) / seg, rest = kc % seg;
-        const double steps_per_tile = (kc / seg) * (0.5 * ch + step_overhead) +
-                                      (rest ? 0.5 * ((rest + kBW - 1) / kBW) + step_overhead : 0.0);
-        const int t = (batch.p[i].nt + n - 1) / n, visits = (t + kVisitTiles - 1) / kVisitTiles;
+    // the tokens kernel, times in us of a workgroup: a "round" is one chunk for each of its 8 waves
+    const int blocks = (M + kTokenBlock - 1) / kTokenBlock;
+    const int held = tokens_path ? tokens_variant(bits, blocks, INT_MAX).tiles : 1;
+    const double round_tile = (bits == 2 ? 0.40 : bits == 3 ? 0.52 : 0.85) + 0.06 * blocks;
+    const double round_stage = 0.15 + 0.3 * blocks, pass = 1.5;
+    auto layer_time = [&](int i, int n) {
+        const int kc = batch.p[i].kc, t = (batch.p[i].nt + n - 1) / n;
+        if (tokens_path) {
+            const int rounds = (kc + kBW - 1) / kBW, passes = (t + held - 1) / held;
+            return passes * (pass + rounds * round_stage) + rounds * t * round_tile;
+        }
+        const double startup_steps = light_steps ? 3.5 : 2.0, segment_steps = light_steps ? 1.8 : 0.4, step_overhead = 0.1;
+        const int segs = (kc + kBSeg - 1) / kBSeg, rest = kc % kBSeg;
+        const double steps_per_tile = (kc / kBSeg) * (0.5 * kBCH + step_overhead) + (rest ? 0.5 * ((rest + kBW - 1) / kBW) + step_overhead : 0.0);
+        const int visits = (t + kVisitTiles - 1) / kVisitTiles;
         return startup_steps + steps_per_tile * t + segs * visits * segment_steps;
     };
-    auto split = [&](int ch, int *nwg) {
-        auto layer_time = [&](int i, int n) { return layer_time_with(ch, i, n); };
+    auto split = [&](int *nwg) {
         // smallest number of workgroups with which layer i takes at most T (0: not even one per tile does)
         auto need = [&](int i, double T) {
             const int nt = batch.p[i].nt;
@@ -1081,7 +769,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     if (known) {
         for (int i = 0; i < count; ++i) nwg[i] = memo.nwg[i];
     } else {
-        split(kBCH, nwg);
+        split(nwg);
         memo.count = count; memo.M = M; memo.bits = bits; memo.grid = grid; memo.ahead = (int)staged_ahead; memo.route = route;
         for (int i = 0; i < count; ++i) { memo.nt[i] = batch.p[i].nt; memo.kc[i] = batch.p[i].kc; memo.nwg[i] = nwg[i]; }
     }
@@ -1090,7 +778,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     {
         int order[kMaxGroup];
         double t[kMaxGroup];
-        for (int i = 0; i < count; ++i) { order[i] = i; t[i] = layer_time_with(kBCH, i, nwg[i]); }
+        for (int i = 0; i < count; ++i) { order[i] = i; t[i] = layer_time(i, nwg[i]); }
         std::stable_sort(order, order + count, [&](int a, int b) { return t[a] > t[b]; });
         BucketProblem sorted_p[kMaxGroup];
         int sorted_n[kMaxGroup];
@@ -1114,23 +802,27 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     WgTable table;
     for (int i = 0; i < kMaxGroup / 2; ++i) table.t[i] = (uint32_t)wg_begin[2 * i + 1] | (uint32_t)wg_begin[2 * i + 2] << 16;
     for (int i = 0; i < count; ++i) batch.p[i].wg_first = wg_begin[i];
-    const int NC = bits == 2 ? 4 : 8;
     size_t lds;
     const void *fn;
+    int variant;
     if (!tokens_path) {
         lds = (size_t)MT * ((size_t)kBSeg * kTileCols * 2 + (size_t)kBW * kVisitTiles * 16 * 4) + (bits == 3 && int8_codes ? (size_t)kBSeg * kTileCols : 0);
         fn = bits == 3 ? (int8_codes ? (const void *)gemv_bucket_kernel<3, 1, true> : (const void *)gemv_bucket_kernel<3>)
              : int8_codes ? (MT == 4 ? (M == 3 ? (const void *)gemv_bucket_kernel<2, 4, true, 3> : (const void *)gemv_bucket_kernel<2, 4, true>)
                              : MT == 2 ? (const void *)gemv_bucket_kernel<2, 2, true> : (const void *)gemv_bucket_kernel<2, 1, true>)
              : MT == 2 ? (const void *)gemv_bucket_kernel<2, 2> : (const void *)gemv_bucket_kernel<2>;
+        // (variant 2 at 3 bits is the kernel with the int8 plain pass)
+        variant = 2 * (int8_codes ? (MT == 4 ? (M == 3 ? 5 : 4) : MT == 2 ? 3 : 2) : MT == 2 ? 1 : 0) + (bits - 2);
     } else {
-        lds = (size_t)kBW * 16 * kStageStride * 2 + (size_t)2 * 2 * kBW * 256 * 4 + (size_t)kVisitTiles * 256 * 4;
-        fn = bits == 2 ? (const void *)gemv_tokens_kernel<2, kBCH> : bits == 3 ? (const void *)gemv_tokens_kernel<3, kBCH>
-                                                                              : (const void *)gemv_tokens_kernel<4, kBCH>;
+        int most = 1;
+        for (int i = 0; i < count; ++i) most = std::max(most, (batch.p[i].nt + nwg[i] - 1) / nwg[i]);
+        const TokensVariant tv = tokens_variant(bits, blocks, most);
+        lds = tv.lds_bytes;
+        fn = tv.fn;
+        variant = 12 + tv.id;
     }
-    static PerDeviceFlags<21> lds_raised;   // (variant 3 at 3 bits is the kernel with the int8 plain pass)
-    const int variant = tokens_path ? 1 : int8_codes ? (MT == 4 ? (M == 3 ? 6 : 5) : MT == 2 ? 4 : 3) : MT == 2 ? 2 : 0;
-    if (hipError_t e = raise_lds_limit_once(lds_raised, variant * 3 + (bits - 2), fn, lds)) return (int)e;
+    static PerDeviceFlags<12 + kTokensVariants> lds_raised;
+    if (hipError_t e = raise_lds_limit_once(lds_raised, variant, fn, lds)) return (int)e;
     void *args[] = {&table.t[0], &table.t[1], &table.t[2], &table.t[3], &table.t[4], &table.t[5], &table.t[6], &table.t[7],
                     &batch, const_cast<int *>(&M)};   // the bucket kernel takes no M
     if (hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(kBW * 64), args, lds, stream)) return (int)e;

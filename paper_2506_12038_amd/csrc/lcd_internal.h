@@ -29,7 +29,8 @@ struct GroupItem {
     const void *packed; const void *lut; const uint16_t *x; const float *s; uint16_t *y; int N, K;
     float act_scale;   // 0: fp16 activations; s_q > 0: INT8 activation codes (paper Sec. 4.1)
 };
-// one launch for `count` decode problems (1 <= M <= 16 tokens each)
+constexpr int kDecodeTokens = 64;   // most tokens the decode kernels take (the decode entry points stop at 16)
+// one launch for `count` decode problems (1 <= M <= kDecodeTokens tokens each)
 // (workspace: decode_codes_bytes(M, K) per item, in item order, when M > 1 and act_scale != 0)
 // force_prepass: the activations are transformed ahead of the product (into the workspace) whenever the
 // several-token kernel runs, not only where that is the faster route

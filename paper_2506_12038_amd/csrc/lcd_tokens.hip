@@ -1,0 +1,279 @@
+// Decode and short-prompt path (2 <= M <= 64 tokens; every M with 4 bits) of the smoothed
+// table-lookup product, gfx950: the tokens kernel.
+//
+// A batched product with few tokens: the packed indices are dequantised in registers (v_perm_b32
+// through per-row byte-split codebook tables) into the A operand of v_mfma_f32_16x16x32_f16, blocks of
+// 16 tokens are its columns, one dequantised operand serves every block.
+//
+// Work split.  A workgroup owns a contiguous run of row tiles (16 rows) of ONE layer and takes them
+// R at a time; its 8 waves split K, wave w takes the 256-column chunks w, w + 8, ...  Per chunk a
+// wave stages the activations of its 256 columns once (smoothing, Sec. 3.4, and the turn into operand
+// order through its own piece of LDS), then multiplies the chunk of every one of the R row tiles;
+// the accumulators stay in registers over all of K.  No wave waits for another before the end: one
+// barrier, then the 8 partial tiles are added in the order of the waves, rounded once and stored.
+// The order of the additions of one output depends on K alone -- not on the grouping of layers,
+// on R or on the number of tokens -- so grouped, single and captured calls agree bit for bit.
+//
+// What bounds it: with many row tiles per workgroup the vector pipe (the dequantiser: 92 of about 105
+// vector instructions per 16 x 256 tile-chunk at 2 bits), about 1.0 us per row tile of K = 4096; with one
+// row tile per workgroup the staging of the activations (about 2000 shader cycles per round of 8 chunks
+// and 16 tokens: LDS writes, reads and the smoothing of 8 waves in step) and the latencies in front.
+// Measured against the kernel before it (K in segments, partial tiles of two row tiles exchanged through
+// LDS at a barrier after every second tile, no more than 16 tokens): 4096 x 11008, 3 bits, 3 tokens
+// 16.5 -> 9.8 us a call; blocks of 2, 3 and 4-bit layers (5120 / 13824), 6 tokens, 104 -> 72 us a block; 7B
+// block, 2 bits, 16 tokens 46 -> 42.5 us.  7B block, 3 bits, 40 tokens, which the 256 x 128-tile prefill kernel
+// had on 16 to 86 of the 256 compute units: 262 -> 93 us.
+#include <hip/hip_runtime.h>
+#include "lcd_decode.h"
+
+namespace lcd {
+
+constexpr int kStageStride = kTileCols + 8;   // halfs per token row of a wave's stage (+16 B: no bank conflicts)
+constexpr int kStageBytes = kTokenBlock * kStageStride * 2;
+
+template <int TB, int R>
+constexpr int tokens_wave_bytes() { return R * TB * 1024 > kStageBytes ? R * TB * 1024 : kStageBytes; }
+
+template <int BITS>
+struct TokTile {
+    uint4v lo;
+    uint2v hi;     // 3 bits: the third-bit words
+    uint4v hi4;    // 4 bits: the second plane
+};
+
+template <int BITS> struct TokTables { typedef RowTables type; };
+template <> struct TokTables<4> { typedef RowTables4 type; };
+
+template <int BITS, int TB, int R>
+__global__ void __launch_bounds__(kBW * 64, 1) gemv_tokens_kernel(const uint32_t t0, const uint32_t t1, const uint32_t t2, const uint32_t t3,
+                                                                   const uint32_t t4, const uint32_t t5, const uint32_t t6, const uint32_t t7,
+                                                                   const BucketBatch batch, const int M)
+{
+    constexpr uint32_t TBYTES = kTileRows * kTileCols * BITS / 8;
+    constexpr int NC = BITS == 2 ? 4 : 8;
+    constexpr int D = R <= 2 && TB < 4 ? 2 : 1;   // chunks whose packed words are loaded ahead
+    constexpr int kWaveBytes = tokens_wave_bytes<TB, R>();
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // one piece per wave: its stage, in the end its partial tiles
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: keeps addresses scalar
+    const int q = lane >> 4, j = lane & 15;
+    const int kg = lane & 31, th = lane >> 5;   // staging: 8 columns [8 kg, +8) of the chunk, tokens th, th + 2, ...
+
+    const int pi = layer_of_workgroup(blockIdx.x, t0, t1, t2, t3, t4, t5, t6, t7);
+    const BucketProblem pb = batch.p[pi];
+    const int li = (int)blockIdx.x - pb.wg_first;
+    const int ta = li * pb.tiles_base + min(li, pb.tiles_extra);
+    const int tb_end = ta + pb.tiles_base + (li < pb.tiles_extra ? 1 : 0);
+    const int kc = pb.kc, K = kc * kTileCols, N = pb.nt * kTileRows;
+    const bool x_ready = pb.x_ready != 0;                       // wave-uniform
+    const float out_scale = pb.act_scale != 0.0f ? pb.act_scale : 1.0f;
+    const __amdgpu_buffer_rsrc_t rs_packed = make_rsrc(pb.packed, (uint32_t)pb.nt * (uint32_t)kc * TBYTES);
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(pb.x, (uint32_t)M * (uint32_t)K * 2);
+    const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(pb.s, (uint32_t)K * 4);
+    // byte-split tables: behind the bucket multipliers (2 and 3 bits), the whole table (4 bits)
+    const __amdgpu_buffer_rsrc_t rs_tb = make_rsrc(reinterpret_cast<const uint8_t *>(pb.lutA) + (BITS == 4 ? 0 : (size_t)N * NC * 4),
+                                                   (uint32_t)N * (BITS == 2 ? 8 : BITS == 3 ? 16 : 32));
+    _Float16 *stage = reinterpret_cast<_Float16 *>(smem + wave * kWaveBytes);
+
+    // activations of one chunk as loaded: TB x 8 registers of 8 fp16 numbers (columns 8 kg .., tokens th + 2 mm).
+    // The (token pair, chunk) part of the address is wave-uniform and travels as the scalar offset; lanes
+    // of a token past the last one read zeros through an offset that is out of range.
+    uint4v xr[TB][8];
+    const uint32_t row_bytes = (uint32_t)K * 2;
+    const uint32_t x_lane = 16 * kg + th * row_bytes, x_last = th ? kOob : 16u * kg;
+    auto load_x = [&](int chunk) {
+        uint32_t o = __builtin_amdgcn_readfirstlane((uint32_t)chunk * (kTileCols * 2));
+        const int left = __builtin_amdgcn_readfirstlane(chunk < kc ? M : 0);   // tokens of this chunk
+        asm volatile("" : "+s"(o));   // one addition per pair instead of 8 TB addresses kept in registers
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int mm = 0; mm < 8; ++mm) {
+                const int base = t * kTokenBlock + 2 * mm;
+                const uint32_t v = left > base + 1 ? x_lane : left > base ? x_last : kOob;
+                xr[t][mm] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, v, left > base ? o : 0u, 0);
+                o += 2 * row_bytes;
+            }
+    };
+    float4v sa, sb;
+    auto load_s = [&](int chunk) {
+        const bool cv = chunk < kc;
+        const uint32_t k0 = (uint32_t)chunk * kTileCols + 8 * kg;
+        sa = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs_s, cv ? k0 * 4 : kOob, 0, 0));
+        sb = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs_s, cv ? k0 * 4 + 16 : kOob, 0, 0));
+    };
+    // packed words of the R row tiles from v0 (tiles past v1 and chunks past the layer's read zeros, no traffic)
+    auto load_tile = [&](TokTile<BITS> &p, int tile, int v1, int chunk) {
+        const bool v = tile < v1 && chunk < kc;
+        // the (tile, chunk) part of the address is wave-uniform and travels as the scalar offset
+        const uint32_t o = v ? ((uint32_t)tile * (uint32_t)kc + (uint32_t)chunk) * TBYTES : 0u;
+        p.lo = __builtin_amdgcn_raw_buffer_load_b128(rs_packed, v ? 16 * lane : kOob, o, kStreamPolicy);
+        if (BITS == 3) p.hi = __builtin_amdgcn_raw_buffer_load_b64(rs_packed, v ? 8 * lane : kOob, o + 1024, kStreamPolicy);
+        if (BITS == 4) p.hi4 = __builtin_amdgcn_raw_buffer_load_b128(rs_packed, v ? 16 * lane : kOob, o + 1024, kStreamPolicy);
+    };
+
+    uint4v B[TB][8];       // B operands of the current chunk: lane (q, token j) holds columns 64 q + 8 g .. of its token
+    auto stage_x = [&]() {
+        float rs[8];
+        if (!x_ready) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) rs[e] = __builtin_amdgcn_rcpf(e < 4 ? sa[e] : sb[e - 4]);
+        }
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            // operand slot order 0,4,1,5,2,6,3,7 (the dequantiser pairs weight v with weight 4 + v); rows past the last
+            // token keep what the stage held: their columns of the product are never stored
+#pragma unroll
+            for (int mm = 0; mm < 8; ++mm) {
+                if (t * kTokenBlock + 2 * mm >= M) break;      // uniform
+                const uint4v v = xr[t][mm];   // register i: columns 2i, 2i+1; result register i: columns i, 4+i
+                uint4v o;
+                if (!x_ready) {
+                    o[0] = smooth_pair<0, 0>(v[0], rs[0], v[2], rs[4]);
+                    o[1] = smooth_pair<1, 1>(v[0], rs[1], v[2], rs[5]);
+                    o[2] = smooth_pair<0, 0>(v[1], rs[2], v[3], rs[6]);
+                    o[3] = smooth_pair<1, 1>(v[1], rs[3], v[3], rs[7]);
+                } else {   // x already holds the operands, only the slot order is left
+                    o[0] = __builtin_amdgcn_perm(v[2], v[0], 0x05040100u); o[1] = __builtin_amdgcn_perm(v[2], v[0], 0x07060302u);
+                    o[2] = __builtin_amdgcn_perm(v[3], v[1], 0x05040100u); o[3] = __builtin_amdgcn_perm(v[3], v[1], 0x07060302u);
+                }
+                *reinterpret_cast<uint4v *>(&stage[(2 * mm + th) * kStageStride + 8 * kg]) = o;
+            }
+            // written by this wave only: LDS operations of a wave stay in order
+#pragma unroll
+            for (int g = 0; g < 8; ++g)
+                B[t][g] = *reinterpret_cast<const uint4v *>(&stage[j * kStageStride + 64 * q + 8 * g]);
+        }
+    };
+
+    float4v acc[R][TB];
+    typename TokTables<BITS>::type tab[R];
+    TokTile<BITS> P[D][R];
+    auto tile_product = [&](const TokTile<BITS> &p, const typename TokTables<BITS>::type &t, float4v (&a)[TB]) {
+        uint4v op0, op1;
+        auto multiply = [&](int d) {
+#pragma unroll
+            for (int b = 0; b < TB; ++b) {
+                a[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op0), as_half8(B[b][2 * d]), a[b], 0, 0, 0);
+                a[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op1), as_half8(B[b][2 * d + 1]), a[b], 0, 0, 0);
+            }
+        };
+        if constexpr (BITS == 4) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) { decode_word4(p.lo[d], p.hi4[d], t, op0, op1); multiply(d); }
+        } else {
+            HighBits hb{0u, 0u};
+            if (BITS == 3) hb = regroup_high(p.hi);
+            decode_word<BITS, 0>(p.lo[0], hb, t, op0, op1); multiply(0);
+            decode_word<BITS, 1>(p.lo[1], hb, t, op0, op1); multiply(1);
+            decode_word<BITS, 2>(p.lo[2], hb, t, op0, op1); multiply(2);
+            decode_word<BITS, 3>(p.lo[3], hb, t, op0, op1); multiply(3);
+        }
+    };
+
+    for (int v0 = ta; v0 < tb_end; v0 += R) {
+        const int v1 = min(tb_end, v0 + R);
+        load_s(wave);
+        load_x(wave);     // the longest dependency chain: ahead of the packed words
+#pragma unroll
+        for (int dd = 0; dd < D; ++dd)
+#pragma unroll
+            for (int r = 0; r < R; ++r) load_tile(P[dd][r], v0 + r, v1, wave + dd * kBW);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool tv = v0 + r < v1;
+            const uint32_t row = (uint32_t)(v0 + r) * kTileRows + j;
+            if constexpr (BITS == 2) {
+                const uint2v t = __builtin_amdgcn_raw_buffer_load_b64(rs_tb, tv ? row * 8 : kOob, 0, 0);
+                tab[r] = RowTables{{t[0], 0u}, {t[1], 0u}};
+            } else if constexpr (BITS == 3) {
+                const uint4v t = __builtin_amdgcn_raw_buffer_load_b128(rs_tb, tv ? row * 16 : kOob, 0, 0);
+                tab[r] = RowTables{{t[0], t[1]}, {t[2], t[3]}};
+            } else {
+                const uint4v t = __builtin_amdgcn_raw_buffer_load_b128(rs_tb, tv ? row * 32 : kOob, 0, 0);
+                const uint4v u = __builtin_amdgcn_raw_buffer_load_b128(rs_tb, tv ? row * 32 + 16 : kOob, 0, 0);
+                tab[r] = RowTables4{{t[0], t[1], t[2], t[3]}, {u[0], u[1], u[2], u[3]}};
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int b = 0; b < TB; ++b) acc[r][b] = float4v{0.f, 0.f, 0.f, 0.f};
+
+        auto chunk_products = [&](TokTile<BITS> (&p)[R], int chunk) {
+            stage_x();
+            if (TB == 1) { load_s(chunk + kBW); load_x(chunk + kBW); }   // room for the next chunk's activations while this one multiplies
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (r > 0 && v0 + r >= v1) break;               // uniform
+                tile_product(p[r], tab[r], acc[r]);
+                load_tile(p[r], v0 + r, v1, chunk + D * kBW);
+            }
+            if (TB > 1) { load_s(chunk + kBW); load_x(chunk + kBW); }    // into the registers the B operands leave
+        };
+        for (int c = wave; c < kc; c += D * kBW) {
+            chunk_products(P[0], c);
+            if (D == 2) {
+                if (c + kBW >= kc) break;
+                chunk_products(P[D - 1], c + kBW);
+            }
+        }
+
+        // ---- partial tiles to LDS, one barrier, sum over the waves in order, one rounding, store
+        float *part = reinterpret_cast<float *>(smem + wave * kWaveBytes);    // [tile][block][token 16][row 16]
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+                *reinterpret_cast<float4v *>(&part[(r * TB + b) * 256 + j * 16 + 4 * q]) = acc[r][b];   // lane (q, j): rows 4q..4q+3 of token j
+        __syncthreads();
+        const int n_tiles = v1 - v0, quads = n_tiles * 4;    // row quads of one token
+        for (int e = threadIdx.x; e < quads * M; e += kBW * 64) {
+            const int m = e / quads, rest = e - m * quads, r = rest >> 2, rq = rest & 3;
+            const float *src = reinterpret_cast<const float *>(smem) + (r * TB + (m >> 4)) * 256 + (m & 15) * 16 + 4 * rq;
+            float4v sum = *reinterpret_cast<const float4v *>(src);
+#pragma unroll
+            for (int w = 1; w < kBW; ++w) sum += *reinterpret_cast<const float4v *>(src + w * (kWaveBytes / 4));
+            typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+            half4 o;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] = (_Float16)(sum[u] * out_scale);
+            *reinterpret_cast<half4 *>(pb.y + (size_t)m * N + (size_t)(v0 + r) * kTileRows + 4 * rq) = o;
+        }
+        if (v1 < tb_end) __syncthreads();   // the next tiles' stages overwrite the partial tiles
+    }
+}
+
+// Row tiles a variant holds, by index width and token blocks: as many as the registers of two waves per
+// SIMD allow next to the B operands (32 per block), the staged activations and the tables.
+template <int BITS, int TB> struct TokensHeld { static constexpr int most = BITS == 4 ? (TB == 1 ? 4 : TB == 2 ? 3 : 2) : (TB == 1 ? 6 : TB == 2 ? 5 : 3); };
+
+template <int BITS, int TB, int R>
+static TokensVariant variant_of(int slot)
+{
+    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R>, R, (size_t)kBW * tokens_wave_bytes<TB, R>(),
+                         ((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 4 + slot};
+}
+
+template <int BITS, int TB>
+static TokensVariant pick_tiles(int tiles)
+{
+    if (tiles <= 1) return variant_of<BITS, TB, 1>(0);
+    if (tiles <= 2) return variant_of<BITS, TB, 2>(1);
+    return variant_of<BITS, TB, TokensHeld<BITS, TB>::most>(2);
+}
+
+template <int BITS>
+static TokensVariant pick_blocks(int blocks, int tiles)
+{
+    return blocks <= 1 ? pick_tiles<BITS, 1>(tiles) : blocks == 2 ? pick_tiles<BITS, 2>(tiles)
+         : blocks == 3 ? pick_tiles<BITS, 3>(tiles) : pick_tiles<BITS, 4>(tiles);
+}
+
+TokensVariant tokens_variant(int bits, int blocks, int tiles)
+{
+    return bits == 2 ? pick_blocks<2>(blocks, tiles) : bits == 3 ? pick_blocks<3>(blocks, tiles) : pick_blocks<4>(blocks, tiles);
+}
+
+}  // namespace lcd

@@ -20,6 +20,16 @@ def test_gemv_batched_small(bits, M, shape):
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("M", [16, 17, 32, 33, 48, 49, 63, 64, 65])
+@pytest.mark.parametrize("shape", [(16, 256), (48, 2304), (16 * 700, 512), (16 * 1800, 256)])
+def test_gemm_token_block_edges(bits, M, shape):
+    # the tokens kernel behind lcd_lut_gemm: every number of 16-token blocks and one token either side, fewer chunks than
+    # waves, a short last round of chunks, and 1, 2, 3 and 7-8 row tiles per workgroup (one and several passes over K)
+    N, K = shape
+    check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("M", [1, 5, 64, 130, 257])
 @pytest.mark.parametrize("shape", [(16, 256), (48, 768), (272, 1024), (1040, 512)])
 def test_gemm_small(bits, M, shape):
