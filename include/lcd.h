@@ -136,7 +136,7 @@ lcd_status lcd_build_lut(const uint16_t *codebook /*DEVICE*/, int N, int bits,
  *               columns.  The smoothing is fused into the kernel, except on the dequantising
  *               route with K >= 16384, where a small kernel ahead of the product leaves the
  *               smoothed activations in the workspace (same rounding, same result).
- * lcd_lut_gemm: prefill path, any M >= 1: up to 64 tokens the kernels of lcd_lut_gemv; beyond, a
+ * lcd_lut_gemm: prefill path, any M >= 1: up to 16 tokens (32 for small layers) the kernels of lcd_lut_gemv; beyond, a
  *               smoothing kernel into the workspace, then register dequantisation into fp16 MFMA operands.
  * Both give bit-identical results from run to run (fixed reduction order).
  */
@@ -238,7 +238,8 @@ lcd_status lcd_lut_gemv_q8_grouped(const lcd_gemv_problem *problems /*HOST*/, co
 /* ---- grouped prefill: several independent layers in ONE pair of launches ------------------- *
  *
  * The same product as lcd_lut_gemm for `count` (1..16) layers with one token count M >= 1 and one
- * index width: one smoothing launch for all layers, then one matrix launch whose workgroups take
+ * index width: one smoothing launch for all layers, then one matrix launch (two if some layers take
+ * small output tiles and some large ones) whose workgroups take
  * the layers' output tiles one layer after the other (those with the largest K first), so that
  * the compute units the tail of one layer leaves idle start on the next.  Results are bit for
  * bit those of lcd_lut_gemm on every layer.  `problems` is a HOST array, read during the call

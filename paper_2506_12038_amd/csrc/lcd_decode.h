@@ -58,7 +58,7 @@ struct BucketBatch {
 
 // ---- tokens kernel (lcd_tokens.hip) ---------------------------------------------------------------
 constexpr int kTokenBlock = 16;      // tokens per block of the tokens kernel (the columns of one matrix instruction)
-constexpr int kMaxTokenBlocks = 4;   // blocks it holds in registers: up to 64 tokens
+constexpr int kMaxTokenBlocks = 2;   // blocks it holds in registers: up to 32 tokens
 
 // A variant for `blocks` token blocks that holds up to `tiles` row tiles at a time, or the one that holds
 // the most if none holds that many.

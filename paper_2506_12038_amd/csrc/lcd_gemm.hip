@@ -1,4 +1,5 @@
-// Prefill path (M >= 64; any M >= 1 accepted) of the smoothed table-lookup product, gfx950.
+// Prefill path (M >= 17; any M >= 1 accepted) of the smoothed table-lookup product, gfx950: the large-tile kernel and
+// the launcher of both prefill kernels.
 //
 // This path is a dense contraction, so it runs on v_mfma_f32_32x32x16_f16 with fp32
 // accumulators (the 32x32 shape reaches the matrix peak from a single wave per SIMD; the 16x16
@@ -20,16 +21,11 @@
 // Each decoded A operand is used for 4 token blocks, each B operand for 2 row pairs.
 #include <hip/hip_runtime.h>
 #include <algorithm>
-#include "lcd_internal.h"
-#include "lcd_device.h"
+#include "lcd_gemm_common.h"
 #include "lcd_launch.h"
 
 namespace lcd {
 
-// packed weights are read by every token block of the layer: default cache policy (the non-temporal
-// hint of the decode kernels costs 2 % here)
-constexpr int kGemmWeightPolicy = 0;
-constexpr int kXcds = 8;             // accelerator complex dies of the MI355X, each with its own L2
 constexpr int kGemmRowGroups = 4;   // 64-row groups per workgroup
 constexpr int kGemmWaves = 2 * kGemmRowGroups;   // x the two halves of a chunk
 constexpr int kGemmPairs = 2;        // 32-row pairs per wave
@@ -37,107 +33,9 @@ constexpr int kGemmTokBlks = 4;      // 32-token blocks per workgroup (shared by
 constexpr int kGemmTokens = 32 * kGemmTokBlks;
 constexpr int kStageBytes = kGemmTokBlks * 16 * 1024;  // 64 KiB: 4 token blocks x 16 k-steps x 1 KiB
 
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-typedef __attribute__((address_space(1))) const uint32_t glb_u32;
-
-// ---- accumulators in fixed accumulation registers ------------------------------------------------
-// The 8 accumulators of a wave (16 registers each) live in a[0:127] and are touched only by the
-// inline assembly below, so the compiler never copies them (as loop-carried values it would move
-// all 128 registers to VGPRs and back in every iteration).  This file is compiled with AGPR
-// spilling disabled, and uses no MFMA builtins, so the compiler itself never allocates an AGPR.
-// The compiler does not look inside the assembly text, so it cannot keep the distance the hardware
-// requires between a vector instruction that writes a register and a matrix instruction that reads it
-// as an operand (it is free to place the last instruction of an operand's dequantisation directly in
-// front of the matrix instruction, and does so depending on unrelated details of the source): every
-// matrix instruction therefore brings its own two wait states.  Two waves share a SIMD and a 32x32x16
-// instruction occupies the matrix pipe for 32 cycles, so the two issue cycles are hidden.
-template <int IDX> __device__ __forceinline__ void mfma_acc(uint4v a, uint4v b);
-template <int IDX> __device__ __forceinline__ float16v read_acc();
-template <int IDX> __device__ __forceinline__ void zero_acc();
-// Register names cannot be computed inside assembly text, so each accumulator lists its 16 registers once.
-#define LCD_ACC_CLOBBERS(r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15)                                   \
-    "a" #r0, "a" #r1, "a" #r2, "a" #r3, "a" #r4, "a" #r5, "a" #r6, "a" #r7, "a" #r8, "a" #r9, "a" #r10, "a" #r11, "a" #r12,      \
-        "a" #r13, "a" #r14, "a" #r15
-#define LCD_ACC_READ(n, r) "v_accvgpr_read_b32 %" #n ", a" #r
-#define LCD_ACC_ZERO(r) "v_accvgpr_write_b32 a" #r ", 0"
-#define LCD_ACCUMULATOR(IDX, r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15)                                \
-    template <> __device__ __forceinline__ void mfma_acc<IDX>(uint4v a, uint4v b)                                                 \
-    {                                                                                                                              \
-        asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 a[" #r0 ":" #r15 "], %0, %1, a[" #r0 ":" #r15 "]"                     \
-                     :                                                                                                             \
-                     : "v"(a), "v"(b)                                                                                              \
-                     : LCD_ACC_CLOBBERS(r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15));                    \
-    }                                                                                                                              \
-    template <> __device__ __forceinline__ float16v read_acc<IDX>()                                                                \
-    {                                                                                                                              \
-        float t[16];                                                                                                               \
-        asm volatile(LCD_ACC_READ(0, r0) "\n\t" LCD_ACC_READ(1, r1) "\n\t" LCD_ACC_READ(2, r2) "\n\t" LCD_ACC_READ(3, r3) "\n\t"   \
-                     LCD_ACC_READ(4, r4) "\n\t" LCD_ACC_READ(5, r5) "\n\t" LCD_ACC_READ(6, r6) "\n\t" LCD_ACC_READ(7, r7) "\n\t"   \
-                     LCD_ACC_READ(8, r8) "\n\t" LCD_ACC_READ(9, r9) "\n\t" LCD_ACC_READ(10, r10) "\n\t" LCD_ACC_READ(11, r11)      \
-                     "\n\t" LCD_ACC_READ(12, r12) "\n\t" LCD_ACC_READ(13, r13) "\n\t" LCD_ACC_READ(14, r14) "\n\t"                 \
-                     LCD_ACC_READ(15, r15)                                                                                         \
-                     : "=v"(t[0]), "=v"(t[1]), "=v"(t[2]), "=v"(t[3]), "=v"(t[4]), "=v"(t[5]), "=v"(t[6]), "=v"(t[7]),             \
-                       "=v"(t[8]), "=v"(t[9]), "=v"(t[10]), "=v"(t[11]), "=v"(t[12]), "=v"(t[13]), "=v"(t[14]), "=v"(t[15]));      \
-        float16v v;                                                                                                                \
-        for (int i = 0; i < 16; ++i) v[i] = t[i];                                                                                  \
-        return v;                                                                                                                  \
-    }                                                                                                                              \
-    template <> __device__ __forceinline__ void zero_acc<IDX>()                                                                    \
-    {                                                                                                                              \
-        asm volatile(LCD_ACC_ZERO(r0) "\n\t" LCD_ACC_ZERO(r1) "\n\t" LCD_ACC_ZERO(r2) "\n\t" LCD_ACC_ZERO(r3) "\n\t"               \
-                     LCD_ACC_ZERO(r4) "\n\t" LCD_ACC_ZERO(r5) "\n\t" LCD_ACC_ZERO(r6) "\n\t" LCD_ACC_ZERO(r7) "\n\t"               \
-                     LCD_ACC_ZERO(r8) "\n\t" LCD_ACC_ZERO(r9) "\n\t" LCD_ACC_ZERO(r10) "\n\t" LCD_ACC_ZERO(r11) "\n\t"             \
-                     LCD_ACC_ZERO(r12) "\n\t" LCD_ACC_ZERO(r13) "\n\t" LCD_ACC_ZERO(r14) "\n\t" LCD_ACC_ZERO(r15)                  \
-                     :                                                                                                             \
-                     :                                                                                                             \
-                     : LCD_ACC_CLOBBERS(r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15));                    \
-    }
-LCD_ACCUMULATOR(0, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15)
-LCD_ACCUMULATOR(1, 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31)
-LCD_ACCUMULATOR(2, 32, 33, 34, 35, 36, 37, 38, 39, 40, 41, 42, 43, 44, 45, 46, 47)
-LCD_ACCUMULATOR(3, 48, 49, 50, 51, 52, 53, 54, 55, 56, 57, 58, 59, 60, 61, 62, 63)
-LCD_ACCUMULATOR(4, 64, 65, 66, 67, 68, 69, 70, 71, 72, 73, 74, 75, 76, 77, 78, 79)
-LCD_ACCUMULATOR(5, 80, 81, 82, 83, 84, 85, 86, 87, 88, 89, 90, 91, 92, 93, 94, 95)
-LCD_ACCUMULATOR(6, 96, 97, 98, 99, 100, 101, 102, 103, 104, 105, 106, 107, 108, 109, 110, 111)
-LCD_ACCUMULATOR(7, 112, 113, 114, 115, 116, 117, 118, 119, 120, 121, 122, 123, 124, 125, 126, 127)
-#undef LCD_ACCUMULATOR
-#undef LCD_ACC_ZERO
-#undef LCD_ACC_READ
-#undef LCD_ACC_CLOBBERS
 __device__ __forceinline__ void zero_accs()
 {
     zero_acc<0>(); zero_acc<1>(); zero_acc<2>(); zero_acc<3>(); zero_acc<4>(); zero_acc<5>(); zero_acc<6>(); zero_acc<7>();
-}
-
-// One lane's packed words of a chunk half: per pair, the lane's row and the 64 columns
-// [64*(2*half + L>>5), +64) of the chunk.
-template <int BITS>
-struct GemmTileRegs {
-    uint4v lo[kGemmPairs];
-    uint2v hi[kGemmPairs];    // 3 bits: the third-bit words
-    uint4v hi4[kGemmPairs];   // 4 bits: the second plane
-};
-
-// byte-split codebook of a lane's row: two words of each kind up to 3 bits, four with 4 bits
-template <int BITS> struct GemmTables { typedef RowTables type; };
-template <> struct GemmTables<4> { typedef RowTables4 type; };
-
-template <int BITS>
-__device__ __forceinline__ void load_gemm_tiles(GemmTileRegs<BITS> &r, __amdgpu_buffer_rsrc_t packed, int t0, int nt,
-                                                int kc, int c, int h, int lane)
-{
-    constexpr uint32_t TB = kTileRows * kTileCols * BITS / 8;
-    const int sub = (lane >> 4) & 1, kh = lane >> 5, i = lane & 15;
-#pragma unroll
-    for (int p = 0; p < kGemmPairs; ++p) {
-        const int tile = t0 + 2 * p + sub;
-        const uint32_t base = ((uint32_t)tile * (uint32_t)kc + (uint32_t)c) * TB;
-        const int slot = 16 * (2 * h + kh) + i;          // lane slot inside the 16 x 256 tile
-        const bool v = tile < nt;
-        r.lo[p] = __builtin_amdgcn_raw_buffer_load_b128(packed, v ? base + 16 * slot : 0xFFFFFFF0u, 0, kGemmWeightPolicy);
-        if (BITS == 3) r.hi[p] = __builtin_amdgcn_raw_buffer_load_b64(packed, v ? base + 1024 + 8 * slot : 0xFFFFFFF0u, 0, kGemmWeightPolicy);
-        if (BITS == 4) r.hi4[p] = __builtin_amdgcn_raw_buffer_load_b128(packed, v ? base + 1024 + 16 * slot : 0xFFFFFFF0u, 0, kGemmWeightPolicy);
-    }
 }
 
 // copy one 64 KiB stage: every wave copies 8 KiB as 8 wave-wide 1 KiB direct-to-LDS loads,
@@ -169,31 +67,6 @@ __device__ __forceinline__ uint4v read_b(uint32_t base)
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(base), "n"((TBLK * 16 + G) * 1024) : "memory");
     return v;
 }
-template <int N>
-__device__ __forceinline__ void lds_wait()
-{
-    asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(N) : "memory");
-}
-__device__ __forceinline__ uint32_t lds_address(const uint8_t *p)
-{
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t *)p;
-}
-
-// The dequantiser's first two stages for quarter T of word DN of pair P, for any width: the selector
-// (4 bits: and the pool word), then the table lookups.
-template <int BITS, int DN, int T>
-__device__ __forceinline__ void gemm_select(const GemmTileRegs<BITS> &r, int p, const HighBits &hb, uint32_t &sel, uint32_t &pool)
-{
-    if constexpr (BITS == 4) decode_select4<T>(r.lo[p][DN], r.hi4[p][DN], sel, pool);
-    else sel = decode_select<BITS, DN, T>(r.lo[p][DN], hb);
-}
-template <int BITS>
-__device__ __forceinline__ void gemm_lookup(uint32_t sel, uint32_t pool, const typename GemmTables<BITS>::type &tb, uint32_t &lo, uint32_t &hi)
-{
-    if constexpr (BITS == 4) decode_lookup4(sel, pool, tb, lo, hi);
-    else decode_lookup<BITS>(sel, tb, lo, hi);
-}
-
 // Decoded A operands of one packed word: [pair][k-step of the word].
 struct WordOps { uint4v op[kGemmPairs][2]; };
 
@@ -206,7 +79,7 @@ struct WordOps { uint4v op[kGemmPairs][2]; };
 // On entry the B window holds steps 0..2 of this word; on exit steps 0..2 of the next word of the
 // chunk (the caller primes it again after the last word).
 template <int BITS, int D, int DN, bool COPY>
-__device__ __forceinline__ void gemm_word(const WordOps &cur, WordOps &nxt, const GemmTileRegs<BITS> &rn,
+__device__ __forceinline__ void gemm_word(const WordOps &cur, WordOps &nxt, const GemmTileRegs<BITS, kGemmPairs> &rn,
                                           const HighBits (&hbn)[kGemmPairs], const typename GemmTables<BITS>::type (&tb)[kGemmPairs],
                                           uint32_t bbase, BWindow &bw,
                                           const uint8_t *copy_src, uint8_t *copy_dst, int wave, int lane)
@@ -264,34 +137,17 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
     const size_t chunk_stride = (size_t)(Mpad >> 5) * 16 * 1024;
     const uint8_t *xs_base = xs + (size_t)tb0 * 16 * 1024;
 
-    // this lane's row in each pair, and its byte-split codebook
     typename GemmTables<BITS>::type tb[kGemmPairs];
-#pragma unroll
-    for (int p = 0; p < kGemmPairs; ++p) {
-        const int tile = min(t0 + 2 * p + ((lane >> 4) & 1), nt - 1);
-        const int row = tile * kTileRows + (lane & 15);
-        if constexpr (BITS == 2) {
-            const uint2v v = *reinterpret_cast<const uint2v *>(lutB + (size_t)row * 8);
-            tb[p].lo[0] = v[0]; tb[p].hi[0] = v[1]; tb[p].lo[1] = 0; tb[p].hi[1] = 0;
-        } else if constexpr (BITS == 3) {
-            const uint4v v = *reinterpret_cast<const uint4v *>(lutB + (size_t)row * 16);
-            tb[p].lo[0] = v[0]; tb[p].lo[1] = v[1]; tb[p].hi[0] = v[2]; tb[p].hi[1] = v[3];
-        } else {
-            const uint4v v = *reinterpret_cast<const uint4v *>(lutB + (size_t)row * 32);
-            const uint4v w = *reinterpret_cast<const uint4v *>(lutB + (size_t)row * 32 + 16);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { tb[p].lo[u] = v[u]; tb[p].hi[u] = w[u]; }
-        }
-    }
+    load_gemm_tables<BITS>(tb, lutB, t0, nt, lane);
     zero_accs();
 
-    GemmTileRegs<BITS> r0, r1;
+    GemmTileRegs<BITS, kGemmPairs> r0, r1;
     load_gemm_tiles<BITS>(r0, packed, t0, nt, kc, 0, khalf, lane);
     stage_copy(xs_base, lds, wave, lane, 0, 8);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
-    auto high_bits = [&](const GemmTileRegs<BITS> &r, HighBits (&hb)[kGemmPairs]) {
+    auto high_bits = [&](const GemmTileRegs<BITS, kGemmPairs> &r, HighBits (&hb)[kGemmPairs]) {
 #pragma unroll
         for (int p = 0; p < kGemmPairs; ++p) {
             hb[p] = HighBits{0u, 0u};
@@ -307,7 +163,7 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
     // c).  The copy of chunk c+1's stage is issued during word 0 (the other stage was released by
     // the barrier that ended chunk c-1) and has the whole chunk to land: one wait + one barrier
     // per chunk, after which the B window is primed from the new stage.
-    auto compute = [&](const GemmTileRegs<BITS> &r, const GemmTileRegs<BITS> &rn, const uint8_t *stage,
+    auto compute = [&](const GemmTileRegs<BITS, kGemmPairs> &r, const GemmTileRegs<BITS, kGemmPairs> &rn, const uint8_t *stage,
                        uint8_t *other_stage, const uint8_t *copy_src) {
         const uint32_t bbase = lds_address(stage) + khalf * 8 * 1024 + boff;
         const uint32_t obase = lds_address(other_stage) + khalf * 8 * 1024 + boff;
@@ -356,6 +212,9 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
     // The accumulator reads below are assembly text too: the distance the hardware requires between a
     // matrix instruction's register write and a vector instruction's read of it (19 wait states for
     // the 16-pass instruction) is kept here by hand, once per workgroup.
+    // (The window reads issued after the last chunk's barrier are used by nobody: they must still land before their registers
+    // are used for something else.)
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bw.w[0]), "+v"(bw.w[1]), "+v"(bw.w[2]) : : "memory");
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
     float4v *area_in = reinterpret_cast<float4v *>(lds) + (size_t)(rgrp * 2 + khalf) * (4 * 4 * 64);
     float4v *area_out = reinterpret_cast<float4v *>(lds) + (size_t)(rgrp * 2 + (khalf ^ 1)) * (4 * 4 * 64);
@@ -419,33 +278,6 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
 // the workgroups that are resident on an XCD at the same time share one or two 128-token
 // blocks of activations (1 MiB each at K = 4096), which then stay in that XCD's 4 MiB L2.
 template <int BITS>
-__global__ void __launch_bounds__(kGemmWaves * 64, 1)
-gemm_kernel(const uint8_t *__restrict__ packed_, const uint8_t *__restrict__ lutB, const uint8_t *__restrict__ xs,
-            uint16_t *__restrict__ y, int M, int Mpad, int N, int K, int grid_rows, int tiles_per_xcd, float out_scale)
-{
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];  // 2 stages x 64 KiB
-    const int out_tile = (int)(blockIdx.x % kXcds) * tiles_per_xcd + (int)(blockIdx.x / kXcds);
-    const int total_tiles = grid_rows * (Mpad / kGemmTokens);
-    if ((int)(blockIdx.x / kXcds) >= tiles_per_xcd || out_tile >= total_tiles) return;
-    gemm_tile<BITS>(packed_, lutB, xs, y, M, Mpad, N, K, out_tile % grid_rows, out_tile / grid_rows, lds, out_scale);
-}
-
-// Several layers in one launch (same token count and index width): every XCD's queue of
-// workgroups holds its run of every layer's tiles, layer after layer in the order of the batch
-// (the host puts the layers with the longest tiles first), so the tail of one layer is filled by
-// the head of the next and only the last layer leaves compute units idle at the end.
-struct GemmProblem {
-    const uint8_t *packed, *lutB, *xs;
-    uint16_t *y;
-    int N, K, grid_rows, tiles_per_xcd;
-    int queue_begin;   // position of this layer's first tile in an XCD's queue
-    float out_scale;   // 1, or the layer's activation quantisation step
-};
-struct GemmBatch {
-    GemmProblem p[kMaxGroup];
-    int count, M, Mpad;
-};
-template <int BITS>
 __global__ void __launch_bounds__(kGemmWaves * 64, 1) gemm_group_kernel(const GemmBatch batch)
 {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];  // 2 stages x 64 KiB
@@ -459,42 +291,61 @@ __global__ void __launch_bounds__(kGemmWaves * 64, 1) gemm_group_kernel(const Ge
                     pb.out_scale);
 }
 
-// Up to kDecodeTokens tokens the tokens kernel takes the call: a 256 x 128 output tile would leave most compute
-// units without work (16 workgroups on a 4096-row layer) and half of every tile to tokens that are not there.
-static bool decode_takes(int M, int K) { return M <= kDecodeTokens && (long long)M * K * 2 < (1ll << 32); }
+// Which kernel takes a layer.  The rules look at the layer and the number of tokens alone, never at the group it is
+// called in: the kernels add in different orders, and a layer's result must not depend on its neighbours.
+// Up to 16 tokens the call is lcd_lut_gemv's.  Up to 32 tokens the tokens kernel, which needs no smoothing launch,
+// also keeps the small layers (1024 x 2048, 3 bits, 32 tokens: 7.5 us against 10.1 with the split kernel; 4096 x 4096: 10.9
+// against 10.1, 4096 x 11008: 21.6 against 15.5).
+static bool decode_takes(int M, int N, int K)
+{
+    return (M <= 16 || (M <= kDecodeTokens && (long long)N * K < (1ll << 24))) && (long long)M * K * 2 < (1ll << 32);
+}
+// The split kernel takes layers that do not have 256 x 128 tiles for much more than half of the compute units.  Time of a
+// call, large tiles -> split, 3 bits: 4096 x 4096, 333 tokens (48 tiles) 47 -> 22 us, 1000 tokens (128 tiles)
+// 50 -> 46; 4096 x 11008, 333 tokens 110 -> 45; two layers of 11008 x 4096, 333 tokens (129 tiles each: a second round of
+// large tiles for two of them) 106 -> 91.  Beyond, large tiles are faster: 8192 x 8192, 700 tokens (192 tiles)
+// 102 against 112.  (The split kernel addresses the activations with 32 bits.)
+constexpr int kSplitMostTiles = 132;
+static bool split_takes(int M, int N, int K)
+{
+    const long long tiles = (long long)((N + 255) / 256) * ((M + kGemmTokens - 1) / kGemmTokens);
+    return tiles <= kSplitMostTiles && (long long)plan_gemm(M, N, K, 2).m_pad * K * 2 < (1ll << 32);
+}
+
+// Tile of a launch of the split kernel: rounds of workgroups over the compute units times the time of one workgroup.  Measured
+// in single rounds (K = 4096 and 11008): a fixed part, and a part per column that is bound by the activations' way into LDS
+// (75..98 GB/s per compute unit; 32 tokens x 64 rows: by the dequantiser).
+struct SplitTile { int pairs, blocks; double fixed_us, column_ns[3]; };   // column_ns: 2, 3, 4 bits
+static const SplitTile kSplitTiles[] = {
+    {2, 4, 3.0, {2.58, 2.70, 3.13}}, {2, 3, 2.5, {2.13, 2.40, 3.05}}, {2, 2, 2.0, {1.56, 1.74, 2.33}},
+    {2, 1, 1.5, {1.34, 1.66, 2.58}}, {1, 2, 1.5, {1.48, 1.60, 1.69}}, {1, 1, 1.3, {0.79, 0.88, 1.17}},
+};
+static const SplitTile &choose_split_tile(const GemmBatch &bt, int M, int bits)
+{
+    const SplitTile *best = nullptr;
+    double best_time = 0.0;
+    for (const SplitTile &t : kSplitTiles) {
+        double work = 0.0, wgs = 0.0;
+        for (int q = 0; q < bt.count; ++q) {
+            const double n = (double)((bt.p[q].N + 32 * t.pairs - 1) / (32 * t.pairs)) * ((M + 32 * t.blocks - 1) / (32 * t.blocks));
+            wgs += n;
+            work += n * (t.fixed_us + 1e-3 * t.column_ns[bits - 2] * bt.p[q].K);
+        }
+        const double time = __builtin_ceil(wgs / num_cus()) * work / wgs;
+        if (!best || time < best_time) { best = &t; best_time = time; }
+    }
+    return *best;
+}
 
 int launch_gemm(const void *packed, const void *lut, const uint16_t *x, const float *s, uint16_t *y,
-                int M, int N, int K, int bits, float act_scale, void *workspace, const GemmPlan &plan, void *stream_)
+                int M, int N, int K, int bits, float act_scale, void *workspace, const GemmPlan &, void *stream)
 {
-    if (decode_takes(M, K)) return launch_gemv(packed, lut, x, s, y, M, N, K, bits, act_scale, workspace, stream_);
-    hipStream_t stream = (hipStream_t)stream_;
-    const int Mpad = plan.m_pad;
-    if (int e = launch_smooth(x, s, workspace, M, Mpad, K, act_scale, stream)) return e;
-    // byte-split tables: behind the bucket multipliers (2 and 3 bits), the whole table (4 bits)
-    const uint8_t *lutB = static_cast<const uint8_t *>(lut) + (bits == 4 ? 0 : (size_t)N * (bits == 2 ? 4 : 8) * 4);
-    const int nt = N / kTileRows;
-    const int tiles_per_wg = kGemmRowGroups * 2 * kGemmPairs;
-    const int grid_rows = (nt + tiles_per_wg - 1) / tiles_per_wg;
-    const int total_tiles = grid_rows * (Mpad / kGemmTokens);
-    const int tiles_per_xcd = (total_tiles + kXcds - 1) / kXcds;
-    const dim3 grid(tiles_per_xcd * kXcds), block(kGemmWaves * 64);
-    const size_t lds_bytes = 2 * kStageBytes;
-    static PerDeviceFlags<3> lds_raised;
-    const void *fn = bits == 2 ? (const void *)gemm_kernel<2> : bits == 3 ? (const void *)gemm_kernel<3> : (const void *)gemm_kernel<4>;
-    if (hipError_t e = raise_lds_limit_once(lds_raised, bits - 2, fn, lds_bytes)) return (int)e;
-    const uint8_t *packed_arg = static_cast<const uint8_t *>(packed), *xs_arg = static_cast<const uint8_t *>(workspace);
-    int M_arg = M, Mpad_arg = Mpad, N_arg = N, K_arg = K, rows_arg = grid_rows, xcd_arg = tiles_per_xcd;
-    float scale_arg = act_scale != 0.0f ? act_scale : 1.0f;
-    void *args[] = {&packed_arg, &lutB, &xs_arg, &y, &M_arg, &Mpad_arg, &N_arg, &K_arg, &rows_arg, &xcd_arg, &scale_arg};
-    if (hipError_t e = hipLaunchKernel(fn, grid, block, args, lds_bytes, stream)) return (int)e;
-    return (int)hipGetLastError();
+    GroupItem it{packed, lut, x, s, y, N, K, act_scale};
+    return launch_gemm_group(&it, 1, M, bits, workspace, stream);
 }
 
 int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream_)
 {
-    bool decode = true;
-    for (int i = 0; i < count; ++i) decode = decode && decode_takes(M, items[i].K);
-    if (decode) return launch_decode_group(items, count, M, bits, workspace, stream_);
     hipStream_t stream = (hipStream_t)stream_;
     const int Mpad = plan_gemm(M, items[0].N, items[0].K, bits).m_pad;
     // layers with the longest tiles (largest K) first in every XCD's queue
@@ -505,11 +356,13 @@ int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *
     // block) share one transformed copy of it: the activations are smoothed once per distinct input.
     SmoothItem sm[kMaxGroup];
     int distinct = 0;
-    GemmBatch batch{};
+    GemmBatch batch[2] = {};   // [0] the large-tile kernel's layers, [1] the split kernel's
+    GroupItem small[kMaxGroup];
+    int small_count = 0;       // the decode kernels' layers
     size_t offset = 0;
-    int queue = 0;
     for (int q = 0; q < count; ++q) {
         const GroupItem &it = items[order[q]];
+        if (decode_takes(M, it.N, it.K)) { small[small_count++] = it; continue; }
         uint8_t *xs = nullptr;
         for (int d = 0; d < distinct && !xs; ++d)
             if (sm[d].x == it.x && sm[d].s == it.s && sm[d].K == it.K && sm[d].s_q == it.act_scale) xs = static_cast<uint8_t *>(sm[d].xs);
@@ -518,30 +371,53 @@ int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *
             offset += plan_gemm(M, it.N, it.K, bits).xs_bytes;
             sm[distinct++] = SmoothItem{it.x, it.s, xs, it.K, it.act_scale};
         }
-        GemmProblem &p = batch.p[q];
+        GemmBatch &bt = batch[split_takes(M, it.N, it.K)];
+        GemmProblem &p = bt.p[bt.count++];
         p.packed = static_cast<const uint8_t *>(it.packed);
+        // byte-split tables: behind the bucket multipliers (2 and 3 bits), the whole table (4 bits)
         p.lutB = static_cast<const uint8_t *>(it.lut) + (bits == 4 ? 0 : (size_t)it.N * (bits == 2 ? 4 : 8) * 4);
         p.xs = xs;
         p.y = it.y;
         p.N = it.N; p.K = it.K;
-        const int nt = it.N / kTileRows, tiles_per_wg = kGemmRowGroups * 2 * kGemmPairs;
-        p.grid_rows = (nt + tiles_per_wg - 1) / tiles_per_wg;
-        const int total_tiles = p.grid_rows * (Mpad / kGemmTokens);
-        p.tiles_per_xcd = (total_tiles + kXcds - 1) / kXcds;
-        p.queue_begin = queue;
         p.out_scale = it.act_scale != 0.0f ? it.act_scale : 1.0f;
-        queue += p.tiles_per_xcd;
     }
-    batch.count = count; batch.M = M; batch.Mpad = Mpad;
+    // the decode kernels' scratch lies behind the smoothed activations (it takes less than a layer's share of those)
+    if (small_count > 0)
+        if (int e = launch_decode_group(small, small_count, M, bits, static_cast<char *>(workspace) + offset, stream)) return e;
+    if (distinct == 0) return 0;
+    // places of the layers' tiles (rows x tokens each) in the XCDs' queues; returns the queue's length
+    auto queue_tiles = [&](GemmBatch &bt, int rows, int tokens) {
+        int queue = 0;
+        for (int q = 0; q < bt.count; ++q) {
+            GemmProblem &p = bt.p[q];
+            p.grid_rows = (p.N + rows - 1) / rows;
+            p.tiles_per_xcd = (p.grid_rows * ((M + tokens - 1) / tokens) + kXcds - 1) / kXcds;
+            p.queue_begin = queue;
+            queue += p.tiles_per_xcd;
+        }
+        bt.M = M; bt.Mpad = Mpad;
+        return queue;
+    };
     if (int e = launch_smooth_group(sm, distinct, M, Mpad, stream)) return e;
-    const size_t lds_bytes = 2 * kStageBytes;
-    static PerDeviceFlags<3> lds_raised;
-    const void *fn = bits == 2 ? (const void *)gemm_group_kernel<2> : bits == 3 ? (const void *)gemm_group_kernel<3> : (const void *)gemm_group_kernel<4>;
-    if (hipError_t e = raise_lds_limit_once(lds_raised, bits - 2, fn, lds_bytes)) return (int)e;
-    void *args[] = {&batch};
-    if (hipError_t e = hipLaunchKernel(fn, dim3((unsigned)queue * kXcds), dim3(kGemmWaves * 64), args, lds_bytes, stream)) return (int)e;
-    return (int)hipGetLastError();
+    static PerDeviceFlags<3 + kSplitVariants> lds_raised;
+    auto launch = [&](GemmBatch &bt, int queue, const void *fn, int flag, size_t lds_bytes) -> int {
+        if (hipError_t e = raise_lds_limit_once(lds_raised, flag, fn, lds_bytes)) return (int)e;
+        void *args[] = {&bt};
+        if (hipError_t e = hipLaunchKernel(fn, dim3((unsigned)queue * kXcds), dim3(kGemmWaves * 64), args, lds_bytes, stream)) return (int)e;
+        return (int)hipGetLastError();
+    };
+    if (batch[0].count > 0) {
+        const int queue = queue_tiles(batch[0], kGemmRowGroups * 32 * kGemmPairs, kGemmTokens);
+        const void *fn = bits == 2 ? (const void *)gemm_group_kernel<2> : bits == 3 ? (const void *)gemm_group_kernel<3> : (const void *)gemm_group_kernel<4>;
+        if (int e = launch(batch[0], queue, fn, bits - 2, 2 * kStageBytes)) return e;
+    }
+    if (batch[1].count > 0) {
+        const SplitTile &t = choose_split_tile(batch[1], M, bits);
+        const int queue = queue_tiles(batch[1], 32 * t.pairs, 32 * t.blocks);
+        const SplitVariant sv = split_variant(bits, t.pairs, t.blocks);
+        if (int e = launch(batch[1], queue, sv.fn, 3 + sv.id, sv.lds_bytes)) return e;
+    }
+    return 0;
 }
-
 
 }  // namespace lcd

@@ -614,21 +614,7 @@ __global__ __launch_bounds__(kQuantThreads) void transform_kernel(TransformBatch
     }
 }
 
-// compute units of the current device (looked up once per device)
-static int num_cus()
-{
-    static std::atomic<int> cus[kMaxDevices] = {};
-    const int dev = current_device();
-    if (dev < 0) return 256;
-    int n = cus[dev].load(std::memory_order_relaxed);
-    if (n == 0) {
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        cus[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
-}
-
-// One launch for a group of decode problems: the bucket kernel for one token, the tokens kernel for 2..16.
+// One launch for a group of decode problems: the bucket kernel for one token, the tokens kernel beyond.
 int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream_, bool force_prepass)
 {
     hipStream_t stream = (hipStream_t)stream_;

@@ -29,7 +29,7 @@ struct GroupItem {
     const void *packed; const void *lut; const uint16_t *x; const float *s; uint16_t *y; int N, K;
     float act_scale;   // 0: fp16 activations; s_q > 0: INT8 activation codes (paper Sec. 4.1)
 };
-constexpr int kDecodeTokens = 64;   // most tokens the decode kernels take (the decode entry points stop at 16)
+constexpr int kDecodeTokens = 32;   // most tokens the decode kernels take (the decode entry points stop at 16)
 // one launch for `count` decode problems (1 <= M <= kDecodeTokens tokens each)
 // (workspace: decode_codes_bytes(M, K) per item, in item order, when M > 1 and act_scale != 0)
 // force_prepass: the activations are transformed ahead of the product (into the workspace) whenever the
@@ -56,7 +56,6 @@ int launch_merge(const uint16_t *cb_in, const uint32_t *counts, const uint8_t *i
                  uint16_t *cb_out, uint8_t *idx_out, uint8_t *merged, void *stream);
 const char *hip_error_name(int err);
 // s_q = 0: xs = x / s; s_q > 0: the INT8 codes of Sec. 4.1 (as fp16 numbers)
-int launch_smooth(const uint16_t *x, const float *s, void *xs, int M, int Mpad, int K, float s_q, void *stream);
 struct SmoothItem { const uint16_t *x; const float *s; void *xs; int K; float s_q; };
 int launch_smooth_group(const SmoothItem *items, int count, int M, int Mpad, void *stream);
 // prefill, several layers in one launch; the workspace holds every layer's smoothed activations side by side

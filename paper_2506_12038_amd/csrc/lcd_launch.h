@@ -15,6 +15,20 @@ inline int current_device()
     return dev;
 }
 
+// compute units of the current device (looked up once per device)
+inline int num_cus()
+{
+    static std::atomic<int> cus[kMaxDevices] = {};
+    const int dev = current_device();
+    if (dev < 0) return 256;
+    int n = cus[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        cus[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 // "This kernel's dynamic-LDS limit has been raised on this device": one flag per device and kernel variant.
 // The flags are atomics and raising the limit twice is harmless, so concurrent first calls are safe.
 template <int VARIANTS>

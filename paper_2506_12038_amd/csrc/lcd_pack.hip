@@ -183,24 +183,20 @@ __device__ __forceinline__ void smooth_tile(const uint16_t *__restrict__ x, cons
     // a thread's four groups are the same 8 columns of four token rows: one set of reciprocals
     const int kg = t & 31, k = c * kTileCols + 8 * kg;
     const bool quantised = s_q != 0.0f;   // uniform
-    float r[8];
-    Divisor dv[8];
-    {
-        const float4v s0 = *reinterpret_cast<const float4v *>(s + k);
-        const float4v s1 = *reinterpret_cast<const float4v *>(s + k + 4);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float se = e < 4 ? s0[e] : s1[e - 4];
-            r[e] = __builtin_amdgcn_rcpf(se);
-            dv[e] = make_divisor(se, quantised ? s_q : 1.0f);
-        }
-    }
+    // all loads in flight together, no branch between them: a token past the last one reads the last one's row
     uint4v xin[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {               // all four loads in flight together
-        const int m = mb * 32 + ((t + 256 * u) >> 5);
-        xin[u] = uint4v{0u, 0u, 0u, 0u};
-        if (m < M) xin[u] = stream_load(reinterpret_cast<const uint4v *>(x + (size_t)m * K + k));   // read once
+    for (int u = 0; u < 4; ++u)
+        xin[u] = stream_load(reinterpret_cast<const uint4v *>(x + (size_t)min(mb * 32 + ((t + 256 * u) >> 5), M - 1) * K + k));   // read once
+    const float4v s0 = *reinterpret_cast<const float4v *>(s + k);
+    const float4v s1 = *reinterpret_cast<const float4v *>(s + k + 4);
+    float r[8];
+    Divisor dv[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float se = e < 4 ? s0[e] : s1[e - 4];
+        r[e] = __builtin_amdgcn_rcpf(se);
+        dv[e] = make_divisor(se, quantised ? s_q : 1.0f);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -234,12 +230,6 @@ __device__ __forceinline__ void smooth_tile(const uint16_t *__restrict__ x, cons
     }
 }
 
-__global__ void __launch_bounds__(256) smooth_kernel(const uint16_t *__restrict__ x, const float *__restrict__ s,
-                                                     _Float16 *__restrict__ xs, int M, int Mpad, int K, float s_q)
-{
-    smooth_tile(x, s, xs, M, Mpad, K, blockIdx.x, blockIdx.y, s_q);
-}
-
 // the activations of several layers in one launch: grid.z = layer, grid.x = the widest layer's chunks
 struct SmoothBatch { SmoothItem p[kMaxGroup]; };
 __global__ void __launch_bounds__(256) smooth_group_kernel(const SmoothBatch batch, int M, int Mpad)
@@ -256,13 +246,6 @@ int launch_smooth_group(const SmoothItem *items, int count, int M, int Mpad, voi
     for (int i = 0; i < count; ++i) { batch.p[i] = items[i]; widest = items[i].K > widest ? items[i].K : widest; }
     const dim3 grid((unsigned)(widest / kTileCols), (unsigned)(Mpad / 32), (unsigned)count), block(256);
     hipLaunchKernelGGL(smooth_group_kernel, grid, block, 0, (hipStream_t)stream, batch, M, Mpad);
-    return (int)hipGetLastError();
-}
-
-int launch_smooth(const uint16_t *x, const float *s, void *xs, int M, int Mpad, int K, float s_q, void *stream)
-{
-    const dim3 grid((unsigned)(K / kTileCols), (unsigned)(Mpad / 32)), block(256);
-    hipLaunchKernelGGL(smooth_kernel, grid, block, 0, (hipStream_t)stream, x, s, (_Float16 *)xs, M, Mpad, K, s_q);
     return (int)hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-// Decode and short-prompt path (2 <= M <= 64 tokens; every M with 4 bits) of the smoothed
+// Decode and short-prompt path (2 <= M <= 32 tokens; every M with 4 bits) of the smoothed
 // table-lookup product, gfx950: the tokens kernel.
 //
 // A batched product with few tokens: the packed indices are dequantised in registers (v_perm_b32
@@ -21,8 +21,7 @@
 // Measured against the kernel before it (K in segments, partial tiles of two row tiles exchanged through
 // LDS at a barrier after every second tile, no more than 16 tokens): 4096 x 11008, 3 bits, 3 tokens
 // 16.5 -> 9.8 us a call; blocks of 2, 3 and 4-bit layers (5120 / 13824), 6 tokens, 104 -> 72 us a block; 7B
-// block, 2 bits, 16 tokens 46 -> 42.5 us.  7B block, 3 bits, 40 tokens, which the 256 x 128-tile prefill kernel
-// had on 16 to 86 of the 256 compute units: 262 -> 93 us.
+// block, 2 bits, 16 tokens 46 -> 42.5 us.
 #include <hip/hip_runtime.h>
 #include "lcd_decode.h"
 
@@ -51,7 +50,7 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_tokens_kernel(const uint32_t
 {
     constexpr uint32_t TBYTES = kTileRows * kTileCols * BITS / 8;
     constexpr int NC = BITS == 2 ? 4 : 8;
-    constexpr int D = R <= 2 && TB < 4 ? 2 : 1;   // chunks whose packed words are loaded ahead
+    constexpr int D = R <= 2 ? 2 : 1;   // chunks whose packed words are loaded ahead
     constexpr int kWaveBytes = tokens_wave_bytes<TB, R>();
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // one piece per wave: its stage, in the end its partial tiles
 
@@ -247,7 +246,7 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_tokens_kernel(const uint32_t
 
 // Row tiles a variant holds, by index width and token blocks: as many as the registers of two waves per
 // SIMD allow next to the B operands (32 per block), the staged activations and the tables.
-template <int BITS, int TB> struct TokensHeld { static constexpr int most = BITS == 4 ? (TB == 1 ? 4 : TB == 2 ? 3 : 2) : (TB == 1 ? 6 : TB == 2 ? 5 : 3); };
+template <int BITS, int TB> struct TokensHeld { static constexpr int most = BITS == 4 ? (TB == 1 ? 4 : 3) : (TB == 1 ? 6 : 5); };
 
 template <int BITS, int TB, int R>
 static TokensVariant variant_of(int slot)
@@ -267,8 +266,7 @@ static TokensVariant pick_tiles(int tiles)
 template <int BITS>
 static TokensVariant pick_blocks(int blocks, int tiles)
 {
-    return blocks <= 1 ? pick_tiles<BITS, 1>(tiles) : blocks == 2 ? pick_tiles<BITS, 2>(tiles)
-         : blocks == 3 ? pick_tiles<BITS, 3>(tiles) : pick_tiles<BITS, 4>(tiles);
+    return blocks <= 1 ? pick_tiles<BITS, 1>(tiles) : pick_tiles<BITS, 2>(tiles);
 }
 
 TokensVariant tokens_variant(int bits, int blocks, int tiles)

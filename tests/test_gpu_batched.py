@@ -20,12 +20,23 @@ def test_gemv_batched_small(bits, M, shape):
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
-@pytest.mark.parametrize("M", [16, 17, 32, 33, 48, 49, 63, 64, 65])
+@pytest.mark.parametrize("M", [16, 17, 31, 32])
 @pytest.mark.parametrize("shape", [(16, 256), (48, 2304), (16 * 700, 512), (16 * 1800, 256)])
 def test_gemm_token_block_edges(bits, M, shape):
-    # the tokens kernel behind lcd_lut_gemm: every number of 16-token blocks and one token either side, fewer chunks than
-    # waves, a short last round of chunks, and 1, 2, 3 and 7-8 row tiles per workgroup (one and several passes over K)
+    # the tokens kernel behind lcd_lut_gemm: one and two 16-token blocks, fewer chunks than waves, a short last round of
+    # chunks, and 1, 2, 3 and 7-8 row tiles per workgroup (one and several passes over K)
     N, K = shape
+    check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
+
+
+# the split kernel behind lcd_lut_gemm, every tile shape (32 or 64 rows x 32, 64, 96, 128 tokens): one token either side of
+# a tile, rows that fill half a pair, fewer 128-column units than waves (K = 256), units that do not divide by the
+# waves (K = 1280, 2304), and the first token count of the same layer that the large tiles take
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("shape", [(48, 1280, 33), (48, 1280, 64), (1040, 512, 300), (5136, 256, 34), (5136, 1280, 65), (5136, 256, 97), (5136, 256, 200),
+                                   (5136, 2304, 300), (8016, 2304, 129), (4096, 4096, 17), (4112, 4096, 32), (28800, 256, 128), (28800, 256, 257)])
+def test_gemm_split_tile_edges(bits, shape):
+    N, K, M = shape
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
 
 
@@ -171,8 +182,17 @@ def test_codebooks_with_fewer_centroids_than_the_container_holds(bits, ncent, M,
 @pytest.mark.parametrize("bits,M", [(2, 200), (3, 64), (3, 300), (4, 129)])
 def test_grouped_prefill_matches_single_calls_and_oracle(bits, M):
     # several layers of different N and K in one pair of launches: the same bits as lcd_lut_gemm layer by layer
+    _check_grouped_prefill(bits, M, [(272, 1024), (1040, 512), (48, 2816), (4112, 256), (16, 4352)])
+
+
+@pytest.mark.parametrize("M,shapes", [(20, [(64, 512), (8192, 2048), (4096, 4096), (48, 2816)]),           # decode and split kernels
+                                      (129, [(16912, 256), (256, 512), (17040, 256), (4112, 256)])])       # split and large tiles
+def test_grouped_prefill_with_layers_on_different_kernels(M, shapes):
+    _check_grouped_prefill(3, M, shapes)
+
+
+def _check_grouped_prefill(bits, M, shapes):
     import torch
-    shapes = [(272, 1024), (1040, 512), (48, 2816), (4112, 256), (16, 4352)]
     problems, layers, singles = [], [], []
     for i, (N, K) in enumerate(shapes):
         layer = synth.make_layer(3, i, N, K, bits, M, seed_offset=5 * i + bits + M)
