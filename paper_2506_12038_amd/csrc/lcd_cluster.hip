@@ -30,15 +30,65 @@ __device__ __forceinline__ uint16_t half_next_down(uint16_t b)
 // a weight lies strictly above (a weight ON a boundary stays with the lower centroid).  A boundary
 // need not be an fp16 number, but "w > boundary" for an fp16 w is the same as "w >= u" with u the
 // smallest fp16 number above the boundary; u is found once per row in fp64, where the boundary is
-// exact, and the per-weight comparisons are exact fp32 ones.
+// exact.  The comparisons are integer ones on keys that are ordered as the fp16 numbers are, two
+// weights per 32-bit register: a saturating subtraction per boundary leaves "w >= u" in the sign bits, which
+// full adders (two bitwise instructions each) count in bit planes: 11 instructions per weight at 8 centroids, where
+// one comparison and one addition per boundary take 16.  Bound: HBM, 3 bytes per weight (11008 x 4096, 8 centroids: 32 -> 27.5 us,
+// 4.9 TB/s).  The indices are stored with the default cache policy: the next step reads them (assign + 1.5 us, the three
+// steps behind it - 2.5 us).
+typedef short key_pair __attribute__((ext_vector_type(2)));
+typedef unsigned short ukey_pair __attribute__((ext_vector_type(2)));
+
+// Order of the fp16 numbers as 16-bit integers: the sign-magnitude pattern turned into two's complement, moved up so
+// that the positive NaNs wrap round to the bottom: a NaN of either sign is below every boundary.
+__device__ __forceinline__ key_pair ordered_keys(uint32_t halves)
+{
+    const uint32_t sign = __builtin_bit_cast(uint32_t, (key_pair)(__builtin_bit_cast(key_pair, halves) >> 15));
+    const ukey_pair up = {0x3ff, 0x3ff};
+    return __builtin_bit_cast(key_pair, (ukey_pair)(__builtin_bit_cast(ukey_pair, halves ^ (sign & 0x7fff7fffu)) + up));
+}
+
+// full adder at every bit position
+__device__ __forceinline__ uint32_t sum_bit(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+__device__ __forceinline__ uint32_t carry_bit(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8); }
+
+// Number of set words among v[0..N) at every bit position, as bit planes (N = 3, 7 or 15: 2, 3 or 4 planes).
+template <int N>
+__device__ __forceinline__ void count_planes(const uint32_t *v, uint32_t *planes)
+{
+    if constexpr (N == 3) {
+        planes[0] = sum_bit(v[0], v[1], v[2]);
+        planes[1] = carry_bit(v[0], v[1], v[2]);
+    } else {
+        constexpr int H = (N - 1) / 2, P = N == 7 ? 2 : 3;      // two halves and one carry in
+        uint32_t a[P], b[P];
+        count_planes<H>(v, a);
+        count_planes<H>(v + H, b);
+        uint32_t carry = v[N - 1];
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            planes[i] = sum_bit(a[i], b[i], carry);
+            carry = carry_bit(a[i], b[i], carry);
+        }
+        planes[P] = carry;
+    }
+}
+
 template <int NTHR>   // boundaries the container can have: 3, 7 or 15
 __global__ void __launch_bounds__(kAssignThreads) assign_kernel(const uint16_t *__restrict__ w, const uint16_t *__restrict__ codebook,
                                                                 uint8_t *__restrict__ idx, int K, int ncent)
 {
-    __shared__ float thr[16];
+    constexpr int BITS = NTHR == 3 ? 2 : NTHR == 7 ? 3 : 4;
+    __shared__ uint32_t thr[16];
     const int n = blockIdx.x;          // rows on the x axis: N may exceed the y limit of a grid
+    const uint16_t *row_w = w + (size_t)n * K;
+    // the first two passes' weights are on the way while the boundaries are found
+    int k0 = (int)threadIdx.x * 8;     // K is a multiple of 256: 8 columns are all inside or all outside
+    uint4v next = {0u, 0u, 0u, 0u}, after = {0u, 0u, 0u, 0u};
+    if (k0 < K) next = stream_load(reinterpret_cast<const uint4v *>(row_w + k0));
+    if (k0 + kAssignCols < K) after = stream_load(reinterpret_cast<const uint4v *>(row_w + k0 + kAssignCols));
     if (threadIdx.x < NTHR) {
-        float u = 0.0f;
+        uint32_t limit = 0x7fffu;      // never passed: not in use, or NaN
         if ((int)threadIdx.x + 1 < ncent) {
             const uint16_t *row = codebook + (size_t)n * (NTHR + 1);
             const double m = 0.5 * (half_bits_to_double(row[threadIdx.x]) + half_bits_to_double(row[threadIdx.x + 1]));   // exact
@@ -51,61 +101,119 @@ __global__ void __launch_bounds__(kAssignThreads) assign_kernel(const uint16_t *
 #pragma unroll
             for (int it = 0; it < 3; ++it)            // walk up while h is not above m (stops at infinity)
                 if (!(half_bits_to_double(h) > m) && (h & 0x7fffu) != 0x7c00u) h = half_next_up(h);
-            u = (float)__builtin_bit_cast(_Float16, h);
+            if (h == 0) h = 0x8000u;                  // both zeros pass
+            if ((h & 0x7fffu) <= 0x7c00u) limit = (uint16_t)(ordered_keys(h)[0] - 1);   // one below the smallest key that passes
         }
-        thr[threadIdx.x] = u;
+        thr[threadIdx.x] = limit * 0x10001u;
     }
     __syncthreads();
+    key_pair limit[NTHR];
+#pragma unroll
+    for (int i = 0; i < NTHR; ++i) limit[i] = __builtin_bit_cast(key_pair, thr[i]);
     // the workgroup walks its row: the boundaries are found once per row
-    for (int k0 = (int)threadIdx.x * 8; k0 < K; k0 += kAssignCols) {   // K is a multiple of 256: 8 columns are all inside or all outside
-        const uint4v v = stream_load(reinterpret_cast<const uint4v *>(w + (size_t)n * K + k0));
-        float wf[8];
-        uint32_t cnt[8];
+    while (k0 < K) {
+        const uint4v v = next;
+        const int k = k0;
+        k0 += kAssignCols;
+        next = after;
+        if (k0 + kAssignCols < K) after = stream_load(reinterpret_cast<const uint4v *>(row_w + k0 + kAssignCols));
+        uint32_t bit[4][BITS];   // [register][index bit], in bits 15 and 31
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            wf[e] = (float)__builtin_bit_cast(_Float16, (uint16_t)(v[e >> 1] >> (16 * (e & 1))));
-            cnt[e] = 0;
-        }
+        for (int j = 0; j < 4; ++j) {
+            const key_pair key = ordered_keys(v[j]);
+            uint32_t above[NTHR];
 #pragma unroll
-        for (int i = 0; i < NTHR; ++i) {
-            if (i + 1 >= ncent) break;     // uniform
-            const float t = thr[i];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) cnt[e] += wf[e] >= t ? 1u : 0u;
+            for (int i = 0; i < NTHR; ++i) above[i] = __builtin_bit_cast(uint32_t, (key_pair)__builtin_elementwise_sub_sat(limit[i], key));
+            count_planes<NTHR>(above, bit[j]);
         }
         uint2v o;
-        o[0] = cnt[0] | (cnt[1] << 8) | (cnt[2] << 16) | (cnt[3] << 24);
-        o[1] = cnt[4] | (cnt[5] << 8) | (cnt[6] << 16) | (cnt[7] << 24);
-        stream_store(reinterpret_cast<uint2v *>(idx + (size_t)n * K + k0), o);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {   // bytes 0..3: the halves of registers 2 h and 2 h + 1; bit 7 of a byte of a plane is the flag
+            uint32_t word = 0;
+#pragma unroll
+            for (int b = BITS - 1; b >= 0; --b) {
+                const uint32_t plane = perm(bit[2 * h + 1][b], bit[2 * h][b], 0x07050301u) >> (BITS - 1 - b);
+                word = b == BITS - 1 ? plane : bfi(0x01010101u * (0x100u - (0x100u >> (BITS - 1 - b))), word, plane);   // the bits above this one's stay
+            }
+            o[h] = (word >> (8 - BITS)) & (0x01010101u * ((1u << BITS) - 1u));
+        }
+        *reinterpret_cast<uint2v *>(idx + (size_t)n * K + k) = o;
     }
 }
 
-// ---- cluster sizes: one wave per row, one private LDS counter per (bin, lane) ---------------------
-__global__ void __launch_bounds__(256) counts_kernel(const uint8_t *__restrict__ idx, uint32_t *__restrict__ counts, int N, int K, int slots)
+// ---- cluster sizes: one wave per row -----------------------------------------------------------------
+// 32 indices of a lane become four words of one bit each (bit planes); a cluster's members among them are the set
+// bits of one AND of the planes, counted by one v_bcnt per cluster: about 3 instructions per index.  Bound: HBM or
+// the last-level cache, 1 byte per index (11008 x 4096, 8 clusters: 18.6 us with a private LDS counter per lane and cluster,
+// now 9 us, 5 TB/s).
+// Sum over the lanes: while a lane holds several counters it hands half of them to its partner, then plain sums.
+template <int HELD, int OFF>
+__device__ __forceinline__ void fold_counters(uint32_t *c, int lane)
 {
-    __shared__ uint32_t hist[4][16][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = (int)blockIdx.x * 4 + wave;     // N is a multiple of 16: every wave has a row
+    if constexpr (OFF > 0) {
+        if constexpr (HELD > 1) {
+            const bool upper = (lane & OFF) != 0;
 #pragma unroll
-    for (int b = 0; b < 16; ++b) hist[wave][b][lane] = 0;
-    const uint8_t *row = idx + (size_t)n * K;
-    for (int k = lane * 16; k < K; k += 64 * 16) {
-        const uint4v v = *reinterpret_cast<const uint4v *>(row + k);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const uint32_t bin = (v[e >> 2] >> (8 * (e & 3))) & 15u;
-            hist[wave][bin][lane] += 1;          // private to this lane: no atomics needed
+            for (int b = 0; b < HELD / 2; ++b) {
+                const uint32_t mine = upper ? c[b + HELD / 2] : c[b], theirs = upper ? c[b] : c[b + HELD / 2];
+                c[b] = mine + __shfl_xor(theirs, OFF);
+            }
+            fold_counters<HELD / 2, OFF / 2>(c, lane);
+        } else {
+            c[0] += __shfl_xor(c[0], OFF);
+            fold_counters<1, OFF / 2>(c, lane);
         }
     }
-    for (int b = 0; b < slots; ++b) {
-        uint32_t c = hist[wave][b][lane];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off);
-        if (lane == 0) counts[(size_t)n * slots + b] = c;
-    }
 }
 
-// ---- merge decision: one thread per row ------------------------------------------------------------
+template <int SLOTS>   // 4, 8 or 16
+__global__ void __launch_bounds__(256) counts_kernel(const uint8_t *__restrict__ idx, uint32_t *__restrict__ counts, int K)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = (int)blockIdx.x * 4 + wave;     // N is a multiple of 16: every wave has a row
+    const uint8_t *row = idx + (size_t)n * K;
+    uint32_t c[SLOTS];
+#pragma unroll
+    for (int b = 0; b < SLOTS; ++b) c[b] = 0;
+    constexpr int GROUPS = 2;                     // groups of 32 indices a lane has in flight
+    for (int k0 = lane * 16; k0 < K; k0 += GROUPS * 2048) {
+        uint4v v[GROUPS][2];
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k = k0 + g * 2048 + h * 1024;   // 16 columns are all inside or all outside
+                v[g][h] = uint4v{0u, 0u, 0u, 0u};
+                if (k < K) v[g][h] = *reinterpret_cast<const uint4v *>(row + k);
+                else c[0] -= 16;                          // 16 zeros that are not there
+            }
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g) {
+            uint32_t p[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int d = 0; d < 8; ++d) {         // word d's bit j of every byte to bit d of every byte of plane j
+                const uint32_t word = v[g][d >> 2][d & 3];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t moved = d >= j ? word << (d >= j ? d - j : 0) : word >> (d >= j ? 0 : j - d);
+                    p[j] |= moved & (0x01010101u << d);
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < SLOTS; ++b) {
+                const uint32_t low = ((b & 1) ? p[0] : ~p[0]) & ((b & 2) ? p[1] : ~p[1]);
+                const uint32_t high = ((b & 4) ? p[2] : ~p[2]) & ((b & 8) ? p[3] : ~p[3]);
+                c[b] += __builtin_popcount(low & high);
+            }
+        }
+    }
+    fold_counters<SLOTS, 32>(c, lane);
+    // which counter a lane ended with: its top bits
+    constexpr int LOG = SLOTS == 4 ? 2 : SLOTS == 8 ? 3 : 4;
+    if ((lane & ((64 >> LOG) - 1)) == 0) counts[(size_t)n * SLOTS + (lane >> (6 - LOG))] = c[0];
+}
+
+// ---- merge ---------------------------------------------------------------------------------------
 // The pair with the smallest gap (gaps are exact in fp64; the lowest pair on equal gaps) becomes the
 // mean of the two weighted by their cluster sizes, correctly rounded to fp16 (ties to even).  A finite
 // fp16 number is an integer multiple of 2^-24 below 2^41 in magnitude and a cluster size is below 2^32,
@@ -136,13 +244,14 @@ __device__ uint16_t weighted_mean_half(uint16_t a, uint16_t b, uint32_t na, uint
     else if (cmp128(pa, pb) >= 0) { num = sub128(pa, pb); neg = sa; }
     else { num = sub128(pb, pa); neg = sb; }
     const uint64_t den = (uint64_t)na + nb;
-    // largest pattern h with units(h) * den <= num (the mean lies between the two centroids: h <= 0x7bff)
-    uint32_t lo = 0, hi = 0x7bffu;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1) >> 1;
-        if (cmp128(mul_64x64(half_units(mid), den), num) <= 0) lo = mid; else hi = mid - 1;
-    }
-    uint32_t h = lo;
+    // largest pattern h with units(h) * den <= num (the mean lies between the two centroids: h <= 0x7bff): the quotient in
+    // binary32 is off by less than 2^-20 of itself, so rounded to fp16 it is that pattern or the next one; one more on
+    // either side is tried
+    const float quotient = ((float)num.hi * 0x1p64f + (float)num.lo) * 0x1p-24f * __builtin_amdgcn_rcpf((float)den);
+    uint32_t h = __builtin_bit_cast(uint16_t, (_Float16)quotient) + 1u;
+    if (h > 0x7bffu) h = 0x7bffu;
+#pragma unroll 1
+    for (int it = 0; it < 3 && cmp128(mul_64x64(half_units(h), den), num) > 0; ++it) --h;   // units(0) is 0: stops there
     if (h < 0x7bffu) {   // nearer of h and h + 1: 2 * num against (units(h) + units(h + 1)) * den
         const U128 twice = add128(num, num);
         const int c = cmp128(twice, mul_64x64(half_units(h) + half_units(h + 1), den));
@@ -152,43 +261,83 @@ __device__ uint16_t weighted_mean_half(uint16_t a, uint16_t b, uint32_t na, uint
     return (uint16_t)(h | (neg ? 0x8000u : 0u));
 }
 
-__global__ void __launch_bounds__(256) merge_kernel(const uint16_t *__restrict__ cb_in, const uint32_t *__restrict__ counts,
-                                                    uint16_t *__restrict__ cb_out, uint8_t *__restrict__ merged, int N, int ncent, int slots)
+// Merge and re-numbering, one workgroup per kMergeRows rows.  One lane per row finds the pair; the
+// re-numbering (idx' = idx - (idx > a), four indices per 32-bit operation) needs nothing else, so the weighted mean, a long
+// serial chain for a few lanes of the first wave, comes after that wave's share of it and hides behind the other waves and
+// workgroups.  Bound: HBM, 2 bytes per index (11008 x 4096: pair and mean in a launch of their own, one thread per row,
+// 6.4 + 13.3 us; now 15.8 us).
+constexpr int kMergeRows = 8;    // N is a multiple of 16
+template <int SLOTS>   // 4, 8 or 16
+__global__ void __launch_bounds__(256) merge_kernel(const uint16_t *cb_in, const uint32_t *counts, const uint8_t *idx,
+                                                    uint16_t *cb_out, uint8_t *out, uint8_t *merged, int K, int ncent)
 {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    const uint16_t *src = cb_in + (size_t)n * slots;
-    int a = 0;
-    double best = half_bits_to_double(src[1]) - half_bits_to_double(src[0]);
-    for (int i = 1; i + 1 < ncent; ++i) {
-        const double g = half_bits_to_double(src[i + 1]) - half_bits_to_double(src[i]);
-        if (g < best) { best = g; a = i; }
-    }
-    const uint16_t nc = weighted_mean_half(src[a], src[a + 1], counts[(size_t)n * slots + a], counts[(size_t)n * slots + a + 1]);
-    uint16_t *dst = cb_out + (size_t)n * slots;
-    for (int i = 0; i < slots; ++i) {
-        uint16_t v = 0;
-        if (i < a) v = src[i];
-        else if (i == a) v = nc;
-        else if (i < ncent - 1) v = src[i + 1];
-        dst[i] = v;
-    }
-    merged[n] = (uint8_t)a;
-}
-
-// ---- re-numbering after a merge: idx' = idx - (idx > a), four indices per 32-bit operation -------
-__global__ void __launch_bounds__(256) remap_kernel(const uint8_t *__restrict__ idx, const uint8_t *__restrict__ merged,
-                                                    uint8_t *__restrict__ out, int K)
-{
-    const int n = blockIdx.x;
-    const int k0 = ((int)blockIdx.y * 256 + (int)threadIdx.x) * 16;
-    if (k0 >= K) return;
-    const uint32_t bias = (127u - merged[n]) * 0x01010101u;     // byte + bias has bit 7 set iff byte > a (bytes < 16)
-    const uint4v v = stream_load(reinterpret_cast<const uint4v *>(idx + (size_t)n * K + k0));
-    uint4v o;
+    __shared__ uint32_t pair[kMergeRows];
+    const int first = (int)blockIdx.x * kMergeRows;
+    // the rows of a workgroup are contiguous: 16 indices per thread and step, AHEAD steps on the way (the first ones
+    // while the pairs are found)
+    constexpr int AHEAD = 4;
+    const int pieces = K / 16, steps = (kMergeRows * pieces + 255 - (int)threadIdx.x) / 256;
+    const uint4v *src = reinterpret_cast<const uint4v *>(idx + (size_t)first * K) + threadIdx.x;
+    uint4v *dst = reinterpret_cast<uint4v *>(out + (size_t)first * K) + threadIdx.x;
+    uint4v v[AHEAD];
 #pragma unroll
-    for (int d = 0; d < 4; ++d) o[d] = v[d] - (((v[d] + bias) >> 7) & 0x01010101u);
-    stream_store(reinterpret_cast<uint4v *>(out + (size_t)n * K + k0), o);
+    for (int u = 0; u < AHEAD; ++u)
+        if (u < steps) v[u] = *(src + (size_t)u * 256);
+    const bool decides = threadIdx.x < kMergeRows;
+    const int n = first + (int)threadIdx.x;                     // a deciding lane's row
+    uint16_t cb[SLOTS];
+    uint32_t sizes[SLOTS];
+    int a = 0;
+    if (decides) {
+#pragma unroll
+        for (int i = 0; i < SLOTS / 4; ++i) {                   // the whole row at once
+            const uint2v c = *reinterpret_cast<const uint2v *>(cb_in + (size_t)n * SLOTS + 4 * i);
+            const uint4v m = *reinterpret_cast<const uint4v *>(counts + (size_t)n * SLOTS + 4 * i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { cb[4 * i + e] = (uint16_t)(c[e >> 1] >> (16 * (e & 1))); sizes[4 * i + e] = m[e]; }
+        }
+        double best = half_bits_to_double(cb[1]) - half_bits_to_double(cb[0]);
+#pragma unroll
+        for (int i = 1; i + 1 < SLOTS; ++i) {
+            const double g = half_bits_to_double(cb[i + 1]) - half_bits_to_double(cb[i]);
+            if (i + 1 < ncent && g < best) { best = g; a = i; }
+        }
+        pair[threadIdx.x] = (uint32_t)a;
+        merged[n] = (uint8_t)a;
+    }
+    __syncthreads();
+    const int rows_per_step = 256 / pieces, rest = 256 - rows_per_step * pieces;   // uniform
+    int row = (int)threadIdx.x / pieces, at = (int)threadIdx.x - row * pieces;
+    for (int s0 = 0; s0 < steps; s0 += AHEAD) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            if (s0 + u >= steps) break;
+            const uint32_t bias = (127u - pair[row]) * 0x01010101u;     // byte + bias has bit 7 set iff byte > a (bytes < 16)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) v[u][d] -= ((v[u][d] + bias) >> 7) & 0x01010101u;
+            dst[(size_t)(s0 + u) * 256] = v[u];
+            if (s0 + u + AHEAD < steps) v[u] = *(src + (size_t)(s0 + u + AHEAD) * 256);
+            row += rows_per_step;
+            at += rest;
+            if (at >= pieces) { at -= pieces; ++row; }
+        }
+    }
+    if (decides) {
+        uint16_t ca = 0, cc = 0;
+        uint32_t na = 0, nb = 0;
+#pragma unroll
+        for (int i = 0; i + 1 < SLOTS; ++i)
+            if (i == a) { ca = cb[i]; cc = cb[i + 1]; na = sizes[i]; nb = sizes[i + 1]; }
+        const uint16_t nc = weighted_mean_half(ca, cc, na, nb);
+#pragma unroll
+        for (int i = 0; i < SLOTS; ++i) {
+            uint16_t v = 0;
+            if (i < a) v = cb[i];
+            else if (i == a) v = nc;
+            else if (i < ncent - 1) v = cb[i + 1 < SLOTS ? i + 1 : i];
+            cb_out[(size_t)n * SLOTS + i] = v;
+        }
+    }
 }
 
 int launch_assign(const uint16_t *w, const uint16_t *codebook, int ncent, int N, int K, int bits, uint8_t *idx, void *stream)
@@ -202,18 +351,20 @@ int launch_assign(const uint16_t *w, const uint16_t *codebook, int ncent, int N,
 
 int launch_counts(const uint8_t *idx, int N, int K, int bits, uint32_t *counts, void *stream)
 {
-    hipLaunchKernelGGL(counts_kernel, dim3((unsigned)(N / 4)), dim3(256), 0, (hipStream_t)stream, idx, counts, N, K, 1 << bits);
+    const dim3 grid((unsigned)(N / 4)), block(256);
+    if (bits == 2) hipLaunchKernelGGL(counts_kernel<4>, grid, block, 0, (hipStream_t)stream, idx, counts, K);
+    else if (bits == 3) hipLaunchKernelGGL(counts_kernel<8>, grid, block, 0, (hipStream_t)stream, idx, counts, K);
+    else hipLaunchKernelGGL(counts_kernel<16>, grid, block, 0, (hipStream_t)stream, idx, counts, K);
     return (int)hipGetLastError();
 }
 
 int launch_merge(const uint16_t *cb_in, const uint32_t *counts, const uint8_t *idx_in, int ncent, int N, int K, int bits,
                  uint16_t *cb_out, uint8_t *idx_out, uint8_t *merged, void *stream)
 {
-    hipLaunchKernelGGL(merge_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, (hipStream_t)stream, cb_in, counts, cb_out, merged,
-                       N, ncent, 1 << bits);
-    if (hipError_t e = hipGetLastError()) return (int)e;
-    hipLaunchKernelGGL(remap_kernel, dim3((unsigned)N, (unsigned)((K + 4095) / 4096)), dim3(256), 0, (hipStream_t)stream, idx_in, merged,
-                       idx_out, K);
+    const dim3 grid((unsigned)(N / kMergeRows)), block(256);
+    if (bits == 2) hipLaunchKernelGGL(merge_kernel<4>, grid, block, 0, (hipStream_t)stream, cb_in, counts, idx_in, cb_out, idx_out, merged, K, ncent);
+    else if (bits == 3) hipLaunchKernelGGL(merge_kernel<8>, grid, block, 0, (hipStream_t)stream, cb_in, counts, idx_in, cb_out, idx_out, merged, K, ncent);
+    else hipLaunchKernelGGL(merge_kernel<16>, grid, block, 0, (hipStream_t)stream, cb_in, counts, idx_in, cb_out, idx_out, merged, K, ncent);
     return (int)hipGetLastError();
 }
 

@@ -53,6 +53,28 @@ def test_assign_indices_is_the_nearest_centroid(bits, ncent, shape):
     assert np.array_equal(got, expect)
 
 
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_assign_indices_at_the_ends_of_the_number_range(bits):
+    # every fp16 bit pattern as a weight (both zeros, subnormals, infinities, NaNs of either sign) against boundaries at
+    # zero, between neighbouring subnormals, of one sign only, and at the largest finite numbers
+    ncent = 1 << bits
+    half = lambda b: np.array(b, dtype=np.uint16).view(np.float16)
+    rows = [np.arange(ncent) - ncent // 2,                                          # 2^-24 steps around zero
+            (np.arange(ncent) - ncent // 2) * 2 + 1,                                # boundaries on fp16 numbers, zero among them
+            np.arange(ncent) + 0x7c00 - ncent]                                      # up to 65504
+    cb = np.zeros((16, ncent), dtype=np.float16)
+    for n in range(16):
+        r = rows[n % 3]
+        up = half(np.where(r < 0, 0x8000 - r, r).astype(np.uint16))
+        cb[n] = up if n % 2 == 0 else -up[::-1]
+    assert np.all(np.diff(cb.astype(np.float64), axis=1) > 0)
+    w = np.tile(np.arange(65536, dtype=np.uint16).view(np.float16), (16, 1))
+    got = lcd.lcd_assign_indices(to_dev(w), to_dev(cb), ncent, bits).cpu().numpy()
+    mid = (cb[:, 1:].astype(np.float64) + cb[:, :-1].astype(np.float64)) / 2
+    expect = (w.astype(np.float64)[:, :, None] > mid[:, None, :]).sum(axis=2)       # no comparison holds for a NaN
+    assert np.array_equal(got, expect)
+
+
 def test_assign_then_pack_then_product_reproduces_the_clustered_weights():
     # dense weights -> indices on the GPU -> the decode path; equals the oracle product on the
     # oracle's own assignment of the same weights
@@ -79,6 +101,50 @@ def test_cluster_counts_are_exact(bits, shape):
     idx[1, :] = (1 << bits) - 1               # one cluster holds a whole row
     got = lcd.lcd_cluster_counts(to_dev(idx), bits).cpu().numpy().view(np.uint32)
     assert np.array_equal(got, oracle.cluster_counts(idx, 1 << bits))
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("K", [256, 1280, 2048, 4096, 6400])
+def test_cluster_counts_with_indices_beyond_the_container(bits, K):
+    # K that leaves some or all of a lane's pieces empty; indices up to 15 that no cluster of a small container counts
+    idx = np.random.default_rng(K + bits).integers(0, 16, size=(16, K), dtype=np.uint8)
+    got = lcd.lcd_cluster_counts(to_dev(idx), bits).cpu().numpy().view(np.uint32)
+    assert np.array_equal(got, np.stack([(idx == i).sum(axis=1) for i in range(1 << bits)], axis=1))
+
+
+@pytest.mark.parametrize("K", [256, 2304, 4096, 8448])
+def test_merge_closest_row_lengths(K):
+    # rows of a workgroup shorter and longer than one step of its threads, and no multiple of it
+    N, bits, ncent = 32, 3, 7
+    cb = _row_codebooks(N, ncent, bits, K)
+    idx = np.random.default_rng(K).integers(0, ncent, size=(N, K), dtype=np.uint8)
+    counts = oracle.cluster_counts(idx, 1 << bits)
+    cb_ref, merged_ref, idx_ref = oracle.merge_closest_stored(cb, counts, idx, ncent)
+    cb_out, idx_out, merged = lcd.lcd_merge_closest(to_dev(cb), lcd.lcd_cluster_counts(to_dev(idx), bits), to_dev(idx), ncent, bits)
+    assert np.array_equal(merged.cpu().numpy(), merged_ref)
+    assert np.array_equal(idx_out.cpu().numpy(), idx_ref)
+    assert np.array_equal(cb_out.cpu().numpy().view(np.uint16), cb_ref.view(np.uint16))
+
+
+@pytest.mark.parametrize("bits,ncent", [(2, 3), (3, 8), (4, 9)])
+def test_merge_closest_means_over_the_whole_number_range(bits, ncent):
+    # centroids of any finite size (subnormals, opposite signs) and cluster sizes up to 2^32 - 1, none among them
+    N, K = 2048, 256
+    rng = np.random.default_rng(bits)
+    cb = np.zeros((N, 1 << bits), dtype=np.float16)
+    for n in range(N):
+        near = rng.integers(0, 0x7c00 - 64) if n % 2 else 0        # far apart, or a few steps from one another
+        pats = rng.integers(0, 0x7c00, size=4 * ncent) if n % 4 == 0 else near + rng.integers(0, 64, size=4 * ncent)
+        vals = np.unique((pats | (rng.integers(0, 2, size=4 * ncent) << 15)).astype(np.uint16).view(np.float16) + np.float16(0))
+        cb[n, :ncent] = np.sort(rng.choice(vals, size=ncent, replace=False))
+    idx = rng.integers(0, ncent, size=(N, K), dtype=np.uint8)
+    counts = (rng.integers(0, 1 << 32, size=(N, 1 << bits), dtype=np.uint64) >> rng.integers(0, 32, size=(N, 1 << bits), dtype=np.uint64)).astype(np.uint32)
+    counts[rng.random(counts.shape) < 0.1] = 0
+    cb_ref, merged_ref, idx_ref = oracle.merge_closest_stored(cb, counts, idx, ncent)
+    cb_out, idx_out, merged = lcd.lcd_merge_closest(to_dev(cb), to_dev(counts.view(np.int32)), to_dev(idx), ncent, bits)
+    assert np.array_equal(merged.cpu().numpy(), merged_ref)
+    assert np.array_equal(idx_out.cpu().numpy(), idx_ref)
+    assert np.array_equal(cb_out.cpu().numpy().view(np.uint16), cb_ref.view(np.uint16))
 
 
 @pytest.mark.parametrize("bits,ncent", [(2, 4), (2, 2), (3, 8), (3, 6), (4, 16), (4, 11)])
