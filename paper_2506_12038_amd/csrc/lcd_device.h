@@ -86,16 +86,46 @@ __device__ __forceinline__ Divisor make_divisor(float s, float s_q)
     return Divisor{-d, __builtin_fmaf(e, y0, y0)};
 }
 
-// The code is returned as an fp16 number: integers up to 128 are exact.
-__device__ __forceinline__ _Float16 quantise_one(uint16_t xbits, Divisor dv)
+// The clipped quotient of one half of a register (HALF 0: the low one), before the rounding to an integer: clipping first gives
+// the same code, the limits being integers.  v_fma_mix_f32 takes the fp16 operand as it is (no shift, no conversion), so
+// a quotient is five instructions and the clip one.
+template <int HALF>
+__device__ __forceinline__ float clipped_quotient(uint32_t x, Divisor dv)
 {
-    const float xf = (float)__builtin_bit_cast(_Float16, xbits);
-    float qt = xf * dv.y;
-    qt = __builtin_fmaf(__builtin_fmaf(dv.neg_d, qt, xf), dv.y, qt);
-    qt = __builtin_fmaf(__builtin_fmaf(dv.neg_d, qt, xf), dv.y, qt);
-    float r = __builtin_rintf(qt);
-    r = __builtin_fminf(__builtin_fmaxf(r, -128.0f), 127.0f);
-    return (_Float16)r;
+    float qt, e;
+    if (HALF == 0) asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(qt) : "v"(x), "v"(dv.y));
+    else asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(qt) : "v"(x), "v"(dv.y));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if (HALF == 0) asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[0,0,1]" : "=v"(e) : "v"(dv.neg_d), "v"(qt), "v"(x));
+        else asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(e) : "v"(dv.neg_d), "v"(qt), "v"(x));
+        qt = __builtin_fmaf(e, dv.y, qt);
+    }
+    return __builtin_amdgcn_fmed3f(qt, -128.0f, 127.0f);
+}
+// The code as an fp16 number: integers up to 128 are exact.
+template <int HALF>
+__device__ __forceinline__ _Float16 quantise_half(uint32_t x, Divisor dv) { return (_Float16)__builtin_rintf(clipped_quotient<HALF>(x, dv)); }
+// The codes of eight columns (four registers of two) as int8 numbers, and as fp16 numbers (HALVES): adding 1.5 * 2^23 rounds to an
+// integer, half to even, and leaves its two's complement in the low bits.
+template <bool HALVES>
+__device__ __forceinline__ uint2v quantise_bytes(uint4v x, const Divisor (&dv)[8], half8 &halves)
+{
+    constexpr float kMagic = 12582912.0f;
+    uint2v o;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        uint32_t r[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t xp = x[2 * h + (e >> 1)];
+            const float v = ((e & 1) ? clipped_quotient<1>(xp, dv[4 * h + e]) : clipped_quotient<0>(xp, dv[4 * h + e])) + kMagic;
+            r[e] = __builtin_bit_cast(uint32_t, v);
+            if (HALVES) halves[4 * h + e] = (_Float16)(v - kMagic);
+        }
+        o[h] = __builtin_amdgcn_perm(r[1], r[0], 0x0c0c0400u) | __builtin_amdgcn_perm(r[3], r[2], 0x04000c0cu);
+    }
+    return o;
 }
 
 // a ^ (b & c): one v_bitop3_b32.

@@ -500,25 +500,25 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_bucket_kernel(const uint32_t
         for (cur.sg = 0; cur.sg < nseg; ++cur.sg) {
             {   // smooth this thread's 8 activations of the segment (loaded one segment ago)
                 const bool in_k = wave_chunk(cur.sg, wave, lane >> 5) < kc;
+                Divisor dv[8];
+                if (I8 || quantised) {   // wave-uniform
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) dv[e] = make_divisor(e < 4 ? s0[e] : s1[e - 4], pb.act_scale);
+                }
 #pragma unroll
                 for (int t = 0; t < NTOK; ++t) {
                     half8 o;
-                    if (!quantised) {
+                    if constexpr (I8) {   // the codes as int8 numbers, one byte per column (a chunk past the layer's last is never used)
+                        *reinterpret_cast<uint2v *>(xs8 + t * kSegHalfs + 8 * threadIdx.x) = quantise_bytes<kHalfOps>(xv[t], dv, o);
+                        __builtin_amdgcn_sched_barrier(0);   // one token after the other: four at a time do not fit the registers
+                    } else if (!quantised) {
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
                             o[e] = !in_k ? (_Float16)0.0f : smooth_one((uint16_t)(xv[t][e >> 1] >> (16 * (e & 1))), e < 4 ? s0[e] : s1[e - 4]);
-                    } else {   // wave-uniform branch
+                    } else {
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
-                            o[e] = !in_k ? (_Float16)0.0f
-                                         : quantise_one((uint16_t)(xv[t][e >> 1] >> (16 * (e & 1))), make_divisor(e < 4 ? s0[e] : s1[e - 4], pb.act_scale));
-                    }
-                    if constexpr (I8) {   // the codes as int8 numbers, one byte per column
-                        int c[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) c[e] = (int)(float)o[e] & 0xff;
-                        const uint2v packed8 = {(uint32_t)(c[0] | c[1] << 8 | c[2] << 16 | c[3] << 24), (uint32_t)(c[4] | c[5] << 8 | c[6] << 16 | c[7] << 24)};
-                        *reinterpret_cast<uint2v *>(xs8 + t * kSegHalfs + 8 * threadIdx.x) = packed8;
+                            o[e] = !in_k ? (_Float16)0.0f : (e & 1) ? quantise_half<1>(xv[t][e >> 1], dv[e]) : quantise_half<0>(xv[t][e >> 1], dv[e]);
                     }
                     if constexpr (kHalfOps) *reinterpret_cast<half8 *>(&xs_lds[t * kSegHalfs + 8 * threadIdx.x]) = o;
                 }
@@ -605,9 +605,8 @@ __global__ __launch_bounds__(kQuantThreads) void transform_kernel(TransformBatch
             half8 o;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const uint16_t xb = (uint16_t)(v[i][e >> 1] >> (16 * (e & 1)));
-                if (quantised) o[e] = quantise_one(xb, dv[e]);
-                else o[e] = smooth_one(xb, e < 4 ? s0[e] : s1[e - 4]);   // rounds as the fused path does
+                if (quantised) o[e] = (e & 1) ? quantise_half<1>(v[i][e >> 1], dv[e]) : quantise_half<0>(v[i][e >> 1], dv[e]);
+                else o[e] = smooth_one((uint16_t)(v[i][e >> 1] >> (16 * (e & 1))), e < 4 ? s0[e] : s1[e - 4]);   // rounds as the fused path does
             }
             *reinterpret_cast<half8 *>(it.codes + (size_t)(m0 + i) * it.K + k0) = o;
         }

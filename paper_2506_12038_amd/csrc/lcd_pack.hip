@@ -215,9 +215,9 @@ __device__ __forceinline__ void smooth_tile(const uint16_t *__restrict__ x, cons
             const uint4v xv = xin[u];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const uint16_t xb = (uint16_t)(xv[e >> 1] >> (16 * (e & 1)));
                 const int slot = e < 4 ? 2 * e : 2 * (e - 4) + 1;
-                o[slot] = quantised ? quantise_one(xb, dv[e]) : smooth_with(xb, r[e]);
+                if (quantised) o[slot] = (e & 1) ? quantise_half<1>(xv[e >> 1], dv[e]) : quantise_half<0>(xv[e >> 1], dv[e]);
+                else o[slot] = smooth_with((uint16_t)(xv[e >> 1] >> (16 * (e & 1))), r[e]);
             }
         } else {
 #pragma unroll
