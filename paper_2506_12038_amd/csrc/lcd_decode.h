@@ -65,6 +65,7 @@ constexpr int kMaxTokenBlocks = 2;   // blocks it holds in registers: up to 32 t
 struct TokensVariant {
     const void *fn;
     int tiles;          // row tiles it holds at a time
+    int waves;          // waves of its workgroups
     size_t lds_bytes;
     int id;             // 0 .. kTokensVariants - 1
 };

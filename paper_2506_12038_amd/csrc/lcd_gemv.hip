@@ -789,7 +789,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     for (int i = 0; i < count; ++i) batch.p[i].wg_first = wg_begin[i];
     size_t lds;
     const void *fn;
-    int variant;
+    int variant, waves = kBW;
     if (!tokens_path) {
         lds = (size_t)MT * ((size_t)kBSeg * kTileCols * 2 + (size_t)kBW * kVisitTiles * 16 * 4) + (bits == 3 && int8_codes ? (size_t)kBSeg * kTileCols : 0);
         fn = bits == 3 ? (int8_codes ? (const void *)gemv_bucket_kernel<3, 1, true> : (const void *)gemv_bucket_kernel<3>)
@@ -804,13 +804,14 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
         const TokensVariant tv = tokens_variant(bits, blocks, most);
         lds = tv.lds_bytes;
         fn = tv.fn;
+        waves = tv.waves;
         variant = 12 + tv.id;
     }
     static PerDeviceFlags<12 + kTokensVariants> lds_raised;
     if (hipError_t e = raise_lds_limit_once(lds_raised, variant, fn, lds)) return (int)e;
     void *args[] = {&table.t[0], &table.t[1], &table.t[2], &table.t[3], &table.t[4], &table.t[5], &table.t[6], &table.t[7],
                     &batch, const_cast<int *>(&M)};   // the bucket kernel takes no M
-    if (hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(kBW * 64), args, lds, stream)) return (int)e;
+    if (hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(waves * 64), args, lds, stream)) return (int)e;
     return (int)hipGetLastError();
 }
 

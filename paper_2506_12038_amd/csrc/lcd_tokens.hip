@@ -6,11 +6,13 @@
 // 16 tokens are its columns, one dequantised operand serves every block.
 //
 // Work split.  A workgroup owns a contiguous run of row tiles (16 rows) of ONE layer and takes them
-// R at a time; its 8 waves split K, wave w takes the 256-column chunks w, w + 8, ...  Per chunk a
-// wave stages the activations of its 256 columns once (smoothing, Sec. 3.4, and the turn into operand
-// order through its own piece of LDS), then multiplies the chunk of every one of the R row tiles;
-// the accumulators stay in registers over all of K.  No wave waits for another before the end: one
-// barrier, then the 8 partial tiles are added in the order of the waves, rounded once and stored.
+// R at a time; its 8 waves split K, wave w takes the 256-column chunks w, w + 8, ...  (one row tile: 16 waves, which
+// hide one another's staging and latencies better: 7B block, 2 bits, 16 tokens 41.5 -> 39.4 us, 4 bits 60.7 -> 57.3.
+// With more row tiles the registers are not there for it, and the dequantiser bounds it anyway.)  Per chunk a wave stages
+// the activations of its 256 columns once (smoothing, Sec. 3.4, and the turn into operand order through its own piece of
+// LDS), then multiplies the chunk of every one of the R row tiles; the accumulators stay in registers over all of K.  No wave waits for another before the end: one
+// barrier, then the partial tiles are added, rounded once and stored.  An output is the sum, in order, of 8 sums of two:
+// chunks w, w + 16, ... and chunks w + 8, w + 24, ... -- two sets of accumulators of one wave, or one set of two waves.
 // The order of the additions of one output depends on K alone -- not on the grouping of layers,
 // on R or on the number of tokens -- so grouped, single and captured calls agree bit for bit.
 //
@@ -21,7 +23,7 @@
 // Measured against the kernel before it (K in segments, partial tiles of two row tiles exchanged through
 // LDS at a barrier after every second tile, no more than 16 tokens): 4096 x 11008, 3 bits, 3 tokens
 // 16.5 -> 9.8 us a call; blocks of 2, 3 and 4-bit layers (5120 / 13824), 6 tokens, 104 -> 72 us a block; 7B
-// block, 2 bits, 16 tokens 46 -> 42.5 us.
+// block, 2 bits, 16 tokens 46 -> 39.4 us.
 #include <hip/hip_runtime.h>
 #include "lcd_decode.h"
 
@@ -43,14 +45,15 @@ struct TokTile {
 template <int BITS> struct TokTables { typedef RowTables type; };
 template <> struct TokTables<4> { typedef RowTables4 type; };
 
-template <int BITS, int TB, int R>
-__global__ void __launch_bounds__(kBW * 64, 1) gemv_tokens_kernel(const uint32_t t0, const uint32_t t1, const uint32_t t2, const uint32_t t3,
+template <int BITS, int TB, int R, int WAVES>
+__global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32_t t0, const uint32_t t1, const uint32_t t2, const uint32_t t3,
                                                                    const uint32_t t4, const uint32_t t5, const uint32_t t6, const uint32_t t7,
                                                                    const BucketBatch batch, const int M)
 {
     constexpr uint32_t TBYTES = kTileRows * kTileCols * BITS / 8;
     constexpr int NC = BITS == 2 ? 4 : 8;
-    constexpr int D = R <= 2 ? 2 : 1;   // chunks whose packed words are loaded ahead
+    constexpr int D = R <= 2 && WAVES == kBW ? 2 : 1;   // chunks whose packed words are loaded ahead
+    constexpr int SETS = 2 * kBW / WAVES;         // accumulator sets of a wave (see the order of the additions above)
     constexpr int kWaveBytes = tokens_wave_bytes<TB, R>();
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // one piece per wave: its stage, in the end its partial tiles
 
@@ -146,7 +149,7 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_tokens_kernel(const uint32_t
         }
     };
 
-    float4v acc[R][TB];
+    float4v acc[SETS][R][TB];
     typename TokTables<BITS>::type tab[R];
     TokTile<BITS> P[D][R];
     auto tile_product = [&](const TokTile<BITS> &p, const typename TokTables<BITS>::type &t, float4v (&a)[TB]) {
@@ -178,7 +181,7 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_tokens_kernel(const uint32_t
 #pragma unroll
         for (int dd = 0; dd < D; ++dd)
 #pragma unroll
-            for (int r = 0; r < R; ++r) load_tile(P[dd][r], v0 + r, v1, wave + dd * kBW);
+            for (int r = 0; r < R; ++r) load_tile(P[dd][r], v0 + r, v1, wave + dd * WAVES);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const bool tv = v0 + r < v1;
@@ -198,25 +201,25 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_tokens_kernel(const uint32_t
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int b = 0; b < TB; ++b) acc[r][b] = float4v{0.f, 0.f, 0.f, 0.f};
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int i = 0; i < SETS; ++i) acc[i][r][b] = float4v{0.f, 0.f, 0.f, 0.f};
 
-        auto chunk_products = [&](TokTile<BITS> (&p)[R], int chunk) {
+        auto chunk_products = [&](TokTile<BITS> (&p)[R], float4v (&a)[R][TB], int chunk) {
             stage_x();
-            if (TB == 1) { load_s(chunk + kBW); load_x(chunk + kBW); }   // room for the next chunk's activations while this one multiplies
+            if (TB == 1) { load_s(chunk + WAVES); load_x(chunk + WAVES); }   // room for the next chunk's activations while this one multiplies
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (r > 0 && v0 + r >= v1) break;               // uniform
-                tile_product(p[r], tab[r], acc[r]);
-                load_tile(p[r], v0 + r, v1, chunk + D * kBW);
+                tile_product(p[r], tab[r], a[r]);
+                load_tile(p[r], v0 + r, v1, chunk + D * WAVES);
             }
-            if (TB > 1) { load_s(chunk + kBW); load_x(chunk + kBW); }    // into the registers the B operands leave
+            if (TB > 1) { load_s(chunk + WAVES); load_x(chunk + WAVES); }    // into the registers the B operands leave
         };
-        for (int c = wave; c < kc; c += D * kBW) {
-            chunk_products(P[0], c);
-            if (D == 2) {
-                if (c + kBW >= kc) break;
-                chunk_products(P[D - 1], c + kBW);
-            }
+        for (int c = wave; c < kc; c += 2 * WAVES) {
+            chunk_products(P[0], acc[0], c);
+            if (c + WAVES >= kc) break;
+            chunk_products(P[D - 1], acc[SETS - 1], c + WAVES);
         }
 
         // ---- partial tiles to LDS, one barrier, sum over the waves in order, one rounding, store
@@ -225,15 +228,20 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_tokens_kernel(const uint32_t
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int b = 0; b < TB; ++b)
-                *reinterpret_cast<float4v *>(&part[(r * TB + b) * 256 + j * 16 + 4 * q]) = acc[r][b];   // lane (q, j): rows 4q..4q+3 of token j
+                *reinterpret_cast<float4v *>(&part[(r * TB + b) * 256 + j * 16 + 4 * q]) = SETS == 2 ? acc[0][r][b] + acc[SETS - 1][r][b] : acc[0][r][b];   // lane (q, j): rows 4q..4q+3 of token j
         __syncthreads();
         const int n_tiles = v1 - v0, quads = n_tiles * 4;    // row quads of one token
-        for (int e = threadIdx.x; e < quads * M; e += kBW * 64) {
+        for (int e = threadIdx.x; e < quads * M; e += WAVES * 64) {
             const int m = e / quads, rest = e - m * quads, r = rest >> 2, rq = rest & 3;
             const float *src = reinterpret_cast<const float *>(smem) + (r * TB + (m >> 4)) * 256 + (m & 15) * 16 + 4 * rq;
-            float4v sum = *reinterpret_cast<const float4v *>(src);
+            auto pair_sum = [&](int w) {
+                float4v v = *reinterpret_cast<const float4v *>(src + w * (kWaveBytes / 4));
+                if (SETS == 1) v += *reinterpret_cast<const float4v *>(src + (w + kBW) * (kWaveBytes / 4));
+                return v;
+            };
+            float4v sum = pair_sum(0);
 #pragma unroll
-            for (int w = 1; w < kBW; ++w) sum += *reinterpret_cast<const float4v *>(src + w * (kWaveBytes / 4));
+            for (int w = 1; w < kBW; ++w) sum += pair_sum(w);
             typedef _Float16 half4 __attribute__((ext_vector_type(4)));
             half4 o;
 #pragma unroll
@@ -248,19 +256,19 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_tokens_kernel(const uint32_t
 // SIMD allow next to the B operands (32 per block), the staged activations and the tables.
 template <int BITS, int TB> struct TokensHeld { static constexpr int most = BITS == 4 ? (TB == 1 ? 4 : 3) : (TB == 1 ? 6 : 5); };
 
-template <int BITS, int TB, int R>
+template <int BITS, int TB, int R, int WAVES>
 static TokensVariant variant_of(int slot)
 {
-    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R>, R, (size_t)kBW * tokens_wave_bytes<TB, R>(),
+    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R, WAVES>, R, WAVES, (size_t)WAVES * tokens_wave_bytes<TB, R>(),
                          ((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 4 + slot};
 }
 
 template <int BITS, int TB>
 static TokensVariant pick_tiles(int tiles)
 {
-    if (tiles <= 1) return variant_of<BITS, TB, 1>(0);
-    if (tiles <= 2) return variant_of<BITS, TB, 2>(1);
-    return variant_of<BITS, TB, TokensHeld<BITS, TB>::most>(2);
+    if (tiles <= 1) return variant_of<BITS, TB, 1, 2 * kBW>(0);
+    if (tiles <= 2) return variant_of<BITS, TB, 2, kBW>(1);
+    return variant_of<BITS, TB, TokensHeld<BITS, TB>::most, kBW>(2);
 }
 
 template <int BITS>
