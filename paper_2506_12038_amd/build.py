@@ -24,12 +24,13 @@ FLAGS = [
 
 # lcd_gemm.hip, lcd_gemm_split.hip keep their accumulators in fixed AGPRs through inline assembly: the compiler
 # must not use AGPRs as spill space there.
-# lcd_gemv.hip, lcd_tokens.hip: the decode kernels' eight leading scalar arguments (the table of first workgroups) are
-# preloaded into scalar registers at wave start instead of being read from the argument segment.
+# lcd_gemv.hip, lcd_tokens.hip: the decode kernels' eleven leading arguments (thirteen words: the table of first
+# workgroups or a single layer, and the input the layers share) are preloaded into scalar registers at wave start
+# instead of being read from the argument segment.
 EXTRA = {"lcd_gemm.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_gemm_split.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
-         "lcd_gemv.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=8"],
-         "lcd_tokens.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=8"]}
+         "lcd_gemv.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"],
+         "lcd_tokens.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"]}
 
 
 def _compile(src: str, keep_asm: bool) -> Path:

@@ -35,10 +35,23 @@ struct BucketProblem {
     int x_ready;                  // tokens kernel: x already holds the smoothed activations / the codes (transform_kernel)
     int wg_first;                 // first workgroup of this layer
 };
-// The table of first workgroups (wg_begin[1..16], 16 bits each) also travels as eight leading scalar
-// kernel arguments: those are preloaded into scalar registers when a wave starts, so a workgroup
-// knows its layer without a load and the problem record is the only load between the kernel's
-// entry and its first index loads.  Number of table entries <= b, for b < 2^15 - 1:
+// What a workgroup needs first travels as leading kernel arguments: those are preloaded into scalar registers when a wave
+// starts, while a read of the argument segment takes 0.6 us (measured from a wave's entry).  The first eight words are the
+// table of first workgroups (wg_begin[1..16], 16 bits each), from which a workgroup finds its layer, or, in a launch of
+// a single layer, the layer itself (SingleLayer).  Then x, s and DecodeHead::word for layers that all read one input
+// (q, k, v or gate, up of a decoder block, and every single layer): the activations, which start the longest chain, are asked for
+// without waiting for the layer's record.
+// Measured, 7B blocks: 2 bits, 16 tokens 39.5 -> 37.1 us; 4 tokens of INT8 codes 32.4 -> 31.5; 3 bits, one token 34.6 -> 33.9.
+struct DecodeHead {
+    const uint16_t *x;   // input of all layers (shared)
+    const float *s;
+    uint32_t word;       // bits 0..21 K / 256, 22..27 tokens, then the flags
+};
+constexpr uint32_t kHeadShared = 1u << 28, kHeadReady = 1u << 29, kHeadSingle = 1u << 30;
+__device__ __forceinline__ int head_kc(uint32_t word) { return (int)(word & 0x3fffffu); }
+__device__ __forceinline__ int head_tokens(uint32_t word) { return (int)((word >> 22) & 63u); }
+
+// Number of table entries <= b, for b < 2^15 - 1:
 struct WgTable { uint32_t t[kMaxGroup / 2]; };
 __device__ __forceinline__ int layer_of_workgroup(uint32_t b, uint32_t t0, uint32_t t1, uint32_t t2, uint32_t t3,
                                                   uint32_t t4, uint32_t t5, uint32_t t6, uint32_t t7)
@@ -55,6 +68,42 @@ struct BucketBatch {
     BucketProblem p[kMaxGroup];
     int count;
 };
+
+// The input a workgroup's layer reads: from the leading arguments if the layers share it, else from the record.  (The
+// empty assembly statements keep the branches: as selects they would wait for the record on every path.)
+__device__ __forceinline__ void input_of(const BucketBatch &batch, int pi, uint32_t word, const uint16_t *&x, const float *&s, int &kc, int &ready)
+{
+    kc = head_kc(word);
+    ready = (word & kHeadReady) ? 1 : 0;
+    if (!(word & kHeadShared)) {
+        x = batch.p[pi].x;
+        s = batch.p[pi].s;
+        kc = batch.p[pi].kc;
+        ready = batch.p[pi].x_ready;
+        asm volatile("" : "+s"(x), "+s"(s), "+s"(kc), "+s"(ready));
+    }
+}
+// The rest of the layer: row tiles [ta, tb) are the workgroup's.
+struct LayerPart { const uint8_t *packed; const float *lut; int nt, ta, tb; };
+__device__ __forceinline__ LayerPart part_of(const BucketBatch &batch, int pi, uint32_t word, uint32_t b, uint32_t t0, uint32_t t1, uint32_t t2, uint32_t t3,
+                                             uint32_t t4, uint32_t t5, uint32_t t6)
+{
+    LayerPart l;
+    int li, base, extra;
+    if (word & kHeadSingle) {
+        l.packed = reinterpret_cast<const uint8_t *>((uint64_t)t1 << 32 | t0);
+        l.lut = reinterpret_cast<const float *>((uint64_t)t3 << 32 | t2);
+        l.nt = (int)t4; base = (int)t5; extra = (int)t6; li = (int)b;
+        asm volatile("" : "+s"(l.packed), "+s"(l.lut), "+s"(l.nt), "+s"(base), "+s"(extra));
+    } else {
+        l.packed = batch.p[pi].packed; l.lut = batch.p[pi].lutA;
+        l.nt = batch.p[pi].nt; base = batch.p[pi].tiles_base; extra = batch.p[pi].tiles_extra; li = (int)b - batch.p[pi].wg_first;
+        asm volatile("" : "+s"(l.packed), "+s"(l.lut), "+s"(l.nt), "+s"(base), "+s"(extra), "+s"(li));
+    }
+    l.ta = li * base + min(li, extra);
+    l.tb = l.ta + base + (li < extra ? 1 : 0);
+    return l;
+}
 
 // ---- tokens kernel (lcd_tokens.hip) ---------------------------------------------------------------
 constexpr int kTokenBlock = 16;      // tokens per block of the tokens kernel (the columns of one matrix instruction)

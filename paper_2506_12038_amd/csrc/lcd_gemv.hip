@@ -149,7 +149,7 @@ __device__ __forceinline__ void issue_step_loads(StepRegs<BITS> &r, const Cursor
 template <int BITS, int MT = 1, bool I8 = false, int NTOK = MT>
 __global__ void __launch_bounds__(kBW * 64, 1) gemv_bucket_kernel(const uint32_t t0, const uint32_t t1, const uint32_t t2, const uint32_t t3,
                                                                    const uint32_t t4, const uint32_t t5, const uint32_t t6, const uint32_t t7,
-                                                                   const BucketBatch batch)
+                                                                   const uint16_t *head_x, const float *head_s, const uint32_t head_word, const BucketBatch batch)
 {
     static_assert(MT == 1 || (MT == 2 && BITS == 2) || (MT == 4 && I8), "two tokens: 2-bit indices only; four: int8 operands only");
     static_assert(!I8 || BITS == 2 || MT == 1, "int8 operands: 2-bit indices, or one token at 3 bits");
@@ -176,24 +176,15 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_bucket_kernel(const uint32_t
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: keeps addresses scalar
     const int q = lane >> 4, j = lane & 15, bq = lane >> 4;
 
-    // which layer, which row tiles
-    // (entries past the last layer hold the total, so they never count: no loop over `count`)
-    const int pi = layer_of_workgroup(blockIdx.x, t0, t1, t2, t3, t4, t5, t6, t7);
-    const BucketProblem pb = batch.p[pi];
-    const int li = (int)blockIdx.x - pb.wg_first;
-    const int ta = li * pb.tiles_base + min(li, pb.tiles_extra);
-    const int tb = ta + pb.tiles_base + (li < pb.tiles_extra ? 1 : 0);
-    const int kc = pb.kc, nseg = (kc + kBSeg - 1) / kBSeg;
-    const bool quantised = pb.act_scale != 0.0f;               // wave-uniform
-    const float out_scale = quantised ? pb.act_scale : 1.0f;
-    const __amdgpu_buffer_rsrc_t rs_packed = make_rsrc(pb.packed, (uint32_t)pb.nt * (uint32_t)kc * TB);
-    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(pb.x, (uint32_t)NTOK * (uint32_t)kc * kTileCols * 2);
-    const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(pb.s, (uint32_t)kc * kTileCols * 4);
-    const __amdgpu_buffer_rsrc_t rs_lut = make_rsrc(pb.lutA, (uint32_t)pb.nt * 16 * NB * 4);
-
-    Cursor pf{}, cur{};
-    cursor_begin(pf, ta, tb);
-    cur = pf;
+    // which layer (entries past the last layer hold the total, so they never count: no loop over `count`), and its input
+    int pi = (head_word & kHeadSingle) ? 0 : layer_of_workgroup(blockIdx.x, t0, t1, t2, t3, t4, t5, t6, t7);
+    const uint16_t *x = head_x;
+    const float *s = head_s;
+    int kc, ready;
+    input_of(batch, pi, head_word, x, s, kc, ready);
+    const int nseg = (kc + kBSeg - 1) / kBSeg;
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(x, (uint32_t)NTOK * (uint32_t)kc * kTileCols * 2);
+    const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(s, (uint32_t)kc * kTileCols * 4);
 
     // Activations.  A segment is kBSeg*256 = 8 * (threads of the workgroup) columns, and thread t of
     // wave w smooths columns [8t, 8t+8) of it -- which lie in wave w's own two chunks.  So a wave
@@ -214,9 +205,22 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_bucket_kernel(const uint32_t
         s1 = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs_s, valid ? g * 32 + 16 : kOob, 0, 0));
     };
     load_x(0, true);
+    asm volatile("" ::: "memory");   // these loads first
+    const LayerPart part_l = part_of(batch, pi, head_word, blockIdx.x, t0, t1, t2, t3, t4, t5, t6);
+    const int nt = part_l.nt, ta = part_l.ta, tb = part_l.tb;
+    const __amdgpu_buffer_rsrc_t rs_packed = make_rsrc(part_l.packed, (uint32_t)nt * (uint32_t)kc * TB);
+    const __amdgpu_buffer_rsrc_t rs_lut = make_rsrc(part_l.lut, (uint32_t)nt * 16 * NB * 4);
+    Cursor pf{}, cur{};
+    cursor_begin(pf, ta, tb);
+    cur = pf;
     StepRegs<BITS> rs[kSets];   // always indexed by compile-time constants: four sets of registers
     issue_step_loads<BITS, true, MT>(rs[0], pf, rs_packed, rs_lut, kc, wave, lane); cursor_advance(pf, nseg);
     if (cur.done) return;   // no row tiles (the host never launches such a workgroup); the loads above moved nothing
+    asm volatile("" : "+s"(pi) : : "memory");   // what is needed last is asked for last
+    uint16_t *const y = batch.p[pi].y;
+    const float act_scale = batch.p[pi].act_scale;
+    const bool quantised = act_scale != 0.0f;               // wave-uniform
+    const float out_scale = quantised ? act_scale : 1.0f;
 
     uint4v A[MT][kBCH][NA];   // this wave's smoothed activations of the current segment, NA operands per chunk and token
     uint4v Aq[MT][kBCH][NQ];  // I8: the codes as int8 numbers
@@ -503,7 +507,7 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_bucket_kernel(const uint32_t
                 Divisor dv[8];
                 if (I8 || quantised) {   // wave-uniform
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) dv[e] = make_divisor(e < 4 ? s0[e] : s1[e - 4], pb.act_scale);
+                    for (int e = 0; e < 8; ++e) dv[e] = make_divisor(e < 4 ? s0[e] : s1[e - 4], act_scale);
                 }
 #pragma unroll
                 for (int t = 0; t < NTOK; ++t) {
@@ -553,7 +557,7 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_bucket_kernel(const uint32_t
                 float sum = 0.f;
 #pragma unroll
                 for (int w = 0; w < kBW; ++w) sum += part[t * kPartFloats + w * (kVisitTiles * 16) + e];
-                pb.y[(size_t)t * pb.nt * kTileRows + (size_t)cur.v0 * kTileRows + e] = __builtin_bit_cast(uint16_t, (_Float16)(sum * out_scale));
+                y[(size_t)t * nt * kTileRows + (size_t)cur.v0 * kTileRows + e] = __builtin_bit_cast(uint16_t, (_Float16)(sum * out_scale));
             }
         }
         cursor_next_visit(cur);
@@ -787,6 +791,18 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     WgTable table;
     for (int i = 0; i < kMaxGroup / 2; ++i) table.t[i] = (uint32_t)wg_begin[2 * i + 1] | (uint32_t)wg_begin[2 * i + 2] << 16;
     for (int i = 0; i < count; ++i) batch.p[i].wg_first = wg_begin[i];
+    DecodeHead head{batch.p[0].x, batch.p[0].s, (uint32_t)batch.p[0].kc | (uint32_t)M << 22};
+    bool shared = true;
+    for (int i = 1; i < count; ++i) shared = shared && batch.p[i].x == head.x && batch.p[i].s == head.s && batch.p[i].kc == batch.p[0].kc;
+    if (shared) head.word |= kHeadShared | (batch.p[0].x_ready ? kHeadReady : 0u);
+    if (count == 1) {
+        const BucketProblem &p = batch.p[0];
+        const uint64_t packed = (uint64_t)(uintptr_t)p.packed, lut = (uint64_t)(uintptr_t)p.lutA;
+        const uint32_t layer[7] = {(uint32_t)packed, (uint32_t)(packed >> 32), (uint32_t)lut, (uint32_t)(lut >> 32), (uint32_t)p.nt, (uint32_t)p.tiles_base,
+                                   (uint32_t)p.tiles_extra};
+        for (int i = 0; i < 7; ++i) table.t[i] = layer[i];
+        head.word |= kHeadSingle;
+    }
     size_t lds;
     const void *fn;
     int variant, waves = kBW;
@@ -810,7 +826,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     static PerDeviceFlags<12 + kTokensVariants> lds_raised;
     if (hipError_t e = raise_lds_limit_once(lds_raised, variant, fn, lds)) return (int)e;
     void *args[] = {&table.t[0], &table.t[1], &table.t[2], &table.t[3], &table.t[4], &table.t[5], &table.t[6], &table.t[7],
-                    &batch, const_cast<int *>(&M)};   // the bucket kernel takes no M
+                    &head.x, &head.s, &head.word, &batch};
     if (hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(waves * 64), args, lds, stream)) return (int)e;
     return (int)hipGetLastError();
 }

@@ -6,8 +6,8 @@
 // 16 tokens are its columns, one dequantised operand serves every block.
 //
 // Work split.  A workgroup owns a contiguous run of row tiles (16 rows) of ONE layer and takes them
-// R at a time; its 8 waves split K, wave w takes the 256-column chunks w, w + 8, ...  (one row tile: 16 waves, which
-// hide one another's staging and latencies better: 7B block, 2 bits, 16 tokens 41.5 -> 39.4 us, 4 bits 60.7 -> 57.3.
+// R at a time; its 8 waves split K, wave w takes the 256-column chunks w, w + 8, ...  (one row tile, and two with up to 16
+// tokens: 16 waves, which hide one another's staging and latencies better: 7B block, 2 bits, 16 tokens 41.5 -> 39.4 us, 4 bits 60.7 -> 57.3.
 // With more row tiles the registers are not there for it, and the dequantiser bounds it anyway.)  Per chunk a wave stages
 // the activations of its 256 columns once (smoothing, Sec. 3.4, and the turn into operand order through its own piece of
 // LDS), then multiplies the chunk of every one of the R row tiles; the accumulators stay in registers over all of K.  No wave waits for another before the end: one
@@ -23,7 +23,7 @@
 // Measured against the kernel before it (K in segments, partial tiles of two row tiles exchanged through
 // LDS at a barrier after every second tile, no more than 16 tokens): 4096 x 11008, 3 bits, 3 tokens
 // 16.5 -> 9.8 us a call; blocks of 2, 3 and 4-bit layers (5120 / 13824), 6 tokens, 104 -> 72 us a block; 7B
-// block, 2 bits, 16 tokens 46 -> 39.4 us.
+// block, 2 bits, 16 tokens 46 -> 37.1 us.
 #include <hip/hip_runtime.h>
 #include "lcd_decode.h"
 
@@ -48,7 +48,7 @@ template <> struct TokTables<4> { typedef RowTables4 type; };
 template <int BITS, int TB, int R, int WAVES>
 __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32_t t0, const uint32_t t1, const uint32_t t2, const uint32_t t3,
                                                                    const uint32_t t4, const uint32_t t5, const uint32_t t6, const uint32_t t7,
-                                                                   const BucketBatch batch, const int M)
+                                                                   const uint16_t *head_x, const float *head_s, const uint32_t head_word, const BucketBatch batch)
 {
     constexpr uint32_t TBYTES = kTileRows * kTileCols * BITS / 8;
     constexpr int NC = BITS == 2 ? 4 : 8;
@@ -62,20 +62,15 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     const int q = lane >> 4, j = lane & 15;
     const int kg = lane & 31, th = lane >> 5;   // staging: 8 columns [8 kg, +8) of the chunk, tokens th, th + 2, ...
 
-    const int pi = layer_of_workgroup(blockIdx.x, t0, t1, t2, t3, t4, t5, t6, t7);
-    const BucketProblem pb = batch.p[pi];
-    const int li = (int)blockIdx.x - pb.wg_first;
-    const int ta = li * pb.tiles_base + min(li, pb.tiles_extra);
-    const int tb_end = ta + pb.tiles_base + (li < pb.tiles_extra ? 1 : 0);
-    const int kc = pb.kc, K = kc * kTileCols, N = pb.nt * kTileRows;
-    const bool x_ready = pb.x_ready != 0;                       // wave-uniform
-    const float out_scale = pb.act_scale != 0.0f ? pb.act_scale : 1.0f;
-    const __amdgpu_buffer_rsrc_t rs_packed = make_rsrc(pb.packed, (uint32_t)pb.nt * (uint32_t)kc * TBYTES);
-    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(pb.x, (uint32_t)M * (uint32_t)K * 2);
-    const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(pb.s, (uint32_t)K * 4);
-    // byte-split tables: behind the bucket multipliers (2 and 3 bits), the whole table (4 bits)
-    const __amdgpu_buffer_rsrc_t rs_tb = make_rsrc(reinterpret_cast<const uint8_t *>(pb.lutA) + (BITS == 4 ? 0 : (size_t)N * NC * 4),
-                                                   (uint32_t)N * (BITS == 2 ? 8 : BITS == 3 ? 16 : 32));
+    int pi = (head_word & kHeadSingle) ? 0 : layer_of_workgroup(blockIdx.x, t0, t1, t2, t3, t4, t5, t6, t7);
+    const uint16_t *x = head_x;
+    const float *s = head_s;
+    int kc, ready;
+    input_of(batch, pi, head_word, x, s, kc, ready);
+    const bool x_ready = ready != 0;                           // wave-uniform
+    const int M = head_tokens(head_word), K = kc * kTileCols;
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(x, (uint32_t)M * (uint32_t)K * 2);
+    const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(s, (uint32_t)K * 4);
     _Float16 *stage = reinterpret_cast<_Float16 *>(smem + wave * kWaveBytes);
 
     // activations of one chunk as loaded: TB x 8 registers of 8 fp16 numbers (columns 8 kg .., tokens th + 2 mm).
@@ -105,6 +100,18 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
         sa = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs_s, cv ? k0 * 4 : kOob, 0, 0));
         sb = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs_s, cv ? k0 * 4 + 16 : kOob, 0, 0));
     };
+    load_s(wave);
+    load_x(wave);     // the longest dependency chain: ahead of the packed words
+    asm volatile("" ::: "memory");
+    const LayerPart l = part_of(batch, pi, head_word, blockIdx.x, t0, t1, t2, t3, t4, t5, t6);
+    const int ta = l.ta, tb_end = l.tb, N = l.nt * kTileRows;
+    asm volatile("" : "+s"(pi) : : "memory");   // what is needed last is asked for last
+    uint16_t *const y = batch.p[pi].y;
+    const float act_scale = batch.p[pi].act_scale, out_scale = act_scale != 0.0f ? act_scale : 1.0f;
+    const __amdgpu_buffer_rsrc_t rs_packed = make_rsrc(l.packed, (uint32_t)l.nt * (uint32_t)kc * TBYTES);
+    // byte-split tables: behind the bucket multipliers (2 and 3 bits), the whole table (4 bits)
+    const __amdgpu_buffer_rsrc_t rs_tb = make_rsrc(reinterpret_cast<const uint8_t *>(l.lut) + (BITS == 4 ? 0 : (size_t)N * NC * 4),
+                                                   (uint32_t)N * (BITS == 2 ? 8 : BITS == 3 ? 16 : 32));
     // packed words of the R row tiles from v0 (tiles past v1 and chunks past the layer's read zeros, no traffic)
     auto load_tile = [&](TokTile<BITS> &p, int tile, int v1, int chunk) {
         const bool v = tile < v1 && chunk < kc;
@@ -176,8 +183,6 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
 
     for (int v0 = ta; v0 < tb_end; v0 += R) {
         const int v1 = min(tb_end, v0 + R);
-        load_s(wave);
-        load_x(wave);     // the longest dependency chain: ahead of the packed words
 #pragma unroll
         for (int dd = 0; dd < D; ++dd)
 #pragma unroll
@@ -246,9 +251,14 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
             half4 o;
 #pragma unroll
             for (int u = 0; u < 4; ++u) o[u] = (_Float16)(sum[u] * out_scale);
-            *reinterpret_cast<half4 *>(pb.y + (size_t)m * N + (size_t)(v0 + r) * kTileRows + 4 * rq) = o;
+            *reinterpret_cast<half4 *>(y + (size_t)m * N + (size_t)(v0 + r) * kTileRows + 4 * rq) = o;
         }
-        if (v1 < tb_end) __syncthreads();   // the next tiles' stages overwrite the partial tiles
+        if (WAVES > kBW) break;             // (one pass: the host gives these variants no more row tiles than they hold)
+        if (v1 < tb_end) {
+            load_s(wave);
+            load_x(wave);
+            __syncthreads();                // the next tiles' stages overwrite the partial tiles
+        }
     }
 }
 
@@ -267,7 +277,7 @@ template <int BITS, int TB>
 static TokensVariant pick_tiles(int tiles)
 {
     if (tiles <= 1) return variant_of<BITS, TB, 1, 2 * kBW>(0);
-    if (tiles <= 2) return variant_of<BITS, TB, 2, kBW>(1);
+    if (tiles <= 2) return variant_of<BITS, TB, 2, TB == 1 ? 2 * kBW : kBW>(1);
     return variant_of<BITS, TB, TokensHeld<BITS, TB>::most, kBW>(2);
 }
 
