@@ -32,7 +32,6 @@ struct BucketProblem {
     int nt, kc;
     int tiles_base, tiles_extra;  // workgroup i of this layer owns tiles_base (+1 if i < tiles_extra) row tiles
     float act_scale;              // 0: fp16 activations x/s; s_q > 0: INT8 codes of Sec. 4.1, output scaled by s_q
-    int x_ready;                  // tokens kernel: x already holds the smoothed activations / the codes (transform_kernel)
     int wg_first;                 // first workgroup of this layer
 };
 // What a workgroup needs first travels as leading kernel arguments: those are preloaded into scalar registers when a wave
@@ -47,7 +46,7 @@ struct DecodeHead {
     const float *s;
     uint32_t word;       // bits 0..21 K / 256, 22..27 tokens, then the flags
 };
-constexpr uint32_t kHeadShared = 1u << 28, kHeadReady = 1u << 29, kHeadSingle = 1u << 30;
+constexpr uint32_t kHeadShared = 1u << 28, kHeadSingle = 1u << 29;
 __device__ __forceinline__ int head_kc(uint32_t word) { return (int)(word & 0x3fffffu); }
 __device__ __forceinline__ int head_tokens(uint32_t word) { return (int)((word >> 22) & 63u); }
 
@@ -71,16 +70,14 @@ struct BucketBatch {
 
 // The input a workgroup's layer reads: from the leading arguments if the layers share it, else from the record.  (The
 // empty assembly statements keep the branches: as selects they would wait for the record on every path.)
-__device__ __forceinline__ void input_of(const BucketBatch &batch, int pi, uint32_t word, const uint16_t *&x, const float *&s, int &kc, int &ready)
+__device__ __forceinline__ void input_of(const BucketBatch &batch, int pi, uint32_t word, const uint16_t *&x, const float *&s, int &kc)
 {
     kc = head_kc(word);
-    ready = (word & kHeadReady) ? 1 : 0;
     if (!(word & kHeadShared)) {
         x = batch.p[pi].x;
         s = batch.p[pi].s;
         kc = batch.p[pi].kc;
-        ready = batch.p[pi].x_ready;
-        asm volatile("" : "+s"(x), "+s"(s), "+s"(kc), "+s"(ready));
+        asm volatile("" : "+s"(x), "+s"(s), "+s"(kc));
     }
 }
 // The rest of the layer: row tiles [ta, tb) are the workgroup's.
@@ -118,7 +115,8 @@ struct TokensVariant {
     size_t lds_bytes;
     int id;             // 0 .. kTokensVariants - 1
 };
-constexpr int kTokensVariants = 3 * kMaxTokenBlocks * 4;
-TokensVariant tokens_variant(int bits, int blocks, int tiles);
+constexpr int kTokensVariants = 3 * kMaxTokenBlocks * 3 * 2;
+// ready: x holds the transformed activations in operand order (transform_kernel)
+TokensVariant tokens_variant(int bits, int blocks, int tiles, bool ready);
 
 }  // namespace lcd

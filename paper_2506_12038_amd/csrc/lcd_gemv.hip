@@ -180,8 +180,8 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_bucket_kernel(const uint32_t
     int pi = (head_word & kHeadSingle) ? 0 : layer_of_workgroup(blockIdx.x, t0, t1, t2, t3, t4, t5, t6, t7);
     const uint16_t *x = head_x;
     const float *s = head_s;
-    int kc, ready;
-    input_of(batch, pi, head_word, x, s, kc, ready);
+    int kc;
+    input_of(batch, pi, head_word, x, s, kc);
     const int nseg = (kc + kBSeg - 1) / kBSeg;
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(x, (uint32_t)NTOK * (uint32_t)kc * kTileCols * 2);
     const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(s, (uint32_t)kc * kTileCols * 4);
@@ -569,10 +569,10 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemv_bucket_kernel(const uint32_t
 // ---- activation transformation ahead of the tokens kernel (Sec. 4.1) -----------------------------
 // On the tokens kernel's route (2..16 tokens, and 4 bits) every workgroup of a layer stages the whole activation matrix, so whatever is
 // done to an activation is repeated by each of them.  This small kernel does it once per layer
-// and leaves the result, as fp16 numbers in the layout of x, in the workspace: the INT8 codes of
-// Eq. 10 (always: the divisions are expensive), or the smoothed activations x/s when K is large
-// enough for the saving to exceed the extra launch.  One thread takes 8 columns of a few tokens:
-// the divisor-only part of the division is shared by them.
+// and leaves the result in the workspace, as fp16 numbers in the order of the matrix operands ([chunk][step 8][quarter 4]
+// [token][8 columns, slots 0,4,1,5,2,6,3,7], so that the tokens kernel loads its B operands as they are: no smoothing, no
+// turn through LDS): the INT8 codes of Eq. 10 or the smoothed activations x/s, where the saving exceeds the extra launch.
+// One thread takes 8 columns of a few tokens: the divisor-only part of the division is shared by them.
 struct TransformItem {
     const uint16_t *x;
     const float *s;
@@ -585,7 +585,7 @@ struct TransformBatch {
 };
 constexpr int kQuantThreads = 64;
 constexpr int kQuantTokens = 4;
-constexpr int kPrepassMinK = 16384;   // widest layer of a group from which fp16 activations are smoothed ahead
+constexpr long long kAheadCodes = 50000, kAheadSmoothed = 300000;   // activations per workgroup beyond which they are transformed ahead
 
 __global__ __launch_bounds__(kQuantThreads) void transform_kernel(TransformBatch batch, int M)
 {
@@ -597,6 +597,8 @@ __global__ __launch_bounds__(kQuantThreads) void transform_kernel(TransformBatch
     Divisor dv[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) dv[e] = make_divisor(e < 4 ? s0[e] : s1[e - 4], quantised ? it.s_q : 1.0f);
+    // position of these 8 columns in operand order: chunk, then step g = (k % 64) / 8, then (k % 256) / 64
+    const int group = (k0 / kTileCols) * 32 + ((k0 % 64) / 8) * 4 + (k0 % kTileCols) / 64;
     // blockIdx.z: a group of kQuantTokens tokens (short dependent chains, all loads in flight together)
     const int m0 = (int)blockIdx.z * kQuantTokens;
     uint4v v[kQuantTokens];
@@ -609,16 +611,17 @@ __global__ __launch_bounds__(kQuantThreads) void transform_kernel(TransformBatch
             half8 o;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                if (quantised) o[e] = (e & 1) ? quantise_half<1>(v[i][e >> 1], dv[e]) : quantise_half<0>(v[i][e >> 1], dv[e]);
-                else o[e] = smooth_one((uint16_t)(v[i][e >> 1] >> (16 * (e & 1))), e < 4 ? s0[e] : s1[e - 4]);   // rounds as the fused path does
+                const int slot = e < 4 ? 2 * e : 2 * (e - 4) + 1;
+                if (quantised) o[slot] = (e & 1) ? quantise_half<1>(v[i][e >> 1], dv[e]) : quantise_half<0>(v[i][e >> 1], dv[e]);
+                else o[slot] = smooth_one((uint16_t)(v[i][e >> 1] >> (16 * (e & 1))), e < 4 ? s0[e] : s1[e - 4]);   // rounds as the fused path does
             }
-            *reinterpret_cast<half8 *>(it.codes + (size_t)(m0 + i) * it.K + k0) = o;
+            *reinterpret_cast<half8 *>(it.codes + ((size_t)group * M + m0 + i) * 8) = o;
         }
     }
 }
 
 // One launch for a group of decode problems: the bucket kernel for one token, the tokens kernel beyond.
-int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream_, bool force_prepass)
+int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream_)
 {
     hipStream_t stream = (hipStream_t)stream_;
     BucketBatch batch{};
@@ -631,13 +634,23 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     const int sparse_tokens = bits != 2 ? 1 : all_quantised ? 4 : 2;   // most tokens the bucket kernel takes
     const bool tokens_path = bits == 4 || M > sparse_tokens;
     const int MT = M <= 2 ? M : 4;                                      // token slots of the bucket kernel variant
-    // several tokens: quantised activations are made once, ahead of the product, and so are smoothed
-    // ones when the layers are wide (measured: the launch costs about 3.6 us; re-smoothing in every
-    // workgroup costs 1.9 us for K = 4096 / 11008 and 4.3 us for K = 8192 / 28672)
+    const int blocks = (M + kTokenBlock - 1) / kTokenBlock;
+    const int held = tokens_path ? tokens_variant(bits, blocks, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds
+    // Several tokens: every workgroup transforms its layer's activations once per pass over its row tiles; ahead of the
+    // product they are transformed once, at the price of a launch (3.6 us in a graph).  The line lies where that much work is
+    // saved, counted in activations per workgroup (tokens x widest K x passes).  Per block, ahead / in the product: INT8 codes, 3 bits,
+    // 7B, 4 tokens (16 k to 44 k) 46.9 / 42.1 us, 9 tokens (37 k to 99 k) 48.6 / 49.6, 16 tokens 51.0 / 58.3; 70B MLP, 4 tokens (98 k, 115 k)
+    // 81.2 / 91.2.  fp16: 70B MLP, 4 tokens 83.2 / 83.1, 16 tokens (393 k, 459 k) 94.2 / 96.7 with only the wider K ahead.
     const uint16_t *codes[kMaxGroup] = {};
     int widest = 0;
-    for (int i = 0; i < count; ++i) widest = items[i].K > widest ? items[i].K : widest;
-    if (tokens_path && (force_prepass || items[0].act_scale != 0.0f || widest >= kPrepassMinK)) {
+    long long all_tiles = 0;
+    for (int i = 0; i < count; ++i) {
+        widest = items[i].K > widest ? items[i].K : widest;
+        all_tiles += items[i].N / kTileRows;
+    }
+    const long long per_pass = (long long)num_cus() * held, passes = (all_tiles + per_pass - 1) / per_pass;
+    const long long transforms = (long long)M * widest * passes;
+    if (tokens_path && transforms > (items[0].act_scale != 0.0f ? kAheadCodes : kAheadSmoothed)) {
         // layers that read the same input (same x, s, K and quantisation step: q/k/v or gate/up of a decoder
         // block) share one transformed copy
         TransformBatch qb{};
@@ -666,7 +679,6 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
         p.x = codes[i] ? codes[i] : items[i].x; p.s = items[i].s; p.y = items[i].y;
         p.nt = items[i].N / kTileRows; p.kc = items[i].K / kTileCols;
         p.act_scale = items[i].act_scale;
-        p.x_ready = codes[i] != nullptr;
         tiles += p.nt;
     }
     // Workgroups per layer.  A layer's time is that of its slowest workgroup, in units of two-chunk
@@ -681,10 +693,8 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     const bool light_steps = bits == 2 && M == 1;   // one sparse pass per tile: a step is short next to the fixed costs
     const bool staged_ahead = tokens_path && codes[0] != nullptr;
     // the tokens kernel, times in us of a workgroup: a "round" is one chunk for each of its 8 waves
-    const int blocks = (M + kTokenBlock - 1) / kTokenBlock;
-    const int held = tokens_path ? tokens_variant(bits, blocks, INT_MAX).tiles : 1;
     const double round_tile = (bits == 2 ? 0.40 : bits == 3 ? 0.52 : 0.85) + 0.06 * blocks;
-    const double round_stage = 0.15 + 0.3 * blocks, pass = 1.5;
+    const double round_stage = staged_ahead ? 0.1 * blocks : 0.15 + 0.3 * blocks, pass = 1.5;
     auto layer_time = [&](int i, int n) {
         const int kc = batch.p[i].kc, t = (batch.p[i].nt + n - 1) / n;
         if (tokens_path) {
@@ -794,7 +804,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     DecodeHead head{batch.p[0].x, batch.p[0].s, (uint32_t)batch.p[0].kc | (uint32_t)M << 22};
     bool shared = true;
     for (int i = 1; i < count; ++i) shared = shared && batch.p[i].x == head.x && batch.p[i].s == head.s && batch.p[i].kc == batch.p[0].kc;
-    if (shared) head.word |= kHeadShared | (batch.p[0].x_ready ? kHeadReady : 0u);
+    if (shared) head.word |= kHeadShared;
     if (count == 1) {
         const BucketProblem &p = batch.p[0];
         const uint64_t packed = (uint64_t)(uintptr_t)p.packed, lut = (uint64_t)(uintptr_t)p.lutA;
@@ -817,7 +827,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     } else {
         int most = 1;
         for (int i = 0; i < count; ++i) most = std::max(most, (batch.p[i].nt + nwg[i] - 1) / nwg[i]);
-        const TokensVariant tv = tokens_variant(bits, blocks, most);
+        const TokensVariant tv = tokens_variant(bits, blocks, most, staged_ahead);
         lds = tv.lds_bytes;
         fn = tv.fn;
         waves = tv.waves;
@@ -863,15 +873,14 @@ int launch_gemv_noalloc(const void *packed, const void *lut, const uint16_t *x, 
     void *ws = nullptr;
     if (int e = static_scratch(&ws)) return e;
     GroupItem it{packed, lut, x, s, y, N, K, 0.0f};
-    // the activations always go through the scratch array on the several-token route, whatever K is
-    return launch_decode_group(&it, 1, M, bits, ws, stream_, true);
+    return launch_decode_group(&it, 1, M, bits, ws, stream_);
 }
 
 int launch_gemv(const void *packed, const void *lut, const uint16_t *x, const float *s, uint16_t *y,
                 int M, int N, int K, int bits, float act_scale, void *workspace, void *stream_)
 {
     GroupItem it{packed, lut, x, s, y, N, K, act_scale};
-    return launch_decode_group(&it, 1, M, bits, workspace, stream_, false);
+    return launch_decode_group(&it, 1, M, bits, workspace, stream_);
 }
 
 }  // namespace lcd

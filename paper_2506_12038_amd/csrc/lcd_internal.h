@@ -31,10 +31,8 @@ struct GroupItem {
 };
 constexpr int kDecodeTokens = 32;   // most tokens the decode kernels take (the decode entry points stop at 16)
 // one launch for `count` decode problems (1 <= M <= kDecodeTokens tokens each)
-// (workspace: decode_codes_bytes(M, K) per item, in item order, when M > 1 and act_scale != 0)
-// force_prepass: the activations are transformed ahead of the product (into the workspace) whenever the
-// several-token kernel runs, not only where that is the faster route
-int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream, bool force_prepass = false);
+// (workspace: decode_codes_bytes(M, K) per item: the transformed activations where they are made ahead of the product)
+int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream);
 inline size_t decode_codes_bytes(int M, int K) { return ((size_t)M * K * 2 + 255) / 256 * 256; }
 
 // Launchers implemented in the .hip files.  All return hipError_t as int (0 = success).

@@ -45,7 +45,7 @@ struct TokTile {
 template <int BITS> struct TokTables { typedef RowTables type; };
 template <> struct TokTables<4> { typedef RowTables4 type; };
 
-template <int BITS, int TB, int R, int WAVES>
+template <int BITS, int TB, int R, int WAVES, bool READY>
 __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32_t t0, const uint32_t t1, const uint32_t t2, const uint32_t t3,
                                                                    const uint32_t t4, const uint32_t t5, const uint32_t t6, const uint32_t t7,
                                                                    const uint16_t *head_x, const float *head_s, const uint32_t head_word, const BucketBatch batch)
@@ -65,15 +65,15 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     int pi = (head_word & kHeadSingle) ? 0 : layer_of_workgroup(blockIdx.x, t0, t1, t2, t3, t4, t5, t6, t7);
     const uint16_t *x = head_x;
     const float *s = head_s;
-    int kc, ready;
-    input_of(batch, pi, head_word, x, s, kc, ready);
-    const bool x_ready = ready != 0;                           // wave-uniform
+    int kc;
+    input_of(batch, pi, head_word, x, s, kc);
     const int M = head_tokens(head_word), K = kc * kTileCols;
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(x, (uint32_t)M * (uint32_t)K * 2);
     const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(s, (uint32_t)K * 4);
     _Float16 *stage = reinterpret_cast<_Float16 *>(smem + wave * kWaveBytes);
 
-    // activations of one chunk as loaded: TB x 8 registers of 8 fp16 numbers (columns 8 kg .., tokens th + 2 mm).
+    // activations of one chunk as loaded: TB x 8 registers of 8 fp16 numbers.  READY: register g of a block is the B operand of
+    // columns 64 q + 8 g .. of the lane's token.  Else: columns 8 kg .., tokens th + 2 mm.
     // The (token pair, chunk) part of the address is wave-uniform and travels as the scalar offset; lanes
     // of a token past the last one read zeros through an offset that is out of range.
     uint4v xr[TB][8];
@@ -82,6 +82,16 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     auto load_x = [&](int chunk) {
         uint32_t o = __builtin_amdgcn_readfirstlane((uint32_t)chunk * (kTileCols * 2));
         const int left = __builtin_amdgcn_readfirstlane(chunk < kc ? M : 0);   // tokens of this chunk
+        if constexpr (READY) {        // 16 bytes per token, the tokens of a (chunk, g, q) side by side
+            o = __builtin_amdgcn_readfirstlane((uint32_t)chunk * (uint32_t)M * (kTileCols * 2));
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+#pragma unroll
+                for (int g = 0; g < 8; ++g)
+                    xr[t][g] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, t * kTokenBlock + j < left ? (uint32_t)(q * M + t * kTokenBlock + j) * 16 : kOob,
+                                                                     left ? o + (uint32_t)(4 * g * M) * 16 : 0u, 0);
+            return;
+        }
         asm volatile("" : "+s"(o));   // one addition per pair instead of 8 TB addresses kept in registers
 #pragma unroll
         for (int t = 0; t < TB; ++t)
@@ -95,6 +105,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     };
     float4v sa, sb;
     auto load_s = [&](int chunk) {
+        if constexpr (READY) return;
         const bool cv = chunk < kc;
         const uint32_t k0 = (uint32_t)chunk * kTileCols + 8 * kg;
         sa = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs_s, cv ? k0 * 4 : kOob, 0, 0));
@@ -124,11 +135,18 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
 
     uint4v B[TB][8];       // B operands of the current chunk: lane (q, token j) holds columns 64 q + 8 g .. of its token
     auto stage_x = [&]() {
-        float rs[8];
-        if (!x_ready) {
+        if constexpr (READY) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) rs[e] = __builtin_amdgcn_rcpf(e < 4 ? sa[e] : sb[e - 4]);
+            for (int t = 0; t < TB; ++t)
+#pragma unroll
+                for (int g = 0; g < 8; ++g) B[t][g] = xr[t][g];
+            return;
         }
+        const bool quantised = act_scale != 0.0f;   // wave-uniform
+        float rs[8];                                // 1 / s, or the refined reciprocal of the quantiser's divisor
+        auto step_of = [&](int e) { return e < 4 ? sa[e] : sb[e - 4]; };
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rs[e] = quantised ? make_divisor(step_of(e), act_scale).y : __builtin_amdgcn_rcpf(step_of(e));
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
             // operand slot order 0,4,1,5,2,6,3,7 (the dequantiser pairs weight v with weight 4 + v); rows past the last
@@ -138,14 +156,19 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
                 if (t * kTokenBlock + 2 * mm >= M) break;      // uniform
                 const uint4v v = xr[t][mm];   // register i: columns 2i, 2i+1; result register i: columns i, 4+i
                 uint4v o;
-                if (!x_ready) {
+                if (!quantised) {
                     o[0] = smooth_pair<0, 0>(v[0], rs[0], v[2], rs[4]);
                     o[1] = smooth_pair<1, 1>(v[0], rs[1], v[2], rs[5]);
                     o[2] = smooth_pair<0, 0>(v[1], rs[2], v[3], rs[6]);
                     o[3] = smooth_pair<1, 1>(v[1], rs[3], v[3], rs[7]);
-                } else {   // x already holds the operands, only the slot order is left
-                    o[0] = __builtin_amdgcn_perm(v[2], v[0], 0x05040100u); o[1] = __builtin_amdgcn_perm(v[2], v[0], 0x07060302u);
-                    o[2] = __builtin_amdgcn_perm(v[3], v[1], 0x05040100u); o[3] = __builtin_amdgcn_perm(v[3], v[1], 0x07060302u);
+                } else {
+                    half8 c;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const Divisor dv{-(step_of(e) * act_scale), rs[e]};
+                        c[e < 4 ? 2 * e : 2 * (e - 4) + 1] = (e & 1) ? quantise_half<1>(v[e >> 1], dv) : quantise_half<0>(v[e >> 1], dv);
+                    }
+                    o = as_uint4(c);
                 }
                 *reinterpret_cast<uint4v *>(&stage[(2 * mm + th) * kStageStride + 8 * kg]) = o;
             }
@@ -266,30 +289,36 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
 // SIMD allow next to the B operands (32 per block), the staged activations and the tables.
 template <int BITS, int TB> struct TokensHeld { static constexpr int most = BITS == 4 ? (TB == 1 ? 4 : 3) : (TB == 1 ? 6 : 5); };
 
-template <int BITS, int TB, int R, int WAVES>
+template <int BITS, int TB, int R, int WAVES, bool READY>
 static TokensVariant variant_of(int slot)
 {
-    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R, WAVES>, R, WAVES, (size_t)WAVES * tokens_wave_bytes<TB, R>(),
-                         ((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 4 + slot};
+    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R, WAVES, READY>, R, WAVES, (size_t)WAVES * tokens_wave_bytes<TB, R>(),
+                         (((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 3 + slot) * 2 + (READY ? 1 : 0)};
 }
 
-template <int BITS, int TB>
+template <int BITS, int TB, bool READY>
 static TokensVariant pick_tiles(int tiles)
 {
-    if (tiles <= 1) return variant_of<BITS, TB, 1, 2 * kBW>(0);
-    if (tiles <= 2) return variant_of<BITS, TB, 2, TB == 1 ? 2 * kBW : kBW>(1);
-    return variant_of<BITS, TB, TokensHeld<BITS, TB>::most, kBW>(2);
+    if (tiles <= 1) return variant_of<BITS, TB, 1, 2 * kBW, READY>(0);
+    if (tiles <= 2) return variant_of<BITS, TB, 2, TB == 1 ? 2 * kBW : kBW, READY>(1);
+    return variant_of<BITS, TB, TokensHeld<BITS, TB>::most, kBW, READY>(2);
+}
+
+template <int BITS, bool READY>
+static TokensVariant pick_blocks(int blocks, int tiles)
+{
+    return blocks <= 1 ? pick_tiles<BITS, 1, READY>(tiles) : pick_tiles<BITS, 2, READY>(tiles);
 }
 
 template <int BITS>
-static TokensVariant pick_blocks(int blocks, int tiles)
+static TokensVariant pick(int blocks, int tiles, bool ready)
 {
-    return blocks <= 1 ? pick_tiles<BITS, 1>(tiles) : pick_tiles<BITS, 2>(tiles);
+    return ready ? pick_blocks<BITS, true>(blocks, tiles) : pick_blocks<BITS, false>(blocks, tiles);
 }
 
-TokensVariant tokens_variant(int bits, int blocks, int tiles)
+TokensVariant tokens_variant(int bits, int blocks, int tiles, bool ready)
 {
-    return bits == 2 ? pick_blocks<2>(blocks, tiles) : bits == 3 ? pick_blocks<3>(blocks, tiles) : pick_blocks<4>(blocks, tiles);
+    return bits == 2 ? pick<2>(blocks, tiles, ready) : bits == 3 ? pick<3>(blocks, tiles, ready) : pick<4>(blocks, tiles, ready);
 }
 
 }  // namespace lcd

@@ -36,6 +36,24 @@ def test_gemm_q8_matches_the_quantised_oracle(bits, M, shape):
     assert_parity(y.cpu().numpy(), Y, Q8_TOL)
 
 
+@pytest.mark.parametrize("q8", [True, False])
+@pytest.mark.parametrize("bits,M,N,K", [(3, 4, 48, 12288), (3, 5, 48, 12288), (4, 1, 16, 49920), (4, 1, 16, 50176), (2, 31, 64, 1536), (2, 31, 64, 2304),
+                                        (3, 32, 32, 9216), (3, 32, 32, 9472), (4, 17, 16, 17920)])
+def test_activations_transformed_in_and_ahead_of_the_product(bits, M, N, K, q8):
+    # the tokens kernel on either side of the line between transforming the activations itself and loading them in
+    # operand order: one token block and two, ragged, a last round of chunks that not every wave has
+    layer = synth.make_layer(3, 0, N, K, bits, M, seed_offset=N + K + M + 5)
+    s_q = _step(layer)
+    packed = lcd.lcd_pack_indices(to_dev(layer["idx"]), bits)
+    lut = lcd.lcd_build_lut(to_dev(layer["codebook"]), bits)
+    if q8:
+        y = lcd.lcd_lut_gemm_q8(packed, lut, to_dev(layer["x"]), to_dev(layer["s"]), s_q, N, bits)
+        assert_parity(y.cpu().numpy(), oracle.quantised_lut_matmul(layer["codebook"], layer["idx"], layer["x"], layer["s"], s_q, bits), Q8_TOL)
+    else:
+        y = lcd.lcd_lut_gemm(packed, lut, to_dev(layer["x"]), to_dev(layer["s"]), N, bits)
+        assert_parity(y.cpu().numpy(), oracle.lut_matmul(layer["codebook"], layer["idx"], layer["x"], layer["s"], bits), TOL)
+
+
 def test_gemm_q8_full_width_2048_tokens_sampled():
     # M = 2048 on a 7B-shaped layer: every row for sampled tokens, every token for sampled rows
     import torch
