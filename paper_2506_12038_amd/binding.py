@@ -9,7 +9,6 @@ from __future__ import annotations
 
 import ctypes
 from pathlib import Path
-from typing import Optional
 
 _PKG = Path(__file__).resolve().parent
 LIB_PATH = _PKG / "liblcd.so"
@@ -110,17 +109,32 @@ def _check(status: int) -> None:
         raise LcdError(status, lib.lcd_status_string(status).decode(), lib.lcd_last_error_string().decode())
 
 
-def _stream(stream) -> Optional[int]:
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+_torch = None
+_raw_stream = None     # device index -> handle of its current stream, without a Stream object
 
 
-def _dev(t, dtype, name):
-    if not t.is_cuda or not t.is_contiguous() or t.dtype != dtype:
+def _torch_module():
+    global _torch, _raw_stream
+    if _torch is None:
+        import torch
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _torch = torch
+    return _torch
+
+
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _torch_module()
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _dev(t, dtype, name) -> int:
+    if not t.is_cuda or t.dtype is not dtype or not t.is_contiguous():
         raise TypeError(f"{name}: expected a contiguous CUDA tensor of dtype {dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def lcd_version() -> int:
@@ -145,7 +159,7 @@ def lcd_workspace_bytes(M: int, N: int, K: int, bits: int) -> int:
 
 def lcd_pack_indices(idx, bits: int, out=None, stream=None):
     """idx: CUDA uint8 [N, K] -> packed CUDA uint8 [N*K*bits/8]."""
-    import torch
+    torch = _torch_module()
     lib = load_library()
     N, K = idx.shape
     nbytes = lib.lcd_packed_bytes(N, K, bits)
@@ -157,7 +171,7 @@ def lcd_pack_indices(idx, bits: int, out=None, stream=None):
 
 
 def lcd_unpack_indices(packed, N: int, K: int, bits: int, stream=None):
-    import torch
+    torch = _torch_module()
     lib = load_library()
     idx = torch.empty((N, K), dtype=torch.uint8, device=packed.device)
     _check(lib.lcd_unpack_indices(_dev(packed, torch.uint8, "packed"), N, K, bits, _dev(idx, torch.uint8, "idx"),
@@ -193,7 +207,7 @@ def lcd_unpack_indices_host(packed, N: int, K: int, bits: int):
 
 def lcd_build_lut(codebook, bits: int, stream=None):
     """codebook: CUDA float16 [N, 2**bits] -> opaque CUDA uint8 table."""
-    import torch
+    torch = _torch_module()
     lib = load_library()
     N = codebook.shape[0]
     if codebook.shape[1] != (1 << bits):
@@ -205,30 +219,31 @@ def lcd_build_lut(codebook, bits: int, stream=None):
     return lut
 
 
-def _product(fn_name, packed, lut, x, s, N, bits, y, workspace, stream):
-    import torch
-    lib = load_library()
+def _product(fn, step, packed, lut, x, s, N, bits, y, workspace, stream):
+    """fn: the library's entry point; step: () or (s_q,)."""
+    torch = _torch_module()
     M, K = x.shape
     if y is None:
         y = torch.empty((M, N), dtype=torch.float16, device=x.device)
     if workspace is None:
-        workspace = torch.empty(max(lib.lcd_workspace_bytes(M, N, K, bits), 256), dtype=torch.uint8, device=x.device)
-    _check(getattr(lib, fn_name)(
-        _dev(packed, torch.uint8, "packed"), _dev(lut, torch.uint8, "lut"), _dev(x, torch.float16, "x"),
-        _dev(s, torch.float32, "s"), _dev(y, torch.float16, "y"), M, N, K, bits,
-        _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(stream)))
+        workspace = torch.empty(max(_lib.lcd_workspace_bytes(M, N, K, bits), 256), dtype=torch.uint8, device=x.device)
+    half, byte = torch.float16, torch.uint8
+    status = fn(_dev(packed, byte, "packed"), _dev(lut, byte, "lut"), _dev(x, half, "x"), _dev(s, torch.float32, "s"), *step,
+                _dev(y, half, "y"), M, N, K, bits, _dev(workspace, byte, "workspace"), workspace.numel(), _stream(stream))
+    if status:
+        _check(status)
     return y
 
 
 def lcd_lut_gemv(packed, lut, x, s, N: int, bits: int, y=None, workspace=None, stream=None):
     """Decode path, x: CUDA float16 [M<=16, K] -> y float16 [M, N]."""
-    return _product("lcd_lut_gemv", packed, lut, x, s, N, bits, y, workspace, stream)
+    return _product(load_library().lcd_lut_gemv, (), packed, lut, x, s, N, bits, y, workspace, stream)
 
 
 def lcd_lut_gemv_noalloc(packed, lut, x, s, N: int, bits: int, y, stream=None):
     """lcd_lut_gemv without a workspace: the library's own static device array serves as scratch.
     The caller brings y (this wrapper allocates nothing either)."""
-    import torch
+    torch = _torch_module()
     M, K = x.shape
     _check(load_library().lcd_lut_gemv_noalloc(
         _dev(packed, torch.uint8, "packed"), _dev(lut, torch.uint8, "lut"), _dev(x, torch.float16, "x"),
@@ -238,32 +253,17 @@ def lcd_lut_gemv_noalloc(packed, lut, x, s, N: int, bits: int, y, stream=None):
 
 def lcd_lut_gemv_q8(packed, lut, x, s, s_q: float, N: int, bits: int, y=None, workspace=None, stream=None):
     """Decode path with the INT8 input transformation in front: y = s_q * sum_k q_k * C[n][idx], M <= 16."""
-    return _product_q8("lcd_lut_gemv_q8", packed, lut, x, s, s_q, N, bits, y, workspace, stream)
+    return _product(load_library().lcd_lut_gemv_q8, (float(s_q),), packed, lut, x, s, N, bits, y, workspace, stream)
 
 
 def lcd_lut_gemm_q8(packed, lut, x, s, s_q: float, N: int, bits: int, y=None, workspace=None, stream=None):
     """Prefill path with the INT8 input transformation in front (any M)."""
-    return _product_q8("lcd_lut_gemm_q8", packed, lut, x, s, s_q, N, bits, y, workspace, stream)
-
-
-def _product_q8(fn_name, packed, lut, x, s, s_q, N, bits, y, workspace, stream):
-    import torch
-    lib = load_library()
-    M, K = x.shape
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=x.device)
-    if workspace is None:
-        workspace = torch.empty(max(lib.lcd_workspace_bytes(M, N, K, bits), 256), dtype=torch.uint8, device=x.device)
-    _check(getattr(lib, fn_name)(
-        _dev(packed, torch.uint8, "packed"), _dev(lut, torch.uint8, "lut"), _dev(x, torch.float16, "x"),
-        _dev(s, torch.float32, "s"), float(s_q), _dev(y, torch.float16, "y"), M, N, K, bits,
-        _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(stream)))
-    return y
+    return _product(load_library().lcd_lut_gemm_q8, (float(s_q),), packed, lut, x, s, N, bits, y, workspace, stream)
 
 
 def lcd_lut_gemm(packed, lut, x, s, N: int, bits: int, y=None, workspace=None, stream=None):
     """Prefill path, x: CUDA float16 [M, K] -> y float16 [M, N]."""
-    return _product("lcd_lut_gemm", packed, lut, x, s, N, bits, y, workspace, stream)
+    return _product(load_library().lcd_lut_gemm, (), packed, lut, x, s, N, bits, y, workspace, stream)
 
 
 class GemvGroup:
@@ -276,7 +276,7 @@ class GemvGroup:
     """
 
     def __init__(self, problems, bits: int, workspace=None, s_q=None):
-        import torch
+        torch = _torch_module()
         lib = load_library()
         self.count = len(problems)
         self._bits_arr = None
@@ -296,9 +296,9 @@ class GemvGroup:
             if x.shape[0] != M:
                 raise ValueError("all problems of a group share M")
             K = x.shape[1]
-            arr[i] = _Problem(_dev(packed, torch.uint8, "packed").value, _dev(lut, torch.uint8, "lut").value,
-                              _dev(x, torch.float16, "x").value, _dev(s, torch.float32, "s").value,
-                              _dev(y, torch.float16, "y").value, N, K)
+            arr[i] = _Problem(_dev(packed, torch.uint8, "packed"), _dev(lut, torch.uint8, "lut"),
+                              _dev(x, torch.float16, "x"), _dev(s, torch.float32, "s"),
+                              _dev(y, torch.float16, "y"), N, K)
         self._arr = arr
         self._s_q = None
         if s_q is not None:
@@ -311,7 +311,7 @@ class GemvGroup:
         self.workspace = workspace if workspace is not None else torch.empty(need, dtype=torch.uint8, device=problems[0][2].device)
 
     def __call__(self, stream=None):
-        import torch
+        torch = _torch_module()
         ws = _dev(self.workspace, torch.uint8, "workspace")
         if self._bits_arr is not None:
             _check(load_library().lcd_lut_gemv_grouped_mixed(self._arr, self._bits_arr, self.count, self.M, ws,
@@ -329,7 +329,7 @@ class GemmGroup:
     problems = [(packed, lut, x, s, y, N), ...] with one token count and one index width."""
 
     def __init__(self, problems, bits: int, workspace=None, s_q=None):
-        import torch
+        torch = _torch_module()
         lib = load_library()
         self.count, self.bits = len(problems), bits
         self._keep = list(problems)
@@ -343,9 +343,9 @@ class GemmGroup:
         for i, (packed, lut, x, s, y, N) in enumerate(problems):
             if x.shape[0] != self.M:
                 raise ValueError("all problems of a group share M")
-            arr[i] = _Problem(_dev(packed, torch.uint8, "packed").value, _dev(lut, torch.uint8, "lut").value,
-                              _dev(x, torch.float16, "x").value, _dev(s, torch.float32, "s").value,
-                              _dev(y, torch.float16, "y").value, N, x.shape[1])
+            arr[i] = _Problem(_dev(packed, torch.uint8, "packed"), _dev(lut, torch.uint8, "lut"),
+                              _dev(x, torch.float16, "x"), _dev(s, torch.float32, "s"),
+                              _dev(y, torch.float16, "y"), N, x.shape[1])
         self._arr = arr
         need = lib.lcd_workspace_bytes_gemm_grouped(arr, self.count, self.M, bits)
         if need == 0:
@@ -353,7 +353,7 @@ class GemmGroup:
         self.workspace = workspace if workspace is not None else torch.empty(need, dtype=torch.uint8, device=problems[0][2].device)
 
     def __call__(self, stream=None):
-        import torch
+        torch = _torch_module()
         ws = _dev(self.workspace, torch.uint8, "workspace")
         if self._s_q is None:
             _check(load_library().lcd_lut_gemm_grouped(self._arr, self.count, self.M, self.bits, ws, self.workspace.numel(), _stream(stream)))
@@ -378,7 +378,7 @@ def lcd_lut_gemv_grouped(problems, bits: int, workspace=None, stream=None):
 
 def lcd_assign_indices(w, codebook, ncent: int, bits: int, stream=None):
     """w: CUDA float16 [N, K], codebook: CUDA float16 [N, 2**bits] -> CUDA uint8 [N, K] nearest-centroid indices."""
-    import torch
+    torch = _torch_module()
     N, K = w.shape
     if tuple(codebook.shape) != (N, 1 << bits):
         raise ValueError("codebook must be [N, 2**bits]")
@@ -390,7 +390,7 @@ def lcd_assign_indices(w, codebook, ncent: int, bits: int, stream=None):
 
 def lcd_cluster_counts(idx, bits: int, stream=None):
     """idx: CUDA uint8 [N, K] -> CUDA int32 [N, 2**bits] cluster sizes (the bit patterns are uint32)."""
-    import torch
+    torch = _torch_module()
     N, K = idx.shape
     counts = torch.empty((N, 1 << bits), dtype=torch.int32, device=idx.device)
     _check(load_library().lcd_cluster_counts(_dev(idx, torch.uint8, "idx"), N, K, bits, _dev(counts, torch.int32, "counts"),
@@ -400,7 +400,7 @@ def lcd_cluster_counts(idx, bits: int, stream=None):
 
 def lcd_merge_closest(codebook, counts, idx, ncent: int, bits: int, idx_out=None, stream=None):
     """Merge the two closest centroids of every row; returns (codebook_out, idx_out, merged)."""
-    import torch
+    torch = _torch_module()
     N, K = idx.shape
     cb_out = torch.empty_like(codebook)
     if idx_out is None:

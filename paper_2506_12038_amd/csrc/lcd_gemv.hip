@@ -774,7 +774,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     }
     // Workgroups are dispatched in the order of their ids, the last of a full grid almost 1 us after the
     // first: the layers whose workgroups have the most to do take the lowest ids.
-    {
+    if (count > 1) {
         int order[kMaxGroup];
         double t[kMaxGroup];
         for (int i = 0; i < count; ++i) { order[i] = i; t[i] = layer_time(i, nwg[i]); }
