@@ -19,6 +19,8 @@
 //     double buffered; every wave reads its B operands from LDS (16 bytes per lane,
 //     conflict-free) through a 4-register rotating window.
 // Each decoded A operand is used for 4 token blocks, each B operand for 2 row pairs.
+// The last tiles of a launch may be cut in two of 128 rows (one pair per wave) so that they spread over more compute units;
+// every output's additions keep their order.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include "lcd_gemm_common.h"
@@ -68,28 +70,31 @@ __device__ __forceinline__ uint4v read_b(uint32_t base)
     return v;
 }
 // Decoded A operands of one packed word: [pair][k-step of the word].
-struct WordOps { uint4v op[kGemmPairs][2]; };
+template <int PAIRS> struct WordOps { uint4v op[PAIRS][2]; };
 
 // One packed word per pair (16 weights per lane) = two k-steps x 4 token blocks = 8 matrix steps
-// of 2 MFMAs.  The word's operands `cur` were decoded during the previous word; each matrix step
-// also decodes one eighth of the NEXT word (word DN of `rn`) into `nxt`, so that vector and
+// of PAIRS MFMAs.  The word's operands `cur` were decoded during the previous word; each matrix step
+// also decodes one eighth of the NEXT words (word DN of `rn`) into `nxt`, so that vector and
 // matrix instructions alternate in every wave's stream instead of coming in bursts (two waves of
 // a SIMD leave a barrier in phase; with bursts both would decode, then both would multiply).
 // COPY: the step also issues its share of the next stage's global -> LDS copy.
 // On entry the B window holds steps 0..2 of this word; on exit steps 0..2 of the next word of the
 // chunk (the caller primes it again after the last word).
-template <int BITS, int D, int DN, bool COPY>
-__device__ __forceinline__ void gemm_word(const WordOps &cur, WordOps &nxt, const GemmTileRegs<BITS, kGemmPairs> &rn,
-                                          const HighBits (&hbn)[kGemmPairs], const typename GemmTables<BITS>::type (&tb)[kGemmPairs],
+template <int BITS, int PAIRS, int D, int DN, bool COPY>
+__device__ __forceinline__ void gemm_word(const WordOps<PAIRS> &cur, WordOps<PAIRS> &nxt, const GemmTileRegs<BITS, PAIRS> &rn,
+                                          const HighBits (&hbn)[PAIRS], const typename GemmTables<BITS>::type (&tb)[PAIRS],
                                           uint32_t bbase, BWindow &bw,
                                           const uint8_t *copy_src, uint8_t *copy_dst, int wave, int lane)
 {
 #define LCD_GEMM_FENCE __builtin_amdgcn_sched_barrier(0);
-    uint32_t sel = 0, pool = 0;
+    uint32_t sel = 0, pool = 0, lo = 0, hi = 0, o0, o1;
+    /* quarter Q of the next words is decoded by matrix steps EACH * Q .. EACH * Q + EACH - 1 */
+    constexpr int EACH = 2 / PAIRS;
 #define LCD_GEMM_STEP(ST)                                                                                   \
     {                                                                                                       \
-        constexpr int st = ST, a = st >> 2, blk = st & 3, nx = st + 3, np = st >> 2, nt4 = st & 3;          \
-        uint32_t lo, hi, o0, o1;                                                                            \
+        constexpr int st = ST, a = st >> 2, blk = st & 3, nx = st + 3;                                      \
+        constexpr int qt = st / EACH, qn = st == 7 ? 0 : (st + 1) / EACH;                                   \
+        constexpr bool first = st % EACH == 0, last = (st + 1) % EACH == 0;                                 \
         /* prefetch step st+3 into the slot that step st-1 used */                                          \
         if (nx < 8) bw.w[nx & 3] = read_b<2 * D + (nx >> 2), (nx & 3)>(bbase);                              \
         else if (D < 3) bw.w[nx & 3] = read_b<(2 * D + 2) & 7, (nx - 8) & 3>(bbase);                        \
@@ -102,12 +107,14 @@ __device__ __forceinline__ void gemm_word(const WordOps &cur, WordOps &nxt, cons
         /* quarter st, then the selector of quarter st+1, then the interleave: dependent instructions   */ \
         /* stay a few issue slots apart.                                                                 */ \
         if (COPY && copy_src) stage_copy(copy_src, copy_dst, wave, lane, st, 1);                            \
-        gemm_lookup<BITS>(sel, pool, tb[np], lo, hi);                                                       \
+        if (first) gemm_lookup<BITS>(sel, pool, tb[qt >> 2], lo, hi);                                       \
         LCD_GEMM_FENCE                                                                                      \
-        mfma_acc<4 + blk>(cur.op[1][a], bw.w[st & 3]);                                                      \
-        if (st < 7) gemm_select<BITS, DN, (st + 1) & 3>(rn, (st + 1) >> 2, hbn[(st + 1) >> 2], sel, pool);  \
-        decode_interleave(lo, hi, o0, o1);                                                                  \
-        nxt.op[np][0][nt4] = o0; nxt.op[np][1][nt4] = o1;                                                   \
+        if constexpr (PAIRS == 2) mfma_acc<4 + blk>(cur.op[PAIRS - 1][a], bw.w[st & 3]);                    \
+        if (last) {                                                                                         \
+            if (st < 7) gemm_select<BITS, DN, (qn & 3)>(rn, qn >> 2, hbn[qn >> 2], sel, pool);              \
+            decode_interleave(lo, hi, o0, o1);                                                              \
+            nxt.op[qt >> 2][0][qt & 3] = o0; nxt.op[qt >> 2][1][qt & 3] = o1;                               \
+        }                                                                                                   \
         LCD_GEMM_FENCE                                                                                      \
     }
     LCD_GEMM_STEP(0) LCD_GEMM_STEP(1) LCD_GEMM_STEP(2) LCD_GEMM_STEP(3)
@@ -116,8 +123,9 @@ __device__ __forceinline__ void gemm_word(const WordOps &cur, WordOps &nxt, cons
 }
 
 
-// One output tile (row block bx, token block by) of one layer: the whole life of a workgroup.
-template <int BITS>
+// One output tile (row block bx of 128 * PAIRS rows, token block by) of one layer: the whole life of a workgroup.
+// PAIRS 1: half a tile, the same additions in the same order for every output.
+template <int BITS, int PAIRS>
 __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, const uint8_t *__restrict__ lutB, const uint8_t *__restrict__ xs,
                                           uint16_t *__restrict__ y, int M, int Mpad, int N, int K, int bx, int by, uint8_t *lds,
                                           float out_scale)   // 1, or the quantisation step when xs holds INT8 codes (Eq. 11)
@@ -128,7 +136,7 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: keeps addresses scalar
     const int kc = K / kTileCols, nt = N / kTileRows;
     const int rgrp = wave & (kGemmRowGroups - 1), khalf = wave >> 2;     // row group and chunk half of this wave
-    const int t0 = (bx * kGemmRowGroups + rgrp) * (2 * kGemmPairs);      // first row tile of this wave
+    const int t0 = (bx * kGemmRowGroups + rgrp) * (2 * PAIRS);           // first row tile of this wave
     const int tb0 = by * kGemmTokBlks;                                   // first 32-token block of this workgroup
     const int boff = lane * 16;                                           // lane's 16 bytes inside a 1 KiB operand block
     const __amdgpu_buffer_rsrc_t packed = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(packed_), 0, (uint32_t)nt * (uint32_t)kc * TB, 0x00020000);
@@ -137,43 +145,43 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
     const size_t chunk_stride = (size_t)(Mpad >> 5) * 16 * 1024;
     const uint8_t *xs_base = xs + (size_t)tb0 * 16 * 1024;
 
-    typename GemmTables<BITS>::type tb[kGemmPairs];
+    typename GemmTables<BITS>::type tb[PAIRS];
     load_gemm_tables<BITS>(tb, lutB, t0, nt, lane);
     zero_accs();
 
-    GemmTileRegs<BITS, kGemmPairs> r0, r1;
+    GemmTileRegs<BITS, PAIRS> r0, r1;
     load_gemm_tiles<BITS>(r0, packed, t0, nt, kc, 0, khalf, lane);
     stage_copy(xs_base, lds, wave, lane, 0, 8);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
-    auto high_bits = [&](const GemmTileRegs<BITS, kGemmPairs> &r, HighBits (&hb)[kGemmPairs]) {
+    auto high_bits = [&](const GemmTileRegs<BITS, PAIRS> &r, HighBits (&hb)[PAIRS]) {
 #pragma unroll
-        for (int p = 0; p < kGemmPairs; ++p) {
+        for (int p = 0; p < PAIRS; ++p) {
             hb[p] = HighBits{0u, 0u};
             if (BITS == 3) hb[p] = regroup_high(r.hi[p]);
         }
     };
 
     BWindow bw;
-    WordOps wa, wb;          // operands of the current / next word, swapping roles word by word
-    HighBits hb[kGemmPairs], hbn[kGemmPairs];
+    WordOps<PAIRS> wa, wb;          // operands of the current / next word, swapping roles word by word
+    HighBits hb[PAIRS], hbn[PAIRS];
     // Chunk c is computed from LDS stage c&1 and register set r; word D's matrix steps decode word
     // D+1, the last word's decode the first word of chunk c+1 (set rn, loaded at the top of chunk
     // c).  The copy of chunk c+1's stage is issued during word 0 (the other stage was released by
     // the barrier that ended chunk c-1) and has the whole chunk to land: one wait + one barrier
     // per chunk, after which the B window is primed from the new stage.
-    auto compute = [&](const GemmTileRegs<BITS, kGemmPairs> &r, const GemmTileRegs<BITS, kGemmPairs> &rn, const uint8_t *stage,
+    auto compute = [&](const GemmTileRegs<BITS, PAIRS> &r, const GemmTileRegs<BITS, PAIRS> &rn, const uint8_t *stage,
                        uint8_t *other_stage, const uint8_t *copy_src) {
         const uint32_t bbase = lds_address(stage) + khalf * 8 * 1024 + boff;
         const uint32_t obase = lds_address(other_stage) + khalf * 8 * 1024 + boff;
-        gemm_word<BITS, 0, 1, true>(wa, wb, r, hb, tb, bbase, bw, copy_src, other_stage, wave, lane);
-        gemm_word<BITS, 1, 2, false>(wb, wa, r, hb, tb, bbase, bw, nullptr, nullptr, wave, lane);
-        gemm_word<BITS, 2, 3, false>(wa, wb, r, hb, tb, bbase, bw, nullptr, nullptr, wave, lane);
+        gemm_word<BITS, PAIRS, 0, 1, true>(wa, wb, r, hb, tb, bbase, bw, copy_src, other_stage, wave, lane);
+        gemm_word<BITS, PAIRS, 1, 2, false>(wb, wa, r, hb, tb, bbase, bw, nullptr, nullptr, wave, lane);
+        gemm_word<BITS, PAIRS, 2, 3, false>(wa, wb, r, hb, tb, bbase, bw, nullptr, nullptr, wave, lane);
         high_bits(rn, hbn);
-        gemm_word<BITS, 3, 0, false>(wb, wa, rn, hbn, tb, bbase, bw, nullptr, nullptr, wave, lane);
+        gemm_word<BITS, PAIRS, 3, 0, false>(wb, wa, rn, hbn, tb, bbase, bw, nullptr, nullptr, wave, lane);
 #pragma unroll
-        for (int p = 0; p < kGemmPairs; ++p) hb[p] = hbn[p];
+        for (int p = 0; p < PAIRS; ++p) hb[p] = hbn[p];
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();   // the next stage has landed for every wave, and every wave is done with this one
         bw.w[0] = read_b<0, 0>(obase);
@@ -190,7 +198,7 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
     }
     high_bits(r0, hb);
 #pragma unroll
-    for (int p = 0; p < kGemmPairs; ++p) {
+    for (int p = 0; p < PAIRS; ++p) {
         if constexpr (BITS == 4) decode_word4(r0.lo[p][0], r0.hi4[p][0], tb[p], wa.op[p][0], wa.op[p][1]);
         else decode_word<BITS, 0>(r0.lo[p][0], hb[p], tb[p], wa.op[p][0], wa.op[p][1]);
     }
@@ -206,8 +214,8 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
     }
 
     // The two waves of a row group hold partial sums over the two halves of every chunk.  Each keeps
-    // one 32-row pair and hands the other pair's four accumulators to its partner through LDS (the
-    // stages are free now): per row group two 16 KiB areas, area h read by the wave with khalf == h,
+    // one 32-row pair (half a tile: two token blocks of the only pair) and hands the other accumulators to its partner
+    // through LDS (the stages are free now): per row group two 16 KiB areas, area h read by the wave with khalf == h,
     // [accumulator 4][register quad 4][lane] float4.
     // The accumulator reads below are assembly text too: the distance the hardware requires between a
     // matrix instruction's register write and a vector instruction's read of it (19 wait states for
@@ -222,8 +230,14 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) area_out[(slot * 4 + rg) * 64 + lane] = float4v{v[4 * rg], v[4 * rg + 1], v[4 * rg + 2], v[4 * rg + 3]};
     };
-    if (khalf == 0) { put_acc(read_acc<4>(), 0); put_acc(read_acc<5>(), 1); put_acc(read_acc<6>(), 2); put_acc(read_acc<7>(), 3); }
-    else            { put_acc(read_acc<0>(), 0); put_acc(read_acc<1>(), 1); put_acc(read_acc<2>(), 2); put_acc(read_acc<3>(), 3); }
+    constexpr int KEPT = 2 * PAIRS;   // accumulators (token blocks) a wave keeps
+    if constexpr (PAIRS == 2) {
+        if (khalf == 0) { put_acc(read_acc<4>(), 0); put_acc(read_acc<5>(), 1); put_acc(read_acc<6>(), 2); put_acc(read_acc<7>(), 3); }
+        else            { put_acc(read_acc<0>(), 0); put_acc(read_acc<1>(), 1); put_acc(read_acc<2>(), 2); put_acc(read_acc<3>(), 3); }
+    } else {
+        if (khalf == 0) { put_acc(read_acc<2>(), 0); put_acc(read_acc<3>(), 1); }
+        else            { put_acc(read_acc<0>(), 0); put_acc(read_acc<1>(), 1); }
+    }
     __syncthreads();
 
     // Sum of the two halves, rounded once to fp16.  Accumulator register r of lane l is row
@@ -238,7 +252,7 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
     typedef _Float16 half4 __attribute__((ext_vector_type(4)));
     constexpr int kOutStride = 32 * 2 + 16;   // bytes per token row of the tile (16-byte aligned, spreads the banks)
     uint8_t *tile_out = reinterpret_cast<uint8_t *>(area_in);
-    uint2v outv[4][4];
+    uint2v outv[KEPT][4];
     auto sum_acc = [&](const float16v &own, int slot) {
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) {
@@ -249,26 +263,31 @@ __device__ __forceinline__ void gemm_tile(const uint8_t *__restrict__ packed_, c
             outv[slot][rg] = __builtin_bit_cast(uint2v, o);
         }
     };
-    if (khalf == 0) { sum_acc(read_acc<0>(), 0); sum_acc(read_acc<1>(), 1); sum_acc(read_acc<2>(), 2); sum_acc(read_acc<3>(), 3); }
-    else            { sum_acc(read_acc<4>(), 0); sum_acc(read_acc<5>(), 1); sum_acc(read_acc<6>(), 2); sum_acc(read_acc<7>(), 3); }
+    if constexpr (PAIRS == 2) {
+        if (khalf == 0) { sum_acc(read_acc<0>(), 0); sum_acc(read_acc<1>(), 1); sum_acc(read_acc<2>(), 2); sum_acc(read_acc<3>(), 3); }
+        else            { sum_acc(read_acc<4>(), 0); sum_acc(read_acc<5>(), 1); sum_acc(read_acc<6>(), 2); sum_acc(read_acc<7>(), 3); }
+    } else {
+        if (khalf == 0) { sum_acc(read_acc<0>(), 0); sum_acc(read_acc<1>(), 1); }
+        else            { sum_acc(read_acc<2>(), 0); sum_acc(read_acc<3>(), 1); }
+    }
     // every read above must precede the writes below, which reuse the same bytes: the wait orders
     // them for the compiler too (the two sides use different vector types)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int blk = 0; blk < 4; ++blk) {
+    for (int blk = 0; blk < KEPT; ++blk) {
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg)
             *reinterpret_cast<uint2v *>(tile_out + (blk * 32 + tok) * kOutStride + (8 * rg + 4 * lh) * 2) = outv[blk][rg];
     }
     asm volatile("" ::: "memory");               // LDS operations of one wave complete in order; keep the compiler's order too
     const int r4 = lane & 3;                       // which 8 rows of the pair's 32
-    const int tile_first = t0 + 2 * khalf;         // first 16-row tile of this wave's pair
+    const int tile_first = t0 + (PAIRS == 2 ? 2 * khalf : 0);   // first 16-row tile of this wave's pair
     const bool rows_ok = tile_first + (r4 >> 1) < nt;   // N is a multiple of 16: 8 rows are all inside or all outside
 #pragma unroll
-    for (int it = 0; it < kGemmTokens / 16; ++it) {
+    for (int it = 0; it < 2 * KEPT; ++it) {
         const int tk = it * 16 + (lane >> 2);
         const uint4v v = *reinterpret_cast<const uint4v *>(tile_out + tk * kOutStride + r4 * 16);
-        const int m = tb0 * 32 + tk;
+        const int m = tb0 * 32 + (PAIRS == 2 ? 0 : 64 * khalf) + tk;
         if (m < M && rows_ok) *reinterpret_cast<uint4v *>(y + (size_t)m * N + (size_t)tile_first * kTileRows + r4 * 8) = v;
     }
 }
@@ -281,14 +300,23 @@ template <int BITS>
 __global__ void __launch_bounds__(kGemmWaves * 64, 1) gemm_group_kernel(const GemmBatch batch)
 {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];  // 2 stages x 64 KiB
-    const int xcd = (int)(blockIdx.x % kXcds), pos = (int)(blockIdx.x / kXcds);
+    const int xcd = (int)(blockIdx.x % kXcds);
+    int pos = (int)(blockIdx.x / kXcds);
+    const int past = pos - batch.tail_begin;       // from here on a place of the queue is two workgroups, half a tile each
+    if (past >= 0) pos = batch.tail_begin + (past >> 1);
     int pi = 0;
     for (int i = 1; i < batch.count; ++i) pi += pos >= batch.p[i].queue_begin ? 1 : 0;   // queue_begin grows with i
     const GemmProblem pb = batch.p[pi];
     const int out_tile = xcd * pb.tiles_per_xcd + (pos - pb.queue_begin);
     if (out_tile >= pb.grid_rows * (batch.Mpad / kGemmTokens)) return;
-    gemm_tile<BITS>(pb.packed, pb.lutB, pb.xs, pb.y, batch.M, batch.Mpad, pb.N, pb.K, out_tile % pb.grid_rows, out_tile / pb.grid_rows, lds,
-                    pb.out_scale);
+    const int bx = out_tile % pb.grid_rows, by = out_tile / pb.grid_rows;
+    if (past < 0) {
+        gemm_tile<BITS, kGemmPairs>(pb.packed, pb.lutB, pb.xs, pb.y, batch.M, batch.Mpad, pb.N, pb.K, bx, by, lds, pb.out_scale);
+        return;
+    }
+    const int half = 2 * bx + (past & 1);
+    if (half * (kGemmRowGroups * 32) >= pb.N) return;   // uniform over the workgroup
+    gemm_tile<BITS, 1>(pb.packed, pb.lutB, pb.xs, pb.y, batch.M, batch.Mpad, pb.N, pb.K, half, by, lds, pb.out_scale);
 }
 
 // Which kernel takes a layer.  The rules look at the layer and the number of tokens alone, never at the group it is
@@ -335,6 +363,16 @@ static const SplitTile &choose_split_tile(const GemmBatch &bt, int M, int bits)
         if (!best || time < best_time) { best = &t; best_time = time; }
     }
     return *best;
+}
+
+// Last tiles of an XCD's queue that are cut in two (128 rows each): those of a last round that would leave half of the compute units
+// or more idle, so that the halves still fit one round.
+// 7B block, 3 bits, 2048 tokens (gate and up: 172 tiles per queue, the last 12 of them in a sixth round of 32): 793 -> 780 us.  With
+// more than half a round left the halves would need two rounds of about 0.6 of a whole tile's time each.
+static int half_tiles(int queue)
+{
+    const int cus = num_cus() / kXcds, rest = cus > 0 ? queue % cus : 0;
+    return 2 * rest <= cus ? rest : 0;
 }
 
 int launch_gemm(const void *packed, const void *lut, const uint16_t *x, const float *s, uint16_t *y,
@@ -407,7 +445,10 @@ int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *
         return (int)hipGetLastError();
     };
     if (batch[0].count > 0) {
-        const int queue = queue_tiles(batch[0], kGemmRowGroups * 32 * kGemmPairs, kGemmTokens);
+        int queue = queue_tiles(batch[0], kGemmRowGroups * 32 * kGemmPairs, kGemmTokens);
+        const int tail = half_tiles(queue);
+        batch[0].tail_begin = queue - tail;
+        queue += tail;
         const void *fn = bits == 2 ? (const void *)gemm_group_kernel<2> : bits == 3 ? (const void *)gemm_group_kernel<3> : (const void *)gemm_group_kernel<4>;
         if (int e = launch(batch[0], queue, fn, bits - 2, 2 * kStageBytes)) return e;
     }

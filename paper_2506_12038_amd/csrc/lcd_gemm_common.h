@@ -171,6 +171,7 @@ struct GemmProblem {
 struct GemmBatch {
     GemmProblem p[kMaxGroup];
     int count, M, Mpad;
+    int tail_begin;    // large-tile kernel: places of a queue from here on are cut in two
 };
 
 // A variant of the split kernel (lcd_gemm_split.hip): 32 * pairs rows x 32 * blocks tokens per workgroup; pairs 1 with

@@ -40,6 +40,20 @@ def test_gemm_split_tile_edges(bits, shape):
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
 
 
+# the large-tile kernel's last tiles cut in two: the last 2, 6, 16 of an XCD's queue, rows that end in the first
+# half, in the second half and at the end of a tile, and (M = 1, last block) one token in a half's first token blocks
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("shape", [(4112, 256, 2040), (4240, 512, 2048), (8336, 512, 1025), (6144, 256, 1985)])
+def test_gemm_last_tiles_cut_in_two(bits, shape):
+    N, K, M = shape
+    check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
+
+
+def test_gemm_tiles_cut_in_two_on_their_own_only():
+    # tiles that a single call cuts in two and a group does not: the same bits
+    _check_grouped_prefill(3, 2000, [(4112, 256), (4352, 512)])
+
+
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("M", [1, 5, 64, 130, 257])
 @pytest.mark.parametrize("shape", [(16, 256), (48, 768), (272, 1024), (1040, 512)])
