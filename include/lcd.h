@@ -136,7 +136,7 @@ lcd_status lcd_build_lut(const uint16_t *codebook /*DEVICE*/, int N, int bits,
  *               columns.  The smoothing is fused into the kernel, except on the dequantising
  *               route with many tokens on wide or many layers, where a small kernel ahead of the product
  *               leaves the smoothed activations in the workspace (same rounding, same result).
- * lcd_lut_gemm: prefill path, any M >= 1: up to 16 tokens (32 for small layers) the kernels of lcd_lut_gemv; beyond, a
+ * lcd_lut_gemm: prefill path, any M >= 1: up to 16 tokens (32 for small layers) the dequantising kernel of lcd_lut_gemv; beyond, a
  *               smoothing kernel into the workspace, then register dequantisation into fp16 MFMA operands.
  * Both give bit-identical results from run to run (fixed reduction order).
  */

@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(kGemmWaves * 64, 1) gemm_group_kernel(const Ge
 
 // Which kernel takes a layer.  The rules look at the layer and the number of tokens alone, never at the group it is
 // called in: the kernels add in different orders, and a layer's result must not depend on its neighbours.
-// Up to 16 tokens the call is lcd_lut_gemv's.  Up to 32 tokens the tokens kernel, which needs no smoothing launch,
+// Up to 16 tokens the decode kernels (fp16 activations: the dequantising one, which is right for infinite activations too).  Up to 32 tokens the tokens kernel, which needs no smoothing launch,
 // also keeps the small layers (1024 x 2048, 3 bits, 32 tokens: 7.5 us against 10.1 with the split kernel; 4096 x 4096: 10.9
 // against 10.1, 4096 x 11008: 21.6 against 15.5).
 static bool decode_takes(int M, int N, int K)
@@ -421,7 +421,7 @@ int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *
     }
     // the decode kernels' scratch lies behind the smoothed activations (it takes less than a layer's share of those)
     if (small_count > 0)
-        if (int e = launch_decode_group(small, small_count, M, bits, static_cast<char *>(workspace) + offset, stream)) return e;
+        if (int e = launch_decode_group(small, small_count, M, bits, static_cast<char *>(workspace) + offset, stream, true)) return e;
     if (distinct == 0) return 0;
     // places of the layers' tiles (rows x tokens each) in the XCDs' queues; returns the queue's length
     auto queue_tiles = [&](GemmBatch &bt, int rows, int tokens) {

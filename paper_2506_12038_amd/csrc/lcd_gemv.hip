@@ -621,7 +621,7 @@ __global__ __launch_bounds__(kQuantThreads) void transform_kernel(TransformBatch
 }
 
 // One launch for a group of decode problems: the bucket kernel for one token, the tokens kernel beyond.
-int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream_)
+int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream_, bool dense)
 {
     hipStream_t stream = (hipStream_t)stream_;
     BucketBatch batch{};
@@ -632,7 +632,9 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     bool all_quantised = true;
     for (int i = 0; i < count; ++i) all_quantised = all_quantised && items[i].act_scale != 0.0f;
     const int sparse_tokens = bits != 2 ? 1 : all_quantised ? 4 : 2;   // most tokens the bucket kernel takes
-    const bool tokens_path = bits == 4 || M > sparse_tokens;
+    // (dense, fp16 activations: the routing matrix's zeros turn an infinite activation into a NaN of every bucket, the
+    // dequantised product gives the infinity that plain arithmetic gives; codes are always finite)
+    const bool tokens_path = bits == 4 || M > sparse_tokens || (dense && !all_quantised);
     const int MT = M <= 2 ? M : 4;                                      // token slots of the bucket kernel variant
     const int blocks = (M + kTokenBlock - 1) / kTokenBlock;
     const int held = tokens_path ? tokens_variant(bits, blocks, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds

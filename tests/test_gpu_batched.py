@@ -55,6 +55,24 @@ def test_gemm_tiles_cut_in_two_on_their_own_only():
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("M", [1, 2, 3, 20, 40])
+def test_gemm_infinite_activation_stays_in_its_token(bits, M):
+    # one infinite activation: its token's outputs are the infinity of the centroid's sign (as plain arithmetic
+    # gives), the others are what they are without it -- on every kernel that takes few tokens
+    N, K = 80, 1280
+    layer = synth.make_layer_uniform(N, K, bits, M, seed=bits + M)
+    Y = oracle.lut_matmul(layer["codebook"], layer["idx"], layer["x"], layer["s"], bits)
+    layer["x"] = layer["x"].copy()
+    layer["x"][M - 1, 700] = np.inf
+    y = run_hip(layer, bits, "gemm")
+    centroid = layer["codebook"][np.arange(N), layer["idx"][:, 700]].astype(np.float64)
+    assert np.all(centroid != 0)
+    assert np.array_equal(y[M - 1], np.copysign(np.inf, centroid))
+    if M > 1:
+        assert_parity(y[:M - 1], Y[:M - 1])
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("M", [1, 5, 64, 130, 257])
 @pytest.mark.parametrize("shape", [(16, 256), (48, 768), (272, 1024), (1040, 512)])
 def test_gemm_small(bits, M, shape):
