@@ -92,7 +92,9 @@ size_t lcd_workspace_bytes(int M, int N, int K, int bits);
  *     1024 + 16*l + 16) are a second 128-bit little-endian word whose bits [2w+1 : 2w] hold
  *     idx >> 2.
  * A codebook with fewer centroids than its container holds (5, 6, 10, ...) simply never uses
- * the upper codes; their codebook entries must be finite (zero is the natural choice).
+ * the upper codes; their codebook entries must be finite (zero is the natural choice), and of the
+ * codebook's magnitude for the 3-bit decode entry points (lcd_lut_gemv*), whose one-token kernel
+ * holds sums and differences of the entries four apart.
  * The mapping is a bijection: lcd_unpack_indices(lcd_pack_indices(idx)) == idx, and the
  * device and host packers produce identical bytes.
  *

@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(kGemmWaves * 64, 1) gemm_group_kernel(const Ge
 
 // Which kernel takes a layer.  The rules look at the layer and the number of tokens alone, never at the group it is
 // called in: the kernels add in different orders, and a layer's result must not depend on its neighbours.
-// Up to 16 tokens the decode kernels (fp16 activations: the dequantising one, which is right for infinite activations too).  Up to 32 tokens the tokens kernel, which needs no smoothing launch,
+// Up to 16 tokens the decode kernels (the dequantising one, except for INT8 codes with 2-bit indices).  Up to 32 tokens the tokens kernel, which needs no smoothing launch,
 // also keeps the small layers (1024 x 2048, 3 bits, 32 tokens: 7.5 us against 10.1 with the split kernel; 4096 x 4096: 10.9
 // against 10.1, 4096 x 11008: 21.6 against 15.5).
 static bool decode_takes(int M, int N, int K)

@@ -632,9 +632,10 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     bool all_quantised = true;
     for (int i = 0; i < count; ++i) all_quantised = all_quantised && items[i].act_scale != 0.0f;
     const int sparse_tokens = bits != 2 ? 1 : all_quantised ? 4 : 2;   // most tokens the bucket kernel takes
-    // (dense, fp16 activations: the routing matrix's zeros turn an infinite activation into a NaN of every bucket, the
-    // dequantised product gives the infinity that plain arithmetic gives; codes are always finite)
-    const bool tokens_path = bits == 4 || M > sparse_tokens || (dense && !all_quantised);
+    // (dense: fp16 activations, because the routing matrix's zeros turn an infinite activation into a NaN of every bucket where
+    // the dequantised product gives the infinity that plain arithmetic gives; 3 bits, because the bucket kernel's multipliers are
+    // (C[j] +- C[4 + j]) / 2 in binary32, which loses the centroid next to a large entry that no index names)
+    const bool tokens_path = bits == 4 || M > sparse_tokens || (dense && !(all_quantised && bits == 2));
     const int MT = M <= 2 ? M : 4;                                      // token slots of the bucket kernel variant
     const int blocks = (M + kTokenBlock - 1) / kTokenBlock;
     const int held = tokens_path ? tokens_variant(bits, blocks, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds

@@ -32,7 +32,7 @@ struct GroupItem {
 constexpr int kDecodeTokens = 32;   // most tokens the decode kernels take (the decode entry points stop at 16)
 // one launch for `count` decode problems (1 <= M <= kDecodeTokens tokens each)
 // (workspace: decode_codes_bytes(M, K) per item: the transformed activations where they are made ahead of the product)
-// dense: fp16 activations take the dequantising kernel for any M
+// dense: fp16 activations, and 3-bit indices, take the dequantising kernel for any M
 int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream, bool dense = false);
 inline size_t decode_codes_bytes(int M, int K) { return ((size_t)M * K * 2 + 255) / 256 * 256; }
 

@@ -36,6 +36,32 @@ def test_gemm_q8_matches_the_quantised_oracle(bits, M, shape):
     assert_parity(y.cpu().numpy(), Y, Q8_TOL)
 
 
+@pytest.mark.parametrize("bits,ncent", [(2, 3), (3, 5), (4, 9)])
+@pytest.mark.parametrize("M", [1, 2, 3, 4])
+def test_gemm_q8_ignores_large_finite_entries_of_unused_centroids(bits, ncent, M):
+    # the prefill entry points multiply by the centroids as they are: entries that no index names may be any finite
+    # number.  Single calls and one grouped call.  Tolerance: that of every INT8 product here (nothing is larger in the sum).
+    from paper_2506_12038_amd.binding import GemmGroup
+    import torch
+    problems, steps, refs = [], [], []
+    for i, (N, K, unused) in enumerate([(48, 1280, 1000.0), (80, 2304, 65504.0), (16, 256, -65504.0)]):
+        layer = synth.make_layer(3, i, N, K, bits, M, seed_offset=bits + M)
+        idx = (layer["idx"] % ncent).astype(np.uint8)
+        codebook = layer["codebook"].copy()
+        codebook[:, ncent:] = unused
+        s_q = _step(layer)
+        Y = oracle.quantised_lut_matmul(codebook, idx, layer["x"], layer["s"], s_q, bits)
+        packed, lut = lcd.lcd_pack_indices(to_dev(idx), bits), lcd.lcd_build_lut(to_dev(codebook), bits)
+        x, s = to_dev(layer["x"]), to_dev(layer["s"])
+        assert_parity(lcd.lcd_lut_gemm_q8(packed, lut, x, s, s_q, N, bits).cpu().numpy(), Y, Q8_TOL, (N, K))
+        problems.append((packed, lut, x, s, torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda"), N))
+        steps.append(s_q)
+        refs.append(Y)
+    GemmGroup(problems, bits, s_q=steps)()
+    for p, Y in zip(problems, refs):
+        assert_parity(p[4].cpu().numpy(), Y, Q8_TOL)
+
+
 @pytest.mark.parametrize("q8", [True, False])
 @pytest.mark.parametrize("bits,M,N,K", [(3, 4, 48, 12288), (3, 5, 48, 12288), (4, 1, 16, 49920), (4, 1, 16, 50176), (2, 31, 64, 1536), (2, 31, 64, 2304),
                                         (3, 32, 32, 9216), (3, 32, 32, 9472), (4, 17, 16, 17920)])
