@@ -240,8 +240,7 @@ lcd_status lcd_lut_gemv_q8_grouped(const lcd_gemv_problem *problems /*HOST*/, co
 /* ---- grouped prefill: several independent layers in ONE pair of launches ------------------- *
  *
  * The same product as lcd_lut_gemm for `count` (1..16) layers with one token count M >= 1 and one
- * index width: one smoothing launch for all layers, then one matrix launch (two if some layers take
- * small output tiles and some large ones) whose workgroups take
+ * index width: one smoothing launch for all layers, then one matrix launch whose workgroups take
  * the layers' output tiles one layer after the other (those with the largest K first), so that
  * the compute units the tail of one layer leaves idle start on the next.  Results are bit for
  * bit those of lcd_lut_gemm on every layer.  `problems` is a HOST array, read during the call

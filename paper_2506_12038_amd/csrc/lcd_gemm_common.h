@@ -183,5 +183,8 @@ struct SplitVariant {
 };
 constexpr int kSplitVariants = 3 * 6;
 SplitVariant split_variant(int bits, int pairs, int blocks);
+// The kernel that takes large tiles and split tiles of 64 rows x 32 * blocks tokens, blocks 3 or 4 (lcd_gemm_mixed.hip).
+constexpr int kMixedVariants = 3 * 2;
+SplitVariant mixed_variant(int bits, int blocks);
 
 }  // namespace lcd

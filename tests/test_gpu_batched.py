@@ -217,10 +217,17 @@ def test_grouped_prefill_matches_single_calls_and_oracle(bits, M):
     _check_grouped_prefill(bits, M, [(272, 1024), (1040, 512), (48, 2816), (4112, 256), (16, 4352)])
 
 
-@pytest.mark.parametrize("M,shapes", [(20, [(64, 512), (8192, 2048), (4096, 4096), (48, 2816)]),           # decode and split kernels
-                                      (129, [(16912, 256), (256, 512), (17040, 256), (4112, 256)])])       # split and large tiles
-def test_grouped_prefill_with_layers_on_different_kernels(M, shapes):
-    _check_grouped_prefill(3, M, shapes)
+# layers of one call on different kernels: decode and split; split and large tiles (one launch: split tiles of 96 and 128
+# tokens, the large tiles' last round whole and cut in two, layers that end inside a tile of either kind)
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("M,shapes", [(20, [(64, 512), (8192, 2048), (4096, 4096), (48, 2816)]),
+                                      (129, [(16912, 256), (256, 512), (17040, 256), (4112, 256)]),
+                                      (110, [(34320, 256), (48, 2304), (1040, 512)]),
+                                      (110, [(36624, 256), (1040, 2304), (16, 256)]),
+                                      (257, [(272, 1280), (12304, 512), (16, 4352)]),
+                                      (513, [(12816, 256), (80, 2304), (4112, 256), (13072, 256)])])
+def test_grouped_prefill_with_layers_on_different_kernels(bits, M, shapes):
+    _check_grouped_prefill(bits, M, shapes)
 
 
 def _check_grouped_prefill(bits, M, shapes):
