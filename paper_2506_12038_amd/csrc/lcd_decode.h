@@ -115,7 +115,7 @@ struct TokensVariant {
     size_t lds_bytes;
     int id;             // 0 .. kTokensVariants - 1
 };
-constexpr int kTokensVariants = 3 * kMaxTokenBlocks * 3 * 2;
+constexpr int kTokensVariants = 3 * kMaxTokenBlocks * 4 * 2;
 // ready: x holds the transformed activations in operand order (transform_kernel)
 TokensVariant tokens_variant(int bits, int blocks, int tiles, bool ready);
 

@@ -695,9 +695,11 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     const bool int8_codes = !tokens_path && bits != 4 && all_quantised;   // (3 bits: one token, the plain pass only)
     const bool light_steps = bits == 2 && M == 1;   // one sparse pass per tile: a step is short next to the fixed costs
     const bool staged_ahead = tokens_path && codes[0] != nullptr;
-    // the tokens kernel, times in us of a workgroup: a "round" is one chunk for each of its 8 waves
-    const double round_tile = (bits == 2 ? 0.40 : bits == 3 ? 0.52 : 0.85) + 0.06 * blocks;
-    const double round_stage = staged_ahead ? 0.1 * blocks : 0.15 + 0.3 * blocks, pass = 1.5;
+    // the tokens kernel, times in us of a workgroup: a "round" is one chunk for each of its 8 waves.  Fitted to single layers of
+    // 4096 x t rows (t row tiles per workgroup), K = 4096 and 11008, 4 and 16 tokens; 2 bits, 16 tokens: K = 4096 t = 8, 10, 12
+    // 15.0, 17.1, 19.0 us, 13 in two passes 25.4; K = 11008 t = 4, 5, 6 20.1, 23.0, 26.2.
+    const double round_tile = (bits == 2 ? 0.43 : bits == 3 ? 0.55 : 0.89) + 0.06 * blocks;
+    const double round_stage = staged_ahead ? 0.1 * blocks : 0.08 + 0.035 * M, pass = bits == 2 ? 3.7 : 5.0;
     auto layer_time = [&](int i, int n) {
         const int kc = batch.p[i].kc, t = (batch.p[i].nt + n - 1) / n;
         if (tokens_path) {

@@ -16,14 +16,17 @@
 // The order of the additions of one output depends on K alone -- not on the grouping of layers,
 // on R or on the number of tokens -- so grouped, single and captured calls agree bit for bit.
 //
-// What bounds it: with many row tiles per workgroup the vector pipe (the dequantiser: 92 of about 105
-// vector instructions per 16 x 256 tile-chunk at 2 bits), about 1.0 us per row tile of K = 4096; with one
-// row tile per workgroup the staging of the activations (about 2000 shader cycles per round of 8 chunks
-// and 16 tokens: LDS writes, reads and the smoothing of 8 waves in step) and the latencies in front.
+// What bounds it: with many row tiles per workgroup the vector pipe (the dequantiser), 0.5 / 0.6 / 0.95 us (2 / 3 / 4 bits) per
+// row tile and round of 8 chunks; with one row tile per workgroup the staging of the activations and the latencies in front.  A
+// second pass over the activations costs 4 to 6 us, hence the variant of 14 row tiles (up to 57344 rows on 256 compute units
+// in one pass): seven layers of a 7B block in one launch, 16 tokens, 2 / 3 / 4 bits, passes of 6, 6 and 4 row tiles 24.5 / 30.5 /
+// 44.4 us, now 22.4 / 28.3 / 36.3; two layers of 28672 x 8192, 4 tokens, 3 / 4 bits 54.8 / 77.4 -> 44.1 / 64.6.  Its registers
+// hold the packed words of a few tiles only, in a ring (2 / 3 / 4 bits: 4, 4, 3 tiles ahead, which is enough of them under way), and at 3 and 4 bits
+// no row tables: those are read from LDS one tile ahead.
 // Measured against the kernel before it (K in segments, partial tiles of two row tiles exchanged through
 // LDS at a barrier after every second tile, no more than 16 tokens): 4096 x 11008, 3 bits, 3 tokens
-// 16.5 -> 9.8 us a call; blocks of 2, 3 and 4-bit layers (5120 / 13824), 6 tokens, 104 -> 72 us a block; 7B
-// block, 2 bits, 16 tokens 46 -> 37.1 us.
+// 16.5 -> 9.0 us a call; blocks of 2, 3 and 4-bit layers (5120 / 13824), 6 tokens, 104 -> 71 us a block; 7B
+// block, 2 bits, 16 tokens 44.3 -> 38.4 us.
 #include <hip/hip_runtime.h>
 #include "lcd_decode.h"
 
@@ -32,8 +35,18 @@ namespace lcd {
 constexpr int kStageStride = kTileCols + 8;   // halfs per token row of a wave's stage (+16 B: no bank conflicts)
 constexpr int kStageBytes = kTokenBlock * kStageStride * 2;
 
+// Row tiles a variant holds: one, two, as many as leave room for all their packed words of a chunk next to the B operands (32 registers
+// per block), the staged activations and the tables, or kManyTiles.
+template <int BITS, int TB> constexpr int whole_chunk_tiles() { return BITS == 4 ? (TB == 1 ? 4 : 3) : (TB == 1 ? 6 : 5); }
+constexpr int kManyTiles = 14;
+template <int BITS> constexpr int ring_tiles() { return BITS == 4 ? 3 : 4; }
+template <int BITS, int R> constexpr bool tables_in_lds() { return R == kManyTiles && BITS != 2; }
+
 template <int TB, int R>
 constexpr int tokens_wave_bytes() { return R * TB * 1024 > kStageBytes ? R * TB * 1024 : kStageBytes; }
+template <int BITS> constexpr int row_table_bytes() { return BITS == 2 ? 8 : BITS == 3 ? 16 : 32; }
+template <int BITS, int TB, int R, int WAVES>
+constexpr size_t tokens_lds_bytes() { return (size_t)WAVES * tokens_wave_bytes<TB, R>() + (tables_in_lds<BITS, R>() ? R * kTileRows * row_table_bytes<BITS>() : 0); }
 
 template <int BITS>
 struct TokTile {
@@ -53,9 +66,11 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     constexpr uint32_t TBYTES = kTileRows * kTileCols * BITS / 8;
     constexpr int NC = BITS == 2 ? 4 : 8;
     constexpr int D = R <= 2 && WAVES == kBW ? 2 : 1;   // chunks whose packed words are loaded ahead
+    constexpr int RING = R == kManyTiles ? ring_tiles<BITS>() : R;   // row tiles whose words of a chunk are held
+    constexpr bool TABLES = tables_in_lds<BITS, R>();
     constexpr int SETS = 2 * kBW / WAVES;         // accumulator sets of a wave (see the order of the additions above)
     constexpr int kWaveBytes = tokens_wave_bytes<TB, R>();
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // one piece per wave: its stage, in the end its partial tiles
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // one piece per wave: its stage, in the end its partial tiles; then the row tables
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: keeps addresses scalar
@@ -122,7 +137,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     const __amdgpu_buffer_rsrc_t rs_packed = make_rsrc(l.packed, (uint32_t)l.nt * (uint32_t)kc * TBYTES);
     // byte-split tables: behind the bucket multipliers (2 and 3 bits), the whole table (4 bits)
     const __amdgpu_buffer_rsrc_t rs_tb = make_rsrc(reinterpret_cast<const uint8_t *>(l.lut) + (BITS == 4 ? 0 : (size_t)N * NC * 4),
-                                                   (uint32_t)N * (BITS == 2 ? 8 : BITS == 3 ? 16 : 32));
+                                                   (uint32_t)N * row_table_bytes<BITS>());
     // packed words of the R row tiles from v0 (tiles past v1 and chunks past the layer's read zeros, no traffic)
     auto load_tile = [&](TokTile<BITS> &p, int tile, int v1, int chunk) {
         const bool v = tile < v1 && chunk < kc;
@@ -180,8 +195,31 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     };
 
     float4v acc[SETS][R][TB];
-    typename TokTables<BITS>::type tab[R];
-    TokTile<BITS> P[D][R];
+    typedef typename TokTables<BITS>::type Tables;
+    Tables tab[TABLES ? 2 : R];         // TABLES: of this tile and the next
+    TokTile<BITS> P[D][RING];
+    // a row's table, 16 bytes (8 with 2 bits) at a time: piece i of it
+    auto table_piece = [&](bool valid, uint32_t row, int i) {
+        const uint32_t at = valid ? row * row_table_bytes<BITS>() + 16 * i : kOob;
+        if constexpr (BITS == 2) {
+            const uint2v t = __builtin_amdgcn_raw_buffer_load_b64(rs_tb, at, 0, 0);
+            return uint4v{t[0], t[1], 0u, 0u};
+        } else return __builtin_amdgcn_raw_buffer_load_b128(rs_tb, at, 0, 0);
+    };
+    auto make_tables = [](uint4v t, uint4v u) {
+        if constexpr (BITS == 2) return RowTables{{t[0], 0u}, {t[1], 0u}};
+        else if constexpr (BITS == 3) return RowTables{{t[0], t[1]}, {t[2], t[3]}};
+        else return RowTables4{{t[0], t[1], t[2], t[3]}, {u[0], u[1], u[2], u[3]}};
+    };
+    uint8_t *const row_tables = smem + WAVES * kWaveBytes;
+    auto table_of = [&](int r) {        // tile r of the pass, from LDS
+        const uint8_t *at = row_tables + (r * kTileRows + j) * row_table_bytes<BITS>();
+        if constexpr (BITS == 2) {
+            const uint2v t = *reinterpret_cast<const uint2v *>(at);
+            return make_tables(uint4v{t[0], t[1], 0u, 0u}, uint4v{});
+        } else if constexpr (BITS == 3) return make_tables(*reinterpret_cast<const uint4v *>(at), uint4v{});
+        else return make_tables(*reinterpret_cast<const uint4v *>(at), *reinterpret_cast<const uint4v *>(at + 16));
+    };
     auto tile_product = [&](const TokTile<BITS> &p, const typename TokTables<BITS>::type &t, float4v (&a)[TB]) {
         uint4v op0, op1;
         auto multiply = [&](int d) {
@@ -204,27 +242,39 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
         }
     };
 
-    for (int v0 = ta; v0 < tb_end; v0 += R) {
-        const int v1 = min(tb_end, v0 + R);
+    int pass_tiles = R;
+    if (R == kManyTiles && tb_end - ta > R) {   // passes of one length: a last pass of few tiles would have few loads under way
+        const int passes = (tb_end - ta + R - 1) / R;
+        pass_tiles = (tb_end - ta + passes - 1) / passes;
+    }
+    for (int v0 = ta; v0 < tb_end; v0 += pass_tiles) {
+        const int v1 = min(tb_end, v0 + pass_tiles);
+        uint4v row_t = {0u, 0u, 0u, 0u}, row_u = {0u, 0u, 0u, 0u};   // TABLES: of the pass's rows, one row per thread
+        if constexpr (TABLES) {
+            const bool valid = (int)threadIdx.x < (v1 - v0) * kTileRows;
+            const uint32_t row = (uint32_t)v0 * kTileRows + threadIdx.x;
+            row_t = table_piece(valid, row, 0);
+            if (BITS == 4) row_u = table_piece(valid, row, 1);
+        }
 #pragma unroll
         for (int dd = 0; dd < D; ++dd)
 #pragma unroll
-            for (int r = 0; r < R; ++r) load_tile(P[dd][r], v0 + r, v1, wave + dd * WAVES);
+            for (int r = 0; r < RING; ++r) load_tile(P[dd][r], v0 + r, v1, wave + dd * WAVES);
+        if constexpr (!TABLES) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const bool tv = v0 + r < v1;
-            const uint32_t row = (uint32_t)(v0 + r) * kTileRows + j;
-            if constexpr (BITS == 2) {
-                const uint2v t = __builtin_amdgcn_raw_buffer_load_b64(rs_tb, tv ? row * 8 : kOob, 0, 0);
-                tab[r] = RowTables{{t[0], 0u}, {t[1], 0u}};
-            } else if constexpr (BITS == 3) {
-                const uint4v t = __builtin_amdgcn_raw_buffer_load_b128(rs_tb, tv ? row * 16 : kOob, 0, 0);
-                tab[r] = RowTables{{t[0], t[1]}, {t[2], t[3]}};
-            } else {
-                const uint4v t = __builtin_amdgcn_raw_buffer_load_b128(rs_tb, tv ? row * 32 : kOob, 0, 0);
-                const uint4v u = __builtin_amdgcn_raw_buffer_load_b128(rs_tb, tv ? row * 32 + 16 : kOob, 0, 0);
-                tab[r] = RowTables4{{t[0], t[1], t[2], t[3]}, {u[0], u[1], u[2], u[3]}};
+            for (int r = 0; r < R; ++r) {
+                const uint32_t row = (uint32_t)(v0 + r) * kTileRows + j;
+                const uint4v t = table_piece(v0 + r < v1, row, 0);
+                tab[r] = make_tables(t, BITS == 4 ? table_piece(v0 + r < v1, row, 1) : uint4v{});
             }
+        } else {
+            if (threadIdx.x < R * kTileRows) {
+                uint8_t *to = row_tables + threadIdx.x * row_table_bytes<BITS>();
+                if constexpr (BITS == 2) *reinterpret_cast<uint2v *>(to) = uint2v{row_t[0], row_t[1]};
+                else *reinterpret_cast<uint4v *>(to) = row_t;
+                if constexpr (BITS == 4) *reinterpret_cast<uint4v *>(to + 16) = row_u;
+            }
+            __syncthreads();
         }
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -233,14 +283,23 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
 #pragma unroll
                 for (int i = 0; i < SETS; ++i) acc[i][r][b] = float4v{0.f, 0.f, 0.f, 0.f};
 
-        auto chunk_products = [&](TokTile<BITS> (&p)[R], float4v (&a)[R][TB], int chunk) {
+        auto chunk_products = [&](TokTile<BITS> (&p)[RING], float4v (&a)[R][TB], int chunk) {
+            if constexpr (TABLES) tab[0] = table_of(0);
             stage_x();
             if (TB == 1) { load_s(chunk + WAVES); load_x(chunk + WAVES); }   // room for the next chunk's activations while this one multiplies
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (r > 0 && v0 + r >= v1) break;               // uniform
-                tile_product(p[r], tab[r], a[r]);
-                load_tile(p[r], v0 + r, v1, chunk + D * WAVES);
+                if constexpr (RING == R && !TABLES) {
+                    tile_product(p[r], tab[r], a[r]);
+                    load_tile(p[r], v0 + r, v1, chunk + D * WAVES);
+                } else {
+                    if (TABLES && r + 1 < R) tab[(r + 1) & 1] = table_of(r + 1);
+                    tile_product(p[r % RING], tab[TABLES ? r & 1 : r], a[r]);
+                    // the slot's next tile: of this chunk, or the one it starts the next chunk with
+                    const bool same = r + RING < R && v0 + r + RING < v1;
+                    load_tile(p[r % RING], v0 + (same ? r + RING : r % RING), v1, same ? chunk : chunk + WAVES);
+                }
             }
             if (TB > 1) { load_s(chunk + WAVES); load_x(chunk + WAVES); }    // into the registers the B operands leave
         };
@@ -285,15 +344,11 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     }
 }
 
-// Row tiles a variant holds, by index width and token blocks: as many as the registers of two waves per
-// SIMD allow next to the B operands (32 per block), the staged activations and the tables.
-template <int BITS, int TB> struct TokensHeld { static constexpr int most = BITS == 4 ? (TB == 1 ? 4 : 3) : (TB == 1 ? 6 : 5); };
-
 template <int BITS, int TB, int R, int WAVES, bool READY>
 static TokensVariant variant_of(int slot)
 {
-    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R, WAVES, READY>, R, WAVES, (size_t)WAVES * tokens_wave_bytes<TB, R>(),
-                         (((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 3 + slot) * 2 + (READY ? 1 : 0)};
+    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R, WAVES, READY>, R, WAVES, tokens_lds_bytes<BITS, TB, R, WAVES>(),
+                         (((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 4 + slot) * 2 + (READY ? 1 : 0)};
 }
 
 template <int BITS, int TB, bool READY>
@@ -301,7 +356,9 @@ static TokensVariant pick_tiles(int tiles)
 {
     if (tiles <= 1) return variant_of<BITS, TB, 1, 2 * kBW, READY>(0);
     if (tiles <= 2) return variant_of<BITS, TB, 2, TB == 1 ? 2 * kBW : kBW, READY>(1);
-    return variant_of<BITS, TB, TokensHeld<BITS, TB>::most, kBW, READY>(2);
+    constexpr int whole = whole_chunk_tiles<BITS, TB>();
+    if (TB > 1 || tiles <= whole) return variant_of<BITS, TB, whole, kBW, READY>(2);
+    return variant_of<BITS, 1, kManyTiles, kBW, READY>(3);
 }
 
 template <int BITS, bool READY>

@@ -29,6 +29,43 @@ def test_gemm_token_block_edges(bits, M, shape):
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
 
 
+# The tokens kernel with many row tiles per workgroup: fewer tiles than its ring of packed words has slots in a
+# pass (the last of two), one tile either side of the smaller variants, of what it holds (14) and of two full passes; activations
+# smoothed in the kernel, and (INT8 codes, 16 tokens) transformed ahead.  Most workgroups have `tiles` row tiles, a few one less.
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("tiles,K", [(5, 2304), (7, 4352), (8, 512), (13, 2304), (14, 4352), (15, 2304), (28, 1280), (29, 2304)])
+@pytest.mark.parametrize("M,quantised", [(1, False), (3, False), (16, False), (16, True)])
+def test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised):
+    import torch
+    if M == 1 and bits != 4:
+        pytest.skip("one token takes the bucket kernel")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rows = cus * 16                                   # one tile per workgroup
+    N = tiles * rows - 48
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tiles * K + M)
+    packed = torch.randint(0, 256, (lcd.lcd_packed_bytes(N, K, bits),), dtype=torch.uint8, device="cuda", generator=g)
+    codebook = (torch.randn((N, 1 << bits), device="cuda", generator=g) * 0.02).half()
+    x = torch.randn((M, K), device="cuda", generator=g).half()
+    s = torch.rand((K,), device="cuda", generator=g) + 0.5
+    s_q = 0.03
+    if quantised:
+        call = lambda p, l, n, **kw: lcd.lcd_lut_gemv_q8(p, l, x, s, s_q, n, bits, **kw)
+    else:
+        call = lambda p, l, n, **kw: lcd.lcd_lut_gemv(p, l, x, s, n, bits, **kw)
+    y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+    call(packed, lcd.lcd_build_lut(codebook, bits), N, y=y)
+    for first in range(0, N, rows):                   # the same rows in calls of one tile per workgroup: the same bits
+        n = min(rows, N - first)
+        part = packed[lcd.lcd_packed_bytes(first, K, bits) if first else 0:][:lcd.lcd_packed_bytes(n, K, bits)].clone()
+        cb = codebook[first:first + n].contiguous()
+        assert torch.equal(y[:, first:first + n], call(part, lcd.lcd_build_lut(cb, bits), n)), first
+    idx = lcd.lcd_unpack_indices(part, n, K, bits).cpu().numpy()
+    args = cb.cpu().numpy(), idx, x.cpu().numpy(), s.cpu().numpy()
+    Y = oracle.quantised_lut_matmul(*args, s_q, bits) if quantised else oracle.lut_matmul(*args, bits)
+    assert_parity(y[:, first:].cpu().numpy(), Y, 1e-3 if quantised else TOL)
+
+
 # the split kernel behind lcd_lut_gemm, every tile shape (32 or 64 rows x 32, 64, 96, 128 tokens): one token either side of
 # a tile, rows that fill half a pair, fewer 128-column units than waves (K = 256), units that do not divide by the
 # waves (K = 1280, 2304), and the first token count of the same layer that the large tiles take
