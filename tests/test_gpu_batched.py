@@ -66,14 +66,42 @@ def test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised):
     assert_parity(y[:, first:].cpu().numpy(), Y, 1e-3 if quantised else TOL)
 
 
-# the split kernel behind lcd_lut_gemm, every tile shape (32 or 64 rows x 32, 64, 96, 128 tokens): one token either side of
-# a tile, rows that fill half a pair, fewer 128-column units than waves (K = 256), units that do not divide by the
-# waves (K = 1280, 2304), and the first token count of the same layer that the large tiles take
+# the split kernel behind lcd_lut_gemm: one token either side of a tile, rows that fill half a pair, fewer 128-column units than
+# waves (K = 256), units that do not divide by the waves (K = 1280, 2304), and the first token count of the same
+# layer that the large tiles take
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("shape", [(48, 1280, 33), (48, 1280, 64), (1040, 512, 300), (5136, 256, 34), (5136, 1280, 65), (5136, 256, 97), (5136, 256, 200),
                                    (5136, 2304, 300), (8016, 2304, 129), (4096, 4096, 17), (4112, 4096, 32), (28800, 256, 128), (28800, 256, 257)])
 def test_gemm_split_tile_edges(bits, shape):
     N, K, M = shape
+    check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
+
+
+def _split_tile_of(N, K, M, bits):
+    """(32-row pairs, 32-token blocks) of the split kernel's tile for one layer, by the rule and the table of lcd_gemm.hip."""
+    import math, re, torch
+    from pathlib import Path
+    table = re.findall(r"\{(\d), (\d), ([\d.]+), \{([\d., ]+)\}\}", (Path(lcd.__file__).parent / "csrc" / "lcd_gemm.hip").read_text())
+    assert len(table) == 6
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    times = []
+    for pairs, blocks, fixed_us, column_ns in ((int(a), int(b), float(c), [float(v) for v in d.split(",")]) for a, b, c, d in table):
+        wgs = -(-N // (32 * pairs)) * -(-M // (32 * blocks))
+        times.append((math.ceil(wgs / cus) * (fixed_us + 1e-3 * column_ns[bits - 2] * K), pairs, blocks))
+    return min(times, key=lambda t: t[0])[1:]         # (the first of equal times)
+
+
+# every tile of the split kernel at every width, with an uneven number of 128-column units per wave (K = 2304: 18 units on 8
+# waves; K = 1792, for 64 x 32 at 4 bits, which longer rows do not take: 14), so that a wave refills its ring, its packed words
+# and its operands across units; a last row tile in half a pair, a last token block that is not full
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("tile", [(1, 1), (1, 2), (2, 1), (2, 2), (2, 3), (2, 4)])
+def test_gemm_every_split_tile(bits, tile):
+    rows = [48 + 928 * i for i in range(37)] + [2704]
+    found = [(N, K, M) for K in (2304, 1792) for M in (45, 77, 109, 141, 173, 237) for N in rows
+             if -(-N // 256) * -(-M // 128) <= 128 and _split_tile_of(N, K, M, bits) == tile]
+    assert found
+    N, K, M = found[0]
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
 
 

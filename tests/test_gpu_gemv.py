@@ -231,13 +231,36 @@ def test_grouped_q8_matches_oracle_and_single_calls(bits, M):
         assert torch.equal(y, single)
 
 
+# A decode launch on the dequantising kernel transforms its activations ahead of the product, into the workspace, where
+# tokens x widest K x passes exceeds a line (one pass on these shapes).
+AHEAD_SMOOTHED, AHEAD_CODES = 300_000, 50_000
+
+
+def _k_beyond(line, M):
+    """The smallest K whose activations for M tokens are transformed ahead."""
+    return (line // M // 256 + 1) * 256
+
+
+class _WatchedWorkspace:
+    """A workspace filled with a pattern: how many of its leading bytes a call has written."""
+
+    def __init__(self, nbytes):
+        import torch
+        self.tensor = torch.full((max(nbytes, 256),), 0xA5, dtype=torch.uint8, device="cuda")
+
+    def written(self):
+        touched = (self.tensor != 0xA5).nonzero()
+        return 0 if touched.numel() == 0 else int(touched.max()) + 1
+
+
 @pytest.mark.parametrize("bits,M", [(2, 3), (3, 16), (4, 1), (4, 9)])
 def test_grouped_wide_and_narrow_layers(bits, M):
     # a group with one layer wide enough for the activations to be smoothed ahead of the product:
     # then all its layers take that route, while the single calls of the narrow ones smooth inside
     # the kernel; both round the same way, so the outputs must agree bit for bit
     import torch
-    shapes = [(32, 16384), (64, 1024), (48, 2816)]
+    from paper_2506_12038_amd.binding import GemvGroup
+    shapes = [(32, _k_beyond(AHEAD_SMOOTHED, M)), (64, 1024), (48, 2816)]
     problems, layers, singles = [], [], []
     for i, (N, K) in enumerate(shapes):
         layer = synth.make_layer(1, i, N, K, bits, M, seed_offset=11 * i + bits + M)
@@ -247,9 +270,14 @@ def test_grouped_wide_and_narrow_layers(bits, M):
         y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
         problems.append((packed, lut, x, s, y, N))
         layers.append(layer)
-        singles.append(lcd.lcd_lut_gemv(packed, lut, x, s, N, bits))
-    lcd.lcd_lut_gemv_grouped(problems, bits)
+        ws = _WatchedWorkspace(lcd.lcd_workspace_bytes(M, N, K, bits))
+        singles.append(lcd.lcd_lut_gemv(packed, lut, x, s, N, bits, workspace=ws.tensor))
+        assert (ws.written() > 0) == (i == 0), (N, K)     # the wide layer ahead, the narrow ones inside the kernel
+    need = GemvGroup(problems, bits).workspace.numel()
+    ws = _WatchedWorkspace(need)
+    GemvGroup(problems, bits, workspace=ws.tensor)()
     torch.cuda.synchronize()
+    assert ws.written() > M * (shapes[0][1] + shapes[1][1]) * 2      # all three
     for (packed, lut, x, s, y, N), layer, single in zip(problems, layers, singles):
         Y = oracle.lut_matmul(layer["codebook"], layer["idx"], layer["x"], layer["s"], bits)
         assert oracle.parity_errors(y.cpu().numpy(), Y)["max_rel_floored"] <= TOL
@@ -307,21 +335,24 @@ def test_gemv_q8_decides_hard_cases_like_the_binary32_oracle():
             assert np.array_equal(got, expect), (M, bits16, s0, s_q, got[:, 0], expect[:, 0])
 
 
-@pytest.mark.parametrize("bits,M,quantised", [(2, 4, True), (3, 16, False), (4, 2, True), (2, 1, True)])
+@pytest.mark.parametrize("bits,M,quantised", [(2, 4, True), (2, 1, True), (3, 16, False), (4, 2, True), (2, 16, True), (3, 3, True)])
 def test_grouped_decode_layers_that_share_an_input(bits, M, quantised):
-    # q/k/v-like: three layers read ONE x and s (same pointers), so the ahead-of-time transformation keeps
-    # one copy for them; a fourth layer with the same K has its own input and (quantised) a fifth shares x
-    # with another step.  Not quantised: one layer is wide enough (K >= 16384) to send the whole group through
-    # the ahead-of-time route.  Every output against the oracle and against the single calls.
+    # q/k/v-like: three layers read ONE x and s (same pointers); a fourth layer with the same K has its own input and
+    # (quantised) a fifth shares x with another step.  Where the activations are transformed ahead (every case here but
+    # the sparse kernel's: INT8 codes, 2 bits, up to 4 tokens) layers of one input share one transformed copy.
+    # Every output against the oracle, and against single calls of no more than half the tokens, which stay below the line and
+    # transform inside the kernel: the same bits.
     import torch
     from paper_2506_12038_amd.binding import GemvGroup
-    K = 1024 if quantised else 16384
+    sparse = quantised and bits == 2 and M <= 4
+    K = 1024 if sparse else _k_beyond(AHEAD_CODES if quantised else AHEAD_SMOOTHED, M)
     base = synth.make_layer(2, 0, 64, K, bits, M, seed_offset=1)
     other = synth.make_layer(2, 1, 64, K, bits, M, seed_offset=2)
     x0, s0, x1, s1 = to_dev(base["x"]), to_dev(base["s"]), to_dev(other["x"]), to_dev(other["s"])
     step = lambda L: float(np.float32(np.quantile(np.abs(L["x"].astype(np.float64) / L["s"]), 0.99) / 127.0))
     specs = [(48, x0, s0, base, step(base)), (16, x0, s0, base, step(base)), (80, x0, s0, base, step(base)),
              (32, x1, s1, other, step(other)), (64, x0, s0, base, step(base) * 1.5)]
+    half = M if sparse else max(1, M // 2)
     problems, refs = [], []
     for i, (N, x, s, src, s_q) in enumerate(specs):
         w = synth.make_layer(2, 10 + i, N, K, bits, 1, seed_offset=i)
@@ -329,13 +360,29 @@ def test_grouped_decode_layers_that_share_an_input(bits, M, quantised):
         lut = lcd.lcd_build_lut(to_dev(w["codebook"]), bits)
         y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
         problems.append((packed, lut, x, s, y, N))
+        singles = []
+        for first in range(0, M, half):
+            part = x[first:first + half].contiguous()
+            ws = _WatchedWorkspace(lcd.lcd_workspace_bytes(part.shape[0], N, K, bits))
+            if quantised:
+                singles.append(lcd.lcd_lut_gemv_q8(packed, lut, part, s, s_q, N, bits, workspace=ws.tensor))
+            else:
+                singles.append(lcd.lcd_lut_gemv(packed, lut, part, s, N, bits, workspace=ws.tensor))
+            assert ws.written() == 0
+        # (one token of codes at 3 bits runs on the sparse kernel, which adds in another order)
+        single = None if bits == 3 and half == 1 else torch.cat(singles)
         if quantised:
-            refs.append((oracle.quantised_lut_matmul(w["codebook"], w["idx"], src["x"], src["s"], s_q, bits),
-                         lcd.lcd_lut_gemv_q8(packed, lut, x, s, s_q, N, bits), 1e-3))
+            refs.append((oracle.quantised_lut_matmul(w["codebook"], w["idx"], src["x"], src["s"], s_q, bits), single, 1e-3))
         else:
-            refs.append((oracle.lut_matmul(w["codebook"], w["idx"], src["x"], src["s"], bits), lcd.lcd_lut_gemv(packed, lut, x, s, N, bits), TOL))
-    GemvGroup(problems, bits, s_q=[sp[4] for sp in specs] if quantised else None)()
+            refs.append((oracle.lut_matmul(w["codebook"], w["idx"], src["x"], src["s"], bits), single, TOL))
+    steps = [sp[4] for sp in specs] if quantised else None
+    ws = _WatchedWorkspace(GemvGroup(problems, bits, s_q=steps).workspace.numel())
+    GemvGroup(problems, bits, workspace=ws.tensor, s_q=steps)()
     torch.cuda.synchronize()
+    copies = 0 if sparse else 3 if quantised else 2          # distinct inputs
+    each = (M * K * 2 + 255) // 256 * 256
+    assert (copies - 1) * each < ws.written() <= copies * each if copies else ws.written() == 0
     for p, (Y, single, tol) in zip(problems, refs):
-        assert torch.equal(p[4], single)
+        if single is not None:
+            assert torch.equal(p[4], single)
         assert_parity(p[4].cpu().numpy(), Y, tol)
