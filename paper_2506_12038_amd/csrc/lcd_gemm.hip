@@ -23,16 +23,22 @@ static bool decode_takes(int M, int N, int K)
 {
     return (M <= 16 || (M <= kDecodeTokens && (long long)N * K < (1ll << 24))) && (long long)M * K * 2 < (1ll << 32);
 }
-// The split kernel takes layers that do not have 256 x 128 tiles for much more than half of the compute units.  Time of a
-// call, large tiles -> split, 3 bits: 4096 x 4096, 333 tokens (48 tiles) 47 -> 22 us, 1000 tokens (128 tiles)
-// 50 -> 46; 4096 x 11008, 333 tokens 110 -> 45; two layers of 11008 x 4096, 333 tokens (129 tiles each: a second round of
-// large tiles for two of them) 106 -> 91.  Beyond, large tiles are faster: 8192 x 8192, 700 tokens (192 tiles)
-// 102 against 112.  (The split kernel addresses the activations with 32 bits.)
-constexpr int kSplitMostTiles = 132;
+// The split kernel takes layers that leave many compute units idle as 256 x 128 tiles: up to 64 tiles and a few more where K is large
+// (cut in two, 64 tiles fill half of 256 compute units), and just above 128, which no longer fit one round when cut in two.
+// Time of a call, large tiles / split tiles, 2, 3 and 4 bits:
+//   64 tiles (4096 rows, 512 tokens)    K = 2048 22.0/19.9 23.1/20.2 25.6/21.1   K = 4096 35.3/28.4 37.8/29.9 41.4/31.3   K = 11008 79.7/59.3 84.5/61.6 95.7/66.7
+//   72 tiles (6144 rows, 333 tokens)    K = 2048 22.6/24.3 23.7/25.0 25.3/27.6   K = 4096 35.3/34.5 37.3/37.1 42.4/42.9   K = 11008 80.8/75.1 84.8/79.0 97.0/93.7
+//   80 tiles (4096 rows, 640 tokens)    K = 2048 23.6/27.2 24.7/27.5 26.6/29.4   K = 4096 37.6/38.0 39.6/40.6 42.3/45.1   K = 11008 82.8/79.9 89.0/85.1 99.6/98.2
+//   86 tiles (11008 rows, 200 tokens)   K = 2048 22.5/26.9 23.4/28.4 27.0/31.5   K = 4096 36.6/39.8 40.2/43.3 42.3/47.9   K = 11008 82.5/84.1 89.7/91.6 98.8/103.7
+//   128 tiles (4096 rows, 1024 tokens)  K = 2048 24.1/29.4 25.1/30.5 27.2/34.0   K = 4096 39.9/47.0 41.6/47.7 45.6/51.6   K = 11008 95.0/101.5 100.4/106.4 109.7/117.4
+//   129 tiles (11008 rows, 333 tokens)  K = 2048 32.4/34.3 34.1/36.2 40.3/40.6   K = 4096 53.9/51.6 58.2/56.5 67.8/64.6   K = 11008 121.6/114.0 131.1/119.2 161.3/144.5
+//   144 tiles (4096 rows, 1100 tokens)  K = 2048 30.4/32.7 32.2/34.4 37.3/38.9   K = 4096 49.0/51.7 51.8/54.1 61.0/61.5   K = 11008 114.6/115.7 125.4/122.8 152.5/144.0
+// (The split kernel addresses the activations with 32 bits.)
 static bool split_takes(int M, int N, int K)
 {
     const long long tiles = (long long)((N + 255) / 256) * ((M + kGemmTokens - 1) / kGemmTokens);
-    return tiles <= kSplitMostTiles && (long long)plan_gemm(M, N, K, 2).m_pad * K * 2 < (1ll << 32);
+    const bool idle = tiles <= 64 + K / 512 || (tiles > 128 && tiles <= 136 && K >= 4096);
+    return idle && (long long)plan_gemm(M, N, K, 2).m_pad * K * 2 < (1ll << 32);
 }
 
 // Tile of a launch of the split kernel: rounds of workgroups over the compute units times the time of one workgroup.  Measured

@@ -71,7 +71,7 @@ def test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised):
 # layer that the large tiles take
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("shape", [(48, 1280, 33), (48, 1280, 64), (1040, 512, 300), (5136, 256, 34), (5136, 1280, 65), (5136, 256, 97), (5136, 256, 200),
-                                   (5136, 2304, 300), (8016, 2304, 129), (4096, 4096, 17), (4112, 4096, 32), (28800, 256, 128), (28800, 256, 257)])
+                                   (5136, 2304, 300), (8016, 2304, 129), (4096, 4096, 17), (4112, 4096, 32), (28800, 256, 128), (28800, 256, 257), (16384, 256, 128), (16400, 256, 128)])
 def test_gemm_split_tile_edges(bits, shape):
     N, K, M = shape
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
@@ -99,7 +99,7 @@ def _split_tile_of(N, K, M, bits):
 def test_gemm_every_split_tile(bits, tile):
     rows = [48 + 928 * i for i in range(37)] + [2704]
     found = [(N, K, M) for K in (2304, 1792) for M in (45, 77, 109, 141, 173, 237) for N in rows
-             if -(-N // 256) * -(-M // 128) <= 128 and _split_tile_of(N, K, M, bits) == tile]
+             if -(-N // 256) * -(-M // 128) <= 64 and _split_tile_of(N, K, M, bits) == tile]
     assert found
     N, K, M = found[0]
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
