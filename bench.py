@@ -140,6 +140,25 @@ class LayerSet:
                 shared_ws = g.workspace
                 self.groups.append(g)
 
+    def transforms_ahead(self):
+        """Whether the decode step writes its workspace: a small kernel transforms the activations ahead of the product then."""
+        def written(workspace, call):
+            workspace.fill_(0xA5)
+            call()
+            return bool((workspace != 0xA5).any())
+        if self.per_layer:
+            return any([written(m["ws"], lambda i=i: self.matrix_step(i, 0)) for i, m in enumerate(self.mats)])
+        return written(self.groups[0].workspace, self.groups[0])
+
+    def prefill_kernel(self):
+        """The matrix kernel of a prefill step, by the number of 256 x 128 output tiles of its layers."""
+        if self.M <= 32:
+            return "gemv_tokens_kernel (layers below 2^24 weights), gemm_split_kernel"
+        tiles = [-(-m["spec"].N // 256) * -(-self.M // 128) for m in self.mats]
+        if min(tiles) > 136:
+            return "gemm_group_kernel"
+        return "gemm_split_kernel" if max(tiles) <= 64 else "gemm_split_kernel or gemm_group_kernel, by layer (one gemm_mixed_kernel launch for both)"
+
     def block_step(self, replica):
         """One decode step in dependency order: one grouped launch per stage."""
         for g in self.block_groups[replica]:
@@ -401,7 +420,7 @@ def bench_offline(cfg, steps, warmup):
     rows = {
         "assign_kernel": (timed(lambda: lcd.lcd_assign_indices(w, cb, ncent, bits)), 3 * weights),
         "counts_kernel": (timed(lambda: lcd.lcd_cluster_counts(idx, bits)), weights),
-        "merge_kernel+remap_kernel": (timed(lambda: lcd.lcd_merge_closest(cb, counts, idx, ncent, bits, idx_out=idx_out)), 2 * weights),
+        "merge_kernel": (timed(lambda: lcd.lcd_merge_closest(cb, counts, idx, ncent, bits, idx_out=idx_out)), 2 * weights),
         "pack_kernel": (timed(lambda: lcd.lcd_pack_indices(idx, bits, out=packed)), weights + weights * bits // 8),
         "build_lut_kernel": (timed(lambda: lcd.lcd_build_lut(cb, bits)), N * ncent * 2 + lcd.lcd_lut_bytes(N, bits)),
     }
@@ -437,9 +456,9 @@ def main():
 
     decode = M <= 16
     n_launch = 1 if not args.per_layer else len(ls.mats)
-    decode_kernel = "gemv_bucket_kernel" if (M == 1 and cfg.bits < 4) else "gemv_tokens_kernel"
-    # the tokens kernel is preceded by a small activation-transform kernel for INT8 codes and for wide layers
-    prepass = decode_kernel == "gemv_tokens_kernel" and not args.per_layer and (args.act_int8 or max(s.K for _, s in cfg.matrices()) >= 16384)
+    bucket_tokens = {2: 4 if args.act_int8 else 2, 3: 1, 4: 0}[cfg.bits]   # most tokens the sparse-matrix-core kernel takes
+    decode_kernel = "gemv_bucket_kernel" if M <= bucket_tokens else "gemv_tokens_kernel"
+    prepass = decode and ls.transforms_ahead()
     if decode:
         metric, unit = "lut_gemv_effective_bandwidth_packed_index_bytes", "GB/s"
         value = ls.index_bytes / (wall_ms * 1e-3) / 1e9
@@ -461,7 +480,7 @@ def main():
         roofline = {
             "bound": "mfma", "achieved": ls.flops / (event_ms * 1e-3) / 1e12, "peak": MFMA_F16_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": ls.flops / (event_ms * 1e-3) / 1e12 / MFMA_F16_PEAK_TFLOPS, "traffic": None,
-            "kernel": "gemm_kernel" if args.per_layer else "gemm_group_kernel", "launches_per_step": n_launch,
+            "kernel": ls.prefill_kernel(), "launches_per_step": n_launch,
             "kernels_per_launch": 2, "algorithmic_flops_per_step": ls.flops,
             "avg_launch_us": event_ms * 1e3 / n_launch,
         }

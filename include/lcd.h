@@ -131,15 +131,16 @@ lcd_status lcd_build_lut(const uint16_t *codebook /*DEVICE*/, int N, int bits,
  * y       DEVICE fp16 [M][N] row-major (written, never read)
  * workspace  DEVICE, >= lcd_workspace_bytes(M,N,K,bits) bytes, contents ignored on entry.
  *
- * lcd_lut_gemv: decode path, 1 <= M <= 16, one kernel launch, any K.  M = 1 (and M = 2 with
+ * lcd_lut_gemv: decode path, 1 <= M <= 16, any K, one kernel launch (two on the route named last).  M = 1 (and M = 2 with
  *               2 bits): centroid-bucket sums on the sparse matrix core (Sec. 4.2), one sparse
  *               pass per token; otherwise (3 <= M <= 16, M = 2 with 3 bits, every M with 4 bits):
  *               register dequantisation into fp16 MFMA operands with the tokens as the matrix
  *               columns.  The smoothing is fused into the kernel, except on the dequantising
  *               route with many tokens on wide or many layers, where a small kernel ahead of the product
  *               leaves the smoothed activations in the workspace (same rounding, same result).
- * lcd_lut_gemm: prefill path, any M >= 1: up to 16 tokens (32 for small layers) the dequantising kernel of lcd_lut_gemv; beyond, a
- *               smoothing kernel into the workspace, then register dequantisation into fp16 MFMA operands.
+ * lcd_lut_gemm: prefill path, any M >= 1: up to 16 tokens (32 for layers of fewer than 2^24 weights) the dequantising kernel of
+ *               lcd_lut_gemv (its launches); beyond, a smoothing kernel into the workspace, then register dequantisation into
+ *               fp16 MFMA operands: two launches.
  * Both give bit-identical results from run to run (fixed reduction order).
  */
 lcd_status lcd_lut_gemv(const void *packed, const void *lut, const uint16_t *x, const float *s,
@@ -190,9 +191,10 @@ lcd_status lcd_lut_gemv_q8(const void *packed, const void *lut, const uint16_t *
                            void *workspace, size_t workspace_bytes, void *stream);
 
 /* The prefill path with the same input transformation (Sec. 4.1 applies it to the input of every
- * table-lookup layer, whatever the number of tokens): the smoothing kernel ahead of the matrix kernel
- * quantises instead (same binary32 quantiser, codes bit for bit those of lcd_lut_gemv_q8) and the
- * matrix kernel multiplies the fp32 sums by s_q before the one rounding to fp16.  Any M >= 1;
+ * table-lookup layer, whatever the number of tokens).  Kernels as lcd_lut_gemm, except that with 2 bits up to four
+ * tokens take the sparse matrix core as in lcd_lut_gemv_q8.  Where lcd_lut_gemm smooths ahead of the matrix kernel the
+ * codes are made there instead, elsewhere in the kernel itself (one binary32 quantiser, codes bit for bit those of
+ * lcd_lut_gemv_q8); the fp32 sums are multiplied by s_q before the one rounding to fp16.  Any M >= 1;
  * all other arguments, the workspace and the precondition on s*s_q as above. */
 lcd_status lcd_lut_gemm_q8(const void *packed, const void *lut, const uint16_t *x, const float *s, float s_q,
                            uint16_t *y, int M, int N, int K, int bits,
@@ -205,7 +207,8 @@ lcd_status lcd_lut_gemm_q8(const void *packed, const void *lut, const uint16_t *
  * GPU mostly idle.  lcd_lut_gemv_grouped runs `count` (1..16) independent products
  *     y_i = (x_i / s_i) . What_i^T            (same M and bits for all, any N_i, K_i)
  * with every argument of problems[i] as in lcd_lut_gemv, in one kernel launch for any M in
- * 1..16: the workgroups are shared out over the layers in proportion to their work.
+ * 1..16 (a second one ahead of it where the activations are transformed ahead): the workgroups are shared out over the
+ * layers in proportion to their work.
  * `problems` is a HOST array, read during the call only.  The layers' outputs must not overlap.
  * Workspace: at least lcd_workspace_bytes_grouped(problems, count, M, bits) bytes (DEVICE);
  * for M >= 2 it may receive the layers' transformed activations (at most M*K_i fp16 each).
@@ -227,7 +230,7 @@ lcd_status lcd_lut_gemv_grouped(const lcd_gemv_problem *problems /*HOST*/, int c
 /* Layers of different index widths in one call (the paper assigns a centroid count per layer,
  * Sec. 5: 5, 6, 10, ... centroids): bits is a HOST array of `count` widths, each 2, 3 or 4.
  * All layers are validated first; then the layers of each width that occurs go out as one
- * launch, in the order 2, 3, 4, on `stream`.  Workspace as for lcd_lut_gemv_grouped (its size
+ * lcd_lut_gemv_grouped call, in the order 2, 3, 4, on `stream`.  Workspace as for lcd_lut_gemv_grouped (its size
  * does not depend on the width). */
 lcd_status lcd_lut_gemv_grouped_mixed(const lcd_gemv_problem *problems /*HOST*/, const int *bits /*HOST*/, int count,
                                       int M, void *workspace, size_t workspace_bytes, void *stream);
@@ -237,13 +240,14 @@ lcd_status lcd_lut_gemv_grouped_mixed(const lcd_gemv_problem *problems /*HOST*/,
 lcd_status lcd_lut_gemv_q8_grouped(const lcd_gemv_problem *problems /*HOST*/, const float *s_q /*HOST*/, int count,
                                    int M, int bits, void *workspace, size_t workspace_bytes, void *stream);
 
-/* ---- grouped prefill: several independent layers in ONE pair of launches ------------------- *
+/* ---- grouped prefill: several independent layers in few launches --------------------------- *
  *
  * The same product as lcd_lut_gemm for `count` (1..16) layers with one token count M >= 1 and one
  * index width: one smoothing launch for all layers, then one matrix launch whose workgroups take
  * the layers' output tiles one layer after the other (those with the largest K first), so that
- * the compute units the tail of one layer leaves idle start on the next.  Results are bit for
- * bit those of lcd_lut_gemm on every layer.  `problems` is a HOST array, read during the call
+ * the compute units the tail of one layer leaves idle start on the next.  Layers that lcd_lut_gemm gives to the
+ * decode kernel (all with up to 16 tokens, small ones with up to 32) go out ahead as one decode call, of one or two
+ * launches.  Results are bit for bit those of lcd_lut_gemm on every layer.  `problems` is a HOST array, read during the call
  * only; outputs must not overlap.  Workspace: at least
  * lcd_workspace_bytes_gemm_grouped(problems, count, M, bits) bytes (DEVICE; the sum of the
  * layers' lcd_workspace_bytes): every layer's smoothed activations side by side.

@@ -40,7 +40,7 @@ struct BucketProblem {
 // a single layer, the layer itself (SingleLayer).  Then x, s and DecodeHead::word for layers that all read one input
 // (q, k, v or gate, up of a decoder block, and every single layer): the activations, which start the longest chain, are asked for
 // without waiting for the layer's record.
-// Measured, 7B blocks: 2 bits, 16 tokens 39.5 -> 37.1 us; 4 tokens of INT8 codes 32.4 -> 31.5; 3 bits, one token 34.6 -> 33.9.
+// Measured, 7B blocks: 2 bits, 16 tokens 39.4 -> 38.4 us; 4 tokens of INT8 codes 32.4 -> 31.5; 3 bits, one token 34.6 -> 33.9.
 struct DecodeHead {
     const uint16_t *x;   // input of all layers (shared)
     const float *s;
@@ -65,7 +65,6 @@ __device__ __forceinline__ int layer_of_workgroup(uint32_t b, uint32_t t0, uint3
 }
 struct BucketBatch {
     BucketProblem p[kMaxGroup];
-    int count;
 };
 
 // The input a workgroup's layer reads: from the leading arguments if the layers share it, else from the record.  (The

@@ -17,8 +17,11 @@ __global__ void __launch_bounds__(kGemmWaves * 64, 1) gemm_group_kernel(const Ge
 // Which kernel takes a layer.  The rules look at the layer and the number of tokens alone, never at the group it is
 // called in: the kernels add in different orders, and a layer's result must not depend on its neighbours.
 // Up to 16 tokens the decode kernels (the dequantising one, except for INT8 codes with 2-bit indices).  Up to 32 tokens the tokens kernel, which needs no smoothing launch,
-// also keeps the small layers (1024 x 2048, 3 bits, 32 tokens: 7.5 us against 10.1 with the split kernel; 4096 x 4096: 10.9
-// against 10.1, 4096 x 11008: 21.6 against 15.5).
+// also keeps the small layers.  One call with 32 tokens, weights from memory, tokens kernel / split kernel, 2, 3 and 4 bits: 2048 x 2048
+// 6.4/8.1 6.7/8.9 7.0/9.3 us, 2048 x 4096 8.3/10.6 8.7/11.4 9.3/11.9, 11008 x 1024 7.1/8.7 7.9/9.0 7.7/9.8, 28672 x 512 11.9/12.0 13.2/12.4 16.6/13.3;
+// beyond the line 4096 x 4096 8.9/10.9 9.4/11.6 10.2/12.5, 6144 x 4096 11.6/11.0 12.5/11.8 15.1/13.0, 8192 x 4096 11.7/11.2 13.0/12.1 15.9/13.8.  A
+// layer of 4096 x 4096 alone would gain from the tokens kernel too; three of them in one call, which must take the same kernel, are
+// 12288 x 4096 to it and would lose.
 static bool decode_takes(int M, int N, int K)
 {
     return (M <= 16 || (M <= kDecodeTokens && (long long)N * K < (1ll << 24))) && (long long)M * K * 2 < (1ll << 32);
@@ -43,7 +46,10 @@ static bool split_takes(int M, int N, int K)
 
 // Tile of a launch of the split kernel: rounds of workgroups over the compute units times the time of one workgroup.  Measured
 // in single rounds (K = 4096 and 11008): a fixed part, and a part per column that is bound by the activations' way into LDS
-// (75..98 GB/s per compute unit; 32 tokens x 64 rows: by the dequantiser).
+// (75..98 GB/s per compute unit; 32 tokens x 64 rows: by the dequantiser).  In launches of several rounds every tile takes longer
+// than that (the rounds share the L2), but their order holds: 177 launches timed with each of the six tiles (1 to 3 layers of 1024..13824
+// rows, K = 2048..11008, 33..512 tokens, 2, 3 and 4 bits) took 1.002 times the best tile's time in the mean, 1.03 at the ninth decile,
+// 1.14 at most (three layers of 2048 x 2048, 512 tokens, 3 bits: 32.8 against 28.9 us).
 struct SplitTile { int pairs, blocks; double fixed_us, column_ns[3]; };   // column_ns: 2, 3, 4 bits
 static const SplitTile kSplitTiles[] = {
     {2, 4, 3.0, {2.58, 2.70, 3.13}}, {2, 3, 2.5, {2.13, 2.40, 3.05}}, {2, 2, 2.0, {1.56, 1.74, 2.33}},

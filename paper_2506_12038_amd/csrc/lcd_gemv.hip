@@ -800,7 +800,6 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
         batch.p[i].tiles_extra = batch.p[i].nt % nwg[i];
     }
     for (int i = count; i <= kMaxGroup; ++i) wg_begin[i] = acc;
-    batch.count = count;
     static_assert(kMaxGroup == 16, "eight leading kernel arguments hold wg_begin[1..16]");
     if (acc >= 0x7fff) return (int)hipErrorInvalidConfiguration;   // 16-bit table fields (acc <= max(CUs, count))
     WgTable table;

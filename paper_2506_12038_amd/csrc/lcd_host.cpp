@@ -108,8 +108,8 @@ size_t lcd_lut_bytes(int N, int bits)
 size_t lcd_workspace_bytes(int M, int N, int K, int bits)
 {
     if (check_shape(N, K, bits) != LCD_OK || M < 1) return 0;
-    // the prefill path keeps the smoothed activations there; the decode path only the activation
-    // codes of lcd_lut_gemv_q8 with M > 1 (M*K fp16 numbers, less than the prefill's M padded to 128)
+    // the prefill path keeps the smoothed activations there; the decode path the smoothed activations or the
+    // codes where they are made ahead of the product (M*K fp16 numbers, less than the prefill's M padded to 128)
     const GemmPlan m = plan_gemm(M, N, K, bits);
     return m.xs_bytes < 256 ? 256 : m.xs_bytes;
 }
@@ -266,7 +266,7 @@ lcd_status lcd_lut_gemv_q8(const void *packed, const void *lut, const uint16_t *
 size_t lcd_workspace_bytes_grouped(const lcd_gemv_problem *problems, int count, int M, int bits)
 {
     if (!problems || count < 1 || count > kMaxGroup || M < 1 || M > 16) return 0;
-    size_t need = 256, codes = 0;   // the q8 variant keeps every layer's activation codes side by side
+    size_t need = 256, codes = 0;   // activations that are transformed ahead of the product lie there side by side
     for (int i = 0; i < count; ++i) {
         const size_t w = lcd_workspace_bytes(M, problems[i].N, problems[i].K, bits);
         if (w == 0) return 0;

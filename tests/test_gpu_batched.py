@@ -32,13 +32,11 @@ def test_gemm_token_block_edges(bits, M, shape):
 # The tokens kernel with many row tiles per workgroup: fewer tiles than its ring of packed words has slots in a
 # pass (the last of two), one tile either side of the smaller variants, of what it holds (14) and of two full passes; activations
 # smoothed in the kernel, and (INT8 codes, 16 tokens) transformed ahead.  Most workgroups have `tiles` row tiles, a few one less.
-@pytest.mark.parametrize("bits", [2, 3, 4])
+# (One token: 4 bits only, the other widths take the bucket kernel.)
+@pytest.mark.parametrize("bits,M,quantised", [(4, 1, False)] + [(b, M, q) for b in (2, 3, 4) for M, q in ((3, False), (16, False), (16, True))])
 @pytest.mark.parametrize("tiles,K", [(5, 2304), (7, 4352), (8, 512), (13, 2304), (14, 4352), (15, 2304), (28, 1280), (29, 2304)])
-@pytest.mark.parametrize("M,quantised", [(1, False), (3, False), (16, False), (16, True)])
 def test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised):
     import torch
-    if M == 1 and bits != 4:
-        pytest.skip("one token takes the bucket kernel")
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     rows = cus * 16                                   # one tile per workgroup
     N = tiles * rows - 48
