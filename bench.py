@@ -462,7 +462,7 @@ def main():
     if decode:
         metric, unit = "lut_gemv_effective_bandwidth_packed_index_bytes", "GB/s"
         value = ls.index_bytes / (wall_ms * 1e-3) / 1e9
-        traffic, traffic_file = (measured_traffic(decode_kernel, args.config) if (n_launch == 1 and args.bits is None and not args.act_int8)
+        traffic, traffic_file = (measured_traffic(decode_kernel, args.config) if (n_launch == 1 and M == 1 and args.bits is None and not args.act_int8)
                                  else (None, None))
         roofline = {
             "bound": "hbm", "achieved": ls.index_bytes / (event_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
