@@ -26,21 +26,33 @@ static bool decode_takes(int M, int N, int K)
 {
     return (M <= 16 || (M <= kDecodeTokens && (long long)N * K < (1ll << 24))) && (long long)M * K * 2 < (1ll << 32);
 }
-// The split kernel takes layers that leave many compute units idle as 256 x 128 tiles: up to 64 tiles and a few more where K is large
-// (cut in two, 64 tiles fill half of 256 compute units), and just above 128, which no longer fit one round when cut in two.
+// The split kernel takes layers of few output tiles.  Its advantage lies in rounds of workgroups over the 256 compute units (the whole
+// chip, whatever part of it a process sees: a layer's bits must not depend on that) and in tiles as narrow as the tokens: 256 x 128 tiles
+// spend the same time on 33 tokens as on 128.  It takes what fits
+//   - one round of any of its tiles (64 x 128 being the largest);
+//   - two rounds of 64 x 64;
+//   - two rounds of 64 x 96 where K >= 8192, or where K >= 4096 and a quarter or more of the large tiles' work would be padding;
+//   - just above 128 large tiles, which no longer fit one round when cut in two (K >= 4096).
 // Time of a call, large tiles / split tiles, 2, 3 and 4 bits:
-//   64 tiles (4096 rows, 512 tokens)    K = 2048 22.0/19.9 23.1/20.2 25.6/21.1   K = 4096 35.3/28.4 37.8/29.9 41.4/31.3   K = 11008 79.7/59.3 84.5/61.6 95.7/66.7
-//   72 tiles (6144 rows, 333 tokens)    K = 2048 22.6/24.3 23.7/25.0 25.3/27.6   K = 4096 35.3/34.5 37.3/37.1 42.4/42.9   K = 11008 80.8/75.1 84.8/79.0 97.0/93.7
-//   80 tiles (4096 rows, 640 tokens)    K = 2048 23.6/27.2 24.7/27.5 26.6/29.4   K = 4096 37.6/38.0 39.6/40.6 42.3/45.1   K = 11008 82.8/79.9 89.0/85.1 99.6/98.2
-//   86 tiles (11008 rows, 200 tokens)   K = 2048 22.5/26.9 23.4/28.4 27.0/31.5   K = 4096 36.6/39.8 40.2/43.3 42.3/47.9   K = 11008 82.5/84.1 89.7/91.6 98.8/103.7
-//   128 tiles (4096 rows, 1024 tokens)  K = 2048 24.1/29.4 25.1/30.5 27.2/34.0   K = 4096 39.9/47.0 41.6/47.7 45.6/51.6   K = 11008 95.0/101.5 100.4/106.4 109.7/117.4
-//   129 tiles (11008 rows, 333 tokens)  K = 2048 32.4/34.3 34.1/36.2 40.3/40.6   K = 4096 53.9/51.6 58.2/56.5 67.8/64.6   K = 11008 121.6/114.0 131.1/119.2 161.3/144.5
-//   144 tiles (4096 rows, 1100 tokens)  K = 2048 30.4/32.7 32.2/34.4 37.3/38.9   K = 4096 49.0/51.7 51.8/54.1 61.0/61.5   K = 11008 114.6/115.7 125.4/122.8 152.5/144.0
+//   one round         4096 rows, 512 tokens    K = 2048 22.0/19.9 23.1/20.2 25.6/21.1   K = 4096 35.3/28.4 37.8/29.9 41.4/31.3   K = 11008 79.7/59.3 84.5/61.6 95.7/66.7
+//   two of 64 x 64    28672 rows, 40 tokens    K = 2048 19.7/17.6 21.1/18.8 24.0/21.8   K = 4096 31.6/25.3 33.7/27.7 39.0/32.7   K = 8192 54.1/40.8 58.4/44.4 67.6/53.3
+//                     8448 rows, 192 tokens    K = 2048 20.4/18.5 21.2/19.3 23.9/22.3   K = 4096 33.3/27.0 35.1/29.6 39.5/34.4   K = 8192 56.3/42.8 60.2/47.3 70.0/56.8
+//   two of 64 x 96    11008 rows, 160 tokens   K = 2048 20.8/21.5 21.7/22.0 24.5/24.9   K = 4096 33.9/30.8 35.8/33.6 40.0/39.3   K = 8192 56.7/51.0 61.1/55.2 68.7/66.2
+//                     4096 rows, 545 tokens    K = 2048 22.0/23.2 23.0/23.9 25.9/26.8   K = 4096 35.7/34.6 37.4/37.1 42.1/42.7   K = 8192 59.8/56.4 64.7/60.7 75.8/72.3
+//   two of 64 x 128   11008 rows, 224 tokens   K = 2048 21.6/25.5 22.2/27.9 25.7/29.5   K = 4096 35.3/38.2 37.4/41.6 43.7/46.4   K = 8192 58.9/62.3 62.9/67.5 74.3/76.7
+//                     28672 rows, 128 tokens   K = 2048 22.9/28.2 23.8/29.4 26.6/32.0   K = 4096 38.0/44.1 39.7/46.0 45.1/50.7   K = 8192 65.7/72.3 68.5/74.4 78.2/83.9
+//   129 large tiles   11008 rows, 333 tokens   K = 2048 32.4/34.3 34.1/36.2 40.3/40.6   K = 4096 53.9/51.6 58.2/56.5 67.8/64.6   K = 11008 121.6/114.0 131.1/119.2 161.3/144.5
+// Several layers of a size in one launch fill large tiles' rounds better.  K = 4096, 3 bits: two layers of 11008 rows, 160 tokens 58.7/52.3, 256 tokens 60.5/68.0;
+// three of 4096 rows, 576 tokens 67.1/88.4, 1024 tokens 109/139: hence the padding's share, which leaves those to the large tiles.
 // (The split kernel addresses the activations with 32 bits.)
 static bool split_takes(int M, int N, int K)
 {
-    const long long tiles = (long long)((N + 255) / 256) * ((M + kGemmTokens - 1) / kGemmTokens);
-    const bool idle = tiles <= 64 + K / 512 || (tiles > 128 && tiles <= 136 && K >= 4096);
+    constexpr long long kChip = 256;
+    const long long blocks = (M + kGemmTokens - 1) / kGemmTokens, tiles = (N + 255) / 256 * blocks, rows64 = (N + 63) / 64;
+    const bool padding = 3 * blocks * kGemmTokens >= 4ll * M;
+    const bool one_round = rows64 * blocks <= kChip, narrow = rows64 * ((M + 63) / 64) <= 2 * kChip;
+    const bool medium = rows64 * ((M + 95) / 96) <= 2 * kChip && (K >= 8192 || (K >= 4096 && padding));
+    const bool idle = one_round || narrow || medium || (tiles > 128 && tiles <= 136 && K >= 4096);
     return idle && (long long)plan_gemm(M, N, K, 2).m_pad * K * 2 < (1ll << 32);
 }
 

@@ -69,7 +69,8 @@ def test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised):
 # layer that the large tiles take
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("shape", [(48, 1280, 33), (48, 1280, 64), (1040, 512, 300), (5136, 256, 34), (5136, 1280, 65), (5136, 256, 97), (5136, 256, 200),
-                                   (5136, 2304, 300), (8016, 2304, 129), (4096, 4096, 17), (4112, 4096, 32), (28800, 256, 128), (28800, 256, 257), (16384, 256, 128), (16400, 256, 128)])
+                                   (5136, 2304, 300), (8016, 2304, 129), (4096, 4096, 17), (4112, 4096, 32), (28800, 256, 128), (28800, 256, 257), (16384, 256, 128), (16400, 256, 128),
+                                   (32768, 256, 64), (32784, 256, 64), (10912, 512, 192), (10928, 512, 192)])
 def test_gemm_split_tile_edges(bits, shape):
     N, K, M = shape
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
