@@ -1,4 +1,4 @@
-// What the two decode kernels (lcd_gemv.hip, lcd_tokens.hip) and their launcher share.
+// What the two decode kernels (lcd_bucket.hip, lcd_tokens.hip) and their launcher share.
 #pragma once
 #include <hip/hip_runtime.h>
 #include "lcd_internal.h"
@@ -100,6 +100,19 @@ __device__ __forceinline__ LayerPart part_of(const BucketBatch &batch, int pi, u
     l.tb = l.ta + base + (li < extra ? 1 : 0);
     return l;
 }
+
+// ---- bucket kernel (lcd_bucket.hip) ---------------------------------------------------------------
+struct BucketVariant {
+    const void *fn;
+    int tiles;          // row tiles it holds at a time
+    int waves;          // waves of its workgroups
+    size_t lds_bytes;
+    int id;             // 0 .. kBucketVariants - 1
+};
+constexpr int kBucketVariants = 64;
+// tokens: 1 (2 and 3 bits), 2 (2 bits), 3 and 4 (2 bits, INT8 codes)
+// tiles: most row tiles of a workgroup; kc: chunks of the widest layer
+BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int tiles, int kc);
 
 // ---- tokens kernel (lcd_tokens.hip) ---------------------------------------------------------------
 constexpr int kTokenBlock = 16;      // tokens per block of the tokens kernel (the columns of one matrix instruction)

@@ -106,26 +106,22 @@ __device__ __forceinline__ float clipped_quotient(uint32_t x, Divisor dv)
 // The code as an fp16 number: integers up to 128 are exact.
 template <int HALF>
 __device__ __forceinline__ _Float16 quantise_half(uint32_t x, Divisor dv) { return (_Float16)__builtin_rintf(clipped_quotient<HALF>(x, dv)); }
-// The codes of eight columns (four registers of two) as int8 numbers, and as fp16 numbers (HALVES): adding 1.5 * 2^23 rounds to an
+// The codes of four columns (two registers of two) as int8 numbers, and as fp16 numbers (HALVES): adding 1.5 * 2^23 rounds to an
 // integer, half to even, and leaves its two's complement in the low bits.
 template <bool HALVES>
-__device__ __forceinline__ uint2v quantise_bytes(uint4v x, const Divisor (&dv)[8], half8 &halves)
+__device__ __forceinline__ uint32_t quantise_four(uint2v x, const Divisor (&dv)[4], uint32_t (&halves)[2])
 {
     constexpr float kMagic = 12582912.0f;
-    uint2v o;
+    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+    uint32_t r[4];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        uint32_t r[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t xp = x[2 * h + (e >> 1)];
-            const float v = ((e & 1) ? clipped_quotient<1>(xp, dv[4 * h + e]) : clipped_quotient<0>(xp, dv[4 * h + e])) + kMagic;
-            r[e] = __builtin_bit_cast(uint32_t, v);
-            if (HALVES) halves[4 * h + e] = (_Float16)(v - kMagic);
-        }
-        o[h] = __builtin_amdgcn_perm(r[1], r[0], 0x0c0c0400u) | __builtin_amdgcn_perm(r[3], r[2], 0x04000c0cu);
+        const float v0 = clipped_quotient<0>(x[h], dv[2 * h]) + kMagic, v1 = clipped_quotient<1>(x[h], dv[2 * h + 1]) + kMagic;
+        r[2 * h] = __builtin_bit_cast(uint32_t, v0);
+        r[2 * h + 1] = __builtin_bit_cast(uint32_t, v1);
+        if (HALVES) halves[h] = __builtin_bit_cast(uint32_t, half2v{(_Float16)(v0 - kMagic), (_Float16)(v1 - kMagic)});
     }
-    return o;
+    return __builtin_amdgcn_perm(r[1], r[0], 0x0c0c0400u) | __builtin_amdgcn_perm(r[3], r[2], 0x04000c0cu);
 }
 
 // a ^ (b & c): one v_bitop3_b32.

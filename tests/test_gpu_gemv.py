@@ -22,11 +22,9 @@ def test_gemv_m1_small(bits, shape):
 @pytest.mark.parametrize("bits", [2, 3])
 @pytest.mark.parametrize("tiles_per_workgroup,K", [(3, 4352), (5, 4352), (6, 4352), (7, 4352), (3, 8704), (33, 512)])
 def test_gemv_m1_runs_of_every_length_modulo_four(bits, tiles_per_workgroup, K):
-    # The single-token kernel loads packed words three steps ahead through four register sets; a run of
-    # row tiles (one visit in one K segment) whose length is no multiple of four ends in a short turn and
-    # hands the next run its loads in other sets.  One layer over all compute units gives every workgroup
-    # the same run length: 3, 5, 6, 7 (remainders 3, 1, 2, 3) with two or three segments, and 33 = a full
-    # visit of 32 plus one tile.  M = 2 takes the two-token variant of that kernel at 2 bits and the
+    # One layer over all compute units gives every workgroup the same run of row tiles: runs that are no
+    # multiple of what the bucket kernel takes at a time, over one to three chunks per wave, and 33 = more
+    # than two visits' bucket sums.  M = 2 takes the two-token variant of that kernel at 2 bits and the
     # dequantising kernel at 3 bits over the same sequence; M = 3 the dequantising kernel.
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
@@ -35,6 +33,39 @@ def test_gemv_m1_runs_of_every_length_modulo_four(bits, tiles_per_workgroup, K):
         layer = synth.make_layer_uniform(N, K, bits, M, seed=100 * tiles_per_workgroup + bits + M)
         err = check_layer(layer, bits)
         print(N, K, bits, M, err)
+
+
+# Every variant of the bucket kernel: run lengths either side of the passes (1, 2, 3, 5, 7, 10, 14 row tiles) and of a visit's
+# bucket sums (14 to 16 tiles), fewer chunks than waves, one and several chunks per wave.  Most workgroups have `tiles` row tiles, a few one less.
+@pytest.mark.parametrize("bits,M,quantised", [(2, 1, False), (3, 1, False), (2, 2, False), (2, 1, True), (3, 1, True), (2, 2, True), (2, 3, True), (2, 4, True)])
+@pytest.mark.parametrize("tiles,K", [(2, 2304), (3, 256), (4, 4352), (6, 2304), (8, 4352), (11, 2304), (15, 4352), (17, 512), (29, 2304)])
+def test_bucket_kernel_passes_and_visits(bits, M, quantised, tiles, K):
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rows = cus * 16                                   # one tile per workgroup
+    N = tiles * rows - 48
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tiles * K + M)
+    packed = torch.randint(0, 256, (lcd.lcd_packed_bytes(N, K, bits),), dtype=torch.uint8, device="cuda", generator=g)
+    codebook = (torch.randn((N, 1 << bits), device="cuda", generator=g) * 0.02).half()
+    x = torch.randn((M, K), device="cuda", generator=g).half()
+    s = torch.rand((K,), device="cuda", generator=g) + 0.5
+    s_q = 0.03
+    if quantised:
+        call = lambda p, l, n, **kw: lcd.lcd_lut_gemv_q8(p, l, x, s, s_q, n, bits, **kw)
+    else:
+        call = lambda p, l, n, **kw: lcd.lcd_lut_gemv(p, l, x, s, n, bits, **kw)
+    y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+    call(packed, lcd.lcd_build_lut(codebook, bits), N, y=y)
+    for first in range(0, N, rows):                   # the same rows in calls of one tile per workgroup: the same bits
+        n = min(rows, N - first)
+        part = packed[lcd.lcd_packed_bytes(first, K, bits) if first else 0:][:lcd.lcd_packed_bytes(n, K, bits)].clone()
+        cb = codebook[first:first + n].contiguous()
+        assert torch.equal(y[:, first:first + n], call(part, lcd.lcd_build_lut(cb, bits), n)), first
+    idx = lcd.lcd_unpack_indices(part, n, K, bits).cpu().numpy()
+    args = cb.cpu().numpy(), idx, x.cpu().numpy(), s.cpu().numpy()
+    Y = oracle.quantised_lut_matmul(*args, s_q, bits) if quantised else oracle.lut_matmul(*args, bits)
+    assert_parity(y[:, N - n:].cpu().numpy(), Y, 1e-3 if quantised else TOL)
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
