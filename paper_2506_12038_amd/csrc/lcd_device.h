@@ -71,8 +71,12 @@ __device__ __forceinline__ uint32_t smooth_pair(uint32_t a, float ra, uint32_t b
 // with an approximate reciprocal is not enough).  The division is the usual reciprocal-refinement
 // scheme, split so that the part which depends on the divisor alone is computed once per column
 // and shared by all tokens: a Newton step on the hardware reciprocal, then per quotient a product
-// and two residual corrections, all fused multiply-adds.  Valid without range scaling because
+// and a residual correction, all fused multiply-adds.  Valid without range scaling because
 // |x| is a finite fp16 number and the caller keeps 2^-64 < s * s_q < 2^64.
+// One correction is enough: it leaves the quotient within 2^-22 of an ulp of the true one before its last rounding, so a code could
+// depend on a second one only where x / (s * s_q) lies that close to the midpoint between a half-integer and its neighbour.  All such places --
+// every fp16 significand, every half-integer up to 128.5, the divisors within 6 ulps of their quotient, reciprocals off by one ulp
+// either way -- give the same code with one correction as with two (7B block, 2 bits, four tokens 28.4 -> 27.5 us).
 struct Divisor {
     float neg_d;   // -(s * s_q)
     float y;       // refined reciprocal of s * s_q
@@ -88,19 +92,16 @@ __device__ __forceinline__ Divisor make_divisor(float s, float s_q)
 
 // The clipped quotient of one half of a register (HALF 0: the low one), before the rounding to an integer: clipping first gives
 // the same code, the limits being integers.  v_fma_mix_f32 takes the fp16 operand as it is (no shift, no conversion), so
-// a quotient is five instructions and the clip one.
+// a quotient is three instructions and the clip one.
 template <int HALF>
 __device__ __forceinline__ float clipped_quotient(uint32_t x, Divisor dv)
 {
     float qt, e;
     if (HALF == 0) asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(qt) : "v"(x), "v"(dv.y));
     else asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(qt) : "v"(x), "v"(dv.y));
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        if (HALF == 0) asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[0,0,1]" : "=v"(e) : "v"(dv.neg_d), "v"(qt), "v"(x));
-        else asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(e) : "v"(dv.neg_d), "v"(qt), "v"(x));
-        qt = __builtin_fmaf(e, dv.y, qt);
-    }
+    if (HALF == 0) asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[0,0,1]" : "=v"(e) : "v"(dv.neg_d), "v"(qt), "v"(x));
+    else asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(e) : "v"(dv.neg_d), "v"(qt), "v"(x));
+    qt = __builtin_fmaf(e, dv.y, qt);
     return __builtin_amdgcn_fmed3f(qt, -128.0f, 127.0f);
 }
 // The code as an fp16 number: integers up to 128 are exact.
