@@ -118,7 +118,7 @@ BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int tiles, i
 constexpr int kTokenBlock = 16;      // tokens per block of the tokens kernel (the columns of one matrix instruction)
 constexpr int kMaxTokenBlocks = 2;   // blocks it holds in registers: up to 32 tokens
 
-// A variant for `blocks` token blocks that holds up to `tiles` row tiles at a time, or the one that holds
+// A variant for `tokens` tokens that holds up to `tiles` row tiles at a time, or the one that holds
 // the most if none holds that many.
 struct TokensVariant {
     const void *fn;
@@ -127,8 +127,8 @@ struct TokensVariant {
     size_t lds_bytes;
     int id;             // 0 .. kTokensVariants - 1
 };
-constexpr int kTokensVariants = 3 * kMaxTokenBlocks * 4 * 2;
+constexpr int kTokensVariants = 3 * kMaxTokenBlocks * 4 * 8;
 // ready: x holds the transformed activations in operand order (transform_kernel)
-TokensVariant tokens_variant(int bits, int blocks, int tiles, bool ready);
+TokensVariant tokens_variant(int bits, int tokens, int tiles, int kc, bool ready);
 
 }  // namespace lcd

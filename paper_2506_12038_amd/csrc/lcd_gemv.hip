@@ -80,7 +80,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     // (C[j] +- C[4 + j]) / 2 in binary32, which loses the centroid next to a large entry that no index names)
     const bool tokens_path = bits == 4 || M > sparse_tokens || (dense && !(all_quantised && bits == 2));
     const int blocks = (M + kTokenBlock - 1) / kTokenBlock;
-    const int held = tokens_path ? tokens_variant(bits, blocks, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds
+    const int held = tokens_path ? tokens_variant(bits, M, INT_MAX, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds
     // Several tokens: every workgroup transforms its layer's activations once per pass over its row tiles; ahead of the
     // product they are transformed once, at the price of a launch (3.6 us in a graph).  The line lies where that much work is
     // saved, counted in activations per workgroup (tokens x widest K x passes).  Per block, ahead / in the product: INT8 codes, 3 bits,
@@ -269,7 +269,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
         waves = v.waves;
         variant = v.id;
     } else {
-        const TokensVariant tv = tokens_variant(bits, blocks, most, staged_ahead);
+        const TokensVariant tv = tokens_variant(bits, M, most, widest / kTileCols, staged_ahead);
         lds = tv.lds_bytes;
         fn = tv.fn;
         waves = tv.waves;

@@ -6,9 +6,7 @@
 // 16 tokens are its columns, one dequantised operand serves every block.
 //
 // Work split.  A workgroup owns a contiguous run of row tiles (16 rows) of ONE layer and takes them
-// R at a time; its 8 waves split K, wave w takes the 256-column chunks w, w + 8, ...  (one row tile, and two with up to 16
-// tokens: 16 waves, which hide one another's staging and latencies better: 7B block, 2 bits, 16 tokens 41.5 -> 39.4 us, 4 bits 60.7 -> 57.3.
-// With more row tiles the registers are not there for it, and the dequantiser bounds it anyway.)  Per chunk a wave stages
+// R at a time; its waves (8 or 16) split K, wave w takes the 256-column chunks w, w + W, ...  Per chunk a wave stages
 // the activations of its 256 columns once (smoothing, Sec. 3.4, and the turn into operand order through its own piece of
 // LDS), then multiplies the chunk of every one of the R row tiles; the accumulators stay in registers over all of K.  No wave waits for another before the end: one
 // barrier, then the partial tiles are added, rounded once and stored.  An output is the sum, in order, of 8 sums of two:
@@ -17,17 +15,21 @@
 // on R or on the number of tokens -- so grouped, single and captured calls agree bit for bit.
 //
 // What bounds it: with many row tiles per workgroup the vector pipe (the dequantiser), 0.5 / 0.6 / 0.95 us (2 / 3 / 4 bits) per
-// row tile and round of 8 chunks; with one row tile per workgroup the staging of the activations and the latencies in front.  A
-// second pass over the activations costs 4 to 6 us, hence the variant of 14 row tiles (up to 57344 rows on 256 compute units
-// in one pass): seven layers of a 7B block in one launch, 16 tokens, 2 / 3 / 4 bits, passes of 6, 6 and 4 row tiles 24.5 / 30.5 /
-// 44.4 us, now 22.4 / 28.3 / 36.3; two layers of 28672 x 8192, 4 tokens, 3 / 4 bits 54.8 / 77.4 -> 44.1 / 64.6.  Its registers
+// row tile and round of 8 chunks; with one row tile per workgroup the staging of the activations and the latencies in front.
+// 16 waves hide one another's staging and latencies better where the registers are there for them: up to three row tiles, and any number
+// up to K = 4096, where a wave has one chunk at most: its operands stay (RESIDENT) and row tiles stream past them.  Neither loads of
+// tokens that are not there nor loads behind the last chunk are issued: a load out of range takes the time of its addresses.
+// us a launch in a graph, every load issued whatever is valid and 8 waves beyond two row tiles / now: q, k, v of a 7B block (3 row tiles), 16 tokens, 2 / 3 / 4
+// bits 10.1 / 12.3 / 14.5, 9.1 / 10.7 / 13.8; gate, up (5.4) 12.7 / 16.1 / 21.3, 11.7 / 14.1 / 18.7; o (1) 6.1 / 7.0 / 7.3, 5.5 / 5.8 / 6.8; three tokens, 3 bits:
+// q, k, v 10.4, 8.5; gate, up 13.7, 11.3; o 6.0, 4.5; down (K = 11008) 9.9, 8.0.  Two resident chunks per wave (K = 5120, 8192) spill.
+//
+// Beyond K = 4096 a second pass over the activations costs 4 to 6 us, hence the variant of 14 row tiles (up to 57344 rows on 256 compute units
+// in one pass): two layers of 28672 x 8192, 4 tokens, 3 / 4 bits 54.8 / 77.4 -> 44.1 / 64.6.  Its registers
 // hold the packed words of a few tiles only, in a ring (2 / 3 / 4 bits: 4, 4, 3 tiles ahead, which is enough of them under way), and at 3 and 4 bits
 // no row tables: those are read from LDS one tile ahead.
-// Measured against the kernel before it (K in segments, partial tiles of two row tiles exchanged through
-// LDS at a barrier after every second tile, no more than 16 tokens): 4096 x 11008, 3 bits, 3 tokens
-// 16.5 -> 9.0 us a call; blocks of 2, 3 and 4-bit layers (5120 / 13824), 6 tokens, 104 -> 71 us a block; 7B
-// block, 2 bits, 16 tokens 44.3 -> 38.4 us.
 #include <hip/hip_runtime.h>
+#include <climits>
+#include <type_traits>
 #include "lcd_decode.h"
 
 namespace lcd {
@@ -58,16 +60,17 @@ struct TokTile {
 template <int BITS> struct TokTables { typedef RowTables type; };
 template <> struct TokTables<4> { typedef RowTables4 type; };
 
-template <int BITS, int TB, int R, int WAVES, bool READY>
+// PAIRS: pairs of tokens the launch may have per block
+template <int BITS, int TB, int R, int WAVES, int PAIRS, bool READY, bool RESIDENT>
 __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32_t t0, const uint32_t t1, const uint32_t t2, const uint32_t t3,
                                                                    const uint32_t t4, const uint32_t t5, const uint32_t t6, const uint32_t t7,
                                                                    const uint16_t *head_x, const float *head_s, const uint32_t head_word, const BucketBatch batch)
 {
     constexpr uint32_t TBYTES = kTileRows * kTileCols * BITS / 8;
     constexpr int NC = BITS == 2 ? 4 : 8;
-    constexpr int D = R <= 2 && WAVES == kBW ? 2 : 1;   // chunks whose packed words are loaded ahead
     constexpr int RING = R == kManyTiles ? ring_tiles<BITS>() : R;   // row tiles whose words of a chunk are held
     constexpr bool TABLES = tables_in_lds<BITS, R>();
+    constexpr bool STRAIGHT = TB == 1 && R <= 3 && !(BITS == 4 && R == 2 && PAIRS == 8);   // short code, and registers left: the last chunk has a copy of its own
     constexpr int SETS = 2 * kBW / WAVES;         // accumulator sets of a wave (see the order of the additions above)
     constexpr int kWaveBytes = tokens_wave_bytes<TB, R>();
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // one piece per wave: its stage, in the end its partial tiles; then the row tables
@@ -91,10 +94,11 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     // columns 64 q + 8 g .. of the lane's token.  Else: columns 8 kg .., tokens th + 2 mm.
     // The (token pair, chunk) part of the address is wave-uniform and travels as the scalar offset; lanes
     // of a token past the last one read zeros through an offset that is out of range.
-    uint4v xr[TB][8];
+    constexpr int XR = READY ? 8 : PAIRS;
+    uint4v xr[TB][XR];
     const uint32_t row_bytes = (uint32_t)K * 2;
     const uint32_t x_lane = 16 * kg + th * row_bytes, x_last = th ? kOob : 16u * kg;
-    auto load_x = [&](int chunk) {
+    auto load_x = [&](int chunk) __attribute__((always_inline)) {
         uint32_t o = __builtin_amdgcn_readfirstlane((uint32_t)chunk * (kTileCols * 2));
         const int left = __builtin_amdgcn_readfirstlane(chunk < kc ? M : 0);   // tokens of this chunk
         if constexpr (READY) {        // 16 bytes per token, the tokens of a (chunk, g, q) side by side
@@ -111,7 +115,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
 #pragma unroll
         for (int t = 0; t < TB; ++t)
 #pragma unroll
-            for (int mm = 0; mm < 8; ++mm) {
+            for (int mm = 0; mm < PAIRS; ++mm) {
                 const int base = t * kTokenBlock + 2 * mm;
                 const uint32_t v = left > base + 1 ? x_lane : left > base ? x_last : kOob;
                 xr[t][mm] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, v, left > base ? o : 0u, 0);
@@ -119,7 +123,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
             }
     };
     float4v sa, sb;
-    auto load_s = [&](int chunk) {
+    auto load_s = [&](int chunk) __attribute__((always_inline)) {
         if constexpr (READY) return;
         const bool cv = chunk < kc;
         const uint32_t k0 = (uint32_t)chunk * kTileCols + 8 * kg;
@@ -139,7 +143,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     const __amdgpu_buffer_rsrc_t rs_tb = make_rsrc(reinterpret_cast<const uint8_t *>(l.lut) + (BITS == 4 ? 0 : (size_t)N * NC * 4),
                                                    (uint32_t)N * row_table_bytes<BITS>());
     // packed words of the R row tiles from v0 (tiles past v1 and chunks past the layer's read zeros, no traffic)
-    auto load_tile = [&](TokTile<BITS> &p, int tile, int v1, int chunk) {
+    auto load_tile = [&](TokTile<BITS> &p, int tile, int v1, int chunk) __attribute__((always_inline)) {
         const bool v = tile < v1 && chunk < kc;
         // the (tile, chunk) part of the address is wave-uniform and travels as the scalar offset
         const uint32_t o = v ? ((uint32_t)tile * (uint32_t)kc + (uint32_t)chunk) * TBYTES : 0u;
@@ -149,7 +153,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     };
 
     uint4v B[TB][8];       // B operands of the current chunk: lane (q, token j) holds columns 64 q + 8 g .. of its token
-    auto stage_x = [&]() {
+    auto stage_x = [&]() __attribute__((always_inline)) {
         if constexpr (READY) {
 #pragma unroll
             for (int t = 0; t < TB; ++t)
@@ -167,7 +171,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
             // operand slot order 0,4,1,5,2,6,3,7 (the dequantiser pairs weight v with weight 4 + v); rows past the last
             // token keep what the stage held: their columns of the product are never stored
 #pragma unroll
-            for (int mm = 0; mm < 8; ++mm) {
+            for (int mm = 0; mm < PAIRS; ++mm) {
                 if (t * kTokenBlock + 2 * mm >= M) break;      // uniform
                 const uint4v v = xr[t][mm];   // register i: columns 2i, 2i+1; result register i: columns i, 4+i
                 uint4v o;
@@ -197,22 +201,22 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     float4v acc[SETS][R][TB];
     typedef typename TokTables<BITS>::type Tables;
     Tables tab[TABLES ? 2 : R];         // TABLES: of this tile and the next
-    TokTile<BITS> P[D][RING];
+    TokTile<BITS> P[RING];
     // a row's table, 16 bytes (8 with 2 bits) at a time: piece i of it
-    auto table_piece = [&](bool valid, uint32_t row, int i) {
+    auto table_piece = [&](bool valid, uint32_t row, int i) __attribute__((always_inline)) {
         const uint32_t at = valid ? row * row_table_bytes<BITS>() + 16 * i : kOob;
         if constexpr (BITS == 2) {
             const uint2v t = __builtin_amdgcn_raw_buffer_load_b64(rs_tb, at, 0, 0);
             return uint4v{t[0], t[1], 0u, 0u};
         } else return __builtin_amdgcn_raw_buffer_load_b128(rs_tb, at, 0, 0);
     };
-    auto make_tables = [](uint4v t, uint4v u) {
+    auto make_tables = [](uint4v t, uint4v u) __attribute__((always_inline)) {
         if constexpr (BITS == 2) return RowTables{{t[0], 0u}, {t[1], 0u}};
         else if constexpr (BITS == 3) return RowTables{{t[0], t[1]}, {t[2], t[3]}};
         else return RowTables4{{t[0], t[1], t[2], t[3]}, {u[0], u[1], u[2], u[3]}};
     };
     uint8_t *const row_tables = smem + WAVES * kWaveBytes;
-    auto table_of = [&](int r) {        // tile r of the pass, from LDS
+    auto table_of = [&](int r) __attribute__((always_inline)) {        // tile r of the pass, from LDS
         const uint8_t *at = row_tables + (r * kTileRows + j) * row_table_bytes<BITS>();
         if constexpr (BITS == 2) {
             const uint2v t = *reinterpret_cast<const uint2v *>(at);
@@ -220,9 +224,9 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
         } else if constexpr (BITS == 3) return make_tables(*reinterpret_cast<const uint4v *>(at), uint4v{});
         else return make_tables(*reinterpret_cast<const uint4v *>(at), *reinterpret_cast<const uint4v *>(at + 16));
     };
-    auto tile_product = [&](const TokTile<BITS> &p, const typename TokTables<BITS>::type &t, float4v (&a)[TB]) {
+    auto tile_product = [&](const TokTile<BITS> &p, const typename TokTables<BITS>::type &t, float4v (&a)[TB]) __attribute__((always_inline)) {
         uint4v op0, op1;
-        auto multiply = [&](int d) {
+        auto multiply = [&](int d) __attribute__((always_inline)) {
 #pragma unroll
             for (int b = 0; b < TB; ++b) {
                 a[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(op0), as_half8(B[b][2 * d]), a[b], 0, 0, 0);
@@ -242,6 +246,72 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
         }
     };
 
+    float *part = reinterpret_cast<float *>(smem + wave * kWaveBytes);    // [tile][block][token 16][row 16]
+    auto put_tile = [&](int slot, int b, float4v v) __attribute__((always_inline)) {
+        *reinterpret_cast<float4v *>(&part[(slot * TB + b) * 256 + j * 16 + 4 * q]) = v;   // lane (q, j): rows 4q..4q+3 of token j
+    };
+    // the partial tiles of row tiles [first, end), in LDS from every wave's piece on: sum over the waves in order, one rounding, store
+    auto store_tiles = [&](int first, int end) __attribute__((always_inline)) {
+        __syncthreads();
+        const int quads = (end - first) * 4;                 // row quads of one token
+        for (int e = threadIdx.x; e < quads * M; e += WAVES * 64) {
+            const int m = e / quads, rest = e - m * quads, r = rest >> 2, rq = rest & 3;
+            const float *src = reinterpret_cast<const float *>(smem) + (r * TB + (m >> 4)) * 256 + (m & 15) * 16 + 4 * rq;
+            auto pair_sum = [&](int w) __attribute__((always_inline)) {
+                float4v v = *reinterpret_cast<const float4v *>(src + w * (kWaveBytes / 4));
+                if (SETS == 1) v += *reinterpret_cast<const float4v *>(src + (w + kBW) * (kWaveBytes / 4));
+                return v;
+            };
+            float4v sum = pair_sum(0);
+#pragma unroll
+            for (int w = 1; w < kBW; ++w) sum += pair_sum(w);
+            typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+            half4 o;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] = (_Float16)(sum[u] * out_scale);
+            *reinterpret_cast<half4 *>(y + (size_t)m * N + (size_t)(first + r) * kTileRows + 4 * rq) = o;
+        }
+    };
+
+    if constexpr (RESIDENT) {
+        // No wave has more than one chunk: its B operands are made once and stay, R row tiles after R row tiles go past, the next
+        // ones' words and tables under way.  Partial tiles wait in the wave's piece of LDS (its stage is used up) until it is full.
+        constexpr int VISIT = kWaveBytes / 1024 / R * R;
+        auto load_both = [&](int r, int tile) __attribute__((always_inline)) {
+            load_tile(P[r], tile, tb_end, wave);
+            const uint32_t row = (uint32_t)tile * kTileRows + j;
+            const uint4v t = table_piece(tile < tb_end, row, 0);
+            tab[r] = make_tables(t, BITS == 4 ? table_piece(tile < tb_end, row, 1) : uint4v{});
+        };
+#pragma unroll
+        for (int r = 0; r < R; ++r) load_both(r, ta + r);
+        stage_x();
+        int v0 = ta, visit = ta;
+        auto pass = [&](auto TAIL_) __attribute__((always_inline)) {
+            float4v a[R][TB];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                a[r][0] = float4v{0.f, 0.f, 0.f, 0.f};
+                if (wave < kc && v0 + r < tb_end) tile_product(P[r], tab[r], a[r]);      // uniform
+                if constexpr (!decltype(TAIL_)::value) load_both(r, v0 + R + r);
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) put_tile(v0 + r - visit, 0, a[r][0]);
+            v0 += R;
+        };
+        while (v0 + R < tb_end) {
+            pass(std::false_type{});
+            if (v0 - visit == VISIT) {
+                store_tiles(visit, v0);
+                visit = v0;
+                __syncthreads();
+            }
+        }
+        pass(std::true_type{});
+        store_tiles(visit, tb_end);
+        return;
+    }
+
     int pass_tiles = R;
     if (R == kManyTiles && tb_end - ta > R) {   // passes of one length: a last pass of few tiles would have few loads under way
         const int passes = (tb_end - ta + R - 1) / R;
@@ -257,9 +327,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
             if (BITS == 4) row_u = table_piece(valid, row, 1);
         }
 #pragma unroll
-        for (int dd = 0; dd < D; ++dd)
-#pragma unroll
-            for (int r = 0; r < RING; ++r) load_tile(P[dd][r], v0 + r, v1, wave + dd * WAVES);
+        for (int r = 0; r < RING; ++r) load_tile(P[r], v0 + r, v1, wave);
         if constexpr (!TABLES) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -283,58 +351,63 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
 #pragma unroll
                 for (int i = 0; i < SETS; ++i) acc[i][r][b] = float4v{0.f, 0.f, 0.f, 0.f};
 
-        auto chunk_products = [&](TokTile<BITS> (&p)[RING], float4v (&a)[R][TB], int chunk) {
+        // One chunk of the pass's row tiles.  The loads of the wave's next chunk are issued whatever is valid (one that may or may not have
+        // been issued makes the compiler wait for every load under way), but not behind the last chunk (TAIL): out of range they would
+        // still take the time of their addresses.
+        auto chunk_products = [&](auto TAIL_, float4v (&a)[R][TB], int chunk) __attribute__((always_inline)) {
+            constexpr bool TAIL = decltype(TAIL_)::value;
             if constexpr (TABLES) tab[0] = table_of(0);
             stage_x();
-            if (TB == 1) { load_s(chunk + WAVES); load_x(chunk + WAVES); }   // room for the next chunk's activations while this one multiplies
+            if constexpr (TB == 1 && !TAIL) { load_s(chunk + WAVES); load_x(chunk + WAVES); }   // room for the next chunk's activations while this one multiplies
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                if (r > 0 && v0 + r >= v1) break;               // uniform
-                if constexpr (RING == R && !TABLES) {
-                    tile_product(p[r], tab[r], a[r]);
-                    load_tile(p[r], v0 + r, v1, chunk + D * WAVES);
+                if constexpr (STRAIGHT) {
+                    if (r == 0 || v0 + r < v1) tile_product(P[r], tab[r], a[r]);     // uniform
+                    if constexpr (!TAIL) load_tile(P[r], v0 + r, v1, chunk + WAVES);
                 } else {
+                    if (r > 0 && v0 + r >= v1) break;           // uniform
+                    if constexpr (RING == R && !TABLES) {
+                        tile_product(P[r], tab[r], a[r]);
+                        load_tile(P[r], v0 + r, v1, chunk + WAVES);
+                        continue;
+                    }
                     if (TABLES && r + 1 < R) tab[(r + 1) & 1] = table_of(r + 1);
-                    tile_product(p[r % RING], tab[TABLES ? r & 1 : r], a[r]);
+                    tile_product(P[r % RING], tab[TABLES ? r & 1 : r], a[r]);
                     // the slot's next tile: of this chunk, or the one it starts the next chunk with
                     const bool same = r + RING < R && v0 + r + RING < v1;
-                    load_tile(p[r % RING], v0 + (same ? r + RING : r % RING), v1, same ? chunk : chunk + WAVES);
+                    load_tile(P[r % RING], v0 + (same ? r + RING : r % RING), v1, same ? chunk : chunk + WAVES);
                 }
             }
-            if (TB > 1) { load_s(chunk + WAVES); load_x(chunk + WAVES); }    // into the registers the B operands leave
+            if constexpr (TB > 1 && !TAIL) { load_s(chunk + WAVES); load_x(chunk + WAVES); }    // into the registers the B operands leave
         };
-        for (int c = wave; c < kc; c += 2 * WAVES) {
-            chunk_products(P[0], acc[0], c);
-            if (c + WAVES >= kc) break;
-            chunk_products(P[D - 1], acc[SETS - 1], c + WAVES);
+        if constexpr (!STRAIGHT) {
+            for (int c = wave; c < kc; c += 2 * WAVES) {
+                chunk_products(std::false_type{}, acc[0], c);
+                if (c + WAVES >= kc) break;
+                chunk_products(std::false_type{}, acc[SETS - 1], c + WAVES);
+            }
+        } else if constexpr (SETS == 1) {
+            int c = wave;
+#pragma unroll 1
+            for (; c + WAVES < kc; c += WAVES) chunk_products(std::false_type{}, acc[0], c);
+            if (c < kc) chunk_products(std::true_type{}, acc[0], c);
+        } else {
+            int c = wave;
+#pragma unroll 1
+            for (; c + WAVES < kc; c += 2 * WAVES) {
+                chunk_products(std::false_type{}, acc[0], c);
+                if (c + 2 * WAVES >= kc) { chunk_products(std::true_type{}, acc[SETS - 1], c + WAVES); c = kc; break; }
+                chunk_products(std::false_type{}, acc[SETS - 1], c + WAVES);
+            }
+            if (c < kc) chunk_products(std::true_type{}, acc[0], c);
         }
 
         // ---- partial tiles to LDS, one barrier, sum over the waves in order, one rounding, store
-        float *part = reinterpret_cast<float *>(smem + wave * kWaveBytes);    // [tile][block][token 16][row 16]
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int b = 0; b < TB; ++b)
-                *reinterpret_cast<float4v *>(&part[(r * TB + b) * 256 + j * 16 + 4 * q]) = SETS == 2 ? acc[0][r][b] + acc[SETS - 1][r][b] : acc[0][r][b];   // lane (q, j): rows 4q..4q+3 of token j
-        __syncthreads();
-        const int n_tiles = v1 - v0, quads = n_tiles * 4;    // row quads of one token
-        for (int e = threadIdx.x; e < quads * M; e += WAVES * 64) {
-            const int m = e / quads, rest = e - m * quads, r = rest >> 2, rq = rest & 3;
-            const float *src = reinterpret_cast<const float *>(smem) + (r * TB + (m >> 4)) * 256 + (m & 15) * 16 + 4 * rq;
-            auto pair_sum = [&](int w) {
-                float4v v = *reinterpret_cast<const float4v *>(src + w * (kWaveBytes / 4));
-                if (SETS == 1) v += *reinterpret_cast<const float4v *>(src + (w + kBW) * (kWaveBytes / 4));
-                return v;
-            };
-            float4v sum = pair_sum(0);
-#pragma unroll
-            for (int w = 1; w < kBW; ++w) sum += pair_sum(w);
-            typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-            half4 o;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) o[u] = (_Float16)(sum[u] * out_scale);
-            *reinterpret_cast<half4 *>(y + (size_t)m * N + (size_t)(v0 + r) * kTileRows + 4 * rq) = o;
-        }
+            for (int b = 0; b < TB; ++b) put_tile(r, b, SETS == 2 ? acc[0][r][b] + acc[SETS - 1][r][b] : acc[0][r][b]);
+        store_tiles(v0, v1);
         if (WAVES > kBW) break;             // (one pass: the host gives these variants no more row tiles than they hold)
         if (v1 < tb_end) {
             load_s(wave);
@@ -344,38 +417,39 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     }
 }
 
-template <int BITS, int TB, int R, int WAVES, bool READY>
+template <int BITS, int TB, int R, int WAVES, int PAIRS, bool READY, bool RESIDENT = false>
 static TokensVariant variant_of(int slot)
 {
-    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R, WAVES, READY>, R, WAVES, tokens_lds_bytes<BITS, TB, R, WAVES>(),
-                         (((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 4 + slot) * 2 + (READY ? 1 : 0)};
+    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R, WAVES, PAIRS, READY, RESIDENT>, RESIDENT ? INT_MAX : R, WAVES, tokens_lds_bytes<BITS, TB, R, WAVES>(),
+                         (((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 4 + (READY ? 3 : PAIRS == 2 ? 0 : PAIRS == 4 ? 1 : 2)) * 8 + slot};
 }
 
-template <int BITS, int TB, bool READY>
-static TokensVariant pick_tiles(int tiles)
+template <int BITS, int TB, int PAIRS, bool READY>
+static TokensVariant pick_tiles(int tiles, int kc)   // (of 16 waves and three row tiles those that do not spill)
 {
-    if (tiles <= 1) return variant_of<BITS, TB, 1, 2 * kBW, READY>(0);
-    if (tiles <= 2) return variant_of<BITS, TB, 2, TB == 1 ? 2 * kBW : kBW, READY>(1);
+    if (tiles <= 1) return variant_of<BITS, TB, 1, 2 * kBW, PAIRS, READY>(0);
+    if (tiles <= 2) return variant_of<BITS, TB, 2, TB == 1 ? 2 * kBW : kBW, PAIRS, READY>(1);
+    if constexpr (TB == 1) {
+        if (kc <= 2 * kBW) return variant_of<BITS, 1, 3, 2 * kBW, PAIRS, READY, true>(5);
+        if constexpr (BITS == 2 || (BITS == 3 && (READY || PAIRS < 8))) if (tiles == 3) return variant_of<BITS, 1, 3, 2 * kBW, PAIRS, READY>(2);
+    }
+    if (tiles <= 3) return variant_of<BITS, TB, 3, kBW, PAIRS, READY>(6);
     constexpr int whole = whole_chunk_tiles<BITS, TB>();
-    if (TB > 1 || tiles <= whole) return variant_of<BITS, TB, whole, kBW, READY>(2);
-    return variant_of<BITS, 1, kManyTiles, kBW, READY>(3);
-}
-
-template <int BITS, bool READY>
-static TokensVariant pick_blocks(int blocks, int tiles)
-{
-    return blocks <= 1 ? pick_tiles<BITS, 1, READY>(tiles) : pick_tiles<BITS, 2, READY>(tiles);
+    if (TB > 1 || tiles <= whole) return variant_of<BITS, TB, whole, kBW, PAIRS, READY>(3);
+    return variant_of<BITS, 1, kManyTiles, kBW, PAIRS, READY>(4);
 }
 
 template <int BITS>
-static TokensVariant pick(int blocks, int tiles, bool ready)
+static TokensVariant pick(int tokens, int tiles, int kc, bool ready)
 {
-    return ready ? pick_blocks<BITS, true>(blocks, tiles) : pick_blocks<BITS, false>(blocks, tiles);
+    if (tokens > kTokenBlock) return ready ? pick_tiles<BITS, 2, 8, true>(tiles, kc) : pick_tiles<BITS, 2, 8, false>(tiles, kc);
+    if (ready) return pick_tiles<BITS, 1, 8, true>(tiles, kc);
+    return tokens <= 4 ? pick_tiles<BITS, 1, 2, false>(tiles, kc) : tokens <= 8 ? pick_tiles<BITS, 1, 4, false>(tiles, kc) : pick_tiles<BITS, 1, 8, false>(tiles, kc);
 }
 
-TokensVariant tokens_variant(int bits, int blocks, int tiles, bool ready)
+TokensVariant tokens_variant(int bits, int tokens, int tiles, int kc, bool ready)
 {
-    return bits == 2 ? pick<2>(blocks, tiles, ready) : bits == 3 ? pick<3>(blocks, tiles, ready) : pick<4>(blocks, tiles, ready);
+    return bits == 2 ? pick<2>(tokens, tiles, kc, ready) : bits == 3 ? pick<3>(tokens, tiles, kc, ready) : pick<4>(tokens, tiles, kc, ready);
 }
 
 }  // namespace lcd

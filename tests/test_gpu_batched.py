@@ -29,12 +29,14 @@ def test_gemm_token_block_edges(bits, M, shape):
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
 
 
-# The tokens kernel with many row tiles per workgroup: fewer tiles than its ring of packed words has slots in a
-# pass (the last of two), one tile either side of the smaller variants, of what it holds (14) and of two full passes; activations
-# smoothed in the kernel, and (INT8 codes, 16 tokens) transformed ahead.  Most workgroups have `tiles` row tiles, a few one less.
+# The tokens kernel with several row tiles per workgroup: fewer tiles than its ring of packed words has slots in a
+# pass (the last of two), one tile either side of the smaller variants, of what it holds (14) and of two full passes; up to K = 4096, where every
+# wave's operands stay, passes of three tiles that fill the partial tiles' places (six) or not; activations
+# smoothed in the kernel, for 4, 8 or 16 tokens, and (INT8 codes, 16 tokens) transformed ahead.  Most workgroups have `tiles` row tiles, a few one less.
 # (One token: 4 bits only, the other widths take the bucket kernel.)
-@pytest.mark.parametrize("bits,M,quantised", [(4, 1, False)] + [(b, M, q) for b in (2, 3, 4) for M, q in ((3, False), (16, False), (16, True))])
-@pytest.mark.parametrize("tiles,K", [(5, 2304), (7, 4352), (8, 512), (13, 2304), (14, 4352), (15, 2304), (28, 1280), (29, 2304)])
+@pytest.mark.parametrize("bits,M,quantised", [(4, 1, False)] + [(b, M, q) for b in (2, 3, 4) for M, q in ((3, False), (6, False), (16, False), (16, True))])
+@pytest.mark.parametrize("tiles,K", [(2, 4352), (3, 4096), (3, 8704), (4, 2304), (5, 2304), (5, 4352), (6, 4096), (7, 4352), (8, 512), (13, 2304), (14, 4352), (15, 2304), (15, 4352),
+                                     (28, 1280), (29, 2304), (29, 4352)])
 def test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised):
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
