@@ -12,7 +12,7 @@ CSRC = PKG / "csrc"
 LIB = PKG / "liblcd.so"
 BUILD = ROOT / "_build"
 
-SOURCES = ["lcd_host.cpp", "lcd_pack.hip", "lcd_gemv.hip", "lcd_bucket.hip", "lcd_tokens.hip", "lcd_gemm.hip", "lcd_gemm_split.hip", "lcd_gemm_mixed.hip",
+SOURCES = ["lcd_host.cpp", "lcd_pack.hip", "lcd_gemv.hip", "lcd_bucket.hip", "lcd_tokens.hip", "lcd_tokens_mixed.hip", "lcd_gemm.hip", "lcd_gemm_split.hip", "lcd_gemm_mixed.hip",
            "lcd_cluster.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -25,14 +25,15 @@ FLAGS = [
 
 # The prefill kernels (lcd_gemm*.hip) keep their accumulators in fixed AGPRs through inline assembly: the compiler
 # must not use AGPRs as spill space there.
-# lcd_bucket.hip, lcd_tokens.hip: the decode kernels' eleven leading arguments (thirteen words: the table of first
-# workgroups or a single layer, and the input the layers share) are preloaded into scalar registers at wave start
+# lcd_bucket.hip, lcd_tokens.hip, lcd_tokens_mixed.hip: the decode kernels' eleven (twelve) leading arguments (the table of first
+# workgroups or a single layer, the input the layers share, the widths' first workgroups) are preloaded into scalar registers at wave start
 # instead of being read from the argument segment.
 EXTRA = {"lcd_gemm.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_gemm_split.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_gemm_mixed.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_bucket.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"],
-         "lcd_tokens.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"]}
+         "lcd_tokens.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"],
+         "lcd_tokens_mixed.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=12"]}
 
 
 def _compile(src: str, keep_asm: bool) -> Path:

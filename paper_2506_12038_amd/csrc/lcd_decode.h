@@ -1,4 +1,4 @@
-// What the two decode kernels (lcd_bucket.hip, lcd_tokens.hip) and their launcher share.
+// What the two decode kernels (lcd_bucket.hip, lcd_tokens.h) and their launcher share.
 #pragma once
 #include <hip/hip_runtime.h>
 #include "lcd_internal.h"
@@ -114,7 +114,7 @@ constexpr int kBucketVariants = 64;
 // tiles: most row tiles of a workgroup; kc: chunks of the widest layer
 BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int tiles, int kc);
 
-// ---- tokens kernel (lcd_tokens.hip) ---------------------------------------------------------------
+// ---- tokens kernel (lcd_tokens.h) ---------------------------------------------------------------
 constexpr int kTokenBlock = 16;      // tokens per block of the tokens kernel (the columns of one matrix instruction)
 constexpr int kMaxTokenBlocks = 2;   // blocks it holds in registers: up to 32 tokens
 
@@ -130,5 +130,8 @@ struct TokensVariant {
 constexpr int kTokensVariants = 3 * kMaxTokenBlocks * 4 * 8;
 // ready: x holds the transformed activations in operand order (transform_kernel)
 TokensVariant tokens_variant(int bits, int tokens, int tiles, int kc, bool ready);
+// for layers of several widths, up to 16 tokens (lcd_tokens_mixed.hip); ids of their own
+constexpr int kMixedTokensVariants = 15;
+TokensVariant tokens_mixed_variant(int tokens, int tiles, int kc);
 
 }  // namespace lcd

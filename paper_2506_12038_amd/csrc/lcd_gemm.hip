@@ -167,7 +167,7 @@ static int mixed_half_tiles(const GemmBatch &large, int queue, const GemmBatch &
 int launch_gemm(const void *packed, const void *lut, const uint16_t *x, const float *s, uint16_t *y,
                 int M, int N, int K, int bits, float act_scale, void *workspace, const GemmPlan &, void *stream)
 {
-    GroupItem it{packed, lut, x, s, y, N, K, act_scale};
+    GroupItem it{packed, lut, x, s, y, N, K, act_scale, bits};
     return launch_gemm_group(&it, 1, M, bits, workspace, stream);
 }
 

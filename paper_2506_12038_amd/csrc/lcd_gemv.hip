@@ -63,39 +63,57 @@ __global__ __launch_bounds__(kQuantThreads) void transform_kernel(TransformBatch
     }
 }
 
-// One launch for a group of decode problems: the bucket kernel for one token, the tokens kernel beyond.
-int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream_, bool dense)
+// Which kernel takes layers of a width.
+// 4 bits: the register dequantiser serves one token too; 2 bits: the sparse-matrix-core kernel also takes
+// two tokens (one sparse pass per token costs less than dequantising once)
+// (with the INT8 codes of Sec. 4.1 as int8 operands the sparse-matrix-core kernel has room for four tokens)
+// (dense: fp16 activations, because the routing matrix's zeros turn an infinite activation into a NaN of every bucket where
+// the dequantised product gives the infinity that plain arithmetic gives; 3 bits, because the bucket kernel's multipliers are
+// (C[j] +- C[4 + j]) / 2 in binary32, which loses the centroid next to a large entry that no index names)
+static bool tokens_kernel_takes(int bits, int M, bool all_quantised, bool dense)
 {
-    hipStream_t stream = (hipStream_t)stream_;
-    BucketBatch batch{};
-    int tiles = 0;
-    // 4 bits: the register dequantiser serves one token too; 2 bits: the sparse-matrix-core kernel also takes
-    // two tokens (one sparse pass per token costs less than dequantising once)
-    // (with the INT8 codes of Sec. 4.1 as int8 operands the sparse-matrix-core kernel has room for four tokens)
-    bool all_quantised = true;
-    for (int i = 0; i < count; ++i) all_quantised = all_quantised && items[i].act_scale != 0.0f;
     const int sparse_tokens = bits != 2 ? 1 : all_quantised ? 4 : 2;   // most tokens the bucket kernel takes
-    // (dense: fp16 activations, because the routing matrix's zeros turn an infinite activation into a NaN of every bucket where
-    // the dequantised product gives the infinity that plain arithmetic gives; 3 bits, because the bucket kernel's multipliers are
-    // (C[j] +- C[4 + j]) / 2 in binary32, which loses the centroid next to a large entry that no index names)
-    const bool tokens_path = bits == 4 || M > sparse_tokens || (dense && !(all_quantised && bits == 2));
-    const int blocks = (M + kTokenBlock - 1) / kTokenBlock;
-    const int held = tokens_path ? tokens_variant(bits, M, INT_MAX, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds
-    // Several tokens: every workgroup transforms its layer's activations once per pass over its row tiles; ahead of the
-    // product they are transformed once, at the price of a launch (3.6 us in a graph).  The line lies where that much work is
-    // saved, counted in activations per workgroup (tokens x widest K x passes).  Per block, ahead / in the product: INT8 codes, 3 bits,
-    // 7B, 4 tokens (16 k to 44 k) 46.9 / 42.1 us, 9 tokens (37 k to 99 k) 48.6 / 49.6, 16 tokens 51.0 / 58.3; 70B MLP, 4 tokens (98 k, 115 k)
-    // 81.2 / 91.2.  fp16: 70B MLP, 4 tokens 83.2 / 83.1, 16 tokens (393 k, 459 k) 94.2 / 96.7 with only the wider K ahead.
-    const uint16_t *codes[kMaxGroup] = {};
+    return bits == 4 || M > sparse_tokens || (dense && !(all_quantised && bits == 2));
+}
+
+// Several tokens: every workgroup transforms its layer's activations once per pass over its row tiles; ahead of the
+// product they are transformed once, at the price of a launch (3.6 us in a graph).  The line lies where that much work is
+// saved, counted in activations per workgroup (tokens x widest K x passes).  Per block, ahead / in the product: INT8 codes, 3 bits,
+// 7B, 4 tokens (16 k to 44 k) 46.9 / 42.1 us, 9 tokens (37 k to 99 k) 48.6 / 49.6, 16 tokens 51.0 / 58.3; 70B MLP, 4 tokens (98 k, 115 k)
+// 81.2 / 91.2.  fp16: 70B MLP, 4 tokens 83.2 / 83.1, 16 tokens (393 k, 459 k) 94.2 / 96.7 with only the wider K ahead.
+static bool transforms_ahead(const GroupItem *items, int count, int M)
+{
+    const int held = tokens_variant(items[0].bits, M, INT_MAX, INT_MAX, false).tiles;   // row tiles a workgroup of the tokens kernel holds
     int widest = 0;
     long long all_tiles = 0;
     for (int i = 0; i < count; ++i) {
-        widest = items[i].K > widest ? items[i].K : widest;
+        widest = std::max(widest, items[i].K);
         all_tiles += items[i].N / kTileRows;
     }
     const long long per_pass = (long long)num_cus() * held, passes = (all_tiles + per_pass - 1) / per_pass;
-    const long long transforms = (long long)M * widest * passes;
-    if (tokens_path && transforms > (items[0].act_scale != 0.0f ? kAheadCodes : kAheadSmoothed)) {
+    return (long long)M * widest * passes > (items[0].act_scale != 0.0f ? kAheadCodes : kAheadSmoothed);
+}
+
+// One launch (and transform_kernel's, where it pays) for layers that one kernel takes: of one width, or of several on the tokens kernel.
+static int launch_decode_layers(const GroupItem *items, int count, int M, void *workspace, hipStream_t stream, bool dense)
+{
+    BucketBatch batch{};
+    int tiles = 0;
+    bool all_quantised = true, mixed = false;
+    const int bits = items[0].bits;
+    int width[kMaxGroup];
+    for (int i = 0; i < count; ++i) {
+        all_quantised = all_quantised && items[i].act_scale != 0.0f;
+        mixed = mixed || items[i].bits != bits;
+        width[i] = items[i].bits;
+    }
+    const bool tokens_path = tokens_kernel_takes(bits, M, all_quantised, dense);
+    const int blocks = (M + kTokenBlock - 1) / kTokenBlock;
+    const int held = tokens_path ? tokens_variant(bits, M, INT_MAX, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds
+    const uint16_t *codes[kMaxGroup] = {};
+    int widest = 0;
+    for (int i = 0; i < count; ++i) widest = std::max(widest, items[i].K);
+    if (tokens_path && transforms_ahead(items, count, M)) {
         // layers that read the same input (same x, s, K and quantisation step: q/k/v or gate/up of a decoder
         // block) share one transformed copy
         TransformBatch qb{};
@@ -137,8 +155,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
     // the tokens kernel, times in us of a workgroup: a "round" is one chunk for each of its 8 waves.  Fitted to single layers of
     // 4096 x t rows (t row tiles per workgroup), K = 4096 and 11008, 4 and 16 tokens; 2 bits, 16 tokens: K = 4096 t = 8, 10, 12
     // 15.0, 17.1, 19.0 us, 13 in two passes 25.4; K = 11008 t = 4, 5, 6 20.1, 23.0, 26.2.
-    const double round_tile = (bits == 2 ? 0.43 : bits == 3 ? 0.55 : 0.89) + 0.06 * blocks;
-    const double round_stage = staged_ahead ? 0.1 * blocks : 0.08 + 0.035 * M, pass = bits == 2 ? 3.7 : 5.0;
+    const double round_stage = staged_ahead ? 0.1 * blocks : 0.08 + 0.035 * M;
     // the bucket kernel, in us: a round is one chunk for each of its 16 or 8 waves, of which each costs its operands once per pass.
     const double bucket_tile = bits == 3 ? (int8_codes ? 0.45 : 1.05) : M > 1 ? 0.35 : int8_codes ? 0.3 : 0.6;
     const double bucket_chunk = M == 1 ? 0.1 : int8_codes && M > 2 ? 0.15 * M : 0.2;
@@ -146,6 +163,7 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
         const int kc = batch.p[i].kc, t = (batch.p[i].nt + n - 1) / n;
         if (tokens_path) {
             const int rounds = (kc + kBW - 1) / kBW, passes = (t + held - 1) / held;
+            const double round_tile = (width[i] == 2 ? 0.43 : width[i] == 3 ? 0.55 : 0.89) + 0.06 * blocks, pass = width[i] == 2 ? 3.7 : 5.0;
             return passes * (pass + rounds * round_stage) + rounds * t * round_tile;
         }
         const BucketVariant bv = bucket_variant(bits, M, int8_codes, t, kc);
@@ -204,30 +222,30 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
         }
     };
     // the split depends on the shapes only: the last one is kept (serving loops repeat a few groups)
-    struct SplitMemo { int count, M, bits, grid, ahead, route, nt[kMaxGroup], kc[kMaxGroup], nwg[kMaxGroup]; };
+    struct SplitMemo { int count, M, grid, ahead, route, nt[kMaxGroup], kc[kMaxGroup], width[kMaxGroup], nwg[kMaxGroup]; };
     static thread_local SplitMemo memo = {};
     const int route = tokens_path ? 1 : int8_codes ? 2 : 0;   // the cost constants depend on it
-    bool known = memo.count == count && memo.M == M && memo.bits == bits && memo.grid == grid && memo.ahead == (int)staged_ahead && memo.route == route;
-    for (int i = 0; known && i < count; ++i) known = memo.nt[i] == batch.p[i].nt && memo.kc[i] == batch.p[i].kc;
+    bool known = memo.count == count && memo.M == M && memo.grid == grid && memo.ahead == (int)staged_ahead && memo.route == route;
+    for (int i = 0; known && i < count; ++i) known = memo.nt[i] == batch.p[i].nt && memo.kc[i] == batch.p[i].kc && memo.width[i] == width[i];
     int nwg[kMaxGroup];
     if (known) {
         for (int i = 0; i < count; ++i) nwg[i] = memo.nwg[i];
     } else {
         split(nwg);
-        memo.count = count; memo.M = M; memo.bits = bits; memo.grid = grid; memo.ahead = (int)staged_ahead; memo.route = route;
-        for (int i = 0; i < count; ++i) { memo.nt[i] = batch.p[i].nt; memo.kc[i] = batch.p[i].kc; memo.nwg[i] = nwg[i]; }
+        memo.count = count; memo.M = M; memo.grid = grid; memo.ahead = (int)staged_ahead; memo.route = route;
+        for (int i = 0; i < count; ++i) { memo.nt[i] = batch.p[i].nt; memo.kc[i] = batch.p[i].kc; memo.width[i] = width[i]; memo.nwg[i] = nwg[i]; }
     }
     // Workgroups are dispatched in the order of their ids, the last of a full grid almost 1 us after the
-    // first: the layers whose workgroups have the most to do take the lowest ids.
+    // first: the layers whose workgroups have the most to do take the lowest ids (of several widths: the widest first, which the kernel asks for).
     if (count > 1) {
         int order[kMaxGroup];
         double t[kMaxGroup];
         for (int i = 0; i < count; ++i) { order[i] = i; t[i] = layer_time(i, nwg[i]); }
-        std::stable_sort(order, order + count, [&](int a, int b) { return t[a] > t[b]; });
+        std::stable_sort(order, order + count, [&](int a, int b) { return width[a] != width[b] ? width[a] > width[b] : t[a] > t[b]; });
         BucketProblem sorted_p[kMaxGroup];
-        int sorted_n[kMaxGroup];
-        for (int q = 0; q < count; ++q) { sorted_p[q] = batch.p[order[q]]; sorted_n[q] = nwg[order[q]]; }
-        for (int q = 0; q < count; ++q) { batch.p[q] = sorted_p[q]; nwg[q] = sorted_n[q]; }
+        int sorted_n[kMaxGroup], sorted_w[kMaxGroup];
+        for (int q = 0; q < count; ++q) { sorted_p[q] = batch.p[order[q]]; sorted_n[q] = nwg[order[q]]; sorted_w[q] = width[order[q]]; }
+        for (int q = 0; q < count; ++q) { batch.p[q] = sorted_p[q]; nwg[q] = sorted_n[q]; width[q] = sorted_w[q]; }
     }
     grid = 0;
     for (int i = 0; i < count; ++i) grid += nwg[i];
@@ -269,18 +287,51 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
         waves = v.waves;
         variant = v.id;
     } else {
-        const TokensVariant tv = tokens_variant(bits, M, most, widest / kTileCols, staged_ahead);
+        const TokensVariant tv = mixed ? tokens_mixed_variant(M, most, widest / kTileCols) : tokens_variant(bits, M, most, widest / kTileCols, staged_ahead);
         lds = tv.lds_bytes;
         fn = tv.fn;
         waves = tv.waves;
-        variant = kBucketVariants + tv.id;
+        variant = kBucketVariants + (mixed ? kTokensVariants : 0) + tv.id;
     }
-    static PerDeviceFlags<kBucketVariants + kTokensVariants> lds_raised;
+    uint32_t widths = 0;   // first workgroup of the 3-bit layers, and (upper half) of the 2-bit layers
+    for (int i = 0; i < count; ++i) widths += width[i] == 4 ? nwg[i] * 0x10001u : width[i] == 3 ? nwg[i] * 0x10000u : 0u;
+    static PerDeviceFlags<kBucketVariants + kTokensVariants + kMixedTokensVariants> lds_raised;
     if (hipError_t e = raise_lds_limit_once(lds_raised, variant, fn, lds)) return (int)e;
     void *args[] = {&table.t[0], &table.t[1], &table.t[2], &table.t[3], &table.t[4], &table.t[5], &table.t[6], &table.t[7],
                     &head.x, &head.s, &head.word, &batch};
-    if (hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(waves * 64), args, lds, stream)) return (int)e;
+    void *mixed_args[] = {&table.t[0], &table.t[1], &table.t[2], &table.t[3], &table.t[4], &table.t[5], &table.t[6], &table.t[7],
+                          &head.x, &head.s, &head.word, &widths, &batch};
+    if (hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(waves * 64), mixed ? mixed_args : args, lds, stream)) return (int)e;
     return (int)hipGetLastError();
+}
+
+// The launches of a group: one for layers of one width.  Layers of several widths that the tokens kernel takes go out together, unless their
+// activations are transformed ahead (two launches already, and long ones); the bucket kernel's width by width.
+int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream_, bool dense)
+{
+    hipStream_t stream = (hipStream_t)stream_;
+    bool all_quantised = true, mixed = false;
+    for (int i = 0; i < count; ++i) {
+        all_quantised = all_quantised && items[i].act_scale != 0.0f;
+        mixed = mixed || items[i].bits != items[0].bits;
+    }
+    if (bits != 0 || !mixed) return launch_decode_layers(items, count, M, workspace, stream, dense);
+    GroupItem sub[kMaxGroup];
+    int n = 0;
+    for (int i = 0; i < count; ++i)
+        if (tokens_kernel_takes(items[i].bits, M, all_quantised, dense)) sub[n++] = items[i];
+    const bool together = n > 0 && M <= kTokenBlock && !transforms_ahead(sub, n, M);
+    if (together)
+        if (int e = launch_decode_layers(sub, n, M, workspace, stream, dense)) return e;
+    for (int b = 2; b <= 4; ++b) {
+        if (together && tokens_kernel_takes(b, M, all_quantised, dense)) continue;
+        n = 0;
+        for (int i = 0; i < count; ++i)
+            if (items[i].bits == b) sub[n++] = items[i];
+        if (n > 0)
+            if (int e = launch_decode_layers(sub, n, M, workspace, stream, dense)) return e;
+    }
+    return 0;
 }
 
 // ---- scratch for callers that cannot allocate ---------------------------------------------------
@@ -314,14 +365,14 @@ int launch_gemv_noalloc(const void *packed, const void *lut, const uint16_t *x, 
 {
     void *ws = nullptr;
     if (int e = static_scratch(&ws)) return e;
-    GroupItem it{packed, lut, x, s, y, N, K, 0.0f};
+    GroupItem it{packed, lut, x, s, y, N, K, 0.0f, bits};
     return launch_decode_group(&it, 1, M, bits, ws, stream_);
 }
 
 int launch_gemv(const void *packed, const void *lut, const uint16_t *x, const float *s, uint16_t *y,
                 int M, int N, int K, int bits, float act_scale, void *workspace, void *stream_)
 {
-    GroupItem it{packed, lut, x, s, y, N, K, act_scale};
+    GroupItem it{packed, lut, x, s, y, N, K, act_scale, bits};
     return launch_decode_group(&it, 1, M, bits, workspace, stream_);
 }
 

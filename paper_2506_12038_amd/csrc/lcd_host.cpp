@@ -294,7 +294,7 @@ static lcd_status gemv_grouped(const lcd_gemv_problem *problems, const float *s_
     GroupItem items[kMaxGroup];
     for (int i = 0; i < count; ++i)
         items[i] = GroupItem{problems[i].packed, problems[i].lut, problems[i].x, problems[i].s, problems[i].y, problems[i].N, problems[i].K,
-                             s_q ? s_q[i] : 0.0f};
+                             s_q ? s_q[i] : 0.0f, bits};
     if (int e = launch_decode_group(items, count, M, bits, workspace, stream)) return fail(LCD_ERR_HIP, "grouped gemv launch: %s", hip_error_name(e));
     return LCD_OK;
 }
@@ -320,23 +320,19 @@ lcd_status lcd_lut_gemv_grouped_mixed(const lcd_gemv_problem *problems, const in
     if (count < 1 || count > kMaxGroup) return fail(LCD_ERR_SIZE, "count=%d must be in 1..%d", count, kMaxGroup);
     for (int i = 0; i < count; ++i)
         if (bits[i] < 2 || bits[i] > 4) return fail(LCD_ERR_BAD_BITS, "bits[%d]=%d: only 2, 3 and 4 are supported", i, bits[i]);
-    // validate every layer before the first launch, then one launch per index width that occurs
-    for (int pass = 0; pass < 2; ++pass)
-        for (int b = 2; b <= 4; ++b) {
-            lcd_gemv_problem sub[kMaxGroup];
-            int n = 0;
-            for (int i = 0; i < count; ++i)
-                if (bits[i] == b) sub[n++] = problems[i];
-            if (n == 0) continue;
-            if (pass == 0) {
-                if (M > 16) return fail(LCD_ERR_BAD_M, "grouped gemv: M=%d > 16", M);
-                for (int i = 0; i < n; ++i)
-                    if (lcd_status st = check_product(sub[i].packed, sub[i].lut, sub[i].x, sub[i].s, sub[i].y, M, sub[i].N, sub[i].K, b,
-                                                      workspace, workspace_bytes)) return st;
-            } else if (lcd_status st = gemv_grouped(sub, nullptr, n, M, b, workspace, workspace_bytes, stream)) {
-                return st;
-            }
-        }
+    // every layer is validated before the first launch
+    if (M > 16) return fail(LCD_ERR_BAD_M, "grouped gemv: M=%d > 16", M);
+    size_t codes[5] = {};    // scratch of the layers of a width
+    GroupItem items[kMaxGroup];
+    for (int i = 0; i < count; ++i) {
+        const lcd_gemv_problem &p = problems[i];
+        if (lcd_status st = check_product(p.packed, p.lut, p.x, p.s, p.y, M, p.N, p.K, bits[i], workspace, workspace_bytes)) return st;
+        codes[bits[i]] += decode_codes_bytes(M, p.K);
+        items[i] = GroupItem{p.packed, p.lut, p.x, p.s, p.y, p.N, p.K, 0.0f, bits[i]};
+    }
+    for (int b = 2; b <= 4; ++b)
+        if (workspace_bytes < codes[b]) return fail(LCD_ERR_SIZE, "workspace_bytes=%zu < %zu", workspace_bytes, codes[b]);
+    if (int e = launch_decode_group(items, count, M, 0, workspace, stream)) return fail(LCD_ERR_HIP, "grouped gemv launch: %s", hip_error_name(e));
     return LCD_OK;
 }
 
@@ -386,7 +382,7 @@ static lcd_status gemm_grouped(const lcd_gemv_problem *problems, const float *s_
         need += plan_gemm(M, p.N, p.K, bits).xs_bytes;
         if (s_q && (!(s_q[i] > 0.0f) || !(s_q[i] < 3.0e38f)))
             return fail(LCD_ERR_BAD_SCALE, "s_q[%d]=%g must be positive and finite", i, (double)s_q[i]);
-        items[i] = GroupItem{p.packed, p.lut, p.x, p.s, p.y, p.N, p.K, s_q ? s_q[i] : 0.0f};
+        items[i] = GroupItem{p.packed, p.lut, p.x, p.s, p.y, p.N, p.K, s_q ? s_q[i] : 0.0f, bits};
     }
     if (workspace_bytes < need) return fail(LCD_ERR_SIZE, "workspace_bytes=%zu < %zu", workspace_bytes, need);
     if (int e = launch_gemm_group(items, count, M, bits, workspace, stream))

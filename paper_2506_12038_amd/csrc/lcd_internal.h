@@ -28,11 +28,13 @@ constexpr int kMaxGroup = 16;     // problems per grouped launch
 struct GroupItem {
     const void *packed; const void *lut; const uint16_t *x; const float *s; uint16_t *y; int N, K;
     float act_scale;   // 0: fp16 activations; s_q > 0: INT8 activation codes (paper Sec. 4.1)
+    int bits;
 };
 constexpr int kDecodeTokens = 32;   // most tokens the decode kernels take (the decode entry points stop at 16)
-// one launch for `count` decode problems (1 <= M <= kDecodeTokens tokens each)
+// one launch for `count` decode problems (1 <= M <= kDecodeTokens tokens each); of several widths up to 16 tokens: as few launches as the kernels allow
 // (workspace: decode_codes_bytes(M, K) per item: the transformed activations where they are made ahead of the product)
 // dense: fp16 activations, and 3-bit indices, take the dequantising kernel for any M
+// bits: the layers' width, 0: widths of their own (items[i].bits)
 int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream, bool dense = false);
 inline size_t decode_codes_bytes(int M, int K) { return ((size_t)M * K * 2 + 255) / 256 * 256; }
 

@@ -340,6 +340,32 @@ def test_grouped_layers_of_mixed_index_widths(M):
         assert torch.equal(y, lcd.lcd_lut_gemv(packed, lut, x, s, N, bits))
 
 
+# Layers of several widths in one launch of the tokens kernel: every variant (one, two, three row tiles per workgroup, passes of three up to K = 4096, of six
+# (4 bits: four) and of 14 beyond), groups without a 4-bit or a 2-bit layer, inputs shared or not, and a group whose activations are
+# transformed ahead (16 tokens, K = 28672: width by width).  Each layer's bits are those of its own call, which other tests compare with the oracle.
+@pytest.mark.parametrize("widths", [(3, 2, 4, 2), (3, 3, 2), (4, 3)])
+@pytest.mark.parametrize("M", [2, 3, 7, 16])
+@pytest.mark.parametrize("tiles,K", [(1, 4352), (2, 4352), (2, 1024), (4, 4096), (7, 2304), (5, 4352), (9, 4352), (1, 28672)])
+def test_grouped_mixed_widths_give_the_bits_of_single_calls(widths, M, tiles, K):
+    import torch
+    from paper_2506_12038_amd.binding import GemvGroup
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    N = max(1, tiles * cus // len(widths)) * 16          # about `tiles` row tiles per workgroup
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1000 * tiles + K + M)
+    x = torch.randn((M, K), device="cuda", generator=g).half()
+    s = torch.rand((K,), device="cuda", generator=g) + 0.5
+    problems = []
+    for i, bits in enumerate(widths):
+        packed = torch.randint(0, 256, (lcd.lcd_packed_bytes(N, K, bits),), dtype=torch.uint8, device="cuda", generator=g)
+        lut = lcd.lcd_build_lut((torch.randn((N, 1 << bits), device="cuda", generator=g) * 0.02).half(), bits)
+        own = tiles % 2 == 0 and i == 1                  # a layer with an input of its own
+        problems.append((packed, lut, x.roll(1, 1) if own else x, s, torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda"), N))
+    GemvGroup(problems, list(widths))()
+    for (packed, lut, xi, si, y, n), bits in zip(problems, widths):
+        assert torch.equal(y, lcd.lcd_lut_gemv(packed, lut, xi, si, n, bits)), bits
+
+
 def test_gemv_q8_decides_hard_cases_like_the_binary32_oracle():
     # inputs on which the order of roundings decides the code (a double-precision quotient, or a
     # product with a rounded reciprocal, gives the neighbouring integer): the kernel's split division
