@@ -12,7 +12,7 @@ CSRC = PKG / "csrc"
 LIB = PKG / "liblcd.so"
 BUILD = ROOT / "_build"
 
-SOURCES = ["lcd_host.cpp", "lcd_pack.hip", "lcd_gemv.hip", "lcd_bucket.hip", "lcd_tokens.hip", "lcd_tokens_mixed.hip", "lcd_gemm.hip", "lcd_gemm_split.hip", "lcd_gemm_mixed.hip",
+SOURCES = ["lcd_host.cpp", "lcd_pack.hip", "lcd_gemv.hip", "lcd_bucket.hip", "lcd_tokens.hip", "lcd_tokens_mixed.hip", "lcd_narrow.hip", "lcd_gemm.hip", "lcd_gemm_split.hip", "lcd_gemm_mixed.hip",
            "lcd_cluster.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -33,6 +33,7 @@ EXTRA = {"lcd_gemm.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_gemm_mixed.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_bucket.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"],
          "lcd_tokens.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"],
+         "lcd_narrow.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"],
          "lcd_tokens_mixed.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=12"]}
 
 

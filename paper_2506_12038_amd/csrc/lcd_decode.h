@@ -50,6 +50,9 @@ constexpr uint32_t kHeadShared = 1u << 28, kHeadSingle = 1u << 29;
 __device__ __forceinline__ int head_kc(uint32_t word) { return (int)(word & 0x3fffffu); }
 __device__ __forceinline__ int head_tokens(uint32_t word) { return (int)((word >> 22) & 63u); }
 
+// The narrow kernel has more tokens and narrower inputs: its word holds K / 256 in bits 0..18 and the tokens in bits 19..27.
+constexpr uint32_t kNarrowTokensShift = 19, kNarrowTokensMask = 0x1ff;
+
 // Number of table entries <= b, for b < 2^15 - 1:
 struct WgTable { uint32_t t[kMaxGroup / 2]; };
 __device__ __forceinline__ int layer_of_workgroup(uint32_t b, uint32_t t0, uint32_t t1, uint32_t t2, uint32_t t3,
@@ -130,6 +133,10 @@ struct TokensVariant {
 constexpr int kTokensVariants = 3 * kMaxTokenBlocks * 4 * 8;
 // ready: x holds the transformed activations in operand order (transform_kernel)
 TokensVariant tokens_variant(int bits, int tokens, int tiles, int kc, bool ready);
+// the narrow kernel (lcd_narrow.hip), 17 .. 16 kNarrowBlocks tokens; ids of their own
+constexpr int kNarrowBlocks = 6;
+constexpr int kNarrowVariants = 3 * kNarrowBlocks * 4;
+TokensVariant narrow_variant(int bits, int tokens, int tiles);
 // for layers of several widths, up to 16 tokens (lcd_tokens_mixed.hip); ids of their own
 constexpr int kMixedTokensVariants = 15;
 TokensVariant tokens_mixed_variant(int tokens, int tiles, int kc);

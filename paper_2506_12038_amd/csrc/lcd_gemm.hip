@@ -26,6 +26,25 @@ static bool decode_takes(int M, int N, int K)
 {
     return (M <= 16 || (M <= kDecodeTokens && (long long)N * K < (1ll << 24))) && (long long)M * K * 2 < (1ll << 32);
 }
+// The narrow kernel takes layers of few tokens: it reads every activation once per compute unit and pads tokens to 16 only, the split kernel
+// reads a tile's activations once per 64 rows.  So the line lies where a compute unit has one row tile only (up to 4096 rows), which the
+// activations of many tokens or columns do not pay for; beyond 64 tokens it holds three row tiles at a time, so that a fourth costs a second
+// pass.  One call, weights from memory, split (up to 32 tokens and beyond 128 large tiles: as before it) / narrow, 2, 3 and 4 bits, us:
+//   32 tokens   4096 x 4096  9.9/9.5 10.4/10.0 11.9/10.4     4096 x 11008 16.9/15.8 19.9/16.5 22.5/17.9     28672 x 8192, twice 62.6/55.7 81.4/70.5 92.5/94.0
+//   40          4096 x 4096 10.6/10.5 11.1/10.8 12.8/11.4    4096 x 11008 18.3/18.1 20.3/19.4 23.4/20.4     11008 x 4096, twice 27.9/18.2 30.8/20.9 35.4/26.9
+//   48          4096 x 11008 17.9/19.4 20.3/20.5 23.2/21.3   8192 x 8192 20.0/17.8 24.2/19.5 26.1/22.4      28672 x 8192, twice 89.1/67.9 101.6/82.0 121.3/105.7
+//   64          4096 x 4096 10.7/11.8 11.2/12.2 12.8/12.5    8192 x 8192 20.2/20.0 24.4/21.9 26.0/24.5      11008 x 4096, twice 29.5/25.0 31.8/28.0 37.1/32.2
+//   80          4096 x 4096 12.7/13.6 14.5/14.0 15.9/14.5    8192 x 8192 27.7/23.5 30.0/25.1 35.4/27.5      11008 x 4096, twice 36.0/27.9 39.3/30.8 43.5/34.9
+//   old time / new, over all widths   48 tokens, 1024..4096 rows: K = 2048 1.02..1.14, 4096 0.94..1.11, 8192 0.82..1.09     64 tokens: K = 2048 0.95..1.11, 4096 0.87..1.04
+//                                     80 tokens: 5120 rows 0.84..1.25, 6144..11008 1.05..1.33, 16384 0.83..0.94             96 tokens: 6144..11008 rows 0.94..1.23
+static bool narrow_takes(int M, int N, int K, int bits)
+{
+    if (M <= 16 || M > kNarrowTokens || (long long)M * K * 2 >= (1ll << 32)) return false;
+    if (N > 4096) return M <= 64 || (N >= 6144 && N <= 12288);
+    if (M <= 32) return true;
+    if (M <= 48) return K <= 2048 || (N > 2048 && (K <= 4096 || bits > 2));
+    return M <= 64 && N >= 2048 && K <= 2048;
+}
 // The split kernel takes layers of few output tiles.  Its advantage lies in rounds of workgroups over the 256 compute units (the whole
 // chip, whatever part of it a process sees: a layer's bits must not depend on that) and in tiles as narrow as the tokens: 256 x 128 tiles
 // spend the same time on 33 tokens as on 128.  It takes what fits
@@ -184,12 +203,13 @@ int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *
     SmoothItem sm[kMaxGroup];
     int distinct = 0;
     GemmBatch batch[2] = {};   // [0] the large-tile kernel's layers, [1] the split kernel's
-    GroupItem small[kMaxGroup];
-    int small_count = 0;       // the decode kernels' layers
+    GroupItem small[kMaxGroup], narrow[kMaxGroup];
+    int small_count = 0, narrow_count = 0;       // the decode kernels' layers, the narrow kernel's
     size_t offset = 0;
     for (int q = 0; q < count; ++q) {
         const GroupItem &it = items[order[q]];
         if (decode_takes(M, it.N, it.K)) { small[small_count++] = it; continue; }
+        if (narrow_takes(M, it.N, it.K, bits)) { narrow[narrow_count++] = it; continue; }
         uint8_t *xs = nullptr;
         for (int d = 0; d < distinct && !xs; ++d)
             if (sm[d].x == it.x && sm[d].s == it.s && sm[d].K == it.K && sm[d].s_q == it.act_scale) xs = static_cast<uint8_t *>(sm[d].xs);
@@ -211,6 +231,10 @@ int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *
     // the decode kernels' scratch lies behind the smoothed activations (it takes less than a layer's share of those)
     if (small_count > 0)
         if (int e = launch_decode_group(small, small_count, M, bits, static_cast<char *>(workspace) + offset, stream, true)) return e;
+    if (narrow_count > 0) {
+        for (int i = 0; i < small_count; ++i) offset += decode_codes_bytes(M, small[i].K);
+        if (int e = launch_narrow_group(narrow, narrow_count, M, static_cast<char *>(workspace) + offset, stream)) return e;
+    }
     if (distinct == 0) return 0;
     // places of the layers' tiles (rows x tokens each) in the XCDs' queues; returns the queue's length
     auto queue_tiles = [&](GemmBatch &bt, int rows, int tokens) {

@@ -95,7 +95,8 @@ static bool transforms_ahead(const GroupItem *items, int count, int M)
 }
 
 // One launch (and transform_kernel's, where it pays) for layers that one kernel takes: of one width, or of several on the tokens kernel.
-static int launch_decode_layers(const GroupItem *items, int count, int M, void *workspace, hipStream_t stream, bool dense)
+// narrow: prefill of few tokens (lcd_narrow.hip), always behind transform_kernel.
+static int launch_decode_layers(const GroupItem *items, int count, int M, void *workspace, hipStream_t stream, bool dense, bool narrow = false)
 {
     BucketBatch batch{};
     int tiles = 0;
@@ -107,13 +108,13 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
         mixed = mixed || items[i].bits != bits;
         width[i] = items[i].bits;
     }
-    const bool tokens_path = tokens_kernel_takes(bits, M, all_quantised, dense);
+    const bool tokens_path = narrow || tokens_kernel_takes(bits, M, all_quantised, dense);
     const int blocks = (M + kTokenBlock - 1) / kTokenBlock;
-    const int held = tokens_path ? tokens_variant(bits, M, INT_MAX, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds
+    const int held = narrow ? narrow_variant(bits, M, INT_MAX).tiles : tokens_path ? tokens_variant(bits, M, INT_MAX, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds
     const uint16_t *codes[kMaxGroup] = {};
     int widest = 0;
     for (int i = 0; i < count; ++i) widest = std::max(widest, items[i].K);
-    if (tokens_path && transforms_ahead(items, count, M)) {
+    if (narrow || (tokens_path && transforms_ahead(items, count, M))) {
         // layers that read the same input (same x, s, K and quantisation step: q/k/v or gate/up of a decoder
         // block) share one transformed copy
         TransformBatch qb{};
@@ -221,19 +222,28 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
             ++used;
         }
     };
-    // the split depends on the shapes only: the last one is kept (serving loops repeat a few groups)
+    // The split depends on the shapes only: the last few are kept (a block repeats a few groups; working one out takes 5 us of host time).
     struct SplitMemo { int count, M, grid, ahead, route, nt[kMaxGroup], kc[kMaxGroup], width[kMaxGroup], nwg[kMaxGroup]; };
-    static thread_local SplitMemo memo = {};
-    const int route = tokens_path ? 1 : int8_codes ? 2 : 0;   // the cost constants depend on it
-    bool known = memo.count == count && memo.M == M && memo.grid == grid && memo.ahead == (int)staged_ahead && memo.route == route;
-    for (int i = 0; known && i < count; ++i) known = memo.nt[i] == batch.p[i].nt && memo.kc[i] == batch.p[i].kc && memo.width[i] == width[i];
+    constexpr int kMemos = 8;
+    static thread_local SplitMemo memos[kMemos] = {};
+    static thread_local int oldest = 0;
+    const int route = narrow ? 3 : tokens_path ? 1 : int8_codes ? 2 : 0;   // the cost constants depend on it
     int nwg[kMaxGroup];
+    const SplitMemo *known = nullptr;
+    for (int e = 0; e < kMemos && !known; ++e) {
+        const SplitMemo &m = memos[e];
+        bool same = m.count == count && m.M == M && m.grid == grid && m.ahead == (int)staged_ahead && m.route == route;
+        for (int i = 0; same && i < count; ++i) same = m.nt[i] == batch.p[i].nt && m.kc[i] == batch.p[i].kc && m.width[i] == width[i];
+        if (same) known = &m;
+    }
     if (known) {
-        for (int i = 0; i < count; ++i) nwg[i] = memo.nwg[i];
+        for (int i = 0; i < count; ++i) nwg[i] = known->nwg[i];
     } else {
         split(nwg);
-        memo.count = count; memo.M = M; memo.grid = grid; memo.ahead = (int)staged_ahead; memo.route = route;
-        for (int i = 0; i < count; ++i) { memo.nt[i] = batch.p[i].nt; memo.kc[i] = batch.p[i].kc; memo.width[i] = width[i]; memo.nwg[i] = nwg[i]; }
+        SplitMemo &m = memos[oldest];
+        oldest = (oldest + 1) % kMemos;
+        m.count = count; m.M = M; m.grid = grid; m.ahead = (int)staged_ahead; m.route = route;
+        for (int i = 0; i < count; ++i) { m.nt[i] = batch.p[i].nt; m.kc[i] = batch.p[i].kc; m.width[i] = width[i]; m.nwg[i] = nwg[i]; }
     }
     // Workgroups are dispatched in the order of their ids, the last of a full grid almost 1 us after the
     // first: the layers whose workgroups have the most to do take the lowest ids (of several widths: the widest first, which the kernel asks for).
@@ -263,7 +273,7 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
     WgTable table;
     for (int i = 0; i < kMaxGroup / 2; ++i) table.t[i] = (uint32_t)wg_begin[2 * i + 1] | (uint32_t)wg_begin[2 * i + 2] << 16;
     for (int i = 0; i < count; ++i) batch.p[i].wg_first = wg_begin[i];
-    DecodeHead head{batch.p[0].x, batch.p[0].s, (uint32_t)batch.p[0].kc | (uint32_t)M << 22};
+    DecodeHead head{batch.p[0].x, batch.p[0].s, (uint32_t)batch.p[0].kc | (uint32_t)M << (narrow ? kNarrowTokensShift : 22)};
     bool shared = true;
     for (int i = 1; i < count; ++i) shared = shared && batch.p[i].x == head.x && batch.p[i].s == head.s && batch.p[i].kc == batch.p[0].kc;
     if (shared) head.word |= kHeadShared;
@@ -287,15 +297,15 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
         waves = v.waves;
         variant = v.id;
     } else {
-        const TokensVariant tv = mixed ? tokens_mixed_variant(M, most, widest / kTileCols) : tokens_variant(bits, M, most, widest / kTileCols, staged_ahead);
+        const TokensVariant tv = narrow ? narrow_variant(bits, M, most) : mixed ? tokens_mixed_variant(M, most, widest / kTileCols) : tokens_variant(bits, M, most, widest / kTileCols, staged_ahead);
         lds = tv.lds_bytes;
         fn = tv.fn;
         waves = tv.waves;
-        variant = kBucketVariants + (mixed ? kTokensVariants : 0) + tv.id;
+        variant = kBucketVariants + (narrow ? kTokensVariants + kMixedTokensVariants : mixed ? kTokensVariants : 0) + tv.id;
     }
     uint32_t widths = 0;   // first workgroup of the 3-bit layers, and (upper half) of the 2-bit layers
     for (int i = 0; i < count; ++i) widths += width[i] == 4 ? nwg[i] * 0x10001u : width[i] == 3 ? nwg[i] * 0x10000u : 0u;
-    static PerDeviceFlags<kBucketVariants + kTokensVariants + kMixedTokensVariants> lds_raised;
+    static PerDeviceFlags<kBucketVariants + kTokensVariants + kMixedTokensVariants + kNarrowVariants> lds_raised;
     if (hipError_t e = raise_lds_limit_once(lds_raised, variant, fn, lds)) return (int)e;
     void *args[] = {&table.t[0], &table.t[1], &table.t[2], &table.t[3], &table.t[4], &table.t[5], &table.t[6], &table.t[7],
                     &head.x, &head.s, &head.word, &batch};
@@ -332,6 +342,11 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
             if (int e = launch_decode_layers(sub, n, M, workspace, stream, dense)) return e;
     }
     return 0;
+}
+
+int launch_narrow_group(const GroupItem *items, int count, int M, void *workspace, void *stream)
+{
+    return launch_decode_layers(items, count, M, workspace, (hipStream_t)stream, true, true);
 }
 
 // ---- scratch for callers that cannot allocate ---------------------------------------------------

@@ -36,6 +36,9 @@ constexpr int kDecodeTokens = 32;   // most tokens the decode kernels take (the 
 // dense: fp16 activations, and 3-bit indices, take the dequantising kernel for any M
 // bits: the layers' width, 0: widths of their own (items[i].bits)
 int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream, bool dense = false);
+// prefill of 17 .. kNarrowTokens tokens, layers of one width (workspace as above)
+constexpr int kNarrowTokens = 96;
+int launch_narrow_group(const GroupItem *items, int count, int M, void *workspace, void *stream);
 inline size_t decode_codes_bytes(int M, int K) { return ((size_t)M * K * 2 + 255) / 256 * 256; }
 
 // Launchers implemented in the .hip files.  All return hipError_t as int (0 = success).

@@ -70,12 +70,57 @@ def test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised):
 # waves (K = 256), units that do not divide by the waves (K = 1280, 2304), and the first token count of the same
 # layer that the large tiles take
 @pytest.mark.parametrize("bits", [2, 3, 4])
-@pytest.mark.parametrize("shape", [(48, 1280, 33), (48, 1280, 64), (1040, 512, 300), (5136, 256, 34), (5136, 1280, 65), (5136, 256, 97), (5136, 256, 200),
+@pytest.mark.parametrize("shape", [(48, 1280, 33), (48, 1280, 64), (48, 2304, 33), (48, 2304, 64), (5136, 256, 65), (1040, 512, 300), (5136, 256, 34), (5136, 1280, 65), (5136, 256, 97), (5136, 256, 200),
                                    (5136, 2304, 300), (8016, 2304, 129), (4096, 4096, 17), (4112, 4096, 32), (28800, 256, 128), (28800, 256, 257), (16384, 256, 128), (16400, 256, 128),
                                    (32768, 256, 64), (32784, 256, 64), (10912, 512, 192), (10928, 512, 192)])
 def test_gemm_split_tile_edges(bits, shape):
     N, K, M = shape
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
+
+
+def _narrow_takes(M, N, K, bits):
+    """Layers of the narrow kernel, by the rule of lcd_gemm.hip."""
+    if M <= 16 or M > 96:
+        return False
+    if N > 4096:
+        return M <= 64 or 6144 <= N <= 12288
+    if M <= 48:
+        return M <= 32 or K <= 2048 or (N > 2048 and (K <= 4096 or bits > 2))
+    return M <= 64 and N >= 2048 and K <= 2048
+
+
+# the narrow kernel: one token either side of a block of 16, every number of blocks; row tiles per workgroup up to, at and past what a
+# variant holds (6, 4, 3) and in more than one pass; fewer chunks than waves, one and several per wave
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("N,K,M", [(4096, 4096, 17), (4096, 4352, 32), (48, 1280, 33), (4112, 256, 33), (4112, 2304, 48), (2064, 512, 49), (12288, 256, 64), (20496, 512, 64), (16400, 2304, 50),
+                                   (24592, 256, 47), (32800, 512, 20), (6144, 2304, 65), (6160, 256, 80), (12288, 512, 81), (8208, 4352, 96)])
+def test_gemm_narrow_kernel_edges(bits, N, K, M):
+    assert _narrow_takes(M, N, K, bits) and not (M <= 32 and N * K < 1 << 24)
+    check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("M", [24, 40, 64, 90])
+def test_narrow_kernel_grouped_and_quantised(bits, M):
+    # layers on the narrow, the split and (small ones, up to 32 tokens) the tokens kernel in one call, inputs shared or not: the bits of single calls
+    import torch
+    from paper_2506_12038_amd.binding import GemmGroup
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + bits)
+    for q8 in (False, True):
+        problems, steps = [], []
+        shared = {}
+        for i, (N, K) in enumerate([(6160, 2304), (64, 512), (8208, 2304), (4096, 5120), (6144, 4096)]):
+            if K not in shared or i == 2:
+                shared[K] = (torch.randn((M, K), device="cuda", generator=g).half(), torch.rand((K,), device="cuda", generator=g) + 0.5)
+            packed = torch.randint(0, 256, (lcd.lcd_packed_bytes(N, K, bits),), dtype=torch.uint8, device="cuda", generator=g)
+            lut = lcd.lcd_build_lut((torch.randn((N, 1 << bits), device="cuda", generator=g) * 0.02).half(), bits)
+            problems.append((packed, lut, *shared[K], torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda"), N))
+            steps.append(0.03)
+        GemmGroup(problems, bits, s_q=steps if q8 else None)()
+        for packed, lut, x, s, y, N in problems:
+            single = lcd.lcd_lut_gemm_q8(packed, lut, x, s, 0.03, N, bits) if q8 else lcd.lcd_lut_gemm(packed, lut, x, s, N, bits)
+            assert torch.equal(y, single), (N, q8)
 
 
 def _split_tile_of(N, K, M, bits):
@@ -100,7 +145,7 @@ def _split_tile_of(N, K, M, bits):
 def test_gemm_every_split_tile(bits, tile):
     rows = [48 + 928 * i for i in range(37)] + [2704]
     found = [(N, K, M) for K in (2304, 1792) for M in (45, 77, 109, 141, 173, 237) for N in rows
-             if -(-N // 256) * -(-M // 128) <= 64 and _split_tile_of(N, K, M, bits) == tile]
+             if -(-N // 256) * -(-M // 128) <= 64 and not _narrow_takes(M, N, K, bits) and _split_tile_of(N, K, M, bits) == tile]
     assert found
     N, K, M = found[0]
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
