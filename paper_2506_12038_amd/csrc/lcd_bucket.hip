@@ -68,10 +68,10 @@ struct BucketWords {
 };
 
 // R: row tiles of a pass, W: waves.  MT: token slots, NTOK: tokens the launch has (MT = 4 token slots also serve three tokens, which then leave the fourth pass out).
-template <int BITS, int MT, bool I8, int NTOK, int R, int W>
+template <int BITS, int MT, bool I8, int NTOK, int R, int W, class BATCH>
 __global__ void __launch_bounds__(W * 64, 1) gemv_bucket_kernel(
     const uint32_t t0, const uint32_t t1, const uint32_t t2, const uint32_t t3, const uint32_t t4, const uint32_t t5, const uint32_t t6,
-    const uint32_t t7, const uint16_t *head_x, const float *head_s, const uint32_t head_word, const BucketBatch batch)
+    const uint32_t t7, const uint16_t *head_x, const float *head_s, const uint32_t head_word, const BATCH batch)
 {
     static_assert(MT == 1 || (MT == 2 && BITS == 2) || (MT == 4 && BITS == 2 && I8), "two tokens: 2-bit indices only; four: int8 operands only");
     typedef int int4v __attribute__((ext_vector_type(4)));
@@ -90,11 +90,13 @@ __global__ void __launch_bounds__(W * 64, 1) gemv_bucket_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: keeps addresses scalar
     const int q = lane >> 4, j = lane & 15;
 
-    int pi = (head_word & kHeadSingle) ? 0 : layer_of_workgroup(blockIdx.x, t0, t1, t2, t3, t4, t5, t6, t7);
+    constexpr bool SINGLE = std::is_same<BATCH, SingleBatch>::value;
+    const uint32_t word = SINGLE ? head_word | kHeadSingle | kHeadShared : head_word;
+    int pi = SINGLE || (word & kHeadSingle) ? 0 : layer_of_workgroup(blockIdx.x, t0, t1, t2, t3, t4, t5, t6, t7);
     const uint16_t *x = head_x;
     const float *s = head_s;
     int kc;
-    input_of(batch, pi, head_word, x, s, kc);
+    input_of(batch, pi, word, x, s, kc);
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(x, (uint32_t)NTOK * (uint32_t)kc * kTileCols * 2);
     const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(s, (uint32_t)kc * kTileCols * 4);
 
@@ -114,7 +116,7 @@ __global__ void __launch_bounds__(W * 64, 1) gemv_bucket_kernel(
     };
     load_x(wave, wave < kc);
     asm volatile("" ::: "memory");   // these loads first: they start the longest dependency chain
-    const LayerPart part_l = part_of(batch, pi, head_word, blockIdx.x, t0, t1, t2, t3, t4, t5, t6);
+    const LayerPart part_l = part_of(batch, pi, word, blockIdx.x, t0, t1, t2, t3, t4, t5, t6);
     const int nt = part_l.nt, ta = part_l.ta, tb = part_l.tb;
     const __amdgpu_buffer_rsrc_t rs_packed = make_rsrc(part_l.packed, (uint32_t)nt * (uint32_t)kc * TB);
     const __amdgpu_buffer_rsrc_t rs_lut = make_rsrc(part_l.lut, (uint32_t)nt * 16 * NB * 4);
@@ -331,7 +333,7 @@ template <int BITS, int MT, bool I8, int NTOK, int R>
 static BucketVariant variant_of(int id)
 {
     constexpr int W = bucket_waves<MT, I8>();
-    return BucketVariant{(const void *)gemv_bucket_kernel<BITS, MT, I8, NTOK, R, W>, R, W, bucket_lds_bytes<BITS, MT, R, W>(), id};
+    return BucketVariant{(const void *)gemv_bucket_kernel<BITS, MT, I8, NTOK, R, W, BucketBatch>, (const void *)gemv_bucket_kernel<BITS, MT, I8, NTOK, R, W, SingleBatch>, R, W, bucket_lds_bytes<BITS, MT, R, W>(), id};
 }
 
 // The variant for workgroups of up to `tiles` row tiles and kc chunks.  Three row tiles at a time cover the latency of memory; longer passes

@@ -69,10 +69,15 @@ __device__ __forceinline__ int layer_of_workgroup(uint32_t b, uint32_t t0, uint3
 struct BucketBatch {
     BucketProblem p[kMaxGroup];
 };
+// A launch of one layer: the argument segment is written across the bus, 1.4 us of host time per KiB.
+struct SingleBatch {
+    BucketProblem p[1];
+};
 
 // The input a workgroup's layer reads: from the leading arguments if the layers share it, else from the record.  (The
 // empty assembly statements keep the branches: as selects they would wait for the record on every path.)
-__device__ __forceinline__ void input_of(const BucketBatch &batch, int pi, uint32_t word, const uint16_t *&x, const float *&s, int &kc)
+template <class BATCH>
+__device__ __forceinline__ void input_of(const BATCH &batch, int pi, uint32_t word, const uint16_t *&x, const float *&s, int &kc)
 {
     kc = head_kc(word);
     if (!(word & kHeadShared)) {
@@ -84,7 +89,8 @@ __device__ __forceinline__ void input_of(const BucketBatch &batch, int pi, uint3
 }
 // The rest of the layer: row tiles [ta, tb) are the workgroup's.
 struct LayerPart { const uint8_t *packed; const float *lut; int nt, ta, tb; };
-__device__ __forceinline__ LayerPart part_of(const BucketBatch &batch, int pi, uint32_t word, uint32_t b, uint32_t t0, uint32_t t1, uint32_t t2, uint32_t t3,
+template <class BATCH>
+__device__ __forceinline__ LayerPart part_of(const BATCH &batch, int pi, uint32_t word, uint32_t b, uint32_t t0, uint32_t t1, uint32_t t2, uint32_t t3,
                                              uint32_t t4, uint32_t t5, uint32_t t6)
 {
     LayerPart l;
@@ -106,11 +112,11 @@ __device__ __forceinline__ LayerPart part_of(const BucketBatch &batch, int pi, u
 
 // ---- bucket kernel (lcd_bucket.hip) ---------------------------------------------------------------
 struct BucketVariant {
-    const void *fn;
+    const void *fn, *single;   // kernels for a group and for one layer (SingleBatch)
     int tiles;          // row tiles it holds at a time
     int waves;          // waves of its workgroups
     size_t lds_bytes;
-    int id;             // 0 .. kBucketVariants - 1
+    int id;             // 0 .. kBucketVariants - 1, of the two kernels 2 id and 2 id + 1
 };
 constexpr int kBucketVariants = 64;
 // tokens: 1 (2 and 3 bits), 2 (2 bits), 3 and 4 (2 bits, INT8 codes)

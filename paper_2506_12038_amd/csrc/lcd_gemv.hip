@@ -293,19 +293,19 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
     if (!tokens_path) {
         const BucketVariant v = bucket_variant(bits, M, int8_codes, most, widest / kTileCols);
         lds = v.lds_bytes;
-        fn = v.fn;
+        fn = count == 1 ? v.single : v.fn;
         waves = v.waves;
-        variant = v.id;
+        variant = 2 * v.id + (count == 1 ? 1 : 0);
     } else {
         const TokensVariant tv = narrow ? narrow_variant(bits, M, most) : mixed ? tokens_mixed_variant(M, most, widest / kTileCols) : tokens_variant(bits, M, most, widest / kTileCols, staged_ahead);
         lds = tv.lds_bytes;
         fn = tv.fn;
         waves = tv.waves;
-        variant = kBucketVariants + (narrow ? kTokensVariants + kMixedTokensVariants : mixed ? kTokensVariants : 0) + tv.id;
+        variant = 2 * kBucketVariants + (narrow ? kTokensVariants + kMixedTokensVariants : mixed ? kTokensVariants : 0) + tv.id;
     }
     uint32_t widths = 0;   // first workgroup of the 3-bit layers, and (upper half) of the 2-bit layers
     for (int i = 0; i < count; ++i) widths += width[i] == 4 ? nwg[i] * 0x10001u : width[i] == 3 ? nwg[i] * 0x10000u : 0u;
-    static PerDeviceFlags<kBucketVariants + kTokensVariants + kMixedTokensVariants + kNarrowVariants> lds_raised;
+    static PerDeviceFlags<2 * kBucketVariants + kTokensVariants + kMixedTokensVariants + kNarrowVariants> lds_raised;
     if (hipError_t e = raise_lds_limit_once(lds_raised, variant, fn, lds)) return (int)e;
     void *args[] = {&table.t[0], &table.t[1], &table.t[2], &table.t[3], &table.t[4], &table.t[5], &table.t[6], &table.t[7],
                     &head.x, &head.s, &head.word, &batch};
