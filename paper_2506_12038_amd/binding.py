@@ -110,13 +110,17 @@ def _check(status: int) -> None:
 
 
 _torch = None
+_half = _float = _byte = None
 _raw_stream = None     # device index -> handle of its current stream, without a Stream object
+_device = None         # index of the current device (the caller holds device tensors, so CUDA is up)
 
 
 def _torch_module():
-    global _torch, _raw_stream
+    global _torch, _raw_stream, _device, _half, _float, _byte
     if _torch is None:
         import torch
+        _half, _float, _byte = torch.float16, torch.float32, torch.uint8
+        _device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
         _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         _torch = torch
     return _torch
@@ -127,7 +131,7 @@ def _stream(stream) -> int:
         return stream.cuda_stream
     torch = _torch_module()
     if _raw_stream is not None:
-        return _raw_stream(torch.cuda.current_device())
+        return _raw_stream(_device())
     return torch.cuda.current_stream().cuda_stream
 
 
@@ -220,16 +224,22 @@ def lcd_build_lut(codebook, bits: int, stream=None):
 
 
 def _product(fn, step, packed, lut, x, s, N, bits, y, workspace, stream):
-    """fn: the library's entry point; step: () or (s_q,)."""
-    torch = _torch_module()
+    """fn: the library's entry point; step: () or (s_q,).  (An eager call of a small layer is bound by this function: the operands are
+    checked in place, and only what fails goes through _dev, which says what is wrong.)"""
+    torch = _torch or _torch_module()
     M, K = x.shape
     if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=x.device)
+        y = torch.empty((M, N), dtype=_half, device=x.device)
     if workspace is None:
-        workspace = torch.empty(max(_lib.lcd_workspace_bytes(M, N, K, bits), 256), dtype=torch.uint8, device=x.device)
-    half, byte = torch.float16, torch.uint8
-    status = fn(_dev(packed, byte, "packed"), _dev(lut, byte, "lut"), _dev(x, half, "x"), _dev(s, torch.float32, "s"), *step,
-                _dev(y, half, "y"), M, N, K, bits, _dev(workspace, byte, "workspace"), workspace.numel(), _stream(stream))
+        workspace = torch.empty(max(_lib.lcd_workspace_bytes(M, N, K, bits), 256), dtype=_byte, device=x.device)
+    if not (packed.is_cuda and packed.dtype is _byte and packed.is_contiguous() and lut.is_cuda and lut.dtype is _byte and lut.is_contiguous() and
+            x.is_cuda and x.dtype is _half and x.is_contiguous() and s.is_cuda and s.dtype is _float and s.is_contiguous() and
+            y.is_cuda and y.dtype is _half and y.is_contiguous() and workspace.is_cuda and workspace.dtype is _byte and workspace.is_contiguous()):
+        for t, dtype, name in ((packed, _byte, "packed"), (lut, _byte, "lut"), (x, _half, "x"), (s, _float, "s"), (y, _half, "y"),
+                               (workspace, _byte, "workspace")):
+            _dev(t, dtype, name)
+    status = fn(packed.data_ptr(), lut.data_ptr(), x.data_ptr(), s.data_ptr(), *step, y.data_ptr(), M, N, K, bits, workspace.data_ptr(),
+                workspace.numel(), _stream(stream) if stream is not None or _raw_stream is None else _raw_stream(_device()))
     if status:
         _check(status)
     return y
@@ -237,7 +247,7 @@ def _product(fn, step, packed, lut, x, s, N, bits, y, workspace, stream):
 
 def lcd_lut_gemv(packed, lut, x, s, N: int, bits: int, y=None, workspace=None, stream=None):
     """Decode path, x: CUDA float16 [M<=16, K] -> y float16 [M, N]."""
-    return _product(load_library().lcd_lut_gemv, (), packed, lut, x, s, N, bits, y, workspace, stream)
+    return _product((_lib or load_library()).lcd_lut_gemv, (), packed, lut, x, s, N, bits, y, workspace, stream)
 
 
 def lcd_lut_gemv_noalloc(packed, lut, x, s, N: int, bits: int, y, stream=None):
@@ -253,17 +263,17 @@ def lcd_lut_gemv_noalloc(packed, lut, x, s, N: int, bits: int, y, stream=None):
 
 def lcd_lut_gemv_q8(packed, lut, x, s, s_q: float, N: int, bits: int, y=None, workspace=None, stream=None):
     """Decode path with the INT8 input transformation in front: y = s_q * sum_k q_k * C[n][idx], M <= 16."""
-    return _product(load_library().lcd_lut_gemv_q8, (float(s_q),), packed, lut, x, s, N, bits, y, workspace, stream)
+    return _product((_lib or load_library()).lcd_lut_gemv_q8, (float(s_q),), packed, lut, x, s, N, bits, y, workspace, stream)
 
 
 def lcd_lut_gemm_q8(packed, lut, x, s, s_q: float, N: int, bits: int, y=None, workspace=None, stream=None):
     """Prefill path with the INT8 input transformation in front (any M)."""
-    return _product(load_library().lcd_lut_gemm_q8, (float(s_q),), packed, lut, x, s, N, bits, y, workspace, stream)
+    return _product((_lib or load_library()).lcd_lut_gemm_q8, (float(s_q),), packed, lut, x, s, N, bits, y, workspace, stream)
 
 
 def lcd_lut_gemm(packed, lut, x, s, N: int, bits: int, y=None, workspace=None, stream=None):
     """Prefill path, x: CUDA float16 [M, K] -> y float16 [M, N]."""
-    return _product(load_library().lcd_lut_gemm, (), packed, lut, x, s, N, bits, y, workspace, stream)
+    return _product((_lib or load_library()).lcd_lut_gemm, (), packed, lut, x, s, N, bits, y, workspace, stream)
 
 
 class GemvGroup:
