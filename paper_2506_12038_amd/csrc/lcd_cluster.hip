@@ -9,20 +9,17 @@
 namespace lcd {
 
 constexpr int kAssignThreads = 256;
-constexpr int kAssignCols = kAssignThreads * 8;   // columns of a row per pass of its workgroup
+constexpr int kAssignCols = 64 * 8;      // columns of a row per pass of its wave
+constexpr int kAssignAhead = 4;          // passes of loads on the way
+constexpr int kAssignPasses = 8;         // most passes of a wave
 
 __device__ __forceinline__ double half_bits_to_double(uint16_t b) { return (double)(float)__builtin_bit_cast(_Float16, b); }
 
-// neighbours of an fp16 value in the order of the reals (bit patterns; -0 counts as 0)
+// the next fp16 value in the order of the reals (bit patterns; -0 counts as 0)
 __device__ __forceinline__ uint16_t half_next_up(uint16_t b)
 {
     if ((b & 0x7fffu) == 0) return 0x0001u;
     return (b & 0x8000u) ? (uint16_t)(b - 1) : (uint16_t)(b + 1);
-}
-__device__ __forceinline__ uint16_t half_next_down(uint16_t b)
-{
-    if ((b & 0x7fffu) == 0) return 0x8001u;
-    return (b & 0x8000u) ? (uint16_t)(b + 1) : (uint16_t)(b - 1);
 }
 
 // ---- nearest centroid ------------------------------------------------------------------------
@@ -31,11 +28,17 @@ __device__ __forceinline__ uint16_t half_next_down(uint16_t b)
 // need not be an fp16 number, but "w > boundary" for an fp16 w is the same as "w >= u" with u the
 // smallest fp16 number above the boundary; u is found once per row in fp64, where the boundary is
 // exact.  The comparisons are integer ones on keys that are ordered as the fp16 numbers are, two
-// weights per 32-bit register: a saturating subtraction per boundary leaves "w >= u" in the sign bits, which
-// full adders (two bitwise instructions each) count in bit planes: 11 instructions per weight at 8 centroids, where
-// one comparison and one addition per boundary take 16.  Bound: HBM, 3 bytes per weight (11008 x 4096, 8 centroids: 32 -> 27.5 us,
-// 4.9 TB/s).  The indices are stored with the default cache policy: the next step reads them (assign + 1.5 us, the three
-// steps behind it - 2.5 us).
+// weights per 32-bit register: a saturating subtraction of the boundary in the middle leaves "w >= u" in the sign bits,
+// which are the index's top bit and choose the half of the boundaries that stays in question (one bitwise select
+// per boundary): 4, 9 and 18 instructions for two weights at 4, 8 and 16 centroids, where counting over all boundaries
+// in bit planes took 5, 15 and 37.  A search needs ascending boundaries; a wave that finds a descent in its row (centroids that
+// do not ascend, a NaN) counts one boundary after the other, as slowly as that is.
+// Bound: HBM, 3 bytes per weight (11008 x 4096, 8 centroids: 27.5 -> 25 us, 5.4 TB/s; 4096 x 4096, 16 centroids, which the counting
+// bound: 19.7 -> 14.9 us).  A wave works alone: no barrier stands between the boundaries and the first weights, and the
+// boundaries, which cost as much as two passes, are found once per eight passes (with workgroups of a row each 28 us, with two passes
+// per wave 30).  Rows longer than eight passes are cut into equal parts: 4096 x 11008 in rows of 22 passes leaves half
+// of the wave slots empty and takes 27 us instead of 25.  The indices are stored with the default cache policy: the next step reads
+// them (assign + 1.5 us, the three steps behind it - 2.5 us).
 typedef short key_pair __attribute__((ext_vector_type(2)));
 typedef unsigned short ukey_pair __attribute__((ext_vector_type(2)));
 
@@ -48,104 +51,115 @@ __device__ __forceinline__ key_pair ordered_keys(uint32_t halves)
     return __builtin_bit_cast(key_pair, (ukey_pair)(__builtin_bit_cast(ukey_pair, halves ^ (sign & 0x7fff7fffu)) + up));
 }
 
-// full adder at every bit position
-__device__ __forceinline__ uint32_t sum_bit(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
-__device__ __forceinline__ uint32_t carry_bit(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8); }
-
-// Number of set words among v[0..N) at every bit position, as bit planes (N = 3, 7 or 15: 2, 3 or 4 planes).
-template <int N>
-__device__ __forceinline__ void count_planes(const uint32_t *v, uint32_t *planes)
+__device__ __forceinline__ uint32_t key_above(key_pair limit, key_pair key)      // bits 15 and 31
 {
-    if constexpr (N == 3) {
-        planes[0] = sum_bit(v[0], v[1], v[2]);
-        planes[1] = carry_bit(v[0], v[1], v[2]);
-    } else {
-        constexpr int H = (N - 1) / 2, P = N == 7 ? 2 : 3;      // two halves and one carry in
-        uint32_t a[P], b[P];
-        count_planes<H>(v, a);
-        count_planes<H>(v + H, b);
-        uint32_t carry = v[N - 1];
+    return __builtin_bit_cast(uint32_t, (key_pair)__builtin_elementwise_sub_sat(limit, key));
+}
+__device__ __forceinline__ key_pair choose(uint32_t mask, key_pair set, key_pair clear)
+{
+    return __builtin_bit_cast(key_pair, bfi(mask, __builtin_bit_cast(uint32_t, set), __builtin_bit_cast(uint32_t, clear)));
+}
+
+template <int NTHR, bool ASCENDING>   // NTHR: boundaries the container can have: 3, 7 or 15
+__device__ __forceinline__ uint2v nearest_of_eight(const uint4v v, const key_pair *limit)
+{
+    constexpr int BITS = NTHR == 3 ? 2 : NTHR == 7 ? 3 : 4;
+    uint32_t bit[4][BITS];   // [register][index bit], in bits 15 and 31
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-            planes[i] = sum_bit(a[i], b[i], carry);
-            carry = carry_bit(a[i], b[i], carry);
+    for (int j = 0; j < 4; ++j) {
+        const key_pair key = ordered_keys(v[j]);
+        if constexpr (ASCENDING) {
+            key_pair part[NTHR];       // the boundaries that are still in question; the middle one decides
+#pragma unroll
+            for (int i = 0; i < NTHR; ++i) part[i] = limit[i];
+#pragma unroll
+            for (int b = BITS - 1, half = NTHR / 2; b >= 0; --b, half /= 2) {
+                bit[j][b] = key_above(part[half], key);
+                const uint32_t mask = __builtin_bit_cast(uint32_t, (key_pair)(__builtin_bit_cast(key_pair, bit[j][b]) >> 15));
+#pragma unroll
+                for (int i = 0; i < half; ++i) part[i] = choose(mask, part[half + 1 + i], part[i]);
+            }
+        } else {
+            uint32_t count = 0;
+#pragma unroll
+            for (int i = 0; i < NTHR; ++i) count += (key_above(limit[i], key) >> 15) & 0x10001u;
+#pragma unroll
+            for (int b = 0; b < BITS; ++b) bit[j][b] = count << (15 - b);   // bits 15 and 31 are read
         }
-        planes[P] = carry;
+    }
+    uint2v o;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {   // bytes 0..3: the halves of registers 2 h and 2 h + 1; bit 7 of a byte of a plane is the flag
+        uint32_t word = 0;
+#pragma unroll
+        for (int b = BITS - 1; b >= 0; --b) {
+            const uint32_t plane = perm(bit[2 * h + 1][b], bit[2 * h][b], 0x07050301u) >> (BITS - 1 - b);
+            word = b == BITS - 1 ? plane : bfi(0x01010101u * (0x100u - (0x100u >> (BITS - 1 - b))), word, plane);   // the bits above this one's stay
+        }
+        o[h] = (word >> (8 - BITS)) & (0x01010101u * ((1u << BITS) - 1u));
+    }
+    return o;
+}
+
+template <int NTHR, bool ASCENDING>
+__device__ __forceinline__ void assign_row(const uint16_t *from, uint8_t *to, int left, const key_pair *limit, uint4v *v)
+{
+    while (left > 0) {
+#pragma unroll
+        for (int u = 0; u < kAssignAhead; ++u) {
+            const uint4v now = v[u];
+            if (left > kAssignAhead * kAssignCols) v[u] = stream_load(reinterpret_cast<const uint4v *>(from + kAssignAhead * kAssignCols));
+            if (left > 0) *reinterpret_cast<uint2v *>(to) = nearest_of_eight<NTHR, ASCENDING>(now, limit);
+            left -= kAssignCols;
+            from += kAssignCols;
+            to += kAssignCols;
+        }
     }
 }
 
-template <int NTHR>   // boundaries the container can have: 3, 7 or 15
-__global__ void __launch_bounds__(kAssignThreads) assign_kernel(const uint16_t *__restrict__ w, const uint16_t *__restrict__ codebook,
-                                                                uint8_t *__restrict__ idx, int K, int ncent)
+template <int NTHR>
+__global__ void __launch_bounds__(kAssignThreads, 8) assign_kernel(const uint16_t *__restrict__ w, const uint16_t *__restrict__ codebook,
+                                                                uint8_t *__restrict__ idx, int K, int ncent, int parts, int width)
 {
-    constexpr int BITS = NTHR == 3 ? 2 : NTHR == 7 ? 3 : 4;
-    __shared__ uint32_t thr[16];
-    const int n = blockIdx.x;          // rows on the x axis: N may exceed the y limit of a grid
-    const uint16_t *row_w = w + (size_t)n * K;
-    // the first two passes' weights are on the way while the boundaries are found
-    int k0 = (int)threadIdx.x * 8;     // K is a multiple of 256: 8 columns are all inside or all outside
-    uint4v next = {0u, 0u, 0u, 0u}, after = {0u, 0u, 0u, 0u};
-    if (k0 < K) next = stream_load(reinterpret_cast<const uint4v *>(row_w + k0));
-    if (k0 + kAssignCols < K) after = stream_load(reinterpret_cast<const uint4v *>(row_w + k0 + kAssignCols));
-    if (threadIdx.x < NTHR) {
-        uint32_t limit = 0x7fffu;      // never passed: not in use, or NaN
-        if ((int)threadIdx.x + 1 < ncent) {
-            const uint16_t *row = codebook + (size_t)n * (NTHR + 1);
-            const double m = 0.5 * (half_bits_to_double(row[threadIdx.x]) + half_bits_to_double(row[threadIdx.x + 1]));   // exact
-            uint16_t h = __builtin_bit_cast(uint16_t, (_Float16)(float)m);   // within an fp16 step or two of m
+    const int lane = threadIdx.x & 63;
+    // N is a multiple of 16: every wave has a part of a row
+    const uint32_t unit = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kAssignThreads / 64) + (threadIdx.x >> 6)));
+    const uint32_t n = unit / (uint32_t)parts;
+    const int first = (int)(unit - n * (uint32_t)parts) * width;
+    const uint16_t *from = w + (size_t)n * K + first + lane * 8;
+    uint8_t *to = idx + (size_t)n * K + first + lane * 8;
+    const int left = min(K - first, width) - lane * 8;     // K is a multiple of 256: 8 columns are all inside or all outside
+    // the first passes' weights are on the way while the boundaries are found
+    uint4v v[kAssignAhead];
 #pragma unroll
-            for (int it = 0; it < 3; ++it) {          // walk down while the lower neighbour is still above m
-                const uint16_t d = half_next_down(h);
-                if (half_bits_to_double(d) > m) h = d;
-            }
-#pragma unroll
-            for (int it = 0; it < 3; ++it)            // walk up while h is not above m (stops at infinity)
-                if (!(half_bits_to_double(h) > m) && (h & 0x7fffu) != 0x7c00u) h = half_next_up(h);
-            if (h == 0) h = 0x8000u;                  // both zeros pass
-            if ((h & 0x7fffu) <= 0x7c00u) limit = (uint16_t)(ordered_keys(h)[0] - 1);   // one below the smallest key that passes
-        }
-        thr[threadIdx.x] = limit * 0x10001u;
+    for (int u = 0; u < kAssignAhead; ++u)
+        if (u * kAssignCols < left) v[u] = stream_load(reinterpret_cast<const uint4v *>(from + u * kAssignCols));
+    uint32_t mine = 0x7fffu;           // never passed: not in use, or NaN
+    if (lane + 1 < ncent) {
+        const uint16_t *row = codebook + (size_t)n * (NTHR + 1);
+        const double m = 0.5 * (half_bits_to_double(row[lane]) + half_bits_to_double(row[lane + 1]));   // exact
+        // rounding, also twice, is monotone: the fp16 value that m rounds to is the smallest above m, or the one below that
+        uint16_t h = __builtin_bit_cast(uint16_t, (_Float16)(float)m);
+        if (!(half_bits_to_double(h) > m) && (h & 0x7fffu) != 0x7c00u) h = half_next_up(h);     // (stops at infinity)
+        if (h == 0) h = 0x8000u;                  // both zeros pass
+        if (m == m) mine = (uint16_t)(ordered_keys(h)[0] - 1);   // one below the smallest key that passes
     }
-    __syncthreads();
+    mine *= 0x10001u;
     key_pair limit[NTHR];
 #pragma unroll
-    for (int i = 0; i < NTHR; ++i) limit[i] = __builtin_bit_cast(key_pair, thr[i]);
-    // the workgroup walks its row: the boundaries are found once per row
-    while (k0 < K) {
-        const uint4v v = next;
-        const int k = k0;
-        k0 += kAssignCols;
-        next = after;
-        if (k0 + kAssignCols < K) after = stream_load(reinterpret_cast<const uint4v *>(row_w + k0 + kAssignCols));
-        uint32_t bit[4][BITS];   // [register][index bit], in bits 15 and 31
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const key_pair key = ordered_keys(v[j]);
-            uint32_t above[NTHR];
-#pragma unroll
-            for (int i = 0; i < NTHR; ++i) above[i] = __builtin_bit_cast(uint32_t, (key_pair)__builtin_elementwise_sub_sat(limit[i], key));
-            count_planes<NTHR>(above, bit[j]);
-        }
-        uint2v o;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {   // bytes 0..3: the halves of registers 2 h and 2 h + 1; bit 7 of a byte of a plane is the flag
-            uint32_t word = 0;
-#pragma unroll
-            for (int b = BITS - 1; b >= 0; --b) {
-                const uint32_t plane = perm(bit[2 * h + 1][b], bit[2 * h][b], 0x07050301u) >> (BITS - 1 - b);
-                word = b == BITS - 1 ? plane : bfi(0x01010101u * (0x100u - (0x100u >> (BITS - 1 - b))), word, plane);   // the bits above this one's stay
-            }
-            o[h] = (word >> (8 - BITS)) & (0x01010101u * ((1u << BITS) - 1u));
-        }
-        *reinterpret_cast<uint2v *>(idx + (size_t)n * K + k) = o;
-    }
+    for (int i = 0; i < NTHR; ++i) limit[i] = __builtin_bit_cast(key_pair, (uint32_t)__builtin_amdgcn_readlane((int)mine, i));
+    // every lane's limit no larger than the next one's (beyond the last: itself)
+    const int next = __shfl((int)mine, lane + 1 < NTHR ? lane + 1 : lane);
+    if (__builtin_amdgcn_ballot_w64(lane < NTHR && (short)mine > (short)next) == 0) assign_row<NTHR, true>(from, to, left, limit, v);
+    else assign_row<NTHR, false>(from, to, left, limit, v);
 }
 
 // ---- cluster sizes: one wave per row -----------------------------------------------------------------
 // 32 indices of a lane become four words of one bit each (bit planes); a cluster's members among them are the set
 // bits of one AND of the planes, counted by one v_bcnt per cluster: about 3 instructions per index.  Bound: HBM or
 // the last-level cache, 1 byte per index (11008 x 4096, 8 clusters: 18.6 us with a private LDS counter per lane and cluster,
-// now 9 us, 5 TB/s).
+// now 9 us, 5 TB/s;
+// 16384 x 1024, 16 clusters, whose second group is empty and is passed over: 11 -> 8 us).
 // Sum over the lanes: while a lane holds several counters it hands half of them to its partner, then plain sums.
 template <int HELD, int OFF>
 __device__ __forceinline__ void fold_counters(uint32_t *c, int lane)
@@ -176,7 +190,8 @@ __global__ void __launch_bounds__(256) counts_kernel(const uint8_t *__restrict__
 #pragma unroll
     for (int b = 0; b < SLOTS; ++b) c[b] = 0;
     constexpr int GROUPS = 2;                     // groups of 32 indices a lane has in flight
-    for (int k0 = lane * 16; k0 < K; k0 += GROUPS * 2048) {
+    for (int first = 0; first < K; first += GROUPS * 2048) {
+        const int k0 = first + lane * 16;
         uint4v v[GROUPS][2];
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g)
@@ -185,10 +200,11 @@ __global__ void __launch_bounds__(256) counts_kernel(const uint8_t *__restrict__
                 const int k = k0 + g * 2048 + h * 1024;   // 16 columns are all inside or all outside
                 v[g][h] = uint4v{0u, 0u, 0u, 0u};
                 if (k < K) v[g][h] = *reinterpret_cast<const uint4v *>(row + k);
-                else c[0] -= 16;                          // 16 zeros that are not there
+                else if (first + g * 2048 < K) c[0] -= 16;   // 16 zeros that are not there
             }
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) {
+            if (first + g * 2048 >= K) break;
             uint32_t p[4] = {0, 0, 0, 0};
 #pragma unroll
             for (int d = 0; d < 8; ++d) {         // word d's bit j of every byte to bit d of every byte of plane j
@@ -342,10 +358,12 @@ __global__ void __launch_bounds__(256) merge_kernel(const uint16_t *cb_in, const
 
 int launch_assign(const uint16_t *w, const uint16_t *codebook, int ncent, int N, int K, int bits, uint8_t *idx, void *stream)
 {
-    const dim3 grid((unsigned)N), block(kAssignThreads);
-    if (bits == 2) hipLaunchKernelGGL(assign_kernel<3>, grid, block, 0, (hipStream_t)stream, w, codebook, idx, K, ncent);
-    else if (bits == 3) hipLaunchKernelGGL(assign_kernel<7>, grid, block, 0, (hipStream_t)stream, w, codebook, idx, K, ncent);
-    else hipLaunchKernelGGL(assign_kernel<15>, grid, block, 0, (hipStream_t)stream, w, codebook, idx, K, ncent);
+    const int passes = (K + kAssignCols - 1) / kAssignCols, parts = (passes + kAssignPasses - 1) / kAssignPasses;
+    const int width = (passes + parts - 1) / parts * kAssignCols;
+    const dim3 grid((unsigned)(N / 4 * parts)), block(kAssignThreads);
+    if (bits == 2) hipLaunchKernelGGL(assign_kernel<3>, grid, block, 0, (hipStream_t)stream, w, codebook, idx, K, ncent, parts, width);
+    else if (bits == 3) hipLaunchKernelGGL(assign_kernel<7>, grid, block, 0, (hipStream_t)stream, w, codebook, idx, K, ncent, parts, width);
+    else hipLaunchKernelGGL(assign_kernel<15>, grid, block, 0, (hipStream_t)stream, w, codebook, idx, K, ncent, parts, width);
     return (int)hipGetLastError();
 }
 

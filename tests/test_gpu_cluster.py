@@ -75,6 +75,27 @@ def test_assign_indices_at_the_ends_of_the_number_range(bits):
     assert np.array_equal(got, expect)
 
 
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("K", [512, 4096, 4352, 8448])      # one pass, the most of a wave, two parts, three parts with a ragged end
+def test_assign_indices_rows_that_do_not_ascend_are_counted(bits, K):
+    # equal centroids are searched as ascending ones are; a row with a descent or a NaN takes as its index the number of boundaries
+    # that its weight is strictly above
+    ncent, N = 1 << bits, 16
+    cb = _row_codebooks(N, ncent, bits, 50 + bits)
+    w = _weights(N, K, cb, ncent, K + bits)
+    cb[1] = cb[1, ::-1].copy()
+    cb[2, 1] = cb[2, 0]
+    cb[3, 1] = np.nan
+    cb[5, -1] = -np.inf
+    cb[6, -1] = np.inf
+    cb[7, 0] = -np.inf
+    got = lcd.lcd_assign_indices(to_dev(w), to_dev(cb), ncent, bits).cpu().numpy()
+    c64 = cb.astype(np.float64)
+    mid = (c64[:, 1:] + c64[:, :-1]) / 2
+    expect = (w.astype(np.float64)[:, :, None] > mid[:, None, :]).sum(axis=2)
+    assert np.array_equal(got, expect)
+
+
 def test_assign_then_pack_then_product_reproduces_the_clustered_weights():
     # dense weights -> indices on the GPU -> the decode path; equals the oracle product on the
     # oracle's own assignment of the same weights
@@ -93,7 +114,7 @@ def test_assign_then_pack_then_product_reproduces_the_clustered_weights():
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
-@pytest.mark.parametrize("shape", [(16, 256), (48, 2304), (64, 11008)])
+@pytest.mark.parametrize("shape", [(16, 256), (16, 1024), (16, 2048), (48, 2304), (16, 4352), (64, 11008)])
 def test_cluster_counts_are_exact(bits, shape):
     N, K = shape
     rng = np.random.default_rng(N + K + bits)
