@@ -38,8 +38,12 @@ __global__ __launch_bounds__(kQuantThreads) void transform_kernel(TransformBatch
     const float4v s0 = *reinterpret_cast<const float4v *>(it.s + k0), s1 = *reinterpret_cast<const float4v *>(it.s + k0 + 4);
     const bool quantised = it.s_q != 0.0f;   // uniform
     Divisor dv[8];
+    float rs[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) dv[e] = make_divisor(e < 4 ? s0[e] : s1[e - 4], quantised ? it.s_q : 1.0f);
+    for (int e = 0; e < 8; ++e) {
+        dv[e] = make_divisor(e < 4 ? s0[e] : s1[e - 4], quantised ? it.s_q : 1.0f);
+        rs[e] = __builtin_amdgcn_rcpf(e < 4 ? s0[e] : s1[e - 4]);
+    }
     // position of these 8 columns in operand order: chunk, then step g = (k % 64) / 8, then (k % 256) / 64
     const int group = (k0 / kTileCols) * 32 + ((k0 % 64) / 8) * 4 + (k0 % kTileCols) / 64;
     // blockIdx.z: a group of kQuantTokens tokens (short dependent chains, all loads in flight together)
@@ -51,14 +55,20 @@ __global__ __launch_bounds__(kQuantThreads) void transform_kernel(TransformBatch
 #pragma unroll
     for (int i = 0; i < kQuantTokens; ++i) {
         if (m0 + i < M) {
-            half8 o;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int slot = e < 4 ? 2 * e : 2 * (e - 4) + 1;
-                if (quantised) o[slot] = (e & 1) ? quantise_half<1>(v[i][e >> 1], dv[e]) : quantise_half<0>(v[i][e >> 1], dv[e]);
-                else o[slot] = smooth_one((uint16_t)(v[i][e >> 1] >> (16 * (e & 1))), e < 4 ? s0[e] : s1[e - 4]);   // rounds as the fused path does
+            // register i of the result: columns i, 4 + i
+            uint4v o;
+            if (quantised) {
+                o[0] = quantise_pair<0, 0>(v[i][0], dv[0], v[i][2], dv[4]);
+                o[1] = quantise_pair<1, 1>(v[i][0], dv[1], v[i][2], dv[5]);
+                o[2] = quantise_pair<0, 0>(v[i][1], dv[2], v[i][3], dv[6]);
+                o[3] = quantise_pair<1, 1>(v[i][1], dv[3], v[i][3], dv[7]);
+            } else {                      // rounds as the fused path does
+                o[0] = smooth_pair<0, 0>(v[i][0], rs[0], v[i][2], rs[4]);
+                o[1] = smooth_pair<1, 1>(v[i][0], rs[1], v[i][2], rs[5]);
+                o[2] = smooth_pair<0, 0>(v[i][1], rs[2], v[i][3], rs[6]);
+                o[3] = smooth_pair<1, 1>(v[i][1], rs[3], v[i][3], rs[7]);
             }
-            *reinterpret_cast<half8 *>(it.codes + ((size_t)group * M + m0 + i) * 8) = o;
+            *reinterpret_cast<uint4v *>(it.codes + ((size_t)group * M + m0 + i) * 8) = o;
         }
     }
 }

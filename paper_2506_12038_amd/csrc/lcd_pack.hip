@@ -210,22 +210,24 @@ __device__ __forceinline__ void smooth_tile(const uint16_t *__restrict__ x, cons
         const int grp = t + 256 * u;            // input order: 32 groups of 8 columns per token row
         const int ml = grp >> 5;
         const int m = mb * 32 + ml;
-        half8 o;
+        uint4v o = {0u, 0u, 0u, 0u};            // register i: columns i, 4 + i
         if (m < M) {
             const uint4v xv = xin[u];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int slot = e < 4 ? 2 * e : 2 * (e - 4) + 1;
-                if (quantised) o[slot] = (e & 1) ? quantise_half<1>(xv[e >> 1], dv[e]) : quantise_half<0>(xv[e >> 1], dv[e]);
-                else o[slot] = smooth_with((uint16_t)(xv[e >> 1] >> (16 * (e & 1))), r[e]);
+            if (quantised) {
+                o[0] = quantise_pair<0, 0>(xv[0], dv[0], xv[2], dv[4]);
+                o[1] = quantise_pair<1, 1>(xv[0], dv[1], xv[2], dv[5]);
+                o[2] = quantise_pair<0, 0>(xv[1], dv[2], xv[3], dv[6]);
+                o[3] = quantise_pair<1, 1>(xv[1], dv[3], xv[3], dv[7]);
+            } else {
+                o[0] = smooth_pair<0, 0>(xv[0], r[0], xv[2], r[4]);
+                o[1] = smooth_pair<1, 1>(xv[0], r[1], xv[2], r[5]);
+                o[2] = smooth_pair<0, 0>(xv[1], r[2], xv[3], r[6]);
+                o[3] = smooth_pair<1, 1>(xv[1], r[3], xv[3], r[7]);
             }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (_Float16)0.0f;
         }
         const int h = kg >> 4, kh = (kg >> 3) & 1, g = kg & 7;
         const int row = (h * 8 + g) * 2 + kh;   // position of this group of 8 columns in operand order
-        *reinterpret_cast<half8 *>(tile + row * kSmoothRowBytes + ml * 16) = o;
+        *reinterpret_cast<uint4v *>(tile + row * kSmoothRowBytes + ml * 16) = o;
     }
     __syncthreads();
     _Float16 *dst = xs + ((size_t)c * (Mpad >> 5) + mb) * (32 * 256);
