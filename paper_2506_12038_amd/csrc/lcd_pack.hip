@@ -248,13 +248,21 @@ __global__ void __launch_bounds__(256) smooth_group_kernel(const SmoothBatch bat
     smooth_tile(it.x, it.s, (_Float16 *)it.xs, M, Mpad, it.K, blockIdx.x, blockIdx.y, it.s_q);
 }
 
+// One input, the usual case: its arguments are in scalar registers when a wave starts, and the argument segment is 48 bytes
+// (4096 x 4096, 3 bits, 100 tokens 14.2 -> 13.7 us).
+__global__ void __launch_bounds__(256) smooth_one_kernel(const uint16_t *x, const float *s, _Float16 *xs, int K, float s_q, int M, int Mpad)
+{
+    smooth_tile(x, s, xs, M, Mpad, K, blockIdx.x, blockIdx.y, s_q);
+}
+
 int launch_smooth_group(const SmoothItem *items, int count, int M, int Mpad, void *stream)
 {
     SmoothBatch batch{};
     int widest = 0;
     for (int i = 0; i < count; ++i) { batch.p[i] = items[i]; widest = items[i].K > widest ? items[i].K : widest; }
     const dim3 grid((unsigned)(widest / kTileCols), (unsigned)(Mpad / 32), (unsigned)count), block(256);
-    hipLaunchKernelGGL(smooth_group_kernel, grid, block, 0, (hipStream_t)stream, batch, M, Mpad);
+    if (count == 1) hipLaunchKernelGGL(smooth_one_kernel, grid, block, 0, (hipStream_t)stream, items[0].x, items[0].s, (_Float16 *)items[0].xs, items[0].K, items[0].s_q, M, Mpad);
+    else hipLaunchKernelGGL(smooth_group_kernel, grid, block, 0, (hipStream_t)stream, batch, M, Mpad);
     return (int)hipGetLastError();
 }
 
