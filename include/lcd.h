@@ -229,8 +229,9 @@ lcd_status lcd_lut_gemv_grouped(const lcd_gemv_problem *problems /*HOST*/, int c
 
 /* Layers of different index widths in one call (the paper assigns a centroid count per layer,
  * Sec. 5: 5, 6, 10, ... centroids): bits is a HOST array of `count` widths, each 2, 3 or 4.
- * All layers are validated first; then the layers of each width that occurs go out as one
- * lcd_lut_gemv_grouped call, in the order 2, 3, 4, on `stream`.  Workspace as for lcd_lut_gemv_grouped (its size
+ * All layers are validated first; then those that run on the register dequantiser go out in one launch whatever
+ * their widths (unless their activations are transformed ahead of it), the others width by width in the order
+ * 2, 3, 4, on `stream`.  Results are bit for bit those of lcd_lut_gemv on every layer.  Workspace as for lcd_lut_gemv_grouped (its size
  * does not depend on the width). */
 lcd_status lcd_lut_gemv_grouped_mixed(const lcd_gemv_problem *problems /*HOST*/, const int *bits /*HOST*/, int count,
                                       int M, void *workspace, size_t workspace_bytes, void *stream);
@@ -247,7 +248,7 @@ lcd_status lcd_lut_gemv_q8_grouped(const lcd_gemv_problem *problems /*HOST*/, co
  * the layers' output tiles one layer after the other (those with the largest K first), so that
  * the compute units the tail of one layer leaves idle start on the next.  Layers that lcd_lut_gemm gives to the
  * decode kernel (all with up to 16 tokens, small ones with up to 32) go out ahead as one decode call, of one or two
- * launches.  Results are bit for bit those of lcd_lut_gemm on every layer.  `problems` is a HOST array, read during the call
+ * launches, and those it gives to the kernel for few tokens (some with up to 96) as one pair of launches.  Results are bit for bit those of lcd_lut_gemm on every layer.  `problems` is a HOST array, read during the call
  * only; outputs must not overlap.  Workspace: at least
  * lcd_workspace_bytes_gemm_grouped(problems, count, M, bits) bytes (DEVICE; the sum of the
  * layers' lcd_workspace_bytes): every layer's smoothed activations side by side.

@@ -12,10 +12,11 @@
 //
 // What bounds it: the activations' way from L2 into LDS (every wave reads its own: 2 bytes per token and
 // column and workgroup, 75..98 GB/s per compute unit), with 32 tokens x 64 rows the dequantiser; around it about 2 us
-// of start-up and epilogue per workgroup and about 5 us of smoothing launch per call.  That is why the tile is
+// of start-up and epilogue per workgroup and about 4 us of smoothing launch per call.  That is why the tile is
 // as small as fills the compute units.  Measured against 256 x 128 tiles (16..86 workgroups on these), per call: 11008 x 4096,
-// 4 bits, 100 tokens 57 -> 23 us; 7B block (q, k, v | o | gate, up | down), 2 bits and INT8 codes, 333 tokens
-// 298 -> 191 us; 3 bits, 40 tokens 264 -> 71 us (the tokens kernel: 90).
+// 4 bits, 100 tokens 57 -> 22 us; 7B block (q, k, v | o | gate, up | down), 2 bits and INT8 codes, 333 tokens
+// 298 -> 185 us.  Rings of 5 or 6 k-steps instead of 4 and tiles of 128 rows x 64..128 tokens whose activations all waves share gained nothing
+// over the range (the latter 1.2 to 1.3 on some groups, 0.66 to 1 on the others and on single layers).
 #pragma once
 #include <type_traits>
 #include "lcd_gemm_common.h"
