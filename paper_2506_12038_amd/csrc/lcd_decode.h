@@ -123,6 +123,11 @@ constexpr int kBucketVariants = 64;
 // tiles: most row tiles of a workgroup; kc: chunks of the widest layer
 BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int tiles, int kc);
 
+// Partial tiles in LDS (tokens and narrow kernel): where row quad q of token j of a tile stands, in floats; r: the tile's row tile in the pass.
+// 16 lanes that write (one q, all j) and 16 that read (the quads of one token, row tile after row tile) each cover all banks; in
+// plain [token][row] order both met in a quarter of them.  PLACEHOLDER
+__device__ __forceinline__ int partial_quad(int r, int q, int j) { return 4 * ((4 * j + (q ^ (j >> 2))) ^ ((r & 3) << 2)); }
+
 // ---- tokens kernel (lcd_tokens.h) ---------------------------------------------------------------
 constexpr int kTokenBlock = 16;      // tokens per block of the tokens kernel (the columns of one matrix instruction)
 constexpr int kMaxTokenBlocks = 2;   // blocks it holds in registers: up to 32 tokens

@@ -51,7 +51,7 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemm_narrow_kernel(const uint32_t
     constexpr uint32_t ROW_TABLE = BITS == 2 ? 8 : BITS == 3 ? 16 : 32;
     constexpr int NC = BITS == 2 ? 4 : 8;
     typedef typename NarrowTables<BITS>::type Tables;
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // partial tiles [wave][tile][block][token 16][row 16]
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // partial tiles [wave][tile][block][partial_quad]
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: keeps addresses scalar
@@ -164,12 +164,12 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemm_narrow_kernel(const uint32_t
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int t = 0; t < TB; ++t) *reinterpret_cast<float4v *>(&part[(r * TB + t) * 256 + j * 16 + 4 * q]) = acc[r][t];   // lane (q, j): rows 4q..4q+3 of token j
+            for (int t = 0; t < TB; ++t) *reinterpret_cast<float4v *>(&part[(r * TB + t) * 256 + partial_quad(r, q, j)]) = acc[r][t];   // lane (q, j): rows 4q..4q+3 of token j
         __syncthreads();
         const int quads = n * 4;                 // row quads of one token
         for (int e = threadIdx.x; e < quads * M; e += kBW * 64) {
             const int m = e / quads, rest = e - m * quads, r = rest >> 2, rq = rest & 3;
-            const float *src = reinterpret_cast<const float *>(smem) + (r * TB + (m >> 4)) * 256 + (m & 15) * 16 + 4 * rq;
+            const float *src = reinterpret_cast<const float *>(smem) + (r * TB + (m >> 4)) * 256 + partial_quad(r, rq, m & 15);
             float4v sum = *reinterpret_cast<const float4v *>(src);
 #pragma unroll
             for (int w = 1; w < kBW; ++w) sum += *reinterpret_cast<const float4v *>(src + w * (R * TB * 256));

@@ -246,9 +246,9 @@ __device__ __forceinline__ void tokens_workgroup(const uint32_t t0, const uint32
         }
     };
 
-    float *part = reinterpret_cast<float *>(smem + wave * kWaveBytes);    // [tile][block][token 16][row 16]
+    float *part = reinterpret_cast<float *>(smem + wave * kWaveBytes);    // [tile][block][partial_quad]
     auto put_tile = [&](int slot, int b, float4v v) __attribute__((always_inline)) {
-        *reinterpret_cast<float4v *>(&part[(slot * TB + b) * 256 + j * 16 + 4 * q]) = v;   // lane (q, j): rows 4q..4q+3 of token j
+        *reinterpret_cast<float4v *>(&part[(slot * TB + b) * 256 + partial_quad(slot, q, j)]) = v;   // lane (q, j): rows 4q..4q+3 of token j
     };
     // the partial tiles of row tiles [first, end), in LDS from every wave's piece on: sum over the waves in order, one rounding, store
     auto store_tiles = [&](int first, int end) __attribute__((always_inline)) {
@@ -256,7 +256,7 @@ __device__ __forceinline__ void tokens_workgroup(const uint32_t t0, const uint32
         const int quads = (end - first) * 4;                 // row quads of one token
         for (int e = threadIdx.x; e < quads * M; e += WAVES * 64) {
             const int m = e / quads, rest = e - m * quads, r = rest >> 2, rq = rest & 3;
-            const float *src = reinterpret_cast<const float *>(smem) + (r * TB + (m >> 4)) * 256 + (m & 15) * 16 + 4 * rq;
+            const float *src = reinterpret_cast<const float *>(smem) + (r * TB + (m >> 4)) * 256 + partial_quad(r, rq, m & 15);
             auto pair_sum = [&](int w) __attribute__((always_inline)) {
                 float4v v = *reinterpret_cast<const float4v *>(src + w * (kWaveBytes / 4));
                 if (SETS == 1) v += *reinterpret_cast<const float4v *>(src + (w + kBW) * (kWaveBytes / 4));
