@@ -15,7 +15,7 @@ namespace lcd {
 // and leaves the result in the workspace, as fp16 numbers in the order of the matrix operands ([chunk][step 8][quarter 4]
 // [token][8 columns, slots 0,4,1,5,2,6,3,7], so that the tokens kernel loads its B operands as they are: no smoothing, no
 // turn through LDS): the INT8 codes of Eq. 10 or the smoothed activations x/s, where the saving exceeds the extra launch.
-// One thread takes 8 columns of a few tokens: the divisor-only part of the division is shared by them.
+// One thread takes 8 columns of one token, or of four that share the divisor-only part of the division.
 struct TransformItem {
     const uint16_t *x;
     const float *s;
@@ -27,9 +27,14 @@ struct TransformBatch {
     TransformItem p[kMaxGroup];
 };
 constexpr int kQuantThreads = 64;
-constexpr int kQuantTokens = 4;
+// Four tokens per thread only where one per thread is more than two waves per compute unit (kQuantWaves): the launch is a chain of
+// latencies, which one token makes shorter.  A product of 8192 rows, 3 bits, behind it, four / one, us: 17 tokens, K = 2048 6.5 / 6.4 (INT8
+// codes 6.7 / 6.3), 4096 8.8 / 8.5 (9.1 / 8.8), 11008 16.0 / 15.7 (16.3 / 15.8); 40 tokens, 4096 9.9 / 9.9 (10.4 / 9.9), 11008 20.0 / 20.4
+// (20.4 / 20.4); 64 tokens, 4096 10.4 / 10.3 (10.9 / 10.3), 11008 24.7 / 25.2 (25.1 / 25.3); 80 tokens, 4096 12.3 / 12.6 (12.7 / 12.6).
+constexpr int kQuantTokens = 4, kQuantWaves = 512;
 constexpr long long kAheadCodes = 50000, kAheadSmoothed = 300000;   // activations per workgroup beyond which they are transformed ahead
 
+template <int TOKENS>
 __device__ __forceinline__ void transform_columns(const TransformItem &it, int M)
 {
     const int k0 = ((int)blockIdx.x * kQuantThreads + (int)threadIdx.x) * 8;
@@ -45,14 +50,14 @@ __device__ __forceinline__ void transform_columns(const TransformItem &it, int M
     }
     // position of these 8 columns in operand order: chunk, then step g = (k % 64) / 8, then (k % 256) / 64
     const int group = (k0 / kTileCols) * 32 + ((k0 % 64) / 8) * 4 + (k0 % kTileCols) / 64;
-    // blockIdx.z: a group of kQuantTokens tokens (short dependent chains, all loads in flight together)
-    const int m0 = (int)blockIdx.z * kQuantTokens;
-    uint4v v[kQuantTokens];
+    // blockIdx.z: a group of tokens (short dependent chains, all loads in flight together)
+    const int m0 = (int)blockIdx.z * TOKENS;
+    uint4v v[TOKENS];
 #pragma unroll
-    for (int i = 0; i < kQuantTokens; ++i)
+    for (int i = 0; i < TOKENS; ++i)
         if (m0 + i < M) v[i] = *reinterpret_cast<const uint4v *>(it.x + (size_t)(m0 + i) * it.K + k0);
 #pragma unroll
-    for (int i = 0; i < kQuantTokens; ++i) {
+    for (int i = 0; i < TOKENS; ++i) {
         if (m0 + i < M) {
             // register i of the result: columns i, 4 + i
             uint4v o;
@@ -72,13 +77,15 @@ __device__ __forceinline__ void transform_columns(const TransformItem &it, int M
     }
 }
 
-__global__ __launch_bounds__(kQuantThreads) void transform_kernel(const TransformBatch batch, int M) { transform_columns(batch.p[blockIdx.y], M); }
+template <int TOKENS>
+__global__ __launch_bounds__(kQuantThreads) void transform_kernel(const TransformBatch batch, int M) { transform_columns<TOKENS>(batch.p[blockIdx.y], M); }
 
 // One input, the usual case: its arguments are in scalar registers when a wave starts, and the argument segment is 40 bytes
 // (4096 x 4096, 3 bits: 20 tokens 9.0 -> 8.6 us, 48 tokens 10.5 -> 10.2).
+template <int TOKENS>
 __global__ __launch_bounds__(kQuantThreads) void transform_one_kernel(const uint16_t *x, const float *s, uint16_t *codes, int K, float s_q, int M)
 {
-    transform_columns(TransformItem{x, s, codes, K, s_q}, M);
+    transform_columns<TOKENS>(TransformItem{x, s, codes, K, s_q}, M);
 }
 
 // Which kernel takes layers of a width.
@@ -152,8 +159,10 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
         const int per_block = kQuantThreads * 8;
         TransformItem &one = qb.p[0];
         void *args[] = {&qb, &M}, *one_args[] = {&one.x, &one.s, &one.codes, &one.K, &one.s_q, &M};
-        const void *fn = distinct == 1 ? (const void *)transform_one_kernel : (const void *)transform_kernel;
-        if (hipError_t e = hipLaunchKernel(fn, dim3((max_k + per_block - 1) / per_block, distinct, (M + kQuantTokens - 1) / kQuantTokens),
+        const int columns = (max_k + per_block - 1) / per_block, tokens = columns * distinct * M <= kQuantWaves ? 1 : kQuantTokens;
+        const void *fn = distinct == 1 ? (tokens == 1 ? (const void *)transform_one_kernel<1> : (const void *)transform_one_kernel<kQuantTokens>)
+                                       : (tokens == 1 ? (const void *)transform_kernel<1> : (const void *)transform_kernel<kQuantTokens>);
+        if (hipError_t e = hipLaunchKernel(fn, dim3(columns, distinct, (M + tokens - 1) / tokens),
                                            dim3(kQuantThreads), distinct == 1 ? one_args : args, 0, stream)) return (int)e;
     }
     for (int i = 0; i < count; ++i) {

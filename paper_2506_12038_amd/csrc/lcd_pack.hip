@@ -174,27 +174,31 @@ __global__ void __launch_bounds__(256) build_lut_kernel(const uint16_t *__restri
 //   [chunk k/256][token block m/32][half (k%256)/128][step g=(k%64)/8][(k%128)/64][m%32][8 slots],
 // inside a group of 8 the slot order 0,4,1,5,2,6,3,7 that the register dequantiser produces;
 // tokens padded with zeros up to Mpad (a multiple of 128).
-// One workgroup per (chunk, token block): 32 tokens x 256 columns = 16 KiB in, 16 KiB out, both
-// contiguous per row / per block.  Rows are read coalesced (32 threads per 512-byte row), each
-// thread smooths 8 values, and the tile is turned into operand order through LDS so that the
-// stores are coalesced too (16-byte stores scattered 1 KiB apart ran at a third of the rate).
-constexpr int kSmoothRowBytes = 32 * 16 + 16;   // one [m 32][16 B] row of the tile in LDS, padded
+// One workgroup per (chunk, TOKENS tokens): rows are read coalesced (32 threads per 512-byte row), each thread smooths 8 columns of
+// every eighth token, and the tile is turned into operand order through LDS so that the stores are coalesced too (16-byte stores
+// scattered 1 KiB apart ran at a third of the rate).  Bound: latency with few tokens, HBM with many.  Tiles of 32 tokens leave
+// compute units without one where there are few and make a longer chain, so up to kSmoothSmall of them (two per compute unit) go as tiles
+// of 8.  lcd_lut_gemm, 2 bits, 4096 rows, 32 / 8, us (fp16; INT8 codes): 100 tokens, K = 2048 7.9 / 7.6; 8.3 / 7.8, 4096 10.4 / 10.2; 10.9 / 10.2,
+// 11008 20.8 / 20.3; 20.6 / 20.1; 1000 tokens (512 tiles), 4096 39.7 / 39.2; 37.9 / 37.4; 565 tokens (540), 6912 29.2 / 29.7; 600 tokens (860),
+// 11008 72.7 / 72.9; 70.0 / 69.5; 2048 tokens (2752), 11008 164.3 / 164.5; 153.8 / 153.7.
+constexpr int kSmoothSmall = 512;
 // s_q != 0: the input transformation of Sec. 4.1 (Eq. 10-11) instead -- the activations leave as INT8 codes
 // (integers up to 128 in magnitude, exact as fp16 numbers); the divisor-only part of the division is
-// shared by the thread's four token rows.
+// shared by the thread's token rows.
+template <int TOKENS>
 __device__ __forceinline__ void smooth_tile(const uint16_t *__restrict__ x, const float *__restrict__ s,
-                                            _Float16 *__restrict__ xs, int M, int Mpad, int K, int c, int mb, float s_q)
+                                            _Float16 *__restrict__ xs, int M, int Mpad, int K, float s_q)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t tile[32 * kSmoothRowBytes];
-    const int t = threadIdx.x;
-    // a thread's four groups are the same 8 columns of four token rows: one set of reciprocals
+    constexpr int ROWS = TOKENS / 8, STRIDE = TOKENS * 16 + 16;   // token rows of a thread; one [token][16 B] row of the tile in LDS, padded
+    __shared__ __attribute__((aligned(16))) uint8_t tile[32 * STRIDE];
+    const int t = threadIdx.x, c = (int)blockIdx.x, m0 = (int)blockIdx.y * TOKENS;
     const int kg = t & 31, k = c * kTileCols + 8 * kg;
     const bool quantised = s_q != 0.0f;   // uniform
     // all loads in flight together, no branch between them: a token past the last one reads the last one's row
-    uint4v xin[4];
+    uint4v xin[ROWS];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        xin[u] = stream_load(reinterpret_cast<const uint4v *>(x + (size_t)min(mb * 32 + ((t + 256 * u) >> 5), M - 1) * K + k));   // read once
+    for (int u = 0; u < ROWS; ++u)
+        xin[u] = stream_load(reinterpret_cast<const uint4v *>(x + (size_t)min(m0 + (t >> 5) + 8 * u, M - 1) * K + k));   // read once
     const float4v s0 = *reinterpret_cast<const float4v *>(s + k);
     const float4v s1 = *reinterpret_cast<const float4v *>(s + k + 4);
     float r[8];
@@ -206,12 +210,10 @@ __device__ __forceinline__ void smooth_tile(const uint16_t *__restrict__ x, cons
         dv[e] = make_divisor(se, quantised ? s_q : 1.0f);
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int grp = t + 256 * u;            // input order: 32 groups of 8 columns per token row
-        const int ml = grp >> 5;
-        const int m = mb * 32 + ml;
+    for (int u = 0; u < ROWS; ++u) {
+        const int ml = (t >> 5) + 8 * u;
         uint4v o = {0u, 0u, 0u, 0u};            // register i: columns i, 4 + i
-        if (m < M) {
+        if (m0 + ml < M) {
             const uint4v xv = xin[u];
             if (quantised) {
                 o[0] = quantise_pair<0, 0>(xv[0], dv[0], xv[2], dv[4]);
@@ -227,32 +229,42 @@ __device__ __forceinline__ void smooth_tile(const uint16_t *__restrict__ x, cons
         }
         const int h = kg >> 4, kh = (kg >> 3) & 1, g = kg & 7;
         const int row = (h * 8 + g) * 2 + kh;   // position of this group of 8 columns in operand order
-        *reinterpret_cast<uint4v *>(tile + row * kSmoothRowBytes + ml * 16) = o;
+        *reinterpret_cast<uint4v *>(tile + row * STRIDE + ml * 16) = o;
     }
     __syncthreads();
-    _Float16 *dst = xs + ((size_t)c * (Mpad >> 5) + mb) * (32 * 256);
+    _Float16 *dst = xs + ((size_t)c * (Mpad >> 5) + (m0 >> 5)) * (32 * 256) + (m0 & 31) * 8;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int grp = t + 256 * u;            // output order: [row 32][m 32] groups of 8 halfs
-        const int row = grp >> 5, ml = grp & 31;
-        *reinterpret_cast<half8 *>(dst + (size_t)grp * 8) = *reinterpret_cast<const half8 *>(tile + row * kSmoothRowBytes + ml * 16);
+    for (int u = 0; u < ROWS; ++u) {
+        const int grp = t + 256 * u, row = grp / TOKENS, ml = grp % TOKENS;   // output order: [row 32][token 32] groups of 8 halfs
+        *reinterpret_cast<half8 *>(dst + (row * 32 + ml) * 8) = *reinterpret_cast<const half8 *>(tile + row * STRIDE + ml * 16);
     }
 }
 
 // the activations of several layers in one launch: grid.z = layer, grid.x = the widest layer's chunks
 struct SmoothBatch { SmoothItem p[kMaxGroup]; };
+template <int TOKENS>
 __global__ void __launch_bounds__(256) smooth_group_kernel(const SmoothBatch batch, int M, int Mpad)
 {
     const SmoothItem it = batch.p[blockIdx.z];
     if ((int)blockIdx.x * kTileCols >= it.K) return;   // uniform over the workgroup
-    smooth_tile(it.x, it.s, (_Float16 *)it.xs, M, Mpad, it.K, blockIdx.x, blockIdx.y, it.s_q);
+    smooth_tile<TOKENS>(it.x, it.s, (_Float16 *)it.xs, M, Mpad, it.K, it.s_q);
 }
 
 // One input, the usual case: its arguments are in scalar registers when a wave starts, and the argument segment is 48 bytes
 // (4096 x 4096, 3 bits, 100 tokens 14.2 -> 13.7 us).
+template <int TOKENS>
 __global__ void __launch_bounds__(256) smooth_one_kernel(const uint16_t *x, const float *s, _Float16 *xs, int K, float s_q, int M, int Mpad)
 {
-    smooth_tile(x, s, xs, M, Mpad, K, blockIdx.x, blockIdx.y, s_q);
+    smooth_tile<TOKENS>(x, s, xs, M, Mpad, K, s_q);
+}
+
+template <int TOKENS>
+static void launch_smooth(const SmoothBatch &batch, int count, int widest, int M, int Mpad, hipStream_t stream)
+{
+    const dim3 grid((unsigned)(widest / kTileCols), (unsigned)(Mpad / TOKENS), (unsigned)count), block(256);
+    const SmoothItem &one = batch.p[0];
+    if (count == 1) hipLaunchKernelGGL(smooth_one_kernel<TOKENS>, grid, block, 0, stream, one.x, one.s, (_Float16 *)one.xs, one.K, one.s_q, M, Mpad);
+    else hipLaunchKernelGGL(smooth_group_kernel<TOKENS>, grid, block, 0, stream, batch, M, Mpad);
 }
 
 int launch_smooth_group(const SmoothItem *items, int count, int M, int Mpad, void *stream)
@@ -260,9 +272,9 @@ int launch_smooth_group(const SmoothItem *items, int count, int M, int Mpad, voi
     SmoothBatch batch{};
     int widest = 0;
     for (int i = 0; i < count; ++i) { batch.p[i] = items[i]; widest = items[i].K > widest ? items[i].K : widest; }
-    const dim3 grid((unsigned)(widest / kTileCols), (unsigned)(Mpad / 32), (unsigned)count), block(256);
-    if (count == 1) hipLaunchKernelGGL(smooth_one_kernel, grid, block, 0, (hipStream_t)stream, items[0].x, items[0].s, (_Float16 *)items[0].xs, items[0].K, items[0].s_q, M, Mpad);
-    else hipLaunchKernelGGL(smooth_group_kernel, grid, block, 0, (hipStream_t)stream, batch, M, Mpad);
+    const long long tiles = (long long)(widest / kTileCols) * (Mpad / 32) * count;
+    if (tiles <= kSmoothSmall) launch_smooth<8>(batch, count, widest, M, Mpad, (hipStream_t)stream);
+    else launch_smooth<32>(batch, count, widest, M, Mpad, (hipStream_t)stream);
     return (int)hipGetLastError();
 }
 

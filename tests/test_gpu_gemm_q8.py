@@ -80,6 +80,25 @@ def test_activations_transformed_in_and_ahead_of_the_product(bits, M, N, K, q8):
         assert_parity(y.cpu().numpy(), oracle.lut_matmul(layer["codebook"], layer["idx"], layer["x"], layer["s"], bits), TOL)
 
 
+@pytest.mark.parametrize("q8", [True, False])
+@pytest.mark.parametrize("bits,M,N,K", [(2, 64, 4112, 4096), (2, 65, 6144, 4096), (4, 17, 4112, 8192), (3, 33, 4112, 7936), (2, 97, 32, 768), (3, 135, 48, 512)])
+def test_transformation_of_few_tokens_per_thread(bits, M, N, K, q8):
+    # ahead of the narrow kernel: on the line between one and four tokens per thread (512 waves; a last group of one token, a last
+    # workgroup of which half is past K); ahead of the split kernel: groups of 8 tokens of which the last is ragged or padding
+    layer = synth.make_layer(3, 0, N, K, bits, M, seed_offset=N + K + M + 7)
+    packed = lcd.lcd_pack_indices(to_dev(layer["idx"]), bits)
+    lut = lcd.lcd_build_lut(to_dev(layer["codebook"]), bits)
+    rows = np.unique(np.linspace(0, N - 1, 64).astype(int))          # sampled rows, every token
+    args = (layer["codebook"][rows], layer["idx"][rows], layer["x"], layer["s"])
+    if q8:
+        s_q = _step(layer)
+        y = lcd.lcd_lut_gemm_q8(packed, lut, to_dev(layer["x"]), to_dev(layer["s"]), s_q, N, bits)
+        assert_parity(y.cpu().numpy()[:, rows], oracle.quantised_lut_matmul(*args, s_q, bits), Q8_TOL)
+    else:
+        y = lcd.lcd_lut_gemm(packed, lut, to_dev(layer["x"]), to_dev(layer["s"]), N, bits)
+        assert_parity(y.cpu().numpy()[:, rows], oracle.lut_matmul(*args, bits), TOL)
+
+
 def test_gemm_q8_full_width_2048_tokens_sampled():
     # M = 2048 on a 7B-shaped layer: every row for sampled tokens, every token for sampled rows
     import torch
