@@ -32,7 +32,7 @@ constexpr int kQuantThreads = 64;
 // codes 6.7 / 6.3), 4096 8.8 / 8.5 (9.1 / 8.8), 11008 16.0 / 15.7 (16.3 / 15.8); 40 tokens, 4096 9.9 / 9.9 (10.4 / 9.9), 11008 20.0 / 20.4
 // (20.4 / 20.4); 64 tokens, 4096 10.4 / 10.3 (10.9 / 10.3), 11008 24.7 / 25.2 (25.1 / 25.3); 80 tokens, 4096 12.3 / 12.6 (12.7 / 12.6).
 constexpr int kQuantTokens = 4, kQuantWaves = 512;
-constexpr long long kAheadCodes = 50000, kAheadSmoothed = 300000;   // activations per workgroup beyond which they are transformed ahead
+constexpr long long kAheadCodes = 50000, kAheadSmoothed = 300000, kAheadTiles = 200000;   // activations per workgroup beyond which they are transformed ahead
 
 template <int TOKENS>
 __device__ __forceinline__ void transform_columns(const TransformItem &it, int M)
@@ -102,21 +102,32 @@ static bool tokens_kernel_takes(int bits, int M, bool all_quantised, bool dense)
 }
 
 // Several tokens: every workgroup transforms its layer's activations once per pass over its row tiles; ahead of the
-// product they are transformed once, at the price of a launch (3.6 us in a graph).  The line lies where that much work is
-// saved, counted in activations per workgroup (tokens x widest K x passes).  Per block, ahead / in the product: INT8 codes, 3 bits,
-// 7B, 4 tokens (16 k to 44 k) 46.9 / 42.1 us, 9 tokens (37 k to 99 k) 48.6 / 49.6, 16 tokens 51.0 / 58.3; 70B MLP, 4 tokens (98 k, 115 k)
-// 81.2 / 91.2.  fp16: 70B MLP, 4 tokens 83.2 / 83.1, 16 tokens (393 k, 459 k) 94.2 / 96.7 with only the wider K ahead.
+// product they are transformed once, at the price of a launch (about 3 us in a graph).  The line lies where that much work is
+// saved, counted in activations per workgroup (tokens x widest K x passes).  In the product / ahead, 2, 3, 4 bits, us a launch:
+//   INT8 codes  4096 x 4096, 12 tokens (49 k) 6.5/6.7 6.8/7.0 7.4/7.5, 16 (66 k) 7.4/7.0 7.6/7.3 8.3/7.7; 4096 x 11008, 5 (55 k) 9.1/9.5 9.8/10.4 11.5/11.7,
+//               8 (88 k) 10.2/9.5 10.8/10.5 12.4/11.9; 28672 x 8192, twice, 9 (74 k) 37.4/31.9 45.0/41.8 64.5/61.1
+//   fp16        4096 x 13824, 16 (221 k) 12.2/12.6 13.5/14.3 15.9/15.9; 8192 x 28672, 8 (229 k) 22.1/22.0 28.2/26.1 36.4/34.0
+// fp16 activations of 9 to 16 tokens: a workgroup of several row tiles has no registers left to load them early beyond K = 4096, so that from about
+// two row tiles of K = 8192, or four of 6656, on they go ahead:
+//               8192 x 8192, 9 tokens 9.8/9.7 11.0/11.1 15.1/13.9, 16 10.8/10.4 12.1/12.0 16.2/14.6; 16384 x 8192, 9 15.3/14.1 18.4/17.8 23.9/22.6;
+//               16384 x 6912, 9 13.3/13.2 16.2/15.9 21.2/20.0, 12288 x 6912, 9 10.4/11.2 12.0/12.6 15.9/16.1, 16384 x 5120, 9 10.8/11.2 12.9/12.7 15.8/16.4;
+//               8192 x 13824, 9 14.2/13.5 16.9/16.1 22.8/20.0, 8 13.2/13.9 16.0/16.6 20.7/20.2; 28672 x 8192, twice, 16 39.6/36.6 47.8/45.8 65.6/64.6
+// Layers of several widths, whose launches the transformation would set apart, stay with the higher line.
 static bool transforms_ahead(const GroupItem *items, int count, int M)
 {
     const int held = tokens_variant(items[0].bits, M, INT_MAX, INT_MAX, false).tiles;   // row tiles a workgroup of the tokens kernel holds
     int widest = 0;
     long long all_tiles = 0;
+    bool mixed = false;
     for (int i = 0; i < count; ++i) {
         widest = std::max(widest, items[i].K);
         all_tiles += items[i].N / kTileRows;
+        mixed = mixed || items[i].bits != items[0].bits;
     }
-    const long long per_pass = (long long)num_cus() * held, passes = (all_tiles + per_pass - 1) / per_pass;
-    return (long long)M * widest * passes > (items[0].act_scale != 0.0f ? kAheadCodes : kAheadSmoothed);
+    const long long cus = num_cus(), per_pass = cus * held, passes = (all_tiles + per_pass - 1) / per_pass, activations = (long long)M * widest * passes;
+    if (items[0].act_scale != 0.0f) return activations > kAheadCodes;
+    if (mixed || M > kTokenBlock || all_tiles <= cus || widest <= 2 * kBW * kTileCols) return activations > kAheadSmoothed;
+    return activations > kAheadTiles || (M > kTokenBlock / 2 && (widest >= 8192 || (widest >= 6656 && all_tiles > 3 * cus)));
 }
 
 // One launch (and transform_kernel's, where it pays) for layers that one kernel takes: of one width, or of several on the tokens kernel.

@@ -423,3 +423,24 @@ def test_grouped_prefill_smallest_and_largest_group(count):
     for p, single in zip(problems, singles):
         assert torch.equal(p[4], single)
 
+
+
+@pytest.mark.parametrize("bits,M,N,K", [(2, 9, 4112, 8192), (4, 16, 4112, 8192), (3, 9, 4112, 7936), (3, 10, 12304, 6656), (2, 16, 12288, 6656), (4, 11, 4096, 8448)])
+def test_gemv_smoothed_in_and_ahead_of_the_product(bits, M, N, K):
+    # either side of the lines for fp16 activations of 9 to 16 tokens (row tiles per compute unit, columns): whole calls against calls
+    # of up to 8 tokens, which smooth inside the kernel, bit for bit (the order of the additions depends on K alone), single and two layers in one launch
+    import torch
+    from paper_2506_12038_amd.binding import GemvGroup
+    layer = synth.make_layer_uniform(N, K, bits, M, seed=N + K + M)
+    packed, lut = lcd.lcd_pack_indices(to_dev(layer["idx"]), bits), lcd.lcd_build_lut(to_dev(layer["codebook"]), bits)
+    x, s = to_dev(layer["x"]), to_dev(layer["s"])
+    x2, half = (x * 0.5).contiguous(), (M + 1) // 2      # (halves: a part of one or two tokens could be the bucket kernel's)
+    parts = lambda a: torch.cat([lcd.lcd_lut_gemv(packed, lut, a[m:m + half].contiguous(), s, N, bits) for m in range(0, M, half)])
+    ref, ref2 = parts(x), parts(x2)
+    y = lcd.lcd_lut_gemv(packed, lut, x, s, N, bits)
+    assert torch.equal(y, ref)
+    outs = [torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2)]
+    GemvGroup([(packed, lut, x, s, outs[0], N), (packed, lut, x2, s, outs[1], N)], bits)()
+    assert torch.equal(outs[0], ref) and torch.equal(outs[1], ref2)
+    rows = np.unique(np.linspace(0, N - 1, 48).astype(int))
+    assert_parity(y.cpu().numpy()[:, rows], oracle.lut_matmul(layer["codebook"][rows], layer["idx"][rows], layer["x"], layer["s"], bits), TOL)
