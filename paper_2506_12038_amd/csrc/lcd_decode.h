@@ -125,7 +125,8 @@ BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int tiles, i
 
 // Partial tiles in LDS (tokens and narrow kernel): where row quad q of token j of a tile stands, in floats; r: the tile's row tile in the pass.
 // 16 lanes that write (one q, all j) and 16 that read (the quads of one token, row tile after row tile) each cover all banks; in
-// plain [token][row] order both met in a quarter of them.  PLACEHOLDER
+// plain [token][row] order both met in a quarter of them.  7B block, 3 bits, 40 tokens 58.9 -> 58.1 us; blocks of mixed widths, six tokens
+// 214.5 -> 211.7 (four blocks).
 __device__ __forceinline__ int partial_quad(int r, int q, int j) { return 4 * ((4 * j + (q ^ (j >> 2))) ^ ((r & 3) << 2)); }
 
 // ---- tokens kernel (lcd_tokens.h) ---------------------------------------------------------------
