@@ -177,7 +177,7 @@ lcd_status lcd_lut_gemv_noalloc(const void *packed, const void *lut, const uint1
  * with s_q > 0 the (per-layer) activation quantisation step.  Every step of the quantiser is
  * IEEE binary32 (the product s[k]*s_q, the correctly rounded quotient, the rounding), so the
  * codes are reproducible bit for bit on a CPU; the sum is fp32 (exact on the integer bucket
- * sums), one rounding to fp16 at the store.  Precondition on the data: every s[k]*s_q lies in
+ * sums up to K = 2^17), one rounding to fp16 at the store.  Precondition on the data: every s[k]*s_q lies in
  * (2^-64, 2^64) and X is finite (the quotient is computed without range scaling).
  * All other arguments as lcd_lut_gemv (1 <= M <= 16).
  * Routing: as lcd_lut_gemv, except that with 2 bits the codes travel as int8 numbers through the

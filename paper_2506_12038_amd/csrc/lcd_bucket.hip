@@ -67,8 +67,13 @@ struct BucketWords {
     uint2v hi;   // 3 bits: its 64 third bits
 };
 
+// The most columns whose bucket sums are one run of additions: each may lose 2^-24 of the sum, and a wave of 16 makes 2^12 of them here.  (The int32 sums
+// of a wave's codes hold 2^24 columns.)  Wider layers take the kernels that end a wave's run (WIDE) every kRunCols / W columns and add its
+// sums to a total; layers up to kRunCols get the same bits from both.
+constexpr int kRunCols = 1 << 21;
+
 // R: row tiles of a pass, W: waves.  MT: token slots, NTOK: tokens the launch has (MT = 4 token slots also serve three tokens, which then leave the fourth pass out).
-template <int BITS, int MT, bool I8, int NTOK, int R, int W, class BATCH>
+template <int BITS, int MT, bool I8, int NTOK, int R, int W, bool WIDE, class BATCH>
 __global__ void __launch_bounds__(W * 64, 1) gemv_bucket_kernel(
     const uint32_t t0, const uint32_t t1, const uint32_t t2, const uint32_t t3, const uint32_t t4, const uint32_t t5, const uint32_t t6,
     const uint32_t t7, const uint16_t *head_x, const float *head_s, const uint32_t head_word, const BATCH batch)
@@ -239,6 +244,20 @@ __global__ void __launch_bounds__(W * 64, 1) gemv_bucket_kernel(
     Sums acc[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = Sums{{0.f, 0.f, 0.f, 0.f}, {0, 0, 0, 0}};
+    auto value_of = [&](const Sums &a) __attribute__((always_inline)) {
+        float4v v;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if constexpr (!I8) v[u] = a.f[u];
+            else if constexpr (BITS == 2) v[u] = (float)a.i[u];   // (integers: exact up to 2^24)
+            else v[u] = (float)a.i[u] + a.f[u];                   // columns 0..3 and 4..7: the other one is zero
+        }
+        return v;
+    };
+    float4v total[WIDE ? R : 1];
+    int run = 0;                     // WIDE: chunks of the present run
+#pragma unroll
+    for (int r = 0; r < (WIDE ? R : 1); ++r) total[r] = float4v{0.f, 0.f, 0.f, 0.f};
     asm volatile("" : "+s"(pi) : : "memory");   // what is needed last is asked for last
     uint16_t *const y = batch.p[pi].y;
     const float out_scale = I8 ? act_scale : 1.0f;
@@ -295,24 +314,29 @@ __global__ void __launch_bounds__(W * 64, 1) gemv_bucket_kernel(
         }
         if constexpr (!TAIL) advance();
         c += W;
+        if constexpr (WIDE) {
+            if (c >= kc || ++run == kRunCols / kTileCols / W) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    total[r] += value_of(acc[r]);
+                    acc[r] = Sums{{0.f, 0.f, 0.f, 0.f}, {0, 0, 0, 0}};
+                }
+                run = 0;
+            }
+        }
         if (c < kc) return;
         c = wave;
         // ---- all of K: the bucket sums to LDS
         if (j < NC) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                float4v v;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if constexpr (!I8) v[u] = acc[r].f[u];
-                    else if constexpr (BITS == 2) v[u] = (float)acc[r].i[u];   // (integers: exact)
-                    else v[u] = (float)acc[r].i[u] + acc[r].f[u];              // columns 0..3 and 4..7: the other one is zero
-                }
-                *reinterpret_cast<float4v *>(&sums[wave * kWaveFloats + (v0 + r - visit) * kTileFloats + (q * NC + j) * 4]) = v;
-            }
+            for (int r = 0; r < R; ++r)
+                *reinterpret_cast<float4v *>(&sums[wave * kWaveFloats + (v0 + r - visit) * kTileFloats + (q * NC + j) * 4]) = WIDE ? total[WIDE ? r : 0] : value_of(acc[r]);
         }
 #pragma unroll
-        for (int r = 0; r < R; ++r) acc[r] = Sums{{0.f, 0.f, 0.f, 0.f}, {0, 0, 0, 0}};
+        for (int r = 0; r < R; ++r) {
+            if constexpr (WIDE) total[r] = float4v{0.f, 0.f, 0.f, 0.f};
+            else acc[r] = Sums{{0.f, 0.f, 0.f, 0.f}, {0, 0, 0, 0}};
+        }
         v0 += R;
         if (v0 >= tb || v0 - visit < kVisit) return;
         store_visit(std::integral_constant<int, 2>{}, visit, v0);
@@ -329,11 +353,14 @@ __global__ void __launch_bounds__(W * 64, 1) gemv_bucket_kernel(
 // single and captured calls agree bit for bit).
 template <int MT, bool I8> constexpr int bucket_waves() { return MT == 1 && !I8 ? 16 : 8; }
 
-template <int BITS, int MT, bool I8, int NTOK, int R>
+template <int BITS, int MT, bool I8, int NTOK, int R, bool WIDE = false>
 static BucketVariant variant_of(int id)
 {
     constexpr int W = bucket_waves<MT, I8>();
-    return BucketVariant{(const void *)gemv_bucket_kernel<BITS, MT, I8, NTOK, R, W, BucketBatch>, (const void *)gemv_bucket_kernel<BITS, MT, I8, NTOK, R, W, SingleBatch>, R, W, bucket_lds_bytes<BITS, MT, R, W>(), id};
+    const void *fn = (const void *)gemv_bucket_kernel<BITS, MT, I8, NTOK, R, W, WIDE, BucketBatch>;
+    const void *single = fn;         // (the group's kernel takes one layer too)
+    if constexpr (!WIDE) single = (const void *)gemv_bucket_kernel<BITS, MT, I8, NTOK, R, W, WIDE, SingleBatch>;
+    return BucketVariant{fn, single, R, W, bucket_lds_bytes<BITS, MT, R, W>(), id};
 }
 
 // The variant for workgroups of up to `tiles` row tiles and kc chunks.  Three row tiles at a time cover the latency of memory; longer passes
@@ -343,6 +370,8 @@ static BucketVariant variant_of(int id)
 template <int BITS, int MT, bool I8, int NTOK, int OPERANDS>
 static BucketVariant pick(int tiles, int kc, int id)
 {
+    // (packed rows of kRunCols columns leave room for 512 row tiles: two for a workgroup)
+    if (kc > kRunCols / kTileCols) return tiles == 1 ? variant_of<BITS, MT, I8, NTOK, 1, true>(9 * id + 7) : variant_of<BITS, MT, I8, NTOK, 2, true>(9 * id + 8);
     constexpr int kSizes[] = {1, 2, 3, 7, 5, 10, 14};
     constexpr int kCount = OPERANDS > 1 ? 7 : BITS == 3 && !I8 ? 3 : 4;
     int best = 0;
@@ -352,7 +381,7 @@ static BucketVariant pick(int tiles, int kc, int id)
         if (i == 0 || cost < least) { best = i; least = cost; }
     }
     if (kc <= bucket_waves<MT, I8>()) best = tiles < 3 ? tiles - 1 : 2;
-    id = 8 * id + best;
+    id = 9 * id + best;
     if constexpr (kCount > 4) {
         if (best == 4) return variant_of<BITS, MT, I8, NTOK, 5>(id);
         if (best == 5) return variant_of<BITS, MT, I8, NTOK, 10>(id);

@@ -118,7 +118,7 @@ struct BucketVariant {
     size_t lds_bytes;
     int id;             // 0 .. kBucketVariants - 1, of the two kernels 2 id and 2 id + 1
 };
-constexpr int kBucketVariants = 64;
+constexpr int kBucketVariants = 72;
 // tokens: 1 (2 and 3 bits), 2 (2 bits), 3 and 4 (2 bits, INT8 codes)
 // tiles: most row tiles of a workgroup; kc: chunks of the widest layer
 BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int tiles, int kc);
