@@ -131,7 +131,7 @@ lcd_status lcd_build_lut(const uint16_t *codebook /*DEVICE*/, int N, int bits,
  * y       DEVICE fp16 [M][N] row-major (written, never read)
  * workspace  DEVICE, >= lcd_workspace_bytes(M,N,K,bits) bytes, contents ignored on entry.
  *
- * lcd_lut_gemv: decode path, 1 <= M <= 16, any K, one kernel launch (two on the route named last).  M = 1 (and M = 2 with
+ * lcd_lut_gemv: decode path, 1 <= M <= 16, any K (activations of 4 GiB and more: as several calls of fewer tokens), one kernel launch (two on the route named last).  M = 1 (and M = 2 with
  *               2 bits): centroid-bucket sums on the sparse matrix core (Sec. 4.2), one sparse
  *               pass per token; otherwise (3 <= M <= 16, M = 2 with 3 bits, every M with 4 bits):
  *               register dequantisation into fp16 MFMA operands with the tokens as the matrix

@@ -359,6 +359,9 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
     return (int)hipGetLastError();
 }
 
+// The kernels address a layer's activations with 32 bits.
+static int tokens_that_fit(int M, int K) { return (int)std::min<long long>(M, ((1ll << 32) - 512) / (2ll * K)); }
+
 // The launches of a group: one for layers of one width.  Layers of several widths that the tokens kernel takes go out together, unless their
 // activations are transformed ahead (two launches already, and long ones); the bucket kernel's width by width.
 int launch_decode_group(const GroupItem *items, int count, int M, int bits, void *workspace, void *stream_, bool dense)
@@ -369,9 +372,23 @@ int launch_decode_group(const GroupItem *items, int count, int M, int bits, void
         all_quantised = all_quantised && items[i].act_scale != 0.0f;
         mixed = mixed || items[i].bits != items[0].bits;
     }
-    if (bits != 0 || !mixed) return launch_decode_layers(items, count, M, workspace, stream, dense);
     GroupItem sub[kMaxGroup];
     int n = 0;
+    // layers of 4 GiB of activations and more: alone (a layer's launches must not depend on its neighbours), some tokens after the other
+    for (int i = 0; i < count; ++i) {
+        const int most = tokens_that_fit(M, items[i].K);
+        if (most == M) { sub[n++] = items[i]; continue; }
+        for (int m = 0; m < M; m += most) {
+            GroupItem part = items[i];
+            part.x += (size_t)m * part.K;
+            part.y += (size_t)m * part.N;
+            if (int e = launch_decode_layers(&part, 1, std::min(most, M - m), workspace, stream, dense)) return e;
+        }
+    }
+    if (n == 0) return 0;
+    if (n < count) return launch_decode_group(sub, n, M, bits, workspace, stream_, dense);
+    if (bits != 0 || !mixed) return launch_decode_layers(items, count, M, workspace, stream, dense);
+    n = 0;
     for (int i = 0; i < count; ++i)
         if (tokens_kernel_takes(items[i].bits, M, all_quantised, dense)) sub[n++] = items[i];
     const bool together = n > 0 && M <= kTokenBlock && !transforms_ahead(sub, n, M);

@@ -66,3 +66,38 @@ def test_bucket_sums_of_equal_activations(bits, M, K):
     codebook[:, 1] = centroid
     y = lcd.lcd_lut_gemv(packed, lcd.lcd_build_lut(codebook, bits), x, s, ROWS, bits, workspace=_workspace(M, K, bits))
     assert_parity(y.cpu().numpy(), x[:, :1].double().cpu().numpy() * K * np.full((1, ROWS), centroid), TOL)
+
+
+@pytest.mark.parametrize("bits,M,quantised", [(2, 16, False), (2, 16, True), (3, 15, False), (4, 16, False)])
+def test_activations_of_four_gibibytes(bits, M, quantised):
+    # 16 tokens of 2^27 columns are 2^32 bytes, one more than the kernels' 32-bit offsets reach (15 tokens fit).  All but some columns
+    # are zero, the first and the last of every token are not.  Single call, and grouped with a layer of ordinary size.
+    import torch
+    from paper_2506_12038_amd.binding import GemvGroup
+    K, g = WIDE, torch.Generator(device="cuda")
+    g.manual_seed(17 * bits + M)
+    idx = torch.randint(0, 1 << bits, (ROWS, K), dtype=torch.uint8, device="cuda", generator=g)
+    columns = torch.randint(0, K, (M, 512), device="cuda", generator=g)
+    columns[:, 0], columns[:, 1] = 0, K - 1
+    s_q = 2.0 ** -5
+    values = torch.randint(-100, 100, (M, 512), device="cuda", generator=g).half() * s_q        # (the codes themselves, s = 1)
+    x = torch.zeros((M, K), dtype=torch.float16, device="cuda").scatter_(1, columns, values)
+    s = torch.ones(K, dtype=torch.float32, device="cuda")
+    codebook = (torch.randn((ROWS, 1 << bits), device="cuda", generator=g) * 0.02).half()
+    weights = torch.stack([codebook.double().gather(1, idx[:, c].long()) for c in columns])      # [M, rows, 512]
+    Y = (weights * x.gather(1, columns).double()[:, None, :])
+    # (a column drawn twice counts once)
+    first = torch.stack([torch.isin(torch.arange(512, device="cuda"), torch.from_numpy(np.unique(c.cpu().numpy(), return_index=True)[1]).cuda()) for c in columns])
+    Y = (Y * first[:, None, :]).sum(dim=2).cpu().numpy()
+    packed, lut = lcd.lcd_pack_indices(idx, bits), lcd.lcd_build_lut(codebook, bits)
+    del idx, weights
+    ws = _workspace(M, K, bits)
+    call = (lambda a, n: lcd.lcd_lut_gemv_q8(*a, s_q, n, bits, workspace=ws)) if quantised else (lambda a, n: lcd.lcd_lut_gemv(*a, n, bits, workspace=ws))
+    y = call((packed, lut, x, s), ROWS)
+    assert_parity(y.cpu().numpy(), Y, TOL)
+    layer = synth.make_layer(1, 0, 48, 1280, bits, M)
+    usual = (lcd.lcd_pack_indices(to_dev(layer["idx"]), bits), lcd.lcd_build_lut(to_dev(layer["codebook"]), bits), to_dev(layer["x"]), to_dev(layer["s"]))
+    outs = [torch.full((M, n), float("nan"), dtype=torch.float16, device="cuda") for n in (48, ROWS)]
+    problems = [(*usual, outs[0], 48), (packed, lut, x, s, outs[1], ROWS)]
+    GemvGroup(problems, bits, s_q=[s_q, s_q] if quantised else None)()
+    assert torch.equal(outs[0], call(usual, 48)) and torch.equal(outs[1], y)
