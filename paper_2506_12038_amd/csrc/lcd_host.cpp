@@ -324,12 +324,14 @@ lcd_status lcd_lut_gemv_grouped_mixed(const lcd_gemv_problem *problems, const in
     if (M > 16) return fail(LCD_ERR_BAD_M, "grouped gemv: M=%d > 16", M);
     size_t codes[5] = {};    // scratch of the layers of a width
     GroupItem items[kMaxGroup];
-    for (int i = 0; i < count; ++i) {
-        const lcd_gemv_problem &p = problems[i];
-        if (lcd_status st = check_product(p.packed, p.lut, p.x, p.s, p.y, M, p.N, p.K, bits[i], workspace, workspace_bytes)) return st;
-        codes[bits[i]] += decode_codes_bytes(M, p.K);
-        items[i] = GroupItem{p.packed, p.lut, p.x, p.s, p.y, p.N, p.K, 0.0f, bits[i]};
-    }
+    for (int b = 2; b <= 4; ++b)     // (of several faulty layers the first of the smallest width is reported)
+        for (int i = 0; i < count; ++i) {
+            if (bits[i] != b) continue;
+            const lcd_gemv_problem &p = problems[i];
+            if (lcd_status st = check_product(p.packed, p.lut, p.x, p.s, p.y, M, p.N, p.K, b, workspace, workspace_bytes)) return st;
+            codes[b] += decode_codes_bytes(M, p.K);
+            items[i] = GroupItem{p.packed, p.lut, p.x, p.s, p.y, p.N, p.K, 0.0f, b};
+        }
     for (int b = 2; b <= 4; ++b)
         if (workspace_bytes < codes[b]) return fail(LCD_ERR_SIZE, "workspace_bytes=%zu < %zu", workspace_bytes, codes[b]);
     if (int e = launch_decode_group(items, count, M, 0, workspace, stream)) return fail(LCD_ERR_HIP, "grouped gemv launch: %s", hip_error_name(e));

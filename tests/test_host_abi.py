@@ -190,6 +190,11 @@ def test_grouped_entry_point_validates_on_host():
     assert st(lib.lcd_lut_gemv_grouped_mixed(arr, widths, 2, 1, ctypes.c_void_p(a), big, None)) == b"LCD_ERR_BAD_SHAPE"
     arr[0].K = 256
     assert st(lib.lcd_lut_gemv_grouped_mixed(arr, widths, 2, 4, ctypes.c_void_p(a), 256, None)) == b"LCD_ERR_SIZE"
+    # of several faulty layers the first of the smallest width is reported, whatever their order
+    arr[0].x, arr[1].K = 0x1002, 100
+    for first, second, status in ((4, 2, b"LCD_ERR_BAD_SHAPE"), (2, 4, b"LCD_ERR_ALIGN"), (3, 3, b"LCD_ERR_ALIGN")):
+        widths[0], widths[1] = first, second
+        assert st(lib.lcd_lut_gemv_grouped_mixed(arr, widths, 2, 4, ctypes.c_void_p(a), big, None)) == status
 
 
 def test_grouped_prefill_entry_point_validates_on_host():
