@@ -38,6 +38,7 @@
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "lcd_decode.h"
+#include "lcd_share.h"
 
 namespace lcd {
 
@@ -349,54 +350,40 @@ __global__ void __launch_bounds__(W * 64, 1) gemv_bucket_kernel(
     store_visit(std::integral_constant<int, W>{}, visit, tb);   // (nothing else lives here: registers for all reads at once)
 }
 
-// Waves: 16 where the registers allow it, with the same number for every R (an output is the sum of the waves' sums: grouped,
-// single and captured calls agree bit for bit).
-template <int MT, bool I8> constexpr int bucket_waves() { return MT == 1 && !I8 ? 16 : 8; }
-
 template <int BITS, int MT, bool I8, int NTOK, int R, bool WIDE = false>
 static BucketVariant variant_of(int id)
 {
-    constexpr int W = bucket_waves<MT, I8>();
+    constexpr int W = bucket_waves(MT, I8);
     const void *fn = (const void *)gemv_bucket_kernel<BITS, MT, I8, NTOK, R, W, WIDE, BucketBatch>;
     const void *single = fn;         // (the group's kernel takes one layer too)
     if constexpr (!WIDE) single = (const void *)gemv_bucket_kernel<BITS, MT, I8, NTOK, R, W, WIDE, SingleBatch>;
     return BucketVariant{fn, single, R, W, bucket_lds_bytes<BITS, MT, R, W>(), id};
 }
 
-// The variant for workgroups of up to `tiles` row tiles and kc chunks.  Three row tiles at a time cover the latency of memory; longer passes
-// make a step's operands, which cost as much as OPERANDS row tiles, less often (a wave's only chunk: once) -- but a slot without a row
-// tile costs the addresses of its loads.  us, passes of 3 / 7: 2 bits, one token, 1792 row tiles, K = 8192 12.2 / 11.6, 3168, K = 4096 10.8 / 11.0;
-// two tokens 13.9 / 11.9 (INT8 codes, K = 8192); four tokens, 3584, K = 8192, passes of 3 / 6 / 10 / 14: 36.5 / 29.6 / 27.8 / 25.3, 640, K = 5120 6.6 / 6.7 / 7.2 / 8.0.
-template <int BITS, int MT, bool I8, int NTOK, int OPERANDS>
+template <int BITS, int MT, bool I8, int NTOK>
 static BucketVariant pick(int tiles, int kc, int id)
 {
     // (packed rows of kRunCols columns leave room for 512 row tiles: two for a workgroup)
     if (kc > kRunCols / kTileCols) return tiles == 1 ? variant_of<BITS, MT, I8, NTOK, 1, true>(9 * id + 7) : variant_of<BITS, MT, I8, NTOK, 2, true>(9 * id + 8);
-    constexpr int kSizes[] = {1, 2, 3, 7, 5, 10, 14};
-    constexpr int kCount = OPERANDS > 1 ? 7 : BITS == 3 && !I8 ? 3 : 4;
-    int best = 0;
-    long long least = 0;
-    for (int i = 0; i < kCount; ++i) {
-        const long long cost = (long long)((tiles + kSizes[i] - 1) / kSizes[i]) * (kSizes[i] + OPERANDS);
-        if (i == 0 || cost < least) { best = i; least = cost; }
-    }
-    if (kc <= bucket_waves<MT, I8>()) best = tiles < 3 ? tiles - 1 : 2;
+    constexpr BucketRule rule = bucket_rule(BITS, NTOK, I8);
+    const int best = bucket_pass(rule, tiles, kc);
     id = 9 * id + best;
-    if constexpr (kCount > 4) {
-        if (best == 4) return variant_of<BITS, MT, I8, NTOK, 5>(id);
-        if (best == 5) return variant_of<BITS, MT, I8, NTOK, 10>(id);
-        if (best == 6) return variant_of<BITS, MT, I8, NTOK, 14>(id);
+    if constexpr (rule.lengths > 4) {
+        if (best == 4) return variant_of<BITS, MT, I8, NTOK, kBucketPass[4]>(id);
+        if (best == 5) return variant_of<BITS, MT, I8, NTOK, kBucketPass[5]>(id);
+        if (best == 6) return variant_of<BITS, MT, I8, NTOK, kBucketPass[6]>(id);
     }
-    if constexpr (kCount > 3) if (best == 3) return variant_of<BITS, MT, I8, NTOK, 7>(id);
-    return best == 0 ? variant_of<BITS, MT, I8, NTOK, 1>(id) : best == 1 ? variant_of<BITS, MT, I8, NTOK, 2>(id) : variant_of<BITS, MT, I8, NTOK, 3>(id);
+    if constexpr (rule.lengths > 3) if (best == 3) return variant_of<BITS, MT, I8, NTOK, kBucketPass[3]>(id);
+    if (best == 0) return variant_of<BITS, MT, I8, NTOK, kBucketPass[0]>(id);
+    return best == 1 ? variant_of<BITS, MT, I8, NTOK, kBucketPass[1]>(id) : variant_of<BITS, MT, I8, NTOK, kBucketPass[2]>(id);
 }
 
 BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int tiles, int kc)
 {
-    if (bits == 3) return int8_codes ? pick<3, 1, true, 1, 1>(tiles, kc, 0) : pick<3, 1, false, 1, 1>(tiles, kc, 1);
-    if (!int8_codes) return tokens == 1 ? pick<2, 1, false, 1, 1>(tiles, kc, 2) : pick<2, 2, false, 2, 2>(tiles, kc, 3);
-    if (tokens <= 2) return tokens == 1 ? pick<2, 1, true, 1, 1>(tiles, kc, 4) : pick<2, 2, true, 2, 1>(tiles, kc, 5);
-    return tokens == 3 ? pick<2, 4, true, 3, 4>(tiles, kc, 6) : pick<2, 4, true, 4, 4>(tiles, kc, 7);
+    if (bits == 3) return int8_codes ? pick<3, 1, true, 1>(tiles, kc, 0) : pick<3, 1, false, 1>(tiles, kc, 1);
+    if (!int8_codes) return tokens == 1 ? pick<2, 1, false, 1>(tiles, kc, 2) : pick<2, 2, false, 2>(tiles, kc, 3);
+    if (tokens <= 2) return tokens == 1 ? pick<2, 1, true, 1>(tiles, kc, 4) : pick<2, 2, true, 2>(tiles, kc, 5);
+    return tokens == 3 ? pick<2, 4, true, 3>(tiles, kc, 6) : pick<2, 4, true, 4>(tiles, kc, 7);
 }
 
 }  // namespace lcd

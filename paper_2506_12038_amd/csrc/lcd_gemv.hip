@@ -6,6 +6,7 @@
 #include <climits>
 #include "lcd_decode.h"
 #include "lcd_launch.h"
+#include "lcd_share.h"
 
 namespace lcd {
 
@@ -145,7 +146,6 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
         width[i] = items[i].bits;
     }
     const bool tokens_path = narrow || tokens_kernel_takes(bits, M, all_quantised, dense);
-    const int blocks = (M + kTokenBlock - 1) / kTokenBlock;
     const int held = narrow ? narrow_variant(bits, M, INT_MAX).tiles : tokens_path ? tokens_variant(bits, M, INT_MAX, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds
     const uint16_t *codes[kMaxGroup] = {};
     int widest = 0;
@@ -185,89 +185,19 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
         p.act_scale = items[i].act_scale;
         tiles += p.nt;
     }
-    // Workgroups per layer.  A layer's time is that of its slowest workgroup: a fixed start-up, then one round of chunks (one for
-    // each wave) after the other.  The split minimises the time of the slowest layer.
+    // workgroups per layer
     int grid = num_cus();
     if (grid > tiles) grid = tiles;
     if (grid < count) grid = count;
     // 2 bits on the sparse matrix core with quantised activations: the codes go in as int8 numbers
     const bool int8_codes = !tokens_path && bits != 4 && all_quantised;   // (3 bits: one token, the plain pass only)
     const bool staged_ahead = tokens_path && codes[0] != nullptr;
-    // the tokens kernel, times in us of a workgroup: a "round" is one chunk for each of its 8 waves.  Fitted to single layers of
-    // 4096 x t rows (t row tiles per workgroup), K = 4096 and 11008, 4 and 16 tokens; 2 bits, 16 tokens: K = 4096 t = 8, 10, 12
-    // 15.0, 17.1, 19.0 us, 13 in two passes 25.4; K = 11008 t = 4, 5, 6 20.1, 23.0, 26.2.
-    const double round_stage = staged_ahead ? 0.1 * blocks : 0.08 + 0.035 * M;
-    // the bucket kernel, in us: a round is one chunk for each of its 16 or 8 waves, of which each costs its operands once per pass.
-    const double bucket_tile = bits == 3 ? (int8_codes ? 0.45 : 1.05) : M > 1 ? 0.35 : int8_codes ? 0.3 : 0.6;
-    const double bucket_chunk = M == 1 ? 0.1 : int8_codes && M > 2 ? 0.15 * M : 0.2;
-    auto layer_time = [&](int i, int n) {
-        const int kc = batch.p[i].kc, t = (batch.p[i].nt + n - 1) / n;
-        if (tokens_path) {
-            const int rounds = (kc + kBW - 1) / kBW, passes = (t + held - 1) / held;
-            const double round_tile = (width[i] == 2 ? 0.43 : width[i] == 3 ? 0.55 : 0.89) + 0.06 * blocks, pass = width[i] == 2 ? 3.7 : 5.0;
-            return passes * (pass + rounds * round_stage) + rounds * t * round_tile;
-        }
-        const BucketVariant bv = bucket_variant(bits, M, int8_codes, t, kc);
-        const int rounds = (kc + bv.waves - 1) / bv.waves, passes = (t + bv.tiles - 1) / bv.tiles;
-        return 2.8 + rounds * (bucket_tile * t + bucket_chunk * passes);
-    };
-    auto split = [&](int *nwg) {
-        if (count == 1) { nwg[0] = grid; return; }
-        int like[kMaxGroup];                   // the first layer of the same shape: its answer is this one's
-        for (int i = 0; i < count; ++i)
-            for (like[i] = 0; batch.p[like[i]].nt != batch.p[i].nt || batch.p[like[i]].kc != batch.p[i].kc || width[like[i]] != width[i];) ++like[i];
-        // smallest number of workgroups with which layer i takes at most T (0: not even one per tile does)
-        auto need = [&](int i, double T) {
-            const int nt = batch.p[i].nt;
-            if (layer_time(i, nt) > T) return 0;
-            int lo = 1, hi = nt;               // layer_time never grows with n
-            while (lo < hi) {
-                const int mid = (lo + hi) / 2;
-                if (layer_time(i, mid) <= T) hi = mid; else lo = mid + 1;
-            }
-            return lo;
-        };
-        auto fits = [&](double T, int *out) {
-            int sum = 0;
-            for (int i = 0; i < count; ++i) {
-                const int n = like[i] < i ? out[like[i]] : need(i, T);
-                if (n == 0) return false;
-                out[i] = n;
-                sum += n;
-            }
-            return sum <= grid;
-        };
-        // the smallest common finish time the grid can reach: bisection over T between "one workgroup per
-        // tile everywhere" and "one workgroup per layer" (the host guarantees grid >= count)
-        double t_lo = 0.0, t_hi = 0.0;
-        for (int i = 0; i < count; ++i) {
-            t_lo = std::max(t_lo, layer_time(i, batch.p[i].nt));
-            t_hi = std::max(t_hi, layer_time(i, 1));
-        }
-        int trial[kMaxGroup];
-        if (fits(t_lo, trial)) t_hi = t_lo;
-        for (int it = 0; it < 24 && t_hi - t_lo > 0.02; ++it) {
-            const double mid = 0.5 * (t_lo + t_hi);
-            if (fits(mid, trial)) t_hi = mid; else t_lo = mid;
-        }
-        fits(t_hi, nwg);
-        int used = 0;
-        for (int i = 0; i < count; ++i) used += nwg[i];
-        while (used < grid) {                  // spare workgroups: one by one to the layer that is slowest then
-            int best = -1;
-            double best_time = 0.0;
-            for (int i = 0; i < count; ++i) {
-                if (nwg[i] >= batch.p[i].nt) continue;
-                const double t = layer_time(i, nwg[i]);
-                if (t > best_time) { best_time = t; best = i; }
-            }
-            if (best < 0) break;
-            ++nwg[best];
-            ++used;
-        }
-    };
-    // The split depends on the shapes only: the last few are kept (a block repeats a few groups; working one out takes 2 us of host time, 8 for seven layers).
-    struct SplitMemo { int count, M, grid, ahead, route, nt[kMaxGroup], kc[kMaxGroup], width[kMaxGroup], nwg[kMaxGroup]; };
+    static_assert(kBW == 8, "lcd_share.h counts rounds of 8 chunks");
+    const DecodeCost cost = tokens_path ? tokens_cost(held, M, staged_ahead) : bucket_cost(bits, M, int8_codes);
+    LayerShape shape[kMaxGroup];
+    for (int i = 0; i < count; ++i) shape[i] = LayerShape{batch.p[i].nt, batch.p[i].kc, items[i].bits};
+    // The split depends on the shapes only: the last few are kept (a block repeats a few groups; working one out takes 0.2 us of host time, 2 to 4 where the layers differ).
+    struct SplitMemo { int count, M, grid, ahead, route, nwg[kMaxGroup]; LayerShape shape[kMaxGroup]; };
     constexpr int kMemos = 8;
     static thread_local SplitMemo memos[kMemos] = {};
     static thread_local int oldest = 0;
@@ -277,24 +207,26 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
     for (int e = 0; e < kMemos && !known; ++e) {
         const SplitMemo &m = memos[e];
         bool same = m.count == count && m.M == M && m.grid == grid && m.ahead == (int)staged_ahead && m.route == route;
-        for (int i = 0; same && i < count; ++i) same = m.nt[i] == batch.p[i].nt && m.kc[i] == batch.p[i].kc && m.width[i] == width[i];
+        for (int i = 0; same && i < count; ++i) same = m.shape[i] == shape[i];
         if (same) known = &m;
     }
     if (known) {
         for (int i = 0; i < count; ++i) nwg[i] = known->nwg[i];
+    } else if (count == 1) {
+        nwg[0] = grid;
     } else {
-        split(nwg);
+        share_workgroups(cost, shape, count, grid, nwg);
         SplitMemo &m = memos[oldest];
         oldest = (oldest + 1) % kMemos;
         m.count = count; m.M = M; m.grid = grid; m.ahead = (int)staged_ahead; m.route = route;
-        for (int i = 0; i < count; ++i) { m.nt[i] = batch.p[i].nt; m.kc[i] = batch.p[i].kc; m.width[i] = width[i]; m.nwg[i] = nwg[i]; }
+        for (int i = 0; i < count; ++i) { m.shape[i] = shape[i]; m.nwg[i] = nwg[i]; }
     }
     // Workgroups are dispatched in the order of their ids, the last of a full grid almost 1 us after the
     // first: the layers whose workgroups have the most to do take the lowest ids (of several widths: the widest first, which the kernel asks for).
     if (count > 1) {
         int order[kMaxGroup];
         double t[kMaxGroup];
-        for (int i = 0; i < count; ++i) { order[i] = i; t[i] = layer_time(i, nwg[i]); }
+        for (int i = 0; i < count; ++i) { order[i] = i; t[i] = cost.time(shape[i].bits, shape[i].kc, round_up_div(shape[i].tiles, nwg[i])); }
         std::stable_sort(order, order + count, [&](int a, int b) { return width[a] != width[b] ? width[a] > width[b] : t[a] > t[b]; });
         BucketProblem sorted_p[kMaxGroup];
         int sorted_n[kMaxGroup], sorted_w[kMaxGroup];

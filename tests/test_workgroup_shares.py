@@ -1,0 +1,93 @@
+"""Workgroups of a grouped decode launch (csrc/lcd_share.h, plain host code): the slowest layer, by the launcher's own cost, is as fast as any
+split of the grid makes it, found here by trying every number of workgroups for every layer."""
+import shutil
+import subprocess
+from pathlib import Path
+
+import pytest
+
+ROOT = Path(__file__).resolve().parent.parent
+
+DRIVER = r"""
+#include <cstdio>
+#include <vector>
+#include "lcd_share.h"
+using namespace lcd;
+
+static double slowest(const DecodeCost &c, const std::vector<LayerShape> &g, const int *n)
+{
+    double t = 0.0;
+    for (size_t i = 0; i < g.size(); ++i) t = std::max(t, c.time(g[i].bits, g[i].kc, round_up_div(g[i].tiles, n[i])));
+    return t;
+}
+// the smallest T for which the layers' smallest numbers of workgroups fit the grid, every number tried
+static double best(const DecodeCost &c, const std::vector<LayerShape> &g, int grid)
+{
+    std::vector<double> times;
+    for (const LayerShape &l : g)
+        for (int n = 1; n <= l.tiles && n <= grid; ++n) times.push_back(c.time(l.bits, l.kc, round_up_div(l.tiles, n)));
+    std::sort(times.begin(), times.end());
+    for (double T : times) {
+        int sum = 0;
+        for (const LayerShape &l : g) {
+            int n = 1;
+            while (n <= l.tiles && n <= grid && c.time(l.bits, l.kc, round_up_div(l.tiles, n)) > T) ++n;
+            sum += n <= l.tiles ? n : grid + 1;
+        }
+        if (sum <= grid) return T;
+    }
+    return -1.0;
+}
+static int check(const char *name, const DecodeCost &c, const std::vector<LayerShape> &g, int cus)
+{
+    int tiles = 0, n[kMaxGroup], used = 0;
+    for (const LayerShape &l : g) tiles += l.tiles;
+    const int grid = std::max((int)g.size(), std::min(cus, tiles));
+    share_workgroups(c, g.data(), (int)g.size(), grid, n);
+    bool ok = true;
+    for (size_t i = 0; i < g.size(); ++i) { used += n[i]; ok = ok && n[i] >= 1 && n[i] <= g[i].tiles; }
+    const double got = slowest(c, g, n), want = best(c, g, grid);
+    ok = ok && used <= grid && got <= want + 0.02 + 1e-9;     // (the bisection stops there)
+    if (!ok) std::printf("%s: grid %d, used %d, %.3f us against %.3f\n", name, grid, used, got, want);
+    return ok ? 0 : 1;
+}
+
+int main()
+{
+    int bad = 0;
+    unsigned seed = 1u;
+    auto rnd = [&](int n) { seed = seed * 1664525u + 1013904223u; return (int)((seed >> 8) % (unsigned)n); };
+    struct { const char *name; DecodeCost c; int bits; } kinds[] = {
+        {"bucket, 3 bits", bucket_cost(3, 1, false), 3}, {"bucket, 3 bits, codes", bucket_cost(3, 1, true), 3}, {"bucket, 2 bits", bucket_cost(2, 1, false), 2},
+        {"bucket, 2 bits, two tokens", bucket_cost(2, 2, false), 2}, {"bucket, 2 bits, two tokens of codes", bucket_cost(2, 2, true), 2},
+        {"bucket, 2 bits, three tokens of codes", bucket_cost(2, 3, true), 2}, {"bucket, 2 bits, four tokens of codes", bucket_cost(2, 4, true), 2},
+        {"tokens, 16", tokens_cost(14, 16, false), 3}, {"tokens, 5, ahead", tokens_cost(14, 5, true), 4}, {"narrow, 40", tokens_cost(6, 40, true), 3}};
+    for (auto &k : kinds) {
+        // row tiles per workgroup around the lengths of the passes: 16 to 22 of them, alone and next to a small layer
+        for (int t = 14; t <= 24; ++t) {
+            bad += check(k.name, k.c, {{128 * t, 17, k.bits}, {128 * t, 17, k.bits}}, 256);
+            bad += check(k.name, k.c, {{200 * t + 3, 43, k.bits}, {56, 17, k.bits}}, 256);
+        }
+        bad += check(k.name, k.c, {{256, 16, k.bits}, {256, 16, k.bits}, {256, 16, k.bits}}, 256);
+        bad += check(k.name, k.c, {{688, 16, k.bits}, {688, 16, k.bits}}, 256);
+        bad += check(k.name, k.c, {{256, 16, k.bits}, {256, 16, k.bits}, {256, 16, k.bits}, {256, 16, k.bits}, {688, 16, k.bits}, {688, 16, k.bits}, {256, 43, k.bits}}, 256);
+        bad += check(k.name, k.c, {{1, 1, k.bits}, {1, 4, k.bits}, {1, 1, k.bits}}, 2);           // fewer compute units than layers
+        for (int r = 0; r < 60; ++r) {
+            std::vector<LayerShape> g(1 + rnd(6));
+            for (LayerShape &l : g) l = r % 3 == 0 && &l != &g[0] ? g[0] : LayerShape{1 + rnd(r % 2 ? 40 : 2000), 1 + rnd(64), k.c.held ? 2 + rnd(3) : k.bits};
+            bad += check(k.name, k.c, g, r % 5 ? 256 : 32);
+        }
+    }
+    std::printf("%d splits worse than the best\n", bad);
+    return bad ? 1 : 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
+def test_shares_are_as_good_as_trying_every_number_of_workgroups(tmp_path):
+    (tmp_path / "shares.cpp").write_text(DRIVER)
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", f"-I{ROOT / 'include'}", f"-I{ROOT / 'paper_2506_12038_amd' / 'csrc'}",
+                           str(tmp_path / "shares.cpp"), "-o", str(tmp_path / "shares")])
+    run = subprocess.run([str(tmp_path / "shares")], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0, run.stdout
