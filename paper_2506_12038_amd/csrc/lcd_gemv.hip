@@ -114,9 +114,11 @@ static bool tokens_kernel_takes(int bits, int M, bool all_quantised, bool dense)
 //               16384 x 6912, 9 13.3/13.2 16.2/15.9 21.2/20.0, 12288 x 6912, 9 10.4/11.2 12.0/12.6 15.9/16.1, 16384 x 5120, 9 10.8/11.2 12.9/12.7 15.8/16.4;
 //               8192 x 13824, 9 14.2/13.5 16.9/16.1 22.8/20.0, 8 13.2/13.9 16.0/16.6 20.7/20.2; 28672 x 8192, twice, 16 39.6/36.6 47.8/45.8 65.6/64.6
 // Layers of several widths, whose launches the transformation would set apart, stay with the higher line.
+// Up to K = 4096 a workgroup makes its activations once whatever its row tiles are, but beyond 14 of them the line is as good as where they would be made again
+// (INT8 codes, 2, 3, 4 bits): four layers of 16384 x 4096, 8 tokens 24.0/24.1 25.8/26.6 36.9/37.2, 12 tokens 23.4/22.9 26.7/27.2 37.6/37.7; five of 16384 x 2048, 13
+// 19.4/19.0 22.5/22.9 30.3/29.9, 16 19.9/19.2 22.8/23.0 30.6/30.1.
 static bool transforms_ahead(const GroupItem *items, int count, int M)
 {
-    const int held = tokens_variant(items[0].bits, M, INT_MAX, INT_MAX, false).tiles;   // row tiles a workgroup of the tokens kernel holds
     int widest = 0;
     long long all_tiles = 0;
     bool mixed = false;
@@ -125,6 +127,7 @@ static bool transforms_ahead(const GroupItem *items, int count, int M)
         all_tiles += items[i].N / kTileRows;
         mixed = mixed || items[i].bits != items[0].bits;
     }
+    const int held = tokens_variant(items[0].bits, M, INT_MAX, INT_MAX, false).tiles;   // row tiles of the longest pass beyond K = 4096
     const long long cus = num_cus(), per_pass = cus * held, passes = (all_tiles + per_pass - 1) / per_pass, activations = (long long)M * widest * passes;
     if (items[0].act_scale != 0.0f) return activations > kAheadCodes;
     if (mixed || M > kTokenBlock || all_tiles <= cus || widest <= 2 * kBW * kTileCols) return activations > kAheadSmoothed;
@@ -146,10 +149,10 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
         width[i] = items[i].bits;
     }
     const bool tokens_path = narrow || tokens_kernel_takes(bits, M, all_quantised, dense);
-    const int held = narrow ? narrow_variant(bits, M, INT_MAX).tiles : tokens_path ? tokens_variant(bits, M, INT_MAX, INT_MAX, false).tiles : 1;   // row tiles a workgroup of the tokens kernel holds
     const uint16_t *codes[kMaxGroup] = {};
     int widest = 0;
     for (int i = 0; i < count; ++i) widest = std::max(widest, items[i].K);
+    const int held = narrow ? narrow_variant(bits, M, INT_MAX).tiles : tokens_path ? tokens_variant(bits, M, INT_MAX, widest / kTileCols, false).tiles : 1;   // row tiles of a pass
     if (narrow || (tokens_path && transforms_ahead(items, count, M))) {
         // layers that read the same input (same x, s, K and quantisation step: q/k/v or gate/up of a decoder
         // block) share one transformed copy

@@ -1,6 +1,5 @@
 // The tokens kernel (lcd_tokens.h) for layers of one index width.
 #include <hip/hip_runtime.h>
-#include <climits>
 #include "lcd_tokens.h"
 
 namespace lcd {
@@ -14,10 +13,11 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_kernel(const uint32
     tokens_workgroup<BITS, TB, R, WAVES, PAIRS, READY, RESIDENT>(t0, t1, t2, t3, t4, t5, t6, t7, head_x, head_s, head_word, batch, smem);
 }
 
+constexpr int kAnyTiles = 1 << 24;     // (more than any layer has)
 template <int BITS, int TB, int R, int WAVES, int PAIRS, bool READY, bool RESIDENT = false>
 static TokensVariant variant_of(int slot)
 {
-    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R, WAVES, PAIRS, READY, RESIDENT>, RESIDENT ? INT_MAX : R, WAVES, tokens_lds_bytes<BITS, TB, R, WAVES>(),
+    return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R, WAVES, PAIRS, READY, RESIDENT>, RESIDENT ? kAnyTiles : R, WAVES, tokens_lds_bytes<BITS, TB, R, WAVES>(),
                          (((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 4 + (READY ? 3 : PAIRS == 2 ? 0 : PAIRS == 4 ? 1 : 2)) * 8 + slot};
 }
 

@@ -61,7 +61,7 @@ int main()
         {"bucket, 3 bits", bucket_cost(3, 1, false), 3}, {"bucket, 3 bits, codes", bucket_cost(3, 1, true), 3}, {"bucket, 2 bits", bucket_cost(2, 1, false), 2},
         {"bucket, 2 bits, two tokens", bucket_cost(2, 2, false), 2}, {"bucket, 2 bits, two tokens of codes", bucket_cost(2, 2, true), 2},
         {"bucket, 2 bits, three tokens of codes", bucket_cost(2, 3, true), 2}, {"bucket, 2 bits, four tokens of codes", bucket_cost(2, 4, true), 2},
-        {"tokens, 16", tokens_cost(14, 16, false), 3}, {"tokens, 5, ahead", tokens_cost(14, 5, true), 4}, {"narrow, 40", tokens_cost(6, 40, true), 3}};
+        {"tokens, 16", tokens_cost(14, 16, false), 3}, {"tokens, 5, ahead", tokens_cost(14, 5, true), 4}, {"tokens, one pass", tokens_cost(1 << 24, 8, false), 2}, {"narrow, 40", tokens_cost(6, 40, true), 3}};
     for (auto &k : kinds) {
         // row tiles per workgroup around the lengths of the passes: 16 to 22 of them, alone and next to a small layer
         for (int t = 14; t <= 24; ++t) {
