@@ -26,7 +26,9 @@
 // Beyond K = 4096 a second pass over the activations costs 4 to 6 us, hence the variant of 14 row tiles (up to 57344 rows on 256 compute units
 // in one pass): two layers of 28672 x 8192, 4 tokens, 3 / 4 bits 54.8 / 77.4 -> 44.1 / 64.6.  Its registers
 // hold the packed words of a few tiles only, in a ring (2 / 3 / 4 bits: 4, 4, 3 tiles ahead, which is enough of them under way), and at 3 and 4 bits
-// no row tables: those are read from LDS one tile ahead.
+// no row tables: those are read from LDS one tile ahead.  At 2 bits with 9 to 16 tokens made in the kernel 14 tiles and their tables spill: 12 tiles have
+// room for both and serve where they need no more passes, 14 read the tables from LDS too (tables in registers / so: 7 tiles x K = 5120 15.3 / 14.7 us,
+// 12 x 5120 21.1 / 20.6, 16 x 5120 30.0 / 28.8, 14 x 6400 31.3 / 29.7, 13 x 5120 21.6 / 21.8, 25 x 4352 39.4 / 39.9).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <type_traits>
@@ -42,13 +44,14 @@ constexpr int kStageBytes = kTokenBlock * kStageStride * 2;
 template <int BITS, int TB> constexpr int whole_chunk_tiles() { return BITS == 4 ? (TB == 1 ? 4 : 3) : (TB == 1 ? 6 : 5); }
 constexpr int kManyTiles = 14;
 template <int BITS> constexpr int ring_tiles() { return BITS == 4 ? 3 : 4; }
-template <int BITS, int R> constexpr bool tables_in_lds() { return R == kManyTiles && BITS != 2; }
+constexpr bool ring_of_words(int tiles) { return tiles > 6; }      // (whole_chunk_tiles: up to 6)
+template <int BITS, int R, int PAIRS, bool READY> constexpr bool tables_in_lds() { return R == kManyTiles && (BITS != 2 || (PAIRS == 8 && !READY)); }
 
 template <int TB, int R>
 constexpr int tokens_wave_bytes() { return R * TB * 1024 > kStageBytes ? R * TB * 1024 : kStageBytes; }
 template <int BITS> constexpr int row_table_bytes() { return BITS == 2 ? 8 : BITS == 3 ? 16 : 32; }
-template <int BITS, int TB, int R, int WAVES>
-constexpr size_t tokens_lds_bytes() { return (size_t)WAVES * tokens_wave_bytes<TB, R>() + (tables_in_lds<BITS, R>() ? R * kTileRows * row_table_bytes<BITS>() : 0); }
+template <int BITS, int TB, int R, int WAVES, int PAIRS, bool READY>
+constexpr size_t tokens_lds_bytes() { return (size_t)WAVES * tokens_wave_bytes<TB, R>() + (tables_in_lds<BITS, R, PAIRS, READY>() ? R * kTileRows * row_table_bytes<BITS>() : 0); }
 
 template <int BITS>
 struct TokTile {
@@ -68,8 +71,8 @@ __device__ __forceinline__ void tokens_workgroup(const uint32_t t0, const uint32
 {
     constexpr uint32_t TBYTES = kTileRows * kTileCols * BITS / 8;
     constexpr int NC = BITS == 2 ? 4 : 8;
-    constexpr int RING = R == kManyTiles ? ring_tiles<BITS>() : R;   // row tiles whose words of a chunk are held
-    constexpr bool TABLES = tables_in_lds<BITS, R>();
+    constexpr int RING = ring_of_words(R) ? ring_tiles<BITS>() : R;   // row tiles whose words of a chunk are held
+    constexpr bool TABLES = tables_in_lds<BITS, R, PAIRS, READY>();
     constexpr bool STRAIGHT = TB == 1 && R <= 3 && !(BITS == 4 && R == 2 && PAIRS == 8);   // short code, and registers left: the last chunk has a copy of its own
     constexpr int SETS = 2 * kBW / WAVES;         // accumulator sets of a wave (see the order of the additions above)
     constexpr int kWaveBytes = tokens_wave_bytes<TB, R>();
@@ -313,7 +316,7 @@ __device__ __forceinline__ void tokens_workgroup(const uint32_t t0, const uint32
     }
 
     int pass_tiles = R;
-    if (R == kManyTiles && tb_end - ta > R) {   // passes of one length: a last pass of few tiles would have few loads under way
+    if (ring_of_words(R) && tb_end - ta > R) {   // passes of one length: a last pass of few tiles would have few loads under way
         const int passes = (tb_end - ta + R - 1) / R;
         pass_tiles = (tb_end - ta + passes - 1) / passes;
     }

@@ -25,7 +25,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemv_tokens_mixed_kernel(const 
 template <int R, int WAVES, int PAIRS, bool RESIDENT = false>
 static TokensVariant variant_of(int slot)
 {
-    return TokensVariant{(const void *)gemv_tokens_mixed_kernel<R, WAVES, PAIRS, RESIDENT>, R, WAVES, tokens_lds_bytes<4, 1, R, WAVES>(),
+    return TokensVariant{(const void *)gemv_tokens_mixed_kernel<R, WAVES, PAIRS, RESIDENT>, R, WAVES, tokens_lds_bytes<4, 1, R, WAVES, PAIRS, false>(),
                          slot * 3 + (PAIRS == 2 ? 0 : PAIRS == 4 ? 1 : 2)};
 }
 
@@ -33,6 +33,8 @@ template <int PAIRS>
 static TokensVariant pick(int tiles, int kc)
 {
     if (tiles <= 1) return variant_of<1, 2 * kBW, PAIRS>(0);
+    // (9 to 16 tokens: the 4-bit part spills 12 registers, which costs less than 8 waves do the others: 4096 rows of 3 and of 2 bits, K = 13824,
+    // 9 tokens 15.8 us, with 8 waves 17.0; 6144 rows of 4 and 2048 of 3 bits the same with either, K = 5120 11.0, 13824 24.4)
     if (tiles <= 2) return variant_of<2, 2 * kBW, PAIRS>(1);
     if (kc <= 2 * kBW) return variant_of<3, 2 * kBW, PAIRS, true>(2);
     return tiles <= whole_chunk_tiles<3, 1>() ? variant_of<whole_chunk_tiles<3, 1>(), kBW, PAIRS>(3) : variant_of<kManyTiles, kBW, PAIRS>(4);

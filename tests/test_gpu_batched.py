@@ -66,6 +66,14 @@ def test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised):
     assert_parity(y[:, first:].cpu().numpy(), Y, 1e-3 if quantised else TOL)
 
 
+# the same for the forms chosen to stay clear of spills, 9 to 16 tokens made in the kernel: 2 bits, 12 row tiles a pass where 14 need as many, row
+# tables in LDS beyond; 4 bits, two row tiles: 8 waves up to 12 chunks and beyond 16, resident between
+@pytest.mark.parametrize("bits,tiles,K", [(2, 12, 4352), (2, 13, 4352), (2, 24, 4352), (2, 25, 4352), (4, 2, 3072), (4, 2, 3328), (4, 2, 4096)])
+@pytest.mark.parametrize("M", [9, 16])
+def test_gemv_forms_clear_of_spills(bits, tiles, K, M):
+    test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, False)
+
+
 # the split kernel behind lcd_lut_gemm: one token either side of a tile, rows that fill half a pair, fewer 128-column units than
 # waves (K = 256), units that do not divide by the waves (K = 1280, 2304), and the first token count of the same
 # layer that the large tiles take
