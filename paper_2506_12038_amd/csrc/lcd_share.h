@@ -11,23 +11,30 @@ struct BucketRule {
     int waves;      // of a workgroup
     int operands;   // row tiles that a chunk's operands cost as much as
     int lengths;
+    bool long_ties;
 };
 
-// Waves: 16 where the registers allow it, with the same number for every R (an output is the sum of the waves' sums: grouped,
-// single and captured calls agree bit for bit).
+// Waves: 16 for one token of fp16 activations, 8 where more operands are held, with the same number for every pass (an output is the sum of the waves' sums:
+// grouped, single and captured calls agree bit for bit).  One token of codes at 2 bits has registers for 16 too, but half of them would wait for nothing up to
+// K = 2048; one row tile per workgroup, 8 / 16 waves, us: K = 1024 2.3 / 2.8, 2048 2.7 / 3.1, 4096 3.4 / 3.4, 8192 4.7 / 4.2, 28672 11.3 / 8.5; seven row tiles
+// 4.1 / 5.0, 4.7 / 5.7, 6.7 / 6.9, 11.1 / 11.1.
 constexpr int bucket_waves(int token_slots, bool int8_codes) { return token_slots == 1 && !int8_codes ? 16 : 8; }
 
 // tokens: 1 (2 and 3 bits), 2 (2 bits), 3 and 4 (2 bits, INT8 codes)
 constexpr BucketRule bucket_rule(int bits, int tokens, bool int8_codes)
 {
     const int operands = tokens > 2 ? 4 : tokens == 2 && !int8_codes ? 2 : 1;
-    return BucketRule{bucket_waves(tokens, int8_codes), operands, operands > 1 ? 7 : bits == 3 && !int8_codes ? 3 : 4};
+    return BucketRule{bucket_waves(tokens, int8_codes), operands, operands > 1 ? 7 : bits == 3 && !int8_codes ? 3 : 4, bits == 2 && operands == 1};
 }
 
 // Which of kBucketPass workgroups of up to `tiles` row tiles and kc chunks take.  Three row tiles at a time cover the latency of memory; longer passes
 // make a step's operands less often (a wave's only chunk: once) -- but a slot without a row
 // tile costs the addresses of its loads.  us, passes of 3 / 7: 2 bits, one token, 1792 row tiles, K = 8192 12.2 / 11.6, 3168, K = 4096 10.8 / 11.0;
 // two tokens 13.9 / 11.9 (INT8 codes, K = 8192); four tokens, 3584, K = 8192, passes of 3 / 6 / 10 / 14: 36.5 / 29.6 / 27.8 / 25.3, 640, K = 5120 6.6 / 6.7 / 7.2 / 8.0.
+// On a tie the longer pass (2 bits; one token, one and two of codes, three / seven, row tiles per workgroup: 5 x K = 5120 6.6 / 6.4 6.8 / 6.1 7.3 / 6.3, 11 x 8192 16.8 / 16.7
+// 16.3 / 16.3 18.0 / 17.0, 22 x 5120 21.3 / 21.1 22.0 / 20.7 23.8 / 21.7; 70B MLP in one launch, 22 tiles 30.9 / 30.5), but not where three divides the row tiles (one
+// token, 6 x 11008 13.2 / 13.8), nor 16 of them (x 8192 25.0 / 28.7: workgroups a power of two apart meet in the same memory channels).  Codes of 3 bits are as fast or faster
+// with three up to K = 5120 (11 x 5120 18.3 / 18.9).
 constexpr int bucket_pass(const BucketRule &rule, int tiles, int kc)
 {
     if (kc <= rule.waves) return tiles < 3 ? tiles - 1 : 2;
@@ -35,7 +42,8 @@ constexpr int bucket_pass(const BucketRule &rule, int tiles, int kc)
     long long least = 0;
     for (int i = 0; i < rule.lengths; ++i) {
         const long long cost = (long long)((tiles + kBucketPass[i] - 1) / kBucketPass[i]) * (kBucketPass[i] + rule.operands);
-        if (i == 0 || cost < least) { best = i; least = cost; }
+        const bool tie = cost == least && rule.long_ties && tiles % 3 != 0 && tiles % 16 != 0 && kBucketPass[i] > 3;
+        if (i == 0 || cost < least || tie) { best = i; least = cost; }
     }
     return best;
 }
