@@ -63,8 +63,9 @@ __device__ __forceinline__ uint32_t smooth_pair(uint32_t a, float ra, uint32_t b
 // |x| is a finite fp16 number and the caller keeps 2^-64 < s * s_q < 2^64.
 // One correction is enough: it leaves the quotient within 2^-22 of an ulp of the true one before its last rounding, so a code could
 // depend on a second one only where x / (s * s_q) lies that close to the midpoint between a half-integer and its neighbour.  All such places --
-// every fp16 significand, every half-integer up to 128.5, the divisors within 6 ulps of their quotient, reciprocals off by one ulp
-// either way -- give the same code with one correction as with two (7B block, 2 bits, four tokens 28.4 -> 27.5 us).
+// every fp16 significand, every half-integer up to 128.5, the divisors within 8 ulps of their quotient, reciprocals off by one ulp
+// either way (tests/test_quotient.py) -- give the same code with one correction as with two (7B block, 2 bits, four tokens 28.4 -> 27.5 us), and
+// that of the division but for one place, where the reciprocal must be the correctly rounded one and is: the largest significand under a power of two.
 struct Divisor {
     float neg_d;   // -(s * s_q)
     float y;       // refined reciprocal of s * s_q
