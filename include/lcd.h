@@ -28,7 +28,7 @@
  *   - Two calls that share a workspace buffer must be ordered on one stream.
  *   - Every call works on the current HIP device; the little state the launchers keep (the
  *     device's compute-unit count, "dynamic-LDS limit raised" flags) is per device and atomic, and
- *     the error string and the remembered workgroup split of the last grouped decode call are per
+ *     the error string and the remembered workgroup splits of the last eight shapes of grouped calls are per
  *     thread, so calls from several threads and on several devices of one process do not disturb
  *     each other.  (This build is tested on one GPU.)
  */

@@ -37,7 +37,7 @@ struct BucketProblem {
 // What a workgroup needs first travels as leading kernel arguments: those are preloaded into scalar registers when a wave
 // starts, while a read of the argument segment takes 0.6 us (measured from a wave's entry).  The first eight words are the
 // table of first workgroups (wg_begin[1..16], 16 bits each), from which a workgroup finds its layer, or, in a launch of
-// a single layer, the layer itself (SingleLayer).  Then x, s and DecodeHead::word for layers that all read one input
+// a single layer, the layer itself (see part_of).  Then x, s and DecodeHead::word for layers that all read one input
 // (q, k, v or gate, up of a decoder block, and every single layer): the activations, which start the longest chain, are asked for
 // without waiting for the layer's record.
 // Measured, 7B blocks: 2 bits, 16 tokens 39.4 -> 38.4 us; 4 tokens of INT8 codes 32.4 -> 31.5; 3 bits, one token 34.6 -> 33.9.

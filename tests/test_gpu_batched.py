@@ -433,22 +433,50 @@ def test_grouped_prefill_smallest_and_largest_group(count):
 
 
 
-@pytest.mark.parametrize("bits,M,N,K", [(2, 9, 4112, 8192), (4, 16, 4112, 8192), (3, 9, 4112, 7936), (3, 10, 12304, 6656), (2, 16, 12288, 6656), (4, 11, 4096, 8448)])
-def test_gemv_smoothed_in_and_ahead_of_the_product(bits, M, N, K):
+class _WatchedWorkspace:
+    """A workspace filled with a pattern: whether a call has written into it."""
+
+    def __init__(self, nbytes):
+        import torch
+        self.tensor = torch.full((max(nbytes, 256),), 0xA5, dtype=torch.uint8, device="cuda")
+
+    def written(self):
+        return bool((self.tensor != 0xA5).any())
+
+
+# ahead: of the single call and of the group of two (256 compute units: 257 row tiles or more, K = 8192; 769 or more, K = 6656)
+@pytest.mark.parametrize("bits,M,N,K,ahead", [(2, 9, 4112, 8192, (True, True)), (4, 16, 4112, 8192, (True, True)), (3, 9, 4112, 7936, (False, False)), (3, 10, 12304, 6656, (True, True)),
+                                              (2, 16, 12288, 6656, (False, True)), (4, 11, 4096, 8448, (False, True)), (3, 8, 4112, 8192, (False, False))])
+def test_gemv_smoothed_in_and_ahead_of_the_product(bits, M, N, K, ahead):
     # either side of the lines for fp16 activations of 9 to 16 tokens (row tiles per compute unit, columns): whole calls against calls
-    # of up to 8 tokens, which smooth inside the kernel, bit for bit (the order of the additions depends on K alone), single and two layers in one launch
+    # of up to 8 tokens, which smooth inside the kernel, bit for bit (the order of the additions depends on K alone), single and two layers in one launch.
+    # Which side a call is on shows in its workspace: smoothed activations are written there.
     import torch
     from paper_2506_12038_amd.binding import GemvGroup
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
     layer = synth.make_layer_uniform(N, K, bits, M, seed=N + K + M)
     packed, lut = lcd.lcd_pack_indices(to_dev(layer["idx"]), bits), lcd.lcd_build_lut(to_dev(layer["codebook"]), bits)
     x, s = to_dev(layer["x"]), to_dev(layer["s"])
     x2, half = (x * 0.5).contiguous(), (M + 1) // 2      # (halves: a part of one or two tokens could be the bucket kernel's)
-    parts = lambda a: torch.cat([lcd.lcd_lut_gemv(packed, lut, a[m:m + half].contiguous(), s, N, bits) for m in range(0, M, half)])
+
+    def parts(a):
+        ys = []
+        for m in range(0, M, half):
+            ws = _WatchedWorkspace(lcd.lcd_workspace_bytes(half, N, K, bits))
+            ys.append(lcd.lcd_lut_gemv(packed, lut, a[m:m + half].contiguous(), s, N, bits, workspace=ws.tensor))
+            assert not ws.written()
+        return torch.cat(ys)
+
     ref, ref2 = parts(x), parts(x2)
-    y = lcd.lcd_lut_gemv(packed, lut, x, s, N, bits)
+    ws = _WatchedWorkspace(lcd.lcd_workspace_bytes(M, N, K, bits))
+    y = lcd.lcd_lut_gemv(packed, lut, x, s, N, bits, workspace=ws.tensor)
+    assert ws.written() == ahead[0]
     assert torch.equal(y, ref)
     outs = [torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2)]
-    GemvGroup([(packed, lut, x, s, outs[0], N), (packed, lut, x2, s, outs[1], N)], bits)()
+    problems = [(packed, lut, x, s, outs[0], N), (packed, lut, x2, s, outs[1], N)]
+    ws = _WatchedWorkspace(GemvGroup(problems, bits).workspace.numel())
+    GemvGroup(problems, bits, workspace=ws.tensor)()
+    assert ws.written() == ahead[1]
     assert torch.equal(outs[0], ref) and torch.equal(outs[1], ref2)
     rows = np.unique(np.linspace(0, N - 1, 48).astype(int))
     assert_parity(y.cpu().numpy()[:, rows], oracle.lut_matmul(layer["codebook"][rows], layer["idx"][rows], layer["x"], layer["s"], bits), TOL)

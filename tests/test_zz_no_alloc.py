@@ -1,6 +1,7 @@
 """GPU: the allocation-free decode entry point (lcd_lut_gemv_noalloc) against lcd_lut_gemv.
 
-The scratch array takes activations that are transformed ahead of the product: more than 300000 of them (tokens x K).
+The scratch array takes activations that are transformed ahead of the product: of the layers here, which have no more row tiles than the
+GPU has compute units, more than 300000 of them (tokens x K; wider and taller layers have lower lines).
 Calls in a row on one GPU share it, the second with a smaller input than the first; each must reproduce bit for bit what
 lcd_lut_gemv gives for half of the tokens at a time, which stays below that line and transforms inside the kernel (both
 routes round the same way), and match the oracle.  The device-memory counters of the allocator and of the driver are read around
