@@ -42,15 +42,6 @@
 
 namespace lcd {
 
-template <int N, class F>
-__device__ __forceinline__ void unrolled(F &&f)
-{
-    if constexpr (N > 0) {
-        unrolled<N - 1>(f);
-        f(std::integral_constant<int, N - 1>{});
-    }
-}
-
 // lane LANE of every row of 16 lanes to all lanes of that row
 template <int LANE>
 __device__ __forceinline__ uint32_t row_broadcast(uint32_t v)

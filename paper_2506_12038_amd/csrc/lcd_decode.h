@@ -129,6 +129,17 @@ BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int tiles, i
 // 214.5 -> 211.7 (four blocks).
 __device__ __forceinline__ int partial_quad(int r, int q, int j) { return 4 * ((4 * j + (q ^ (j >> 2))) ^ ((r & 3) << 2)); }
 
+// What a lane of the tokens and the narrow kernel holds of a (tile, chunk) and of a row.
+template <int BITS>
+struct PackedTile {
+    uint4v lo;
+    uint2v hi;     // 3 bits: the third-bit words
+    uint4v hi4;    // 4 bits: the second plane
+};
+template <int BITS> struct TablesOf { typedef RowTables type; };
+template <> struct TablesOf<4> { typedef RowTables4 type; };
+template <int BITS> constexpr int row_table_bytes() { return BITS == 2 ? 8 : BITS == 3 ? 16 : 32; }
+
 // ---- tokens kernel (lcd_tokens.h) ---------------------------------------------------------------
 constexpr int kTokenBlock = 16;      // tokens per block of the tokens kernel (the columns of one matrix instruction)
 constexpr int kMaxTokenBlocks = 2;   // blocks it holds in registers: up to 32 tokens

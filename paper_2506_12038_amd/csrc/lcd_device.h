@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace lcd {
 
@@ -11,6 +12,16 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+
+// f(0), f(1), ... f(N - 1), each argument a compile-time constant
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F &&f)
+{
+    if constexpr (N > 0) {
+        unrolled<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
 
 // DPP controls: lane exchange inside a row of 16 lanes without touching LDS.
 constexpr int kDppQuadXor1 = 0xB1;       // quad_perm:[1,0,3,2]

@@ -25,15 +25,6 @@ namespace lcd {
 
 constexpr int kSplitWaves = 8;
 
-template <int N, class F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (N > 0) {
-        static_for<N - 1>(f);
-        f(std::integral_constant<int, N - 1>{});
-    }
-}
-
 // k-steps (16 columns) a wave's ring holds
 template <int PAIRS, int TBLK> constexpr int split_ring() { return TBLK >= 3 ? 4 : 8; }
 // a partial block in LDS: [token 32][row], rows padded by 16 bytes (spreads the banks)
@@ -149,7 +140,7 @@ __device__ __forceinline__ void split_workgroup(const GemmBatch &batch, uint32_t
 
     typename GemmTables<BITS>::type tb[PAIRS];
     load_gemm_tables<BITS>(tb, pb.lutB, t0, nt, lane);
-    static_for<PAIRS * TBLK>([&](auto i) __attribute__((always_inline)) { zero_acc<decltype(i)::value>(); });
+    unrolled<PAIRS * TBLK>([&](auto i) __attribute__((always_inline)) { zero_acc<decltype(i)::value>(); });
 
     uint4v window[4];                    // B operands: the read of block f + 3 is issued while block f is multiplied
     struct Ops { uint4v op[PAIRS][2]; };  // A operands of one packed word: [pair][k-step of the word]
@@ -169,7 +160,7 @@ __device__ __forceinline__ void split_workgroup(const GemmBatch &batch, uint32_t
                     const HighBits (&hn)[PAIRS], uint32_t src, uint32_t src_next) __attribute__((always_inline)) {
         constexpr int D = decltype(D_)::value, DN = decltype(DN_)::value;
         constexpr bool LAST = decltype(LAST_)::value;
-        static_for<WSTEPS>([&](auto st_) __attribute__((always_inline)) {
+        unrolled<WSTEPS>([&](auto st_) __attribute__((always_inline)) {
             constexpr int st = decltype(st_)::value, f = D * WSTEPS + st, j = f / TBLK, blk = f % TBLK;
             constexpr int ahead = f + 3, ja = ahead / TBLK, issued = LAST && j - 1 + RING > 7 ? 7 : j - 1 + RING;
             if constexpr (ahead < STEPS || !LAST) {
@@ -184,7 +175,7 @@ __device__ __forceinline__ void split_workgroup(const GemmBatch &batch, uint32_t
             // this step's share of the next word's 4 * PAIRS quarters
             if constexpr (!(LAST && D == 3)) {
                 constexpr int q0 = st * 4 * PAIRS / WSTEPS, q1 = (st + 1) * 4 * PAIRS / WSTEPS;
-                static_for<q1 - q0>([&](auto qi) __attribute__((always_inline)) {
+                unrolled<q1 - q0>([&](auto qi) __attribute__((always_inline)) {
                     constexpr int q = q0 + decltype(qi)::value, p = q >> 2, t = q & 3;
                     uint32_t sel = 0, pool = 0, lo, hi, o0, o1;
                     gemm_select<BITS, DN, t>(rn, p, hn[p], sel, pool);
@@ -229,7 +220,7 @@ __device__ __forceinline__ void split_workgroup(const GemmBatch &batch, uint32_t
     if (wave < units) {
         GemmTileRegs<BITS, PAIRS> r0, r1;
         load_words(r0, wave);
-        static_for<RING>([&](auto j) __attribute__((always_inline)) { copy_step(unit_src(wave), j); });
+        unrolled<RING>([&](auto j) __attribute__((always_inline)) { copy_step(unit_src(wave), j); });
         high_bits(r0, hb);
 #pragma unroll
         for (int p = 0; p < PAIRS; ++p) {
@@ -260,11 +251,11 @@ __device__ __forceinline__ void split_workgroup(const GemmBatch &batch, uint32_t
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
     __syncthreads();      // every wave has left its ring
     constexpr int STRIDE = split_part_stride<PAIRS>(), PART = split_part_bytes<PAIRS>();
-    static_for<TBLK>([&](auto b_) __attribute__((always_inline)) {
+    unrolled<TBLK>([&](auto b_) __attribute__((always_inline)) {
         constexpr int b = decltype(b_)::value;
         uint8_t *buffer = lds + (b & 1) * (kSplitWaves * PART);
         float *mine = reinterpret_cast<float *>(buffer + wave * PART) + (lane & 31) * STRIDE + 4 * (lane >> 5);
-        static_for<PAIRS>([&](auto p_) __attribute__((always_inline)) {
+        unrolled<PAIRS>([&](auto p_) __attribute__((always_inline)) {
             constexpr int p = decltype(p_)::value;
             const float16v v = read_acc<p * TBLK + b>();
 #pragma unroll

@@ -21,24 +21,6 @@
 
 namespace lcd {
 
-template <int BITS>
-struct NarrowTile {
-    uint4v lo;
-    uint2v hi;     // 3 bits: the third-bit words
-    uint4v hi4;    // 4 bits: the second plane
-};
-template <int BITS> struct NarrowTables { typedef RowTables type; };
-template <> struct NarrowTables<4> { typedef RowTables4 type; };
-
-template <int N, class F>
-__device__ __forceinline__ void unrolled(F &&f)
-{
-    if constexpr (N > 0) {
-        unrolled<N - 1>(f);
-        f(std::integral_constant<int, N - 1>{});
-    }
-}
-
 template <int TB, int R> constexpr size_t narrow_lds_bytes() { return (size_t)kBW * R * TB * 1024; }
 constexpr int WINDOW = 4;     // k-steps whose B operands are held or under way
 
@@ -48,9 +30,9 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemm_narrow_kernel(const uint32_t
                                                                   const uint16_t *head_x, const float *head_s, const uint32_t head_word, const BucketBatch batch)
 {
     constexpr uint32_t TBYTES = kTileRows * kTileCols * BITS / 8;
-    constexpr uint32_t ROW_TABLE = BITS == 2 ? 8 : BITS == 3 ? 16 : 32;
+    constexpr uint32_t ROW_TABLE = row_table_bytes<BITS>();
     constexpr int NC = BITS == 2 ? 4 : 8;
-    typedef typename NarrowTables<BITS>::type Tables;
+    typedef typename TablesOf<BITS>::type Tables;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // partial tiles [wave][tile][block][partial_quad]
 
     const int lane = threadIdx.x & 63;
@@ -89,7 +71,7 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemm_narrow_kernel(const uint32_t
     const __amdgpu_buffer_rsrc_t rs_packed = make_rsrc(l.packed, (uint32_t)l.nt * (uint32_t)kc * TBYTES);
     // byte-split tables: behind the bucket multipliers (2 and 3 bits), the whole table (4 bits)
     const __amdgpu_buffer_rsrc_t rs_tb = make_rsrc(reinterpret_cast<const uint8_t *>(l.lut) + (BITS == 4 ? 0 : (size_t)N * NC * 4), (uint32_t)N * ROW_TABLE);
-    auto load_tile = [&](NarrowTile<BITS> &p, int tile, int chunk) __attribute__((always_inline)) {
+    auto load_tile = [&](PackedTile<BITS> &p, int tile, int chunk) __attribute__((always_inline)) {
         const bool v = tile < tb_end && chunk < kc;
         const uint32_t o = v ? ((uint32_t)tile * (uint32_t)kc + (uint32_t)chunk) * TBYTES : 0u;
         p.lo = __builtin_amdgcn_raw_buffer_load_b128(rs_packed, v ? 16 * lane : kOob, o, kStreamPolicy);
@@ -97,7 +79,7 @@ __global__ void __launch_bounds__(kBW * 64, 1) gemm_narrow_kernel(const uint32_t
         if (BITS == 4) p.hi4 = __builtin_amdgcn_raw_buffer_load_b128(rs_packed, v ? 16 * lane : kOob, o + 1024, kStreamPolicy);
     };
     Tables tab[R];
-    NarrowTile<BITS> P[R];
+    PackedTile<BITS> P[R];
     float4v acc[R][TB];
 
     for (int v0 = ta; v0 < tb_end; v0 += R) {

@@ -49,19 +49,8 @@ template <int BITS, int R, int PAIRS, bool READY> constexpr bool tables_in_lds()
 
 template <int TB, int R>
 constexpr int tokens_wave_bytes() { return R * TB * 1024 > kStageBytes ? R * TB * 1024 : kStageBytes; }
-template <int BITS> constexpr int row_table_bytes() { return BITS == 2 ? 8 : BITS == 3 ? 16 : 32; }
 template <int BITS, int TB, int R, int WAVES, int PAIRS, bool READY>
 constexpr size_t tokens_lds_bytes() { return (size_t)WAVES * tokens_wave_bytes<TB, R>() + (tables_in_lds<BITS, R, PAIRS, READY>() ? R * kTileRows * row_table_bytes<BITS>() : 0); }
-
-template <int BITS>
-struct TokTile {
-    uint4v lo;
-    uint2v hi;     // 3 bits: the third-bit words
-    uint4v hi4;    // 4 bits: the second plane
-};
-
-template <int BITS> struct TokTables { typedef RowTables type; };
-template <> struct TokTables<4> { typedef RowTables4 type; };
 
 // The life of a workgroup.  PAIRS: pairs of tokens the launch may have per block; smem: tokens_lds_bytes
 template <int BITS, int TB, int R, int WAVES, int PAIRS, bool READY, bool RESIDENT>
@@ -146,7 +135,7 @@ __device__ __forceinline__ void tokens_workgroup(const uint32_t t0, const uint32
     const __amdgpu_buffer_rsrc_t rs_tb = make_rsrc(reinterpret_cast<const uint8_t *>(l.lut) + (BITS == 4 ? 0 : (size_t)N * NC * 4),
                                                    (uint32_t)N * row_table_bytes<BITS>());
     // packed words of the R row tiles from v0 (tiles past v1 and chunks past the layer's read zeros, no traffic)
-    auto load_tile = [&](TokTile<BITS> &p, int tile, int v1, int chunk) __attribute__((always_inline)) {
+    auto load_tile = [&](PackedTile<BITS> &p, int tile, int v1, int chunk) __attribute__((always_inline)) {
         const bool v = tile < v1 && chunk < kc;
         // the (tile, chunk) part of the address is wave-uniform and travels as the scalar offset
         const uint32_t o = v ? ((uint32_t)tile * (uint32_t)kc + (uint32_t)chunk) * TBYTES : 0u;
@@ -202,9 +191,9 @@ __device__ __forceinline__ void tokens_workgroup(const uint32_t t0, const uint32
     };
 
     float4v acc[SETS][R][TB];
-    typedef typename TokTables<BITS>::type Tables;
+    typedef typename TablesOf<BITS>::type Tables;
     Tables tab[TABLES ? 2 : R];         // TABLES: of this tile and the next
-    TokTile<BITS> P[RING];
+    PackedTile<BITS> P[RING];
     // a row's table, 16 bytes (8 with 2 bits) at a time: piece i of it
     auto table_piece = [&](bool valid, uint32_t row, int i) __attribute__((always_inline)) {
         const uint32_t at = valid ? row * row_table_bytes<BITS>() + 16 * i : kOob;
@@ -227,7 +216,7 @@ __device__ __forceinline__ void tokens_workgroup(const uint32_t t0, const uint32
         } else if constexpr (BITS == 3) return make_tables(*reinterpret_cast<const uint4v *>(at), uint4v{});
         else return make_tables(*reinterpret_cast<const uint4v *>(at), *reinterpret_cast<const uint4v *>(at + 16));
     };
-    auto tile_product = [&](const TokTile<BITS> &p, const typename TokTables<BITS>::type &t, float4v (&a)[TB]) __attribute__((always_inline)) {
+    auto tile_product = [&](const PackedTile<BITS> &p, const typename TablesOf<BITS>::type &t, float4v (&a)[TB]) __attribute__((always_inline)) {
         uint4v op0, op1;
         auto multiply = [&](int d) __attribute__((always_inline)) {
 #pragma unroll
