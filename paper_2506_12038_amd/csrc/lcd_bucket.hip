@@ -352,29 +352,30 @@ static BucketVariant variant_of(int id)
 }
 
 template <int BITS, int MT, bool I8, int NTOK>
-static BucketVariant pick(int tiles, int kc, int id)
+static BucketVariant pick(int pass, int tiles, int kc, int id)
 {
     // (packed rows of kRunCols columns leave room for 512 row tiles: two for a workgroup)
     if (kc > kRunCols / kTileCols) return tiles == 1 ? variant_of<BITS, MT, I8, NTOK, 1, true>(9 * id + 7) : variant_of<BITS, MT, I8, NTOK, 2, true>(9 * id + 8);
-    constexpr BucketRule rule = bucket_rule(BITS, NTOK, I8);
-    const int best = bucket_pass(rule, tiles, kc);
-    id = 9 * id + best;
-    if constexpr (rule.lengths > 4) {
-        if (best == 4) return variant_of<BITS, MT, I8, NTOK, kBucketPass[4]>(id);
-        if (best == 5) return variant_of<BITS, MT, I8, NTOK, kBucketPass[5]>(id);
-        if (best == 6) return variant_of<BITS, MT, I8, NTOK, kBucketPass[6]>(id);
+    constexpr int lengths = bucket_rule(BITS, NTOK, I8).lengths;
+    id = 9 * id + pass;
+    if constexpr (lengths > 5) {
+        if (pass == 5) return variant_of<BITS, MT, I8, NTOK, kBucketPass[5]>(id);
+        if (pass == 6) return variant_of<BITS, MT, I8, NTOK, kBucketPass[6]>(id);
     }
-    if constexpr (rule.lengths > 3) if (best == 3) return variant_of<BITS, MT, I8, NTOK, kBucketPass[3]>(id);
-    if (best == 0) return variant_of<BITS, MT, I8, NTOK, kBucketPass[0]>(id);
-    return best == 1 ? variant_of<BITS, MT, I8, NTOK, kBucketPass[1]>(id) : variant_of<BITS, MT, I8, NTOK, kBucketPass[2]>(id);
+    if constexpr (lengths > 3) {
+        if (pass == 3) return variant_of<BITS, MT, I8, NTOK, kBucketPass[3]>(id);
+        if (pass == 4) return variant_of<BITS, MT, I8, NTOK, kBucketPass[4]>(id);
+    }
+    if (pass == 0) return variant_of<BITS, MT, I8, NTOK, kBucketPass[0]>(id);
+    return pass == 1 ? variant_of<BITS, MT, I8, NTOK, kBucketPass[1]>(id) : variant_of<BITS, MT, I8, NTOK, kBucketPass[2]>(id);
 }
 
-BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int tiles, int kc)
+BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int pass, int tiles, int kc)
 {
-    if (bits == 3) return int8_codes ? pick<3, 1, true, 1>(tiles, kc, 0) : pick<3, 1, false, 1>(tiles, kc, 1);
-    if (!int8_codes) return tokens == 1 ? pick<2, 1, false, 1>(tiles, kc, 2) : pick<2, 2, false, 2>(tiles, kc, 3);
-    if (tokens <= 2) return tokens == 1 ? pick<2, 1, true, 1>(tiles, kc, 4) : pick<2, 2, true, 2>(tiles, kc, 5);
-    return tokens == 3 ? pick<2, 4, true, 3>(tiles, kc, 6) : pick<2, 4, true, 4>(tiles, kc, 7);
+    if (bits == 3) return int8_codes ? pick<3, 1, true, 1>(pass, tiles, kc, 0) : pick<3, 1, false, 1>(pass, tiles, kc, 1);
+    if (!int8_codes) return tokens == 1 ? pick<2, 1, false, 1>(pass, tiles, kc, 2) : pick<2, 2, false, 2>(pass, tiles, kc, 3);
+    if (tokens <= 2) return tokens == 1 ? pick<2, 1, true, 1>(pass, tiles, kc, 4) : pick<2, 2, true, 2>(pass, tiles, kc, 5);
+    return tokens == 3 ? pick<2, 4, true, 3>(pass, tiles, kc, 6) : pick<2, 4, true, 4>(pass, tiles, kc, 7);
 }
 
 }  // namespace lcd

@@ -120,8 +120,8 @@ struct BucketVariant {
 };
 constexpr int kBucketVariants = 72;
 // tokens: 1 (2 and 3 bits), 2 (2 bits), 3 and 4 (2 bits, INT8 codes)
-// tiles: most row tiles of a workgroup; kc: chunks of the widest layer
-BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int tiles, int kc);
+// pass: place in kBucketPass; tiles: most row tiles of a workgroup; kc: chunks of the widest layer
+BucketVariant bucket_variant(int bits, int tokens, bool int8_codes, int pass, int tiles, int kc);
 
 // Partial tiles in LDS (tokens and narrow kernel): where row quad q of token j of a tile stands, in floats; r: the tile's row tile in the pass.
 // 16 lanes that write (one q, all j) and 16 that read (the quads of one token, row tile after row tile) each cover all banks; in

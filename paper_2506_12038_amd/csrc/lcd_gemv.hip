@@ -195,17 +195,17 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
     // 2 bits on the sparse matrix core with quantised activations: the codes go in as int8 numbers
     const bool int8_codes = !tokens_path && bits != 4 && all_quantised;   // (3 bits: one token, the plain pass only)
     const bool staged_ahead = tokens_path && codes[0] != nullptr;
-    static_assert(kBW == 8, "lcd_share.h counts rounds of 8 chunks");
     const DecodeCost cost = tokens_path ? tokens_cost(held, M, staged_ahead) : bucket_cost(bits, M, int8_codes);
     LayerShape shape[kMaxGroup];
     for (int i = 0; i < count; ++i) shape[i] = LayerShape{batch.p[i].nt, batch.p[i].kc, items[i].bits};
-    // The split depends on the shapes only: the last few are kept (a block repeats a few groups; working one out takes 0.2 us of host time, 2 to 4 where the layers differ).
-    struct SplitMemo { int count, M, grid, ahead, route, nwg[kMaxGroup]; LayerShape shape[kMaxGroup]; };
+    // The split depends on the shapes only: the last few are kept (a block repeats a few groups; working one out takes 0.3 us of host time, 2 to 7 where the layers differ).
+    static_assert(kBW == 8, "lcd_share.h counts rounds of 8 chunks");
+    struct SplitMemo { int count, M, grid, ahead, route, pass, nwg[kMaxGroup]; LayerShape shape[kMaxGroup]; };
     constexpr int kMemos = 8;
     static thread_local SplitMemo memos[kMemos] = {};
     static thread_local int oldest = 0;
     const int route = narrow ? 3 : tokens_path ? 1 : int8_codes ? 2 : 0;   // the cost constants depend on it
-    int nwg[kMaxGroup];
+    int nwg[kMaxGroup], pass = 0;      // pass: of the bucket kernel
     const SplitMemo *known = nullptr;
     for (int e = 0; e < kMemos && !known; ++e) {
         const SplitMemo &m = memos[e];
@@ -215,13 +215,16 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
     }
     if (known) {
         for (int i = 0; i < count; ++i) nwg[i] = known->nwg[i];
+        pass = known->pass;
     } else if (count == 1) {
-        nwg[0] = grid;
+        if (tokens_path) nwg[0] = grid;
+        else pass = share_bucket(bits, M, int8_codes, shape, count, grid, nwg);
     } else {
-        share_workgroups(cost, shape, count, grid, nwg);
+        if (tokens_path) share_workgroups(cost, shape, count, grid, nwg);
+        else pass = share_bucket(bits, M, int8_codes, shape, count, grid, nwg);
         SplitMemo &m = memos[oldest];
         oldest = (oldest + 1) % kMemos;
-        m.count = count; m.M = M; m.grid = grid; m.ahead = (int)staged_ahead; m.route = route;
+        m.count = count; m.M = M; m.grid = grid; m.ahead = (int)staged_ahead; m.route = route; m.pass = pass;
         for (int i = 0; i < count; ++i) { m.shape[i] = shape[i]; m.nwg[i] = nwg[i]; }
     }
     // Workgroups are dispatched in the order of their ids, the last of a full grid almost 1 us after the
@@ -229,7 +232,7 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
     if (count > 1) {
         int order[kMaxGroup];
         double t[kMaxGroup];
-        for (int i = 0; i < count; ++i) { order[i] = i; t[i] = cost.time(shape[i].bits, shape[i].kc, round_up_div(shape[i].tiles, nwg[i])); }
+        for (int i = 0; i < count; ++i) { order[i] = i; t[i] = cost.even_time(shape[i].bits, shape[i].kc, round_up_div(shape[i].tiles, nwg[i])); }
         std::stable_sort(order, order + count, [&](int a, int b) { return width[a] != width[b] ? width[a] > width[b] : t[a] > t[b]; });
         BucketProblem sorted_p[kMaxGroup];
         int sorted_n[kMaxGroup], sorted_w[kMaxGroup];
@@ -270,7 +273,7 @@ static int launch_decode_layers(const GroupItem *items, int count, int M, void *
     int most = 1;          // row tiles of a workgroup
     for (int i = 0; i < count; ++i) most = std::max(most, (batch.p[i].nt + nwg[i] - 1) / nwg[i]);
     if (!tokens_path) {
-        const BucketVariant v = bucket_variant(bits, M, int8_codes, most, widest / kTileCols);
+        const BucketVariant v = bucket_variant(bits, M, int8_codes, pass, most, widest / kTileCols);
         lds = v.lds_bytes;
         fn = count == 1 ? v.single : v.fn;
         waves = v.waves;

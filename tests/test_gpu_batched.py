@@ -74,6 +74,13 @@ def test_gemv_forms_clear_of_spills(bits, tiles, K, M):
     test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, False)
 
 
+# the bucket kernel's passes of five and seven row tiles: full ones, one short, one over, with more in the last than in none
+@pytest.mark.parametrize("bits,M,quantised", [(2, 1, True), (2, 2, True), (2, 1, False), (3, 1, True)])
+@pytest.mark.parametrize("tiles,K", [(4, 2304), (5, 4352), (6, 4352), (8, 4352), (9, 2304), (10, 4352), (15, 4352), (16, 4608)])
+def test_bucket_passes(bits, M, quantised, tiles, K):
+    test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised)
+
+
 # the split kernel behind lcd_lut_gemm: one token either side of a tile, rows that fill half a pair, fewer 128-column units than
 # waves (K = 256), units that do not divide by the waves (K = 1280, 2304), and the first token count of the same
 # layer that the large tiles take
