@@ -153,7 +153,7 @@ struct TokensVariant {
     size_t lds_bytes;
     int id;             // 0 .. kTokensVariants - 1
 };
-constexpr int kTokensVariants = 3 * kMaxTokenBlocks * 4 * 8;
+constexpr int kTokensVariants = 3 * kMaxTokenBlocks * 4 * 10;
 // ready: x holds the transformed activations in operand order (transform_kernel)
 TokensVariant tokens_variant(int bits, int tokens, int tiles, int kc, bool ready);
 // the narrow kernel (lcd_narrow.hip), 17 .. 16 kNarrowBlocks tokens; ids of their own

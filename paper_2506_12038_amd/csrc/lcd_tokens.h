@@ -29,6 +29,9 @@
 // no row tables: those are read from LDS one tile ahead.  At 2 bits with 9 to 16 tokens made in the kernel 14 tiles and their tables spill: 12 tiles have
 // room for both and serve where they need no more passes, 14 read the tables from LDS too (tables in registers / so: 7 tiles x K = 5120 15.3 / 14.7 us,
 // 12 x 5120 21.1 / 20.6, 16 x 5120 30.0 / 28.8, 14 x 6400 31.3 / 29.7, 13 x 5120 21.6 / 21.8, 25 x 4352 39.4 / 39.9).
+// Four and five tiles of these have forms of their own, short enough for a copy of the last chunk without loads, and six hold four tiles' words, not all
+// (one form of six with all words / so, 16 tokens: 4 tiles x K = 5120 11.0 / 10.0 us, 5 tiles 12.2 / 11.2, 6 tiles 13.3 / 12.9; 6400 13.8 / 12.3, 15.3 / 14.2, 17.0 / 16.5; six
+// with the copy spill, 14.6 and 18.2).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <type_traits>
@@ -60,9 +63,9 @@ __device__ __forceinline__ void tokens_workgroup(const uint32_t t0, const uint32
 {
     constexpr uint32_t TBYTES = kTileRows * kTileCols * BITS / 8;
     constexpr int NC = BITS == 2 ? 4 : 8;
-    constexpr int RING = ring_of_words(R) ? ring_tiles<BITS>() : R;   // row tiles whose words of a chunk are held
+    constexpr int RING = ring_of_words(R) || (R == 6 && BITS == 2 && PAIRS == 8 && !READY) ? ring_tiles<BITS>() : R;   // row tiles whose words of a chunk are held
     constexpr bool TABLES = tables_in_lds<BITS, R, PAIRS, READY>();
-    constexpr bool STRAIGHT = TB == 1 && R <= 3 && !(BITS == 4 && R == 2 && PAIRS == 8);   // short code, and registers left: the last chunk has a copy of its own
+    constexpr bool STRAIGHT = TB == 1 && (R <= 3 || (BITS == 2 && R <= 5)) && !(BITS == 4 && R == 2 && PAIRS == 8);   // short code, and registers left: the last chunk has a copy of its own
     constexpr int SETS = 2 * kBW / WAVES;         // accumulator sets of a wave (see the order of the additions above)
     constexpr int kWaveBytes = tokens_wave_bytes<TB, R>();
     // smem: one piece per wave (its stage, in the end its partial tiles), then the row tables

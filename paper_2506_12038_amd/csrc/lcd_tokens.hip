@@ -18,7 +18,7 @@ template <int BITS, int TB, int R, int WAVES, int PAIRS, bool READY, bool RESIDE
 static TokensVariant variant_of(int slot)
 {
     return TokensVariant{(const void *)gemv_tokens_kernel<BITS, TB, R, WAVES, PAIRS, READY, RESIDENT>, RESIDENT ? kAnyTiles : R, WAVES, tokens_lds_bytes<BITS, TB, R, WAVES, PAIRS, READY>(),
-                         (((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 4 + (READY ? 3 : PAIRS == 2 ? 0 : PAIRS == 4 ? 1 : 2)) * 8 + slot};
+                         (((BITS - 2) * kMaxTokenBlocks + (TB - 1)) * 4 + (READY ? 3 : PAIRS == 2 ? 0 : PAIRS == 4 ? 1 : 2)) * 10 + slot};
 }
 
 template <int BITS, int TB, int PAIRS, bool READY>
@@ -36,6 +36,10 @@ static TokensVariant pick_tiles(int tiles, int kc)   // (of 16 waves those that 
     }
     if (tiles <= 3) return variant_of<BITS, TB, 3, kBW, PAIRS, READY>(6);
     constexpr int whole = whole_chunk_tiles<BITS, TB>();
+    if constexpr (BITS == 2 && TB == 1 && PAIRS == 8 && !READY) {
+        if (tiles == 4) return variant_of<BITS, 1, 4, kBW, PAIRS, READY>(8);
+        if (tiles == 5) return variant_of<BITS, 1, 5, kBW, PAIRS, READY>(9);
+    }
     if (TB > 1 || tiles <= whole) return variant_of<BITS, TB, whole, kBW, PAIRS, READY>(3);
     if constexpr (BITS == 2 && PAIRS == 8 && !READY) if ((tiles + 11) / 12 == (tiles + 13) / 14) return variant_of<BITS, 1, 12, kBW, PAIRS, READY>(7);
     return variant_of<BITS, 1, kManyTiles, kBW, PAIRS, READY>(4);

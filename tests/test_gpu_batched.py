@@ -67,14 +67,14 @@ def test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised):
 
 
 # the same for the forms chosen to stay clear of spills, 9 to 16 tokens made in the kernel: 2 bits, 12 row tiles a pass where 14 need as many, row
-# tables in LDS beyond; 4 bits, two row tiles: 8 waves up to 12 chunks and beyond 16, resident between
-@pytest.mark.parametrize("bits,tiles,K", [(2, 12, 4352), (2, 13, 4352), (2, 24, 4352), (2, 25, 4352), (4, 2, 3072), (4, 2, 3328), (4, 2, 4096)])
+# tables in LDS beyond, four and five tiles on forms of their own, six with a ring; 4 bits, two row tiles: 8 waves up to 12 chunks and beyond 16, resident between
+@pytest.mark.parametrize("bits,tiles,K", [(2, 12, 4352), (2, 13, 4352), (2, 24, 4352), (2, 25, 4352), (2, 4, 4352), (2, 4, 6400), (2, 5, 4352), (2, 5, 6400), (2, 6, 4352), (2, 6, 6400), (4, 2, 3072), (4, 2, 3328), (4, 2, 4096)])
 @pytest.mark.parametrize("M", [9, 16])
 def test_gemv_forms_clear_of_spills(bits, tiles, K, M):
     test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, False)
 
 
-# the bucket kernel's passes of five and seven row tiles: full ones, one short, one over, with more in the last than in none
+# the bucket kernel's passes of five and seven row tiles: full, one tile short and one over
 @pytest.mark.parametrize("bits,M,quantised", [(2, 1, True), (2, 2, True), (2, 1, False), (3, 1, True)])
 @pytest.mark.parametrize("tiles,K", [(4, 2304), (5, 4352), (6, 4352), (8, 4352), (9, 2304), (10, 4352), (15, 4352), (16, 4608)])
 def test_bucket_passes(bits, M, quantised, tiles, K):
