@@ -109,9 +109,10 @@ static bool tokens_kernel_takes(int bits, int M, bool all_quantised, bool dense)
 //               8 (88 k) 10.2/9.5 10.8/10.5 12.4/11.9; 28672 x 8192, twice, 9 (74 k) 37.4/31.9 45.0/41.8 64.5/61.1
 //   fp16        4096 x 13824, 16 (221 k) 12.2/12.6 13.5/14.3 15.9/15.9; 8192 x 28672, 8 (229 k) 22.1/22.0 28.2/26.1 36.4/34.0
 // fp16 activations of 9 to 16 tokens: a workgroup of several row tiles has no registers left to load them early beyond K = 4096, so that from about
-// two row tiles of K = 8192, or four of 6656, on they go ahead:
-//               8192 x 8192, 9 tokens 9.8/9.7 11.0/11.1 15.1/13.9, 16 10.8/10.4 12.1/12.0 16.2/14.6; 16384 x 8192, 9 15.3/14.1 18.4/17.8 23.9/22.6;
-//               16384 x 6912, 9 13.3/13.2 16.2/15.9 21.2/20.0, 12288 x 6912, 9 10.4/11.2 12.0/12.6 15.9/16.1, 16384 x 5120, 9 10.8/11.2 12.9/12.7 15.8/16.4;
+// two row tiles of K = 8192, or four of 6656 (2 bits: 7424), on they go ahead:
+//               8192 x 8192, 9 tokens 9.8/9.7 11.0/11.1 15.1/13.9, 16 10.8/10.4 12.1/12.0 16.2/14.6; 16384 x 8192, 9 14.2/14.3 18.4/17.8 23.9/22.6, 16, 2 bits 15.7/15.0;
+//               16384 x 6912, 9 11.9/12.9 16.2/15.9 21.2/20.0, 12288 x 6912, 9 10.4/11.2 12.0/12.6 15.9/16.1, 16384 x 5120, 9 9.6/10.6 12.9/12.7 15.8/16.4;
+//               2 bits, 16 tokens, 16384, 20480 and 24576 x 7168 13.7/14.4 15.5/16.2 17.8/18.3, x 7424 15.5/14.8 17.6/17.1 19.6/19.3;
 //               8192 x 13824, 9 14.2/13.5 16.9/16.1 22.8/20.0, 8 13.2/13.9 16.0/16.6 20.7/20.2; 28672 x 8192, twice, 16 39.6/36.6 47.8/45.8 65.6/64.6
 // Layers of several widths, whose launches the transformation would set apart, stay with the higher line.
 // Up to K = 4096 a workgroup makes its activations once whatever its row tiles are, but beyond 14 of them the line is as good as where they would be made again
@@ -131,7 +132,7 @@ static bool transforms_ahead(const GroupItem *items, int count, int M)
     const long long cus = num_cus(), per_pass = cus * held, passes = (all_tiles + per_pass - 1) / per_pass, activations = (long long)M * widest * passes;
     if (items[0].act_scale != 0.0f) return activations > kAheadCodes;
     if (mixed || M > kTokenBlock || all_tiles <= cus || widest <= 2 * kBW * kTileCols) return activations > kAheadSmoothed;
-    return activations > kAheadTiles || (M > kTokenBlock / 2 && (widest >= 8192 || (widest >= 6656 && all_tiles > 3 * cus)));
+    return activations > kAheadTiles || (M > kTokenBlock / 2 && (widest >= 8192 || (widest >= (items[0].bits == 2 ? 7424 : 6656) && all_tiles > 3 * cus)));
 }
 
 // One launch (and transform_kernel's, where it pays) for layers that one kernel takes: of one width, or of several on the tokens kernel.

@@ -68,7 +68,7 @@ def test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, quantised):
 
 # the same for the forms chosen to stay clear of spills, 9 to 16 tokens made in the kernel: 2 bits, 12 row tiles a pass where 14 need as many, row
 # tables in LDS beyond, four and five tiles on forms of their own, six with a ring; 4 bits, two row tiles: 8 waves up to 12 chunks and beyond 16, resident between
-@pytest.mark.parametrize("bits,tiles,K", [(2, 12, 4352), (2, 13, 4352), (2, 24, 4352), (2, 25, 4352), (2, 4, 4352), (2, 4, 6400), (2, 5, 4352), (2, 5, 6400), (2, 6, 4352), (2, 6, 6400), (4, 2, 3072), (4, 2, 3328), (4, 2, 4096)])
+@pytest.mark.parametrize("bits,tiles,K", [(2, 12, 4352), (2, 13, 4352), (2, 24, 4352), (2, 25, 4352), (2, 4, 4352), (2, 4, 6400), (2, 5, 4352), (2, 5, 6400), (2, 6, 4352), (2, 6, 6400), (2, 5, 7168), (4, 2, 3072), (4, 2, 3328), (4, 2, 4096)])
 @pytest.mark.parametrize("M", [9, 16])
 def test_gemv_forms_clear_of_spills(bits, tiles, K, M):
     test_gemv_many_row_tiles_per_workgroup(bits, tiles, K, M, False)
@@ -451,9 +451,10 @@ class _WatchedWorkspace:
         return bool((self.tensor != 0xA5).any())
 
 
-# ahead: of the single call and of the group of two (256 compute units: 257 row tiles or more, K = 8192; 769 or more, K = 6656)
+# ahead: of the single call and of the group of two (256 compute units: 257 row tiles or more, K = 8192; 769 or more, K = 6656, 2 bits 7424)
 @pytest.mark.parametrize("bits,M,N,K,ahead", [(2, 9, 4112, 8192, (True, True)), (4, 16, 4112, 8192, (True, True)), (3, 9, 4112, 7936, (False, False)), (3, 10, 12304, 6656, (True, True)),
-                                              (2, 16, 12288, 6656, (False, True)), (4, 11, 4096, 8448, (False, True)), (3, 8, 4112, 8192, (False, False))])
+                                              (2, 16, 12288, 6656, (False, False)), (3, 16, 12288, 6656, (False, True)), (2, 9, 12304, 7168, (False, False)), (2, 9, 12288, 7424, (False, True)),
+                                              (4, 11, 4096, 8448, (False, True)), (3, 8, 4112, 8192, (False, False))])
 def test_gemv_smoothed_in_and_ahead_of_the_product(bits, M, N, K, ahead):
     # either side of the lines for fp16 activations of 9 to 16 tokens (row tiles per compute unit, columns): whole calls against calls
     # of up to 8 tokens, which smooth inside the kernel, bit for bit (the order of the additions depends on K alone), single and two layers in one launch.
