@@ -33,8 +33,8 @@ __device__ __forceinline__ uint16_t half_next_up(uint16_t b)
 // per boundary): 4, 9 and 18 instructions for two weights at 4, 8 and 16 centroids, where counting over all boundaries
 // in bit planes took 5, 15 and 37.  A search needs ascending boundaries; a wave that finds a descent in its row (centroids that
 // do not ascend, a NaN) counts one boundary after the other, as slowly as that is.
-// Bound: HBM, 3 bytes per weight (11008 x 4096, 8 centroids: 27.5 -> 25 us, 5.4 TB/s; 4096 x 4096, 16 centroids, which the counting
-// bound: 19.7 -> 14.9 us).  A wave works alone: no barrier stands between the boundaries and the first weights, and the
+// Bound: HBM, 3 bytes per weight (11008 x 4096, 8 centroids: 28 -> 24.9 us by events, 5.4 TB/s, in a kernel trace 27 in the mean and 24.5 at least;
+// 4096 x 4096, 16 centroids, which the counting bound: 19.7 -> 14.9 us).  A wave works alone: no barrier stands between the boundaries and the first weights, and the
 // boundaries, which cost as much as two passes, are found once per eight passes (with workgroups of a row each 28 us, with two passes
 // per wave 30).  Rows longer than eight passes are cut into equal parts: 4096 x 11008 in rows of 22 passes leaves half
 // of the wave slots empty and takes 27 us instead of 25.  The indices are stored with the default cache policy: the next step reads
