@@ -58,11 +58,12 @@ struct DecodeCost {
     // 15.0, 17.1, 19.0 us, 13 in two passes 25.4; K = 11008 t = 4, 5, 6 20.1, 23.0, 26.2.
     int held, blocks;
     double stage;             // of a round's activations
-    // the bucket kernel (held = 0): a round's chunks each cost their operands once per pass, passes of `pass` row tiles, every place of which counts,
-    // or (0) of the length that suits the row tiles of a workgroup
+    // the bucket kernel (held = 0): a round's chunks each cost their operands once per pass (a wave's only chunk: once), passes of `pass` row tiles,
+    // every place of which counts, or (0) of the length that suits the row tiles of a workgroup
     BucketRule rule;
     double tile, chunk;
     int pass;
+    double empty;             // what a place without a row tile costs of a row tile's time where it is in a workgroup's only pass (in the last of several: all)
     static constexpr double kStart = 2.8;
 
     int rounds(int kc) const { return round_up_div(kc, held ? 8 : rule.waves); }
@@ -71,7 +72,10 @@ struct DecodeCost {
     double time(int bits, int kc, int t) const
     {
         if (held) return round_up_div(t, held) * ((bits == 2 ? 3.7 : 5.0) + rounds(kc) * stage) + rounds(kc) * t * round_tile(bits);
-        if (pass) return kStart + rounds(kc) * tile * (pass + rule.operands) * round_up_div(t, pass);
+        if (pass) {
+            const int passes = round_up_div(t, pass);
+            return kStart + rounds(kc) * tile * (rule.operands * (kc > rule.waves ? passes : 1) + (t < pass ? t + empty * (pass - t) : pass * passes));
+        }
         return even_time(bits, kc, t);
     }
     // the same where places without a row tile are free
@@ -84,12 +88,12 @@ struct DecodeCost {
 inline DecodeCost tokens_cost(int held, int tokens, bool staged_ahead)
 {
     const int blocks = round_up_div(tokens, 16);
-    return DecodeCost{held, blocks, staged_ahead ? 0.1 * blocks : 0.08 + 0.035 * tokens, {}, 0.0, 0.0, 0};
+    return DecodeCost{held, blocks, staged_ahead ? 0.1 * blocks : 0.08 + 0.035 * tokens, {}, 0.0, 0.0, 0, 0.0};
 }
 inline DecodeCost bucket_cost(int bits, int tokens, bool int8_codes)
 {
     return DecodeCost{0, 0, 0.0, bucket_rule(bits, tokens, int8_codes), bits == 3 ? (int8_codes ? 0.45 : 1.05) : tokens > 1 ? 0.35 : int8_codes ? 0.3 : 0.6,
-                      tokens == 1 ? 0.1 : int8_codes && tokens > 2 ? 0.15 * tokens : 0.2, 0};
+                      tokens == 1 ? 0.1 : int8_codes && tokens > 2 ? 0.15 * tokens : 0.2, 0, int8_codes ? 0.3 : 1.0};
 }
 
 struct LayerShape { int tiles, kc, bits; };   // row tiles, chunks, index width
@@ -107,8 +111,12 @@ inline double share_workgroups(const DecodeCost &cost, const LayerShape *layers,
     auto need = [&](int i, double T) {
         const int tiles = layers[i].tiles;
         if (cost.pass) {
-            const int passes = (int)std::min<double>((T - DecodeCost::kStart) / (time(i, 1) - DecodeCost::kStart) + 1e-9, tiles);
-            return passes > 0 ? round_up_div(tiles, passes * cost.pass) : 0;
+            const double unit = cost.rounds(layers[i].kc) * cost.tile, work = (T - DecodeCost::kStart) / unit + 1e-9;
+            const bool once = layers[i].kc <= cost.rule.waves;     // (a wave makes the operands of its only chunk once)
+            const int passes = (int)std::min<double>(once ? (work - cost.rule.operands) / cost.pass : work / (cost.pass + cost.rule.operands), tiles);
+            int share = passes * cost.pass;
+            if (passes <= 0 && cost.empty < 1.0) share = (int)std::max(0.0, (work - cost.rule.operands - cost.empty * cost.pass) / (1.0 - cost.empty));
+            return share > 0 ? round_up_div(tiles, share) : 0;
         }
         const double most = T / (cost.rounds(layers[i].kc) * cost.round_tile(layers[i].bits));   // more row tiles take longer than T by themselves
         for (int t = most < tiles ? (int)most : tiles; t > 0;) {
@@ -179,7 +187,8 @@ inline double share_workgroups(const DecodeCost &cost, const LayerShape *layers,
 
 // The bucket kernel's shares; returns the place in kBucketPass of the launch's passes.  Layers of different shapes get shares that go with the passes, of the
 // length that makes the slowest layer fastest.  70B MLP in one launch, one and two tokens of codes, passes of five, shares
-// without a look at the passes 34.5 35.0 us, so 30.4 31.5.
+// without a look at the passes 34.5 35.0 us, so 30.4 31.5.  Seven layers of a block, with places in an only pass / and operands of an only chunk
+// in each pass counted whole, so: 7B, one token of codes, 2 and 3 bits 10.7 18.4, 10.3 18.1; 3072 / 8192, fp16 and codes of 3 bits 7.2 11.5, 6.8 9.6.
 inline int share_bucket(int bits, int tokens, bool int8_codes, const LayerShape *layers, int count, int grid, int *out)
 {
     DecodeCost cost = bucket_cost(bits, tokens, int8_codes);

@@ -91,6 +91,12 @@ int main()
         int n[kMaxGroup];
         bad += kBucketPass[share_bucket(2, tokens, true, mlp, 3, 256, n)] != 7 || round_up_div(1792, n[0]) != 21 || round_up_div(1792, n[1]) != 21 || round_up_div(512, n[2]) != 7;
     }
+    // a workgroup's only pass may have places left over: 7B, 13 and 13 row tiles next to 4; operands of an only chunk are made once: 3072 columns, 8 row tiles in threes
+    const LayerShape seven[] = {{256, 16, 3}, {256, 16, 3}, {256, 16, 3}, {256, 16, 3}, {688, 16, 3}, {688, 16, 3}, {256, 43, 3}};
+    const LayerShape gqa[] = {{192, 12, 2}, {192, 12, 2}, {64, 12, 2}, {64, 12, 2}, {512, 12, 2}, {512, 12, 2}, {192, 32, 2}};
+    int n[kMaxGroup];
+    bad += kBucketPass[share_bucket(3, 1, true, seven, 7, 256, n)] != 7 || round_up_div(688, n[4]) != 13 || round_up_div(256, n[6]) != 4;
+    bad += kBucketPass[share_bucket(2, 1, false, gqa, 7, 256, n)] != 3 || round_up_div(512, n[4]) != 8;
     std::printf("%d splits worse than the best, or passes not as stated\n", bad);
     return bad ? 1 : 0;
 }
