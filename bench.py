@@ -151,15 +151,16 @@ class LayerSet:
         return written(self.groups[0].workspace, self.groups[0])
 
     def prefill_kernel(self):
-        """The matrix kernel of a prefill step, by the number of tokens and of 256 x 128 output tiles of its layers."""
+        """The matrix kernel of a prefill step, by the number of tokens and of 64 x 128 output tiles of its layers."""
         if self.M <= 32:
             return "gemv_tokens_kernel (layers below 2^24 weights), gemm_narrow_kernel"
-        tiles = [-(-m["spec"].N // 256) * -(-self.M // 128) for m in self.mats]
-        if min(tiles) > 136:
-            return "gemm_group_kernel"
+        tiles = [-(-m["spec"].N // 64) * -(-self.M // 128) for m in self.mats]
+        most = 224 if self.bits == 2 else 256
         if self.M <= 96:
-            return "gemm_narrow_kernel or gemm_split_kernel, by layer (beyond 128 such tiles gemm_group_kernel)"
-        return "gemm_split_kernel" if max(tiles) <= 64 else "gemm_split_kernel or gemm_group_kernel, by layer (one gemm_mixed_kernel launch for both)"
+            return "gemm_narrow_kernel or gemm_split_kernel, by layer (beyond %d such tiles gemm_wide_kernel)" % most
+        if min(tiles) > most:
+            return "gemm_wide_kernel"
+        return "gemm_split_kernel" if max(tiles) <= most else "gemm_split_kernel or gemm_wide_kernel, by layer (one gemm_mixed_kernel launch for both)"
 
     def block_step(self, replica):
         """One decode step in dependency order: one grouped launch per stage."""

@@ -12,7 +12,7 @@ CSRC = PKG / "csrc"
 LIB = PKG / "liblcd.so"
 BUILD = ROOT / "_build"
 
-SOURCES = ["lcd_host.cpp", "lcd_pack.hip", "lcd_gemv.hip", "lcd_bucket.hip", "lcd_tokens.hip", "lcd_tokens_mixed.hip", "lcd_narrow.hip", "lcd_gemm.hip", "lcd_gemm_split.hip", "lcd_gemm_mixed.hip",
+SOURCES = ["lcd_host.cpp", "lcd_pack.hip", "lcd_gemv.hip", "lcd_bucket.hip", "lcd_tokens.hip", "lcd_tokens_mixed.hip", "lcd_narrow.hip", "lcd_gemm.hip", "lcd_gemm_split.hip", "lcd_gemm_wide.hip", "lcd_gemm_mixed.hip",
            "lcd_cluster.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -31,6 +31,7 @@ FLAGS = [
 # instead of being read from the argument segment.
 EXTRA = {"lcd_gemm.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_gemm_split.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
+         "lcd_gemm_wide.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_gemm_mixed.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_pack.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=10"],
          "lcd_gemv.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=9"],
@@ -40,9 +41,13 @@ EXTRA = {"lcd_gemm.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_tokens_mixed.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=12"]}
 
 
-def _compile(src: str, keep_asm: bool) -> Path:
-    obj = BUILD / (src.rsplit(".", 1)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, *EXTRA.get(src, []), "-c", str(CSRC / src), "-o", str(obj)]
+# Sources that are compiled once for each index width, side by side (one after the other they take minutes).
+EACH_WIDTH = ("lcd_gemm_wide.hip", "lcd_gemm_mixed.hip")
+
+
+def _compile(src: str, width: int, keep_asm: bool) -> Path:
+    obj = BUILD / (src.rsplit(".", 1)[0] + (f"_{width}.o" if width else ".o"))
+    cmd = [HIPCC, *FLAGS, *EXTRA.get(src, []), *([f"-DLCD_GEMM_BITS={width}"] if width else []), "-c", str(CSRC / src), "-o", str(obj)]
     if keep_asm and src.endswith(".hip"):
         cmd += ["-save-temps=obj"]
     subprocess.check_call(cmd, cwd=str(BUILD), stderr=subprocess.DEVNULL if not os.environ.get("LCD_BUILD_VERBOSE") else None)
@@ -53,8 +58,9 @@ def build_library(keep_asm: bool = False) -> Path:
     """Compile every source and link paper_2506_12038_amd/liblcd.so."""
     BUILD.mkdir(exist_ok=True)
     srcs = [s for s in SOURCES if (CSRC / s).exists()]
-    with ThreadPoolExecutor(max_workers=4) as ex:
-        objs = list(ex.map(lambda s: _compile(s, keep_asm), srcs))
+    jobs = sorted(((s, w) for s in srcs for w in ((2, 3, 4) if s in EACH_WIDTH else (0,))), key=lambda j: j[1] == 0)    # (the longest first)
+    with ThreadPoolExecutor(max_workers=8) as ex:
+        objs = list(ex.map(lambda j: _compile(*j, keep_asm), jobs))
     tmp = LIB.with_suffix(".so.tmp%d" % os.getpid())
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *map(str, objs), "-o", str(tmp)])
     os.replace(tmp, LIB)

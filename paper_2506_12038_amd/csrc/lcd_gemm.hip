@@ -1,18 +1,11 @@
-// Prefill path (M >= 17; any M >= 1 accepted) of the smoothed table-lookup product, gfx950: the large-tile kernel
-// (lcd_gemm_large.h) and the launcher of all prefill kernels.
+// Prefill path (M >= 17; any M >= 1 accepted) of the smoothed table-lookup product, gfx950: the wide kernel
+// (lcd_gemm_wide.h) and the launcher of all prefill kernels.
 #include <hip/hip_runtime.h>
 #include <algorithm>
-#include "lcd_gemm_large.h"
+#include "lcd_gemm_common.h"
 #include "lcd_launch.h"
 
 namespace lcd {
-
-template <int BITS>
-__global__ void __launch_bounds__(kGemmWaves * 64, 1) gemm_group_kernel(const GemmBatch batch)
-{
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-    gemm_workgroup<BITS>(batch, blockIdx.x, lds);
-}
 
 // Which kernel takes a layer.  The rules look at the layer and the number of tokens alone, never at the group it is
 // called in: the kernels add in different orders, and a layer's result must not depend on its neighbours.
@@ -45,34 +38,20 @@ static bool narrow_takes(int M, int N, int K, int bits)
     if (M <= 48) return K <= 2048 || (N > 2048 && (K <= 4096 || bits > 2));
     return M <= 64 && N >= 2048 && K <= 2048;
 }
-// The split kernel takes layers of few output tiles.  Its advantage lies in rounds of workgroups over the 256 compute units (the whole
-// chip, whatever part of it a process sees: a layer's bits must not depend on that) and in tiles as narrow as the tokens: 256 x 128 tiles
-// spend the same time on 33 tokens as on 128.  It takes what fits
-//   - one round of any of its tiles (64 x 128 being the largest);
-//   - two rounds of 64 x 64;
-//   - two rounds of 64 x 96 where K >= 8192, or where K >= 4096 and a quarter or more of the large tiles' work would be padding;
-//   - just above 128 large tiles, which no longer fit one round when cut in two (K >= 4096).
-// Time of a call, large tiles / split tiles, 2, 3 and 4 bits:
-//   one round         4096 rows, 512 tokens    K = 2048 22.0/19.9 23.1/20.2 25.6/21.1   K = 4096 35.3/28.4 37.8/29.9 41.4/31.3   K = 11008 79.7/59.3 84.5/61.6 95.7/66.7
-//   two of 64 x 64    28672 rows, 40 tokens    K = 2048 19.7/17.6 21.1/18.8 24.0/21.8   K = 4096 31.6/25.3 33.7/27.7 39.0/32.7   K = 8192 54.1/40.8 58.4/44.4 67.6/53.3
-//                     8448 rows, 192 tokens    K = 2048 20.4/18.5 21.2/19.3 23.9/22.3   K = 4096 33.3/27.0 35.1/29.6 39.5/34.4   K = 8192 56.3/42.8 60.2/47.3 70.0/56.8
-//   two of 64 x 96    11008 rows, 160 tokens   K = 2048 20.8/21.5 21.7/22.0 24.5/24.9   K = 4096 33.9/30.8 35.8/33.6 40.0/39.3   K = 8192 56.7/51.0 61.1/55.2 68.7/66.2
-//                     4096 rows, 545 tokens    K = 2048 22.0/23.2 23.0/23.9 25.9/26.8   K = 4096 35.7/34.6 37.4/37.1 42.1/42.7   K = 8192 59.8/56.4 64.7/60.7 75.8/72.3
-//   two of 64 x 128   11008 rows, 224 tokens   K = 2048 21.6/25.5 22.2/27.9 25.7/29.5   K = 4096 35.3/38.2 37.4/41.6 43.7/46.4   K = 8192 58.9/62.3 62.9/67.5 74.3/76.7
-//                     28672 rows, 128 tokens   K = 2048 22.9/28.2 23.8/29.4 26.6/32.0   K = 4096 38.0/44.1 39.7/46.0 45.1/50.7   K = 8192 65.7/72.3 68.5/74.4 78.2/83.9
-//   129 large tiles   11008 rows, 333 tokens   K = 2048 32.4/34.3 34.1/36.2 40.3/40.6   K = 4096 53.9/51.6 58.2/56.5 67.8/64.6   K = 11008 121.6/114.0 131.1/119.2 161.3/144.5
-// Several layers of a size in one launch fill large tiles' rounds better.  K = 4096, 3 bits: two layers of 11008 rows, 160 tokens 58.7/52.3, 256 tokens 60.5/68.0;
-// three of 4096 rows, 576 tokens 67.1/88.4, 1024 tokens 109/139: hence the padding's share, which leaves those to the large tiles.
+// The split kernel takes layers of few output tiles: those that fit one round of its largest tile (64 x 128) on the 256 compute units (the whole
+// chip, whatever part of it a process sees: a layer's bits must not depend on that).  Beyond that the wide kernel's tiles, which share the activations among
+// four or eight waves, win.  A call without its smoothing, split / wide, 2, 3 and 4 bits, us:
+//   one round         4096 x 4096, 333 tokens 17.3/20.7 19.3/24.4 21.2/29.3, 450 (256 tiles) 22.5/22.7 24.0/26.4 25.7/30.8; 4096 x 11008, 333 39.9/47.9 41.4/54.9 47.4/67.7;
+//                     8192 x 8192, 224 tokens 37.8/39.0 37.7/45.7 41.9/54.0; 11008 x 4096, 100 tokens 15.5/18.5 16.2/24.0 19.5/28.6
+//   beyond            4096 x 4096, 640 tokens (large tiles of 256 x 128 as before / wide) 30.8/26.4 32.8/29.0 36.3/32.9; 11008 x 4096, 160 tokens 25.2/22.5 28.8/26.3 31.7/30.4;
+//                     8192 x 8192, 333 tokens 54.2/49.2 57.7/54.4 68.6/62.5; two of 11008 x 4096, 333 tokens 84.8/69.8 94.5/77.1 103.8/89.5
+//   several layers    three of 4096 x 4096, 333 tokens 45.5/39.8 49.7/42.9 58.9/50.8, 450 58.8/45.7 63.0/49.6 68.8/58.1: hence the lower line at 2 bits, where a
+//                     single layer of a nearly full round is as fast either way
 // (The split kernel addresses the activations with 32 bits.)
-static bool split_takes(int M, int N, int K)
+static bool split_takes(int M, int N, int K, int bits)
 {
-    constexpr long long kChip = 256;
-    const long long blocks = (M + kGemmTokens - 1) / kGemmTokens, tiles = (N + 255) / 256 * blocks, rows64 = (N + 63) / 64;
-    const bool padding = 3 * blocks * kGemmTokens >= 4ll * M;
-    const bool one_round = rows64 * blocks <= kChip, narrow = rows64 * ((M + 63) / 64) <= 2 * kChip;
-    const bool medium = rows64 * ((M + 95) / 96) <= 2 * kChip && (K >= 8192 || (K >= 4096 && padding));
-    const bool idle = one_round || narrow || medium || (tiles > 128 && tiles <= 136 && K >= 4096);
-    return idle && (long long)plan_gemm(M, N, K, 2).m_pad * K * 2 < (1ll << 32);
+    const long long blocks = (M + 127) / 128, rows64 = (N + 63) / 64;
+    return rows64 * blocks <= (bits == 2 ? 224 : 256) && (long long)plan_gemm(M, N, K, 2).m_pad * K * 2 < (1ll << 32);
 }
 
 // Tile of a launch of the split kernel: rounds of workgroups over the compute units times the time of one workgroup.  Measured
@@ -109,78 +88,26 @@ static const SplitTile &choose_split_tile(const GemmBatch &bt, int M, int bits)
     }
     return *best;
 }
-// Next to large tiles there are no rounds of their own to fill: the tile with the least work of the two that cost least per output.
+// Next to wide tiles there are no rounds of their own to fill: the tile with the least work of the two that cost least per output.
 static const SplitTile &choose_mixed_tile(const GemmBatch &bt, int M, int bits)
 {
     double wgs;
     return split_work(bt, kSplitTiles[0], M, bits, wgs) <= split_work(bt, kSplitTiles[1], M, bits, wgs) ? kSplitTiles[0] : kSplitTiles[1];
 }
 
-// Last tiles of an XCD's queue that are cut in two (128 rows each): those of a last round that would leave half of the compute units
-// or more idle, so that the halves still fit one round.
-// 7B block, 3 bits, 2048 tokens (gate and up: 172 tiles per queue, the last 12 of them in a sixth round of 32): 793 -> 780 us.  With
-// more than half a round left the halves would need two rounds of about 0.6 of a whole tile's time each.
-static int half_tiles(int queue)
+// Whether the wide kernel takes a layer whole (lcd_gemm_plan.h); the last few answers are kept (working one out takes 2 us of host time).
+static bool wide_whole(int M, int N, int K, int bits)
 {
-    const int cus = num_cus() / kXcds, rest = cus > 0 ? queue % cus : 0;
-    return 2 * rest <= cus ? rest : 0;
-}
-
-// The same cut where split tiles follow in the queue: they can fill the idle compute units as well, so both ways are played
-// through on an XCD's compute units (each takes the next workgroup of the queue), with the times of workgroups on a full chip:
-// a whole large tile 3 us + 10.5 ns per column (4 bits: 13.7), half a tile 0.65 of it, a split tile 1.5 times what it takes in a
-// round of its own.  3 bits, no cut / cut: q 8192, k, v 1024 rows, K = 8192, 333 tokens 101 / 78 us, 1500 tokens 255 / 271; 8192 x 2048
-// with 2048 x 8192, 333 tokens 45 / 60.
-class CuTimes {
-public:
-    explicit CuTimes(int cus) { t_[0] = 0.0; n_[0] = cus; }
-    void add(int wgs, double us)      // the next `wgs` workgroups of the queue
-    {
-        while (wgs > 0) {
-            const int take = std::min(wgs, n_[0]);
-            const double end = t_[0] + us;
-            wgs -= take;
-            n_[0] -= take;
-            if (n_[0] == 0) {
-                --count_;
-                for (int i = 0; i < count_; ++i) { t_[i] = t_[i + 1]; n_[i] = n_[i + 1]; }
-            }
-            int at = count_;
-            for (; at > 0 && t_[at - 1] > end; --at) { t_[at] = t_[at - 1]; n_[at] = n_[at - 1]; }
-            t_[at] = end;
-            n_[at] = take;
-            ++count_;
-        }
-    }
-    double end() const { return t_[count_ - 1]; }
-
-private:
-    // ascending: n_[i] compute units are free at t_[i].  A call adds one entry at most (its last workgroups may take a part
-    // of one), and a launch makes fewer than three calls per layer.
-    double t_[3 * kMaxGroup + 1];
-    int n_[3 * kMaxGroup + 1], count_ = 1;
-};
-static int mixed_half_tiles(const GemmBatch &large, int queue, const GemmBatch &split, const SplitTile &t, int M, int bits)
-{
-    const int cut = half_tiles(queue), cus = num_cus() / kXcds;
-    if (cut == 0 || cus <= 0) return 0;
-    double time[2];
-    for (int c = 0; c < 2; ++c) {
-        CuTimes cu(cus);
-        for (int q = 0; q < large.count; ++q) {
-            const int end = q + 1 < large.count ? large.p[q + 1].queue_begin : queue;
-            const int whole = std::max(0, std::min(end, c ? queue - cut : queue) - large.p[q].queue_begin);
-            const double us = 3.0 + 1e-3 * (bits == 4 ? 13.7 : 10.5) * large.p[q].K;
-            cu.add(whole, us);
-            cu.add(2 * (end - large.p[q].queue_begin - whole), 0.65 * us);
-        }
-        for (int q = 0; q < split.count; ++q) {
-            const int wgs = (split.p[q].N + 32 * t.pairs - 1) / (32 * t.pairs) * ((M + 32 * t.blocks - 1) / (32 * t.blocks));
-            cu.add((wgs + kXcds - 1) / kXcds, 1.5 * (t.fixed_us + 1e-3 * t.column_ns[bits - 2] * split.p[q].K));
-        }
-        time[c] = cu.end();
-    }
-    return time[1] < 1.08 * time[0] ? cut : 0;   // (the cut where they are near one another: shorter workgroups even out)
+    struct Memo { int M, N, K, bits; bool whole; };
+    constexpr int kMemos = 8;
+    static thread_local Memo memos[kMemos] = {};
+    static thread_local int oldest = 0;
+    for (const Memo &m : memos)
+        if (m.M == M && m.N == N && m.K == K && m.bits == bits) return m.whole;
+    const bool whole = whole_takes(M, N, K, bits);
+    memos[oldest] = Memo{M, N, K, bits, whole};
+    oldest = (oldest + 1) % kMemos;
+    return whole;
 }
 
 int launch_gemm(const void *packed, const void *lut, const uint16_t *x, const float *s, uint16_t *y,
@@ -202,7 +129,7 @@ int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *
     // block) share one transformed copy of it: the activations are smoothed once per distinct input.
     SmoothItem sm[kMaxGroup];
     int distinct = 0;
-    GemmBatch batch[2] = {};   // [0] the large-tile kernel's layers, [1] the split kernel's
+    GemmBatch batch[3] = {};   // the wide kernel's layers in halves, the split kernel's, the wide kernel's whole ones
     GroupItem small[kMaxGroup], narrow[kMaxGroup];
     int small_count = 0, narrow_count = 0;       // the decode kernels' layers, the narrow kernel's
     size_t offset = 0;
@@ -218,7 +145,7 @@ int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *
             offset += plan_gemm(M, it.N, it.K, bits).xs_bytes;
             sm[distinct++] = SmoothItem{it.x, it.s, xs, it.K, it.act_scale};
         }
-        GemmBatch &bt = batch[split_takes(M, it.N, it.K)];
+        GemmBatch &bt = batch[split_takes(M, it.N, it.K, bits) ? 1 : wide_whole(M, it.N, it.K, bits) ? 2 : 0];
         GemmProblem &p = bt.p[bt.count++];
         p.packed = static_cast<const uint8_t *>(it.packed);
         // byte-split tables: behind the bucket multipliers (2 and 3 bits), the whole table (4 bits)
@@ -236,8 +163,9 @@ int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *
         if (int e = launch_narrow_group(narrow, narrow_count, M, static_cast<char *>(workspace) + offset, stream)) return e;
     }
     if (distinct == 0) return 0;
-    // places of the layers' tiles (rows x tokens each) in the XCDs' queues; returns the queue's length
-    auto queue_tiles = [&](GemmBatch &bt, int rows, int tokens) {
+    for (GemmBatch &bt : batch) { bt.M = M; bt.Mpad = Mpad; }
+    // places of the split kernel's tiles (rows x tokens each) in the XCDs' queues; returns the queue's length
+    auto queue_split = [&](GemmBatch &bt, int rows, int tokens) {
         int queue = 0;
         for (int q = 0; q < bt.count; ++q) {
             GemmProblem &p = bt.p[q];
@@ -246,37 +174,57 @@ int launch_gemm_group(const GroupItem *items, int count, int M, int bits, void *
             p.queue_begin = queue;
             queue += p.tiles_per_xcd;
         }
-        bt.M = M; bt.Mpad = Mpad;
         return queue;
     };
+    auto queue_wide = [&](GemmBatch &bt, bool whole) {
+        WideLayer layers[kMaxGroup];
+        for (int q = 0; q < bt.count; ++q) layers[q] = WideLayer{bt.p[q].N, bt.p[q].K};
+        double wgs, more_us = 0.0;      // (split tiles next to others take 1.5 times what they take in a round of their own)
+        if (!whole && batch[1].count > 0) more_us = 1.5 * split_work(batch[1], choose_mixed_tile(batch[1], M, bits), M, bits, wgs) / num_cus();
+        const WideTiles t = choose_wide(whole, layers, bt.count, (M + 31) / 32, bits, num_cus(), nullptr, more_us);
+        long long tiles = 0;
+        for (int q = 0; q < bt.count; ++q) {
+            GemmProblem &p = bt.p[q];
+            p.grid_rows = (p.N + wide_rows(t.form) - 1) / wide_rows(t.form);
+            p.tiles[0] = (uint32_t)p.grid_rows * t.big;
+            p.tiles[1] = (uint32_t)p.grid_rows * (t.columns - t.big);
+            tiles += (long long)p.grid_rows * t.columns;
+        }
+        bt.tiles = t;
+        return (int)((tiles + kXcds - 1) / kXcds);
+    };
     if (int e = launch_smooth_group(sm, distinct, M, Mpad, stream)) return e;
-    static PerDeviceFlags<3 + kSplitVariants + kMixedVariants> lds_raised;
-    auto launch = [&](int queue, const void *fn, int flag, size_t lds_bytes, void **args) -> int {
+    static PerDeviceFlags<kWideVariants + kSplitVariants + kMixedVariants> lds_raised;
+    auto launch = [&](int queue, const void *fn, int flag, int threads, size_t lds_bytes, void **args) -> int {
         if (hipError_t e = raise_lds_limit_once(lds_raised, flag, fn, lds_bytes)) return (int)e;
-        if (hipError_t e = hipLaunchKernel(fn, dim3((unsigned)queue * kXcds), dim3(kGemmWaves * 64), args, lds_bytes, stream)) return (int)e;
+        if (hipError_t e = hipLaunchKernel(fn, dim3((unsigned)queue * kXcds), dim3(threads), args, lds_bytes, stream)) return (int)e;
         return (int)hipGetLastError();
     };
-    const int large = batch[0].count > 0 ? queue_tiles(batch[0], kGemmRowGroups * 32 * kGemmPairs, kGemmTokens) : 0;
-    if (batch[1].count == 0) {
-        const void *fn = bits == 2 ? (const void *)gemm_group_kernel<2> : bits == 3 ? (const void *)gemm_group_kernel<3> : (const void *)gemm_group_kernel<4>;
-        const int tail = half_tiles(large);
-        batch[0].tail_begin = large - tail;
-        void *args[] = {&batch[0]};
-        return launch(large + tail, fn, bits - 2, 2 * kStageBytes, args);
-    }
-    if (batch[0].count == 0) {
-        const SplitTile &t = choose_split_tile(batch[1], M, bits);
+    auto launch_wide = [&](GemmBatch &bt, int queue) -> int {
+        const WideVariant v = bits == 2 ? wide_variant<2>(bt.tiles) : bits == 3 ? wide_variant<3>(bt.tiles) : wide_variant<4>(bt.tiles);
+        void *args[] = {&bt};
+        return launch(queue, v.fn, v.id, v.threads, v.lds_bytes, args);
+    };
+    if (batch[2].count > 0)
+        if (int e = launch_wide(batch[2], queue_wide(batch[2], true))) return e;
+    const int wide = batch[0].count > 0 ? queue_wide(batch[0], false) : 0;
+    // wide tiles of 3 or 4 blocks go out with the split tiles
+    const WideTiles &tiles = batch[0].tiles;
+    const bool together = wide > 0 && batch[1].count > 0 && (tiles.blocks == 4 || (tiles.blocks == 3 && tiles.big == tiles.columns));
+    if (wide > 0 && !together)
+        if (int e = launch_wide(batch[0], wide)) return e;
+    if (batch[1].count == 0) return 0;
+    const SplitTile &t = together ? choose_mixed_tile(batch[1], M, bits) : choose_split_tile(batch[1], M, bits);
+    const int split = queue_split(batch[1], 32 * t.pairs, 32 * t.blocks);
+    if (!together) {
         const SplitVariant sv = split_variant(bits, t.pairs, t.blocks);
         void *args[] = {&batch[1]};
-        return launch(queue_tiles(batch[1], 32 * t.pairs, 32 * t.blocks), sv.fn, 3 + sv.id, sv.lds_bytes, args);
+        return launch(split, sv.fn, kWideVariants + sv.id, 512, sv.lds_bytes, args);
     }
-    const SplitTile &t = choose_mixed_tile(batch[1], M, bits);
-    const SplitVariant sv = mixed_variant(bits, t.blocks);
-    const int split = queue_tiles(batch[1], 32 * t.pairs, 32 * t.blocks), tail = mixed_half_tiles(batch[0], large, batch[1], t, M, bits);
-    batch[0].tail_begin = large - tail;
-    uint32_t large_blocks = (uint32_t)(large + tail) * kXcds;
-    void *args[] = {&batch[0], &batch[1], &large_blocks};
-    return launch(large + tail + split, sv.fn, 3 + kSplitVariants + sv.id, sv.lds_bytes, args);
+    const WideVariant v = bits == 2 ? mixed_variant<2>(tiles, t.blocks) : bits == 3 ? mixed_variant<3>(tiles, t.blocks) : mixed_variant<4>(tiles, t.blocks);
+    uint32_t wide_blocks = (uint32_t)wide * kXcds;
+    void *args[] = {&batch[0], &batch[1], &wide_blocks};
+    return launch(wide + split, v.fn, kWideVariants + kSplitVariants + v.id, v.threads, v.lds_bytes, args);
 }
 
 }  // namespace lcd

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include "lcd_internal.h"
 #include "lcd_device.h"
+#include "lcd_gemm_plan.h"
 
 namespace lcd {
 
@@ -17,7 +18,7 @@ typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef __attribute__((address_space(1))) const uint32_t glb_u32;
 
 // ---- accumulators in fixed accumulation registers ------------------------------------------------
-// The 8 accumulators of a wave (16 registers each) live in a[0:127] and are touched only by the
+// The accumulators of a wave (up to 16 of 16 registers each) live in a[0:255] and are touched only by the
 // inline assembly below, so the compiler never copies them (as loop-carried values it would move
 // all 128 registers to VGPRs and back in every iteration).  The files that include this are compiled
 // with AGPR spilling disabled and use no MFMA builtins, so the compiler itself never allocates an AGPR.
@@ -25,9 +26,9 @@ typedef __attribute__((address_space(1))) const uint32_t glb_u32;
 // requires between a vector instruction that writes a register and a matrix instruction that reads it
 // as an operand (it is free to place the last instruction of an operand's dequantisation directly in
 // front of the matrix instruction, and does so depending on unrelated details of the source): every
-// matrix instruction therefore brings its own two wait states.  Two waves share a SIMD and a 32x32x16
-// instruction occupies the matrix pipe for 32 cycles, so the two issue cycles are hidden.
-template <int IDX> __device__ __forceinline__ void mfma_acc(uint4v a, uint4v b);
+// matrix instruction therefore brings its own two wait states (APART), but for those of the wide kernel, which pins the last instruction of every
+// operand at least one matrix instruction ahead of the one that reads it.
+template <int IDX, bool APART = true> __device__ __forceinline__ void mfma_acc(uint4v a, uint4v b);
 template <int IDX> __device__ __forceinline__ float16v read_acc();
 template <int IDX> __device__ __forceinline__ void zero_acc();
 // Register names cannot be computed inside assembly text, so each accumulator lists its 16 registers once.
@@ -37,7 +38,14 @@ template <int IDX> __device__ __forceinline__ void zero_acc();
 #define LCD_ACC_READ(n, r) "v_accvgpr_read_b32 %" #n ", a" #r
 #define LCD_ACC_ZERO(r) "v_accvgpr_write_b32 a" #r ", 0"
 #define LCD_ACCUMULATOR(IDX, r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15)                                \
-    template <> __device__ __forceinline__ void mfma_acc<IDX>(uint4v a, uint4v b)                                                 \
+    template <> __device__ __forceinline__ void mfma_acc<IDX, false>(uint4v a, uint4v b)                                          \
+    {                                                                                                                              \
+        asm volatile("v_mfma_f32_32x32x16_f16 a[" #r0 ":" #r15 "], %0, %1, a[" #r0 ":" #r15 "]"                                  \
+                     :                                                                                                             \
+                     : "v"(a), "v"(b)                                                                                              \
+                     : LCD_ACC_CLOBBERS(r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15));                    \
+    }                                                                                                                              \
+    template <> __device__ __forceinline__ void mfma_acc<IDX, true>(uint4v a, uint4v b)                                           \
     {                                                                                                                              \
         asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_f16 a[" #r0 ":" #r15 "], %0, %1, a[" #r0 ":" #r15 "]"                     \
                      :                                                                                                             \
@@ -76,6 +84,14 @@ LCD_ACCUMULATOR(4, 64, 65, 66, 67, 68, 69, 70, 71, 72, 73, 74, 75, 76, 77, 78, 7
 LCD_ACCUMULATOR(5, 80, 81, 82, 83, 84, 85, 86, 87, 88, 89, 90, 91, 92, 93, 94, 95)
 LCD_ACCUMULATOR(6, 96, 97, 98, 99, 100, 101, 102, 103, 104, 105, 106, 107, 108, 109, 110, 111)
 LCD_ACCUMULATOR(7, 112, 113, 114, 115, 116, 117, 118, 119, 120, 121, 122, 123, 124, 125, 126, 127)
+LCD_ACCUMULATOR(8, 128, 129, 130, 131, 132, 133, 134, 135, 136, 137, 138, 139, 140, 141, 142, 143)
+LCD_ACCUMULATOR(9, 144, 145, 146, 147, 148, 149, 150, 151, 152, 153, 154, 155, 156, 157, 158, 159)
+LCD_ACCUMULATOR(10, 160, 161, 162, 163, 164, 165, 166, 167, 168, 169, 170, 171, 172, 173, 174, 175)
+LCD_ACCUMULATOR(11, 176, 177, 178, 179, 180, 181, 182, 183, 184, 185, 186, 187, 188, 189, 190, 191)
+LCD_ACCUMULATOR(12, 192, 193, 194, 195, 196, 197, 198, 199, 200, 201, 202, 203, 204, 205, 206, 207)
+LCD_ACCUMULATOR(13, 208, 209, 210, 211, 212, 213, 214, 215, 216, 217, 218, 219, 220, 221, 222, 223)
+LCD_ACCUMULATOR(14, 224, 225, 226, 227, 228, 229, 230, 231, 232, 233, 234, 235, 236, 237, 238, 239)
+LCD_ACCUMULATOR(15, 240, 241, 242, 243, 244, 245, 246, 247, 248, 249, 250, 251, 252, 253, 254, 255)
 #undef LCD_ACCUMULATOR
 #undef LCD_ACC_ZERO
 #undef LCD_ACC_READ
@@ -164,14 +180,15 @@ __device__ __forceinline__ void gemm_lookup(uint32_t sel, uint32_t pool, const t
 struct GemmProblem {
     const uint8_t *packed, *lutB, *xs;
     uint16_t *y;
-    int N, K, grid_rows, tiles_per_xcd;
-    int queue_begin;   // position of this layer's first tile in an XCD's queue
-    float out_scale;   // 1, or the layer's activation quantisation step
+    int N, K, grid_rows;
+    float out_scale;        // 1, or the layer's activation quantisation step
+    uint32_t tiles[2];      // wide kernel: in the columns of the most blocks, and of one block less
+    int tiles_per_xcd, queue_begin;   // split kernel: position of this layer's first tile in an XCD's queue
 };
 struct GemmBatch {
     GemmProblem p[kMaxGroup];
     int count, M, Mpad;
-    int tail_begin;    // large-tile kernel: places of a queue from here on are cut in two
+    WideTiles tiles;        // wide kernel
 };
 
 // A variant of the split kernel (lcd_gemm_split.hip): 32 * pairs rows x 32 * blocks tokens per workgroup; pairs 1 with
@@ -183,8 +200,16 @@ struct SplitVariant {
 };
 constexpr int kSplitVariants = 3 * 6;
 SplitVariant split_variant(int bits, int pairs, int blocks);
-// The kernel that takes large tiles and split tiles of 64 rows x 32 * blocks tokens, blocks 3 or 4 (lcd_gemm_mixed.hip).
-constexpr int kMixedVariants = 3 * 2;
-SplitVariant mixed_variant(int bits, int blocks);
+// A variant of the wide kernel (lcd_gemm_wide.hip), and of the kernel that takes wide tiles (in halves, 3 or 4 blocks) and split tiles of 64 rows x
+// 32 * blocks tokens, blocks 3 or 4 (lcd_gemm_mixed.hip).
+struct WideVariant {
+    const void *fn;
+    size_t lds_bytes;
+    int threads;
+    int id;             // 0 .. kWideVariants - 1, 0 .. kMixedVariants - 1
+};
+constexpr int kWideVariants = 3 * 12, kMixedVariants = 3 * 8;
+template <int BITS> WideVariant wide_variant(const WideTiles &t);
+template <int BITS> WideVariant mixed_variant(const WideTiles &t, int blocks);
 
 }  // namespace lcd

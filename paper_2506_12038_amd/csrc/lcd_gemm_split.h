@@ -2,7 +2,7 @@
 // the split kernel.
 //
 // Output tile per workgroup: 32 or 64 rows x 32..128 tokens; its 8 waves all own the whole tile and
-// split K: wave w takes the 128-column halves w, w + 8, ... of the chunks.  As in the large-tile kernel the
+// split K: wave w takes the 128-column halves w, w + 8, ... of the chunks.  As in the wide kernel the
 // packed words are dequantised in registers straight into A operands of v_mfma_f32_32x32x16_f16, but no
 // B operand is shared between waves, so a wave streams its own through a private ring in LDS
 // (direct-to-LDS loads, RING k-steps ahead, read back through a rotating window of four registers)
@@ -67,7 +67,7 @@ __device__ __forceinline__ void split_workgroup(const GemmBatch &batch, uint32_t
     constexpr int STEPS = 8 * TBLK;             // B blocks of a unit (128 columns): 8 k-steps x token blocks
     constexpr int WSTEPS = 2 * TBLK;            // ... of a packed word (two k-steps)
 
-    // layer and output tile: the same queues per XCD as the large-tile kernel
+    // layer and output tile: every XCD has a queue of workgroups, each layer a run of places in it
     const int xcd = (int)(block % kXcds), pos = (int)(block / kXcds);
     int pi = 0;
     for (int i = 1; i < batch.count; ++i) pi += pos >= batch.p[i].queue_begin ? 1 : 0;   // queue_begin grows with i
