@@ -180,11 +180,14 @@ __device__ __forceinline__ void fold_counters(uint32_t *c, int lane)
     }
 }
 
+// Up to kMergeBackwards indices a workgroup counts the rows of one of the merge kernel's workgroups, which goes through them after it.
+constexpr int kCountRows = 8;    // most rows of a workgroup, one per wave
+constexpr long long kMergeBackwards = 1ll << 26;
 template <int SLOTS>   // 4, 8 or 16
-__global__ void __launch_bounds__(256) counts_kernel(const uint8_t *__restrict__ idx, uint32_t *__restrict__ counts, int K)
+__global__ void __launch_bounds__(kCountRows * 64) counts_kernel(const uint8_t *__restrict__ idx, uint32_t *__restrict__ counts, int K)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = (int)blockIdx.x * 4 + wave;     // N is a multiple of 16: every wave has a row
+    const int n = (int)(blockIdx.x * (blockDim.x / 64)) + wave;     // N is a multiple of 16: every wave has a row
     const uint8_t *row = idx + (size_t)n * K;
     uint32_t c[SLOTS];
 #pragma unroll
@@ -281,14 +284,21 @@ __device__ uint16_t weighted_mean_half(uint16_t a, uint16_t b, uint32_t na, uint
 // re-numbering (idx' = idx - (idx > a), four indices per 32-bit operation) needs nothing else, so the weighted mean, a long
 // serial chain for a few lanes of the first wave, comes after that wave's share of it and hides behind the other waves and
 // workgroups.  Bound: HBM, 2 bytes per index (11008 x 4096: pair and mean in a launch of their own, one thread per row,
-// 6.4 + 13.3 us; now 15.8 us).
+// 6.4 + 13.3 us; in one 16.1 us).  The sizes have usually just been counted: workgroups go round-robin over the XCDs, each with its own L2, so a
+// workgroup takes the rows of the counting workgroup of the same XCD, and the last rows first, which that L2 still holds:
+// 16.1 -> 13.8 us.  (A row order per XCD in the assignment, the counting and the packing too, each the other way round than the
+// one before it, gained nothing there: what a kernel has written is not found again.)
+// Beyond 2^26 indices the last-level cache no longer holds what the round reads and writes, and the other way round costs: a whole round, forwards / backwards:
+// 16384 x 2048 47.0 / 44.8 us, 11008 x 4096 58.8 / 57.1, 8192 x 7168 (4 bits) 82.3 / 81.4, 8192 x 8192 80.6 / 80.7, 16384 x 8192 165.3 / 168.4.
 constexpr int kMergeRows = 8;    // N is a multiple of 16
+static_assert(kCountRows == kMergeRows, "a workgroup's rows were counted on its XCD");
 template <int SLOTS>   // 4, 8 or 16
 __global__ void __launch_bounds__(256) merge_kernel(const uint16_t *cb_in, const uint32_t *counts, const uint8_t *idx,
-                                                    uint16_t *cb_out, uint8_t *out, uint8_t *merged, int K, int ncent)
+                                                    uint16_t *cb_out, uint8_t *out, uint8_t *merged, int K, int ncent, uint32_t rounds)
 {
     __shared__ uint32_t pair[kMergeRows];
-    const int first = (int)blockIdx.x * kMergeRows;
+    const uint32_t group = blockIdx.x < rounds * kXcds ? (rounds - 1 - blockIdx.x / kXcds) * kXcds + blockIdx.x % kXcds : blockIdx.x;
+    const int first = (int)group * kMergeRows;
     // the rows of a workgroup are contiguous: 16 indices per thread and step, AHEAD steps on the way (the first ones
     // while the pairs are found)
     constexpr int AHEAD = 4;
@@ -369,7 +379,8 @@ int launch_assign(const uint16_t *w, const uint16_t *codebook, int ncent, int N,
 
 int launch_counts(const uint8_t *idx, int N, int K, int bits, uint32_t *counts, void *stream)
 {
-    const dim3 grid((unsigned)(N / 4)), block(256);
+    const int rows = (long long)N * K <= kMergeBackwards ? kCountRows : 4;
+    const dim3 grid((unsigned)(N / rows)), block(rows * 64);
     if (bits == 2) hipLaunchKernelGGL(counts_kernel<4>, grid, block, 0, (hipStream_t)stream, idx, counts, K);
     else if (bits == 3) hipLaunchKernelGGL(counts_kernel<8>, grid, block, 0, (hipStream_t)stream, idx, counts, K);
     else hipLaunchKernelGGL(counts_kernel<16>, grid, block, 0, (hipStream_t)stream, idx, counts, K);
@@ -380,9 +391,10 @@ int launch_merge(const uint16_t *cb_in, const uint32_t *counts, const uint8_t *i
                  uint16_t *cb_out, uint8_t *idx_out, uint8_t *merged, void *stream)
 {
     const dim3 grid((unsigned)(N / kMergeRows)), block(256);
-    if (bits == 2) hipLaunchKernelGGL(merge_kernel<4>, grid, block, 0, (hipStream_t)stream, cb_in, counts, idx_in, cb_out, idx_out, merged, K, ncent);
-    else if (bits == 3) hipLaunchKernelGGL(merge_kernel<8>, grid, block, 0, (hipStream_t)stream, cb_in, counts, idx_in, cb_out, idx_out, merged, K, ncent);
-    else hipLaunchKernelGGL(merge_kernel<16>, grid, block, 0, (hipStream_t)stream, cb_in, counts, idx_in, cb_out, idx_out, merged, K, ncent);
+    const uint32_t rounds = (long long)N * K <= kMergeBackwards ? grid.x / kXcds : 0;
+    if (bits == 2) hipLaunchKernelGGL(merge_kernel<4>, grid, block, 0, (hipStream_t)stream, cb_in, counts, idx_in, cb_out, idx_out, merged, K, ncent, rounds);
+    else if (bits == 3) hipLaunchKernelGGL(merge_kernel<8>, grid, block, 0, (hipStream_t)stream, cb_in, counts, idx_in, cb_out, idx_out, merged, K, ncent, rounds);
+    else hipLaunchKernelGGL(merge_kernel<16>, grid, block, 0, (hipStream_t)stream, cb_in, counts, idx_in, cb_out, idx_out, merged, K, ncent, rounds);
     return (int)hipGetLastError();
 }
 

@@ -8,7 +8,6 @@
 
 namespace lcd {
 
-constexpr int kXcds = 8;             // accelerator complex dies of the MI355X, each with its own L2
 
 // packed weights are read by every token block of the layer: default cache policy (the non-temporal
 // hint of the decode kernels costs 2 % here)
