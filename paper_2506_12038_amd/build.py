@@ -46,17 +46,20 @@ EACH_WIDTH = ("lcd_gemm_wide.hip", "lcd_gemm_mixed.hip")
 
 
 def _compile(src: str, width: int, keep_asm: bool) -> Path:
-    obj = BUILD / (src.rsplit(".", 1)[0] + (f"_{width}.o" if width else ".o"))
+    # a folder for each job: kept temporaries are named after the source alone
+    name = src.rsplit(".", 1)[0] + (f"_{width}" if width else "")
+    folder = BUILD / name
+    folder.mkdir(parents=True, exist_ok=True)
+    obj = folder / (name + ".o")
     cmd = [HIPCC, *FLAGS, *EXTRA.get(src, []), *([f"-DLCD_GEMM_BITS={width}"] if width else []), "-c", str(CSRC / src), "-o", str(obj)]
     if keep_asm and src.endswith(".hip"):
         cmd += ["-save-temps=obj"]
-    subprocess.check_call(cmd, cwd=str(BUILD), stderr=subprocess.DEVNULL if not os.environ.get("LCD_BUILD_VERBOSE") else None)
+    subprocess.check_call(cmd, cwd=str(folder), stderr=subprocess.DEVNULL if not os.environ.get("LCD_BUILD_VERBOSE") else None)
     return obj
 
 
 def build_library(keep_asm: bool = False) -> Path:
     """Compile every source and link paper_2506_12038_amd/liblcd.so."""
-    BUILD.mkdir(exist_ok=True)
     srcs = [s for s in SOURCES if (CSRC / s).exists()]
     jobs = sorted(((s, w) for s in srcs for w in ((2, 3, 4) if s in EACH_WIDTH else (0,))), key=lambda j: j[1] == 0)    # (the longest first)
     with ThreadPoolExecutor(max_workers=8) as ex:
