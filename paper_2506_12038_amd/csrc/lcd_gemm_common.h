@@ -20,7 +20,9 @@ typedef __attribute__((address_space(1))) const uint32_t glb_u32;
 // The accumulators of a wave (up to 16 of 16 registers each) live in a[0:255] and are touched only by the
 // inline assembly below, so the compiler never copies them (as loop-carried values it would move
 // all 128 registers to VGPRs and back in every iteration).  The files that include this are compiled
-// with AGPR spilling disabled and use no MFMA builtins, so the compiler itself never allocates an AGPR.
+// with AGPR spilling disabled and use no MFMA builtins, which leaves the compiler one use for an AGPR: a value that it keeps across the
+// loop when a kernel has no vector register left.  It does not know the accumulators to be live between their instructions, so no
+// kernel may come to that: tests/test_prefill_registers.py reads it from the built code, and the distances below as well.
 // The compiler does not look inside the assembly text, so it cannot keep the distance the hardware
 // requires between a vector instruction that writes a register and a matrix instruction that reads it
 // as an operand (it is free to place the last instruction of an operand's dequantisation directly in

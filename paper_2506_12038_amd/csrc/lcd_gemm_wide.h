@@ -298,13 +298,13 @@ __device__ __forceinline__ void wide_tile(const uint8_t *__restrict__ packed_, c
     }
 }
 
-// The life of a workgroup of a launch whose columns have B blocks and B - 1.  XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, each with
-// its own L2.  The tiles of a layer's columns of one width are numbered token-block-major and cut into 8 contiguous runs, one per XCD, so that the workgroups that
-// are resident on an XCD at the same time share one or two columns' activations.  The wider columns come first (of every layer).  Runs differ by one tile; which
-// XCDs have the longer ones goes round from one set of columns to the next, so that no XCD has more than one tile more than another (with all runs of a set as
-// long as its longest, 250 tiles -- two layers of 6400 x 3072, 1244 tokens -- took a second round on six XCDs: 133 us instead of 89).
-template <int BITS, int B, int SPLIT, int PAIRS>
-__device__ __forceinline__ void wide_workgroup(const GemmBatch &batch, uint32_t block, uint8_t *lds)   // lds: wide_lds_bytes of B blocks
+// XCD-aware tile order.  Workgroup ids go round-robin over the 8 XCDs, each with its own L2.  The tiles of a layer's columns of one width are numbered
+// token-block-major and cut into 8 contiguous runs, one per XCD, so that the workgroups that are resident on an XCD at the same time share one or two columns'
+// activations.  The wider columns come first (of every layer).  Runs differ by one tile; which XCDs have the longer ones goes round from one set of columns
+// to the next, so that no XCD has more than one tile more than another (with all runs of a set as long as its longest, 250 tiles -- two layers of 6400 x 3072,
+// 1244 tokens -- took a second round on six XCDs: 133 us instead of 89).
+struct WideTileAt { int layer, second, tile; };    // layer < 0: a workgroup without a tile; second: in the columns of one block less
+__device__ __forceinline__ WideTileAt wide_tile_of(const GemmBatch &batch, uint32_t block)
 {
     const uint32_t xcd = block % kXcds;
     uint32_t pos = block / kXcds, turn = 0;
@@ -313,18 +313,25 @@ __device__ __forceinline__ void wide_workgroup(const GemmBatch &batch, uint32_t 
             const uint32_t tiles = batch.p[i].tiles[second], rest = tiles % kXcds;
             const uint32_t ones = (1u << rest) - 1, longer = (ones << turn | ones >> (kXcds - turn)) & 255u;     // XCDs with a run of one more
             const uint32_t run = tiles / kXcds + (longer >> xcd & 1);
-            if (pos >= run) {
-                pos -= run;
-                turn = (turn + rest) % kXcds;
-                continue;
-            }
-            const GemmProblem &pb = batch.p[i];
-            const int out_tile = (int)(xcd * (tiles / kXcds) + __builtin_popcount(longer & ((1u << xcd) - 1)) + pos);
-            const int bx = out_tile % pb.grid_rows, by = out_tile / pb.grid_rows;
-            if (!second) wide_tile<BITS, B, SPLIT, PAIRS>(pb.packed, pb.lutB, pb.xs, pb.y, batch.M, batch.Mpad >> 5, pb.N, pb.K, bx, by * B, lds, pb.out_scale);
-            else if constexpr (B > 1) wide_tile<BITS, B - 1, SPLIT, PAIRS>(pb.packed, pb.lutB, pb.xs, pb.y, batch.M, batch.Mpad >> 5, pb.N, pb.K, bx, batch.tiles.big * B + by * (B - 1), lds, pb.out_scale);
-            return;
+            if (pos < run) return WideTileAt{i, second, (int)(xcd * (tiles / kXcds) + __builtin_popcount(longer & ((1u << xcd) - 1)) + pos)};
+            pos -= run;
+            turn = (turn + rest) % kXcds;
         }
+    return WideTileAt{-1, 0, 0};
+}
+
+// The life of a workgroup of a launch whose columns have B blocks and B - 1.  The tile is found before either body begins: inside the loop over the layers
+// the compiler moved what a lane's position gives in front of it and kept it through the products, up to 40 registers, in eight kernels some of them in accumulation
+// registers.  Now none are, with 4 vector registers or more to spare; the same time.
+template <int BITS, int B, int SPLIT, int PAIRS>
+__device__ __forceinline__ void wide_workgroup(const GemmBatch &batch, uint32_t block, uint8_t *lds)   // lds: wide_lds_bytes of B blocks
+{
+    const WideTileAt at = wide_tile_of(batch, block);
+    if (at.layer < 0) return;
+    const GemmProblem &pb = batch.p[at.layer];
+    const int bx = at.tile % pb.grid_rows, by = at.tile / pb.grid_rows;
+    if (!at.second) wide_tile<BITS, B, SPLIT, PAIRS>(pb.packed, pb.lutB, pb.xs, pb.y, batch.M, batch.Mpad >> 5, pb.N, pb.K, bx, by * B, lds, pb.out_scale);
+    else if constexpr (B > 1) wide_tile<BITS, B - 1, SPLIT, PAIRS>(pb.packed, pb.lutB, pb.xs, pb.y, batch.M, batch.Mpad >> 5, pb.N, pb.K, bx, batch.tiles.big * B + by * (B - 1), lds, pb.out_scale);
 }
 
 }  // namespace lcd
