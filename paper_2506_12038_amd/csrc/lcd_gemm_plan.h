@@ -1,6 +1,14 @@
-// Which tiles a launch of the wide prefill kernel takes, and which of its two forms takes a layer.  Host code, no HIP.
+// Which tiles a launch of the wide prefill kernel takes, which workgroup takes which tile, and which of the kernel's two forms takes a layer.
+// Host code that any C++ compiler takes, but for wide_tile_of, which the kernel runs too.
 #pragma once
 #include <cmath>
+#include "lcd_internal.h"
+
+#ifdef __HIPCC__
+#define LCD_HOST_DEVICE __host__ __device__ __forceinline__
+#else
+#define LCD_HOST_DEVICE inline
+#endif
 
 namespace lcd {
 
@@ -19,6 +27,31 @@ inline WideTiles wide_columns(int form, int token_blocks, int columns)
 {
     const int blocks = (token_blocks + columns - 1) / columns;
     return WideTiles{form, blocks, token_blocks - columns * (blocks - 1), columns};
+}
+
+// ---- numbering ------------------------------------------------------------------------------------------
+// XCD-aware tile order.  Workgroup ids go round-robin over the 8 XCDs, each with its own L2.  The tiles of a layer's columns of one width are numbered
+// token-block-major and cut into 8 contiguous runs, one per XCD, so that the workgroups that are resident on an XCD at the same time share one or two columns'
+// activations.  The wider columns come first (of every layer).  Runs differ by one tile; which XCDs have the longer ones goes round from one set of columns
+// to the next, so that no XCD has more than one tile more than another (with all runs of a set as long as its longest, 250 tiles -- two layers of 6400 x 3072,
+// 1244 tokens -- took a second round on six XCDs: 133 us instead of 89).
+struct WideTileAt { int layer, second, tile; };    // layer < 0: a workgroup without a tile; second: in the columns of one block less
+// batch.p[i].tiles[second]: a layer's tiles in either set of columns
+template <class Batch>
+LCD_HOST_DEVICE WideTileAt wide_tile_of(const Batch &batch, uint32_t block)
+{
+    const uint32_t xcd = block % kXcds;
+    uint32_t pos = block / kXcds, turn = 0;
+    for (int second = 0; second < 2; ++second)
+        for (int i = 0; i < batch.count; ++i) {
+            const uint32_t tiles = batch.p[i].tiles[second], rest = tiles % kXcds;
+            const uint32_t ones = (1u << rest) - 1, longer = (ones << turn | ones >> (kXcds - turn)) & 255u;     // XCDs with a run of one more
+            const uint32_t run = tiles / kXcds + (longer >> xcd & 1);
+            if (pos < run) return WideTileAt{i, second, (int)(xcd * (tiles / kXcds) + __builtin_popcount(longer & ((1u << xcd) - 1)) + pos)};
+            pos -= run;
+            turn = (turn + rest) % kXcds;
+        }
+    return WideTileAt{-1, 0, 0};
 }
 
 // ---- time ---------------------------------------------------------------------------------------------

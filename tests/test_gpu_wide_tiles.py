@@ -1,4 +1,4 @@
-"""The wide prefill kernel's tiles: the choice (csrc/lcd_gemm_plan.h, compiled here) and the tile numbering on the CPU, every tile shape
+"""The wide prefill kernel's tiles: the choice and the tile numbering (csrc/lcd_gemm_plan.h, compiled here) on the CPU, every tile shape
 on the GPU against the oracle."""
 import functools
 import random
@@ -15,11 +15,27 @@ import paper_2506_12038_amd as lcd
 from gpu_common import assert_parity, to_dev
 
 CSRC = Path(lcd.__file__).parent / "csrc"
+INCLUDE = CSRC.parent.parent / "include"
 MAIN = r"""
 #include <cstdio>
 #include "lcd_gemm_plan.h"
-int main()
+// the numbering: a layer's tiles in either set of columns, then every workgroup's tile
+static int tiles()
 {
+    struct { struct { uint32_t tiles[2]; } p[16]; int count; } batch;
+    unsigned blocks;
+    while (scanf("%d %u", &batch.count, &blocks) == 2) {
+        for (int i = 0; i < batch.count; ++i) if (scanf("%u %u", &batch.p[i].tiles[0], &batch.p[i].tiles[1]) != 2) return 1;
+        for (unsigned b = 0; b < blocks; ++b) {
+            const lcd::WideTileAt at = lcd::wide_tile_of(batch, b);
+            printf("%d %d %d\n", at.layer, at.second, at.tile);
+        }
+    }
+    return 0;
+}
+int main(int argc, char **)
+{
+    if (argc > 1) return tiles();
     int whole, bits, M, count;
     while (scanf("%d %d %d %d", &whole, &bits, &M, &count) == 4) {
         lcd::WideLayer l[16];
@@ -38,7 +54,7 @@ def _program():
     import tempfile
     d = Path(tempfile.mkdtemp())
     (d / "plan.cpp").write_text(MAIN)
-    subprocess.run(["g++", "-O1", "-std=c++17", f"-I{CSRC}", str(d / "plan.cpp"), "-o", str(d / "plan")], check=True)
+    subprocess.run(["g++", "-O1", "-std=c++17", f"-I{CSRC}", f"-I{INCLUDE}", str(d / "plan.cpp"), "-o", str(d / "plan")], check=True)
     return d / "plan"
 
 
@@ -73,26 +89,20 @@ def test_whole_layers_have_whole_tiles():
     assert all(columns > 0 for _, _, _, columns in _choices(cases))
 
 
-def _tile_of(block, tiles):
-    """The kernel's numbering: (set of columns and layer, tile) of workgroup `block`, tiles: their numbers in order."""
-    xcd, pos, turn = block % 8, block // 8, 0
-    for entry, n in enumerate(tiles):
-        rest = n % 8
-        longer = [(x - turn) % 8 < rest for x in range(8)]
-        run = n // 8 + longer[xcd]
-        if pos < run:
-            return entry, xcd * (n // 8) + sum(longer[:xcd]) + pos
-        pos, turn = pos - run, (turn + rest) % 8
-    return None
-
-
 @pytest.mark.parametrize("seed", range(20))
 def test_every_tile_has_one_workgroup(seed):
     rng = random.Random(seed)
-    tiles = [rng.choice([0, rng.randint(1, 20), rng.randint(1, 400)]) for _ in range(rng.randint(1, 12))]
-    queue = -(-sum(tiles) // 8)
-    got = [t for t in (_tile_of(b, tiles) for b in range(8 * queue)) if t is not None]
-    assert sorted(got) == [(e, i) for e, n in enumerate(tiles) for i in range(n)]
+    tiles = [[rng.choice([0, rng.randint(1, 20), rng.randint(1, 400)]) for _ in range(2)] for _ in range(rng.choice([1, 1, 2, 3, 7, 16]))]
+    queue = -(-sum(map(sum, tiles)) // 8)        # the launch: as many workgroups on every XCD
+    text = f"{len(tiles)} {8 * queue}\n" + "\n".join(f"{a} {b}" for a, b in tiles)
+    out = subprocess.run([str(_program()), "tiles"], input=text, capture_output=True, text=True, check=True).stdout
+    got = [tuple(map(int, line.split())) for line in out.splitlines()]
+    assert len(got) == 8 * queue
+    assert sorted(t for t in got if t[0] >= 0) == [(i, s, t) for i, sets in enumerate(tiles) for s in (0, 1) for t in range(sets[s])]
+    # an XCD's workgroups go through the wider columns of all layers first, a layer's tiles in rising order
+    for xcd in range(8):
+        own = [(s, i, t) for i, s, t in got[xcd::8] if i >= 0]
+        assert own == sorted(own)
 
 
 @functools.lru_cache(None)
