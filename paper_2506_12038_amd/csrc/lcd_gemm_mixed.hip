@@ -1,8 +1,8 @@
 // Prefill of a group whose layers take different kernels (gfx950): the wide kernel's tiles (in halves) and the split kernel's in ONE
 // launch.  Both kinds have workgroups of 512 threads that fill a compute unit; every XCD's queue holds the wide tiles
 // first (the longest), so that the compute units their last round leaves idle start on the others.  One launch after the other, each
-// leaves its own last round behind: q 4096, k and v 1024 rows, K = 4096, 3 bits, 1100 tokens (as they were before the wide kernel: 144 tiles of 256 x 128,
-// then 288 split ones): 95 us, in one launch 72.  q 8192, k and v 1024 rows, K = 8192: 700 tokens 147 -> 128, 1100 tokens 235 -> 196.
+// leaves its own last round behind: q 4096, k and v 1024 rows, K = 4096, 3 bits, 1100 tokens 76.8 us, in one launch 67.3; q 8192, k and v 1024 rows,
+// K = 8192, 3 bits, 700 tokens 125.4, in one launch 115.2.  When calls take it: plan_launches in lcd_gemm_plan.h.
 // The tiles are those of the two kernels, so a layer's bits do not depend on its neighbours.
 #include <hip/hip_runtime.h>
 #include "lcd_gemm_wide.h"

@@ -1,4 +1,4 @@
-// Which tiles a launch of the wide prefill kernel takes, which workgroup takes which tile, and which of the kernel's two forms takes a layer.
+// Which prefill kernel takes a layer, which tiles a launch of the wide and of the split kernel takes, and which workgroup takes which wide tile.
 // Host code that any C++ compiler takes, but for wide_tile_of, which the kernel runs too.
 #pragma once
 #include <cmath>
@@ -12,7 +12,58 @@
 
 namespace lcd {
 
-// ---- tiles -------------------------------------------------------------------------------------------
+struct LayerSize { int N, K; };
+
+// ---- kernels -----------------------------------------------------------------------------------------
+// Which kernel takes a layer.  The rules look at the layer and the number of tokens alone, never at the group it is
+// called in: the kernels add in different orders, and a layer's result must not depend on its neighbours.
+// Up to 16 tokens the decode kernels (the dequantising one, except for INT8 codes with 2-bit indices).  Up to 32 tokens the tokens kernel, which needs no smoothing launch,
+// also keeps the small layers.  One call with 32 tokens, weights from memory, tokens kernel / split kernel, 2, 3 and 4 bits: 2048 x 2048
+// 6.4/8.1 6.7/8.9 7.0/9.3 us, 2048 x 4096 8.3/10.6 8.7/11.4 9.3/11.9, 11008 x 1024 7.1/8.7 7.9/9.0 7.7/9.8, 28672 x 512 11.9/12.0 13.2/12.4 16.6/13.3;
+// beyond the line 4096 x 4096 8.9/10.9 9.4/11.6 10.2/12.5, 6144 x 4096 11.6/11.0 12.5/11.8 15.1/13.0, 8192 x 4096 11.7/11.2 13.0/12.1 15.9/13.8.  A
+// layer of 4096 x 4096 alone would gain from the tokens kernel too; three of them in one call, which must take the same kernel, are
+// 12288 x 4096 to it and would lose.
+inline bool decode_takes(int M, int N, int K)
+{
+    return (M <= 16 || (M <= kDecodeTokens && (long long)N * K < (1ll << 24))) && (long long)M * K * 2 < (1ll << 32);
+}
+// The narrow kernel takes layers of few tokens: it reads every activation once per compute unit and pads tokens to 16 only, the split kernel
+// reads a tile's activations once per 64 rows.  So the line lies where a compute unit has one row tile only (up to 4096 rows), which the
+// activations of many tokens or columns do not pay for; beyond 64 tokens it holds three row tiles at a time, so that a fourth costs a second
+// pass.  One call, weights from memory, split (up to 32 tokens and beyond 128 large tiles: as before it) / narrow, 2, 3 and 4 bits, us:
+//   32 tokens   4096 x 4096  9.9/9.5 10.4/10.0 11.9/10.4     4096 x 11008 16.9/15.8 19.9/16.5 22.5/17.9     28672 x 8192, twice 62.6/55.7 81.4/70.5 92.5/94.0
+//   40          4096 x 4096 10.6/10.5 11.1/10.8 12.8/11.4    4096 x 11008 18.3/18.1 20.3/19.4 23.4/20.4     11008 x 4096, twice 27.9/18.2 30.8/20.9 35.4/26.9
+//   48          4096 x 11008 17.9/19.4 20.3/20.5 23.2/21.3   8192 x 8192 20.0/17.8 24.2/19.5 26.1/22.4      28672 x 8192, twice 89.1/67.9 101.6/82.0 121.3/105.7
+//   64          4096 x 4096 10.7/11.8 11.2/12.2 12.8/12.5    8192 x 8192 20.2/20.0 24.4/21.9 26.0/24.5      11008 x 4096, twice 29.5/25.0 31.8/28.0 37.1/32.2
+//   80          4096 x 4096 12.7/13.6 14.5/14.0 15.9/14.5    8192 x 8192 27.7/23.5 30.0/25.1 35.4/27.5      11008 x 4096, twice 36.0/27.9 39.3/30.8 43.5/34.9
+//   old time / new, over all widths   48 tokens, 1024..4096 rows: K = 2048 1.02..1.14, 4096 0.94..1.11, 8192 0.82..1.09     64 tokens: K = 2048 0.95..1.11, 4096 0.87..1.04
+//                                     80 tokens: 5120 rows 0.84..1.25, 6144..11008 1.05..1.33, 16384 0.83..0.94             96 tokens: 6144..11008 rows 0.94..1.23
+inline bool narrow_takes(int M, int N, int K, int bits)
+{
+    if (M <= 16 || M > kNarrowTokens || (long long)M * K * 2 >= (1ll << 32)) return false;
+    if (N > 4096) return M <= 64 || (N >= 6144 && N <= 12288);
+    if (M <= 32) return true;
+    if (M <= 48) return K <= 2048 || (N > 2048 && (K <= 4096 || bits > 2));
+    return M <= 64 && N >= 2048 && K <= 2048;
+}
+// The split kernel takes layers of few output tiles: those that fit one round of its largest tile (64 x 128) on the 256 compute units (the whole
+// chip, whatever part of it a process sees: a layer's bits must not depend on that).  Beyond that the wide kernel's tiles, which share the activations among
+// four or eight waves, win.  A call without its smoothing, split / wide, 2, 3 and 4 bits, us:
+//   one round         4096 x 4096, 333 tokens 17.3/20.7 19.3/24.4 21.2/29.3, 450 (256 tiles) 22.5/22.7 24.0/26.4 25.7/30.8; 4096 x 11008, 333 39.9/47.9 41.4/54.9 47.4/67.7;
+//                     8192 x 8192, 224 tokens 37.8/39.0 37.7/45.7 41.9/54.0; 11008 x 4096, 100 tokens 15.5/18.5 16.2/24.0 19.5/28.6
+//   beyond            4096 x 4096, 640 tokens (large tiles of 256 x 128 as before / wide) 30.8/26.4 32.8/29.0 36.3/32.9; 11008 x 4096, 160 tokens 25.2/22.5 28.8/26.3 31.7/30.4;
+//                     8192 x 8192, 333 tokens 54.2/49.2 57.7/54.4 68.6/62.5; two of 11008 x 4096, 333 tokens 84.8/69.8 94.5/77.1 103.8/89.5
+//   several layers    three of 4096 x 4096, 333 tokens 45.5/39.8 49.7/42.9 58.9/50.8, 450 58.8/45.7 63.0/49.6 68.8/58.1: hence the lower line at 2 bits, where a
+//                     single layer of a nearly full round is as fast either way
+// (The split kernel addresses the activations with 32 bits.)
+inline bool split_takes(int M, int N, int K, int bits)
+{
+    const long long blocks = (M + 127) / 128, rows64 = (N + 63) / 64;
+    return rows64 * blocks <= (bits == 2 ? 224 : 256) && blocks * 128 * K * 2 < (1ll << 32);
+}
+
+
+// ---- wide tiles -------------------------------------------------------------------------------------------
 // A tile of the wide kernel (lcd_gemm_wide.h) is 256 rows (or 128) x up to 8 blocks of 32 tokens.  The blocks of a call are dealt out to columns of tiles as
 // evenly as they go: `big` columns of `blocks`, then columns of one block less.
 struct WideTiles {
@@ -65,10 +116,9 @@ constexpr WideTime kWideTime[3][8] = {
      {5.5, {13.3, 13.85, 15.5}, {20.1, 20.8, 22.5}}, {6.9, {14.8, 15.2, 16.6}, {22.6, 23.1, 24.8}}},
 };
 
-struct WideLayer { int N, K; };
 // Rounds of workgroups over the compute units, the columns of more blocks first.  Each round takes the time of its longest workgroup alone, or what a full chip
 // would take of it, smoothed.  more_us: shorter workgroups of another kind that follow in the same launch, in us of the whole chip: they fill the last round.
-inline double wide_time(const WideTiles &t, const WideLayer *layers, int count, int bits, int cus, double more_us = 0.0)
+inline double wide_time(const WideTiles &t, const LayerSize *layers, int count, int bits, int cus, double more_us = 0.0)
 {
     double us = 2.5, longest = 0.0, energy = 0.0, all = 0.0;
     int room = cus;
@@ -103,7 +153,7 @@ inline double wide_time(const WideTiles &t, const WideLayer *layers, int count, 
 }
 
 // The tiles with the least time of those that a form of the kernel has.
-inline WideTiles choose_wide(bool whole, const WideLayer *layers, int count, int token_blocks, int bits, int cus, double *time = nullptr, double more_us = 0.0)
+inline WideTiles choose_wide(bool whole, const LayerSize *layers, int count, int token_blocks, int bits, int cus, double *time = nullptr)
 {
     WideTiles best{};
     double least = 0.0;
@@ -112,7 +162,7 @@ inline WideTiles choose_wide(bool whole, const WideLayer *layers, int count, int
         for (int b = most; b >= fewest; --b) {
             const WideTiles t = wide_columns(form, token_blocks, (token_blocks + b - 1) / b);
             if (whole && t.blocks < 5) continue;
-            const double us = wide_time(t, layers, count, bits, cus, more_us);
+            const double us = wide_time(t, layers, count, bits, cus);
             if (best.columns == 0 || us < least) { best = t; least = us; }
         }
     }
@@ -123,7 +173,7 @@ inline WideTiles choose_wide(bool whole, const WideLayer *layers, int count, int
 // Which form takes a layer.  They add in different orders, so this looks at the layer and the tokens alone.
 inline bool whole_takes(int M, int N, int K, int bits)
 {
-    const WideLayer pair[2] = {{N, K}, {N, K}};
+    const LayerSize pair[2] = {{N, K}, {N, K}};
     const int blocks = (M + 31) / 32;
     if (blocks < 5) return false;
     double whole[2], halves[2];
@@ -132,6 +182,94 @@ inline bool whole_takes(int M, int N, int K, int bits)
         choose_wide(false, pair, n + 1, blocks, bits, 256, &halves[n]);
     }
     return whole[0] * whole[1] < halves[0] * halves[1] && whole[0] < 1.1 * halves[0];
+}
+
+// The kernel of a layer.  whole: whole_takes, or a copy of its answers.
+enum PrefillKernel { kDecodeKernels, kNarrowKernel, kSplitKernel, kWideHalves, kWideWhole };
+inline PrefillKernel prefill_kernel(int M, int N, int K, int bits, bool (*whole)(int, int, int, int) = whole_takes)
+{
+    if (decode_takes(M, N, K)) return kDecodeKernels;
+    if (narrow_takes(M, N, K, bits)) return kNarrowKernel;
+    if (split_takes(M, N, K, bits)) return kSplitKernel;
+    return whole(M, N, K, bits) ? kWideWhole : kWideHalves;
+}
+
+// ---- split tiles --------------------------------------------------------------------------------------
+// Tile of a launch of the split kernel: rounds of workgroups over the compute units times the time of one workgroup.  Measured
+// in single rounds (K = 4096 and 11008): a fixed part, and a part per column that is bound by the activations' way into LDS
+// (75..98 GB/s per compute unit; 32 tokens x 64 rows: by the dequantiser).  In launches of several rounds every tile takes longer
+// than that (the rounds share the L2), but their order holds: 177 launches timed with each of the six tiles (1 to 3 layers of 1024..13824
+// rows, K = 2048..11008, 33..512 tokens, 2, 3 and 4 bits) took 1.002 times the best tile's time in the mean, 1.03 at the ninth decile,
+// 1.14 at most (three layers of 2048 x 2048, 512 tokens, 3 bits: 32.8 against 28.9 us).
+struct SplitTile { int pairs, blocks; double fixed_us, column_ns[3]; };   // column_ns: 2, 3, 4 bits
+constexpr SplitTile kSplitTiles[] = {
+    {2, 4, 3.0, {2.58, 2.70, 3.13}}, {2, 3, 2.5, {2.13, 2.40, 3.05}}, {2, 2, 2.0, {1.56, 1.74, 2.33}},
+    {2, 1, 1.5, {1.34, 1.66, 2.58}}, {1, 2, 1.5, {1.48, 1.60, 1.69}}, {1, 1, 1.3, {0.79, 0.88, 1.17}},
+};
+// time of all workgroups of a tile's launch one after the other, and their number
+inline double split_work(const LayerSize *layers, int count, const SplitTile &t, int M, int bits, double &wgs)
+{
+    double work = 0.0;
+    wgs = 0.0;
+    for (int q = 0; q < count; ++q) {
+        const double n = (double)((layers[q].N + 32 * t.pairs - 1) / (32 * t.pairs)) * ((M + 32 * t.blocks - 1) / (32 * t.blocks));
+        wgs += n;
+        work += n * (t.fixed_us + 1e-3 * t.column_ns[bits - 2] * layers[q].K);
+    }
+    return work;
+}
+inline const SplitTile &choose_split_tile(const LayerSize *layers, int count, int M, int bits, int cus)
+{
+    const SplitTile *best = nullptr;
+    double best_time = 0.0;
+    for (const SplitTile &t : kSplitTiles) {
+        double wgs;
+        const double work = split_work(layers, count, t, M, bits, wgs), time = __builtin_ceil(wgs / cus) * work / wgs;
+        if (!best || time < best_time) { best = &t; best_time = time; }
+    }
+    return *best;
+}
+// Next to wide tiles there are no rounds of their own to fill: the tile with the least work of the two that cost least per output.
+inline const SplitTile &choose_mixed_tile(const LayerSize *layers, int count, int M, int bits)
+{
+    double wgs;
+    return split_work(layers, count, kSplitTiles[0], M, bits, wgs) <= split_work(layers, count, kSplitTiles[1], M, bits, wgs) ? kSplitTiles[0] : kSplitTiles[1];
+}
+
+
+// ---- the matrix launches of a call ---------------------------------------------------------------------
+// The launches of a call's split layers and wide layers in halves: one for both kinds (lcd_gemm_mixed.hip: wide tiles of 4 blocks, or of 3 throughout), whose
+// split tiles fill the wide tiles' last round, wherever the tokens give such tiles; else one each with the tiles that suit it best.  357 groups with both
+// kinds and such tiles (blocks of 7 layers, q, k, v with fewer rows in k and v, random groups of 2 to 8 layers; 97 to 1100 tokens; 2, 3 and 4 bits): one launch
+// takes 1.003 times the better way's time in the mean, 1.10 at most (4944 + 1200 rows, K = 4096, 531 tokens, 4 bits: 53.5 us, apart 48.8), apart
+// 1.088 and 1.39 (q, k, v of 5120 + 1280 + 1280 rows, K = 5120, 500 tokens, 3 bits 51 and 56; all of a 7B block, 333 tokens, 3 bits 166 and 194).  A model's
+// choice between the two was worse: 1.02.
+struct MatrixLaunches {
+    WideTiles halves;
+    const SplitTile *split;
+    bool together;
+};
+inline bool mixed_has(const WideTiles &t) { return t.blocks == 4 || (t.blocks == 3 && t.big == t.columns); }
+inline MatrixLaunches plan_launches(const LayerSize *halves, int halves_count, const LayerSize *split, int split_count, int M, int bits, int cus)
+{
+    const int token_blocks = (M + 31) / 32;
+    MatrixLaunches l{};
+    if (halves_count > 0 && split_count > 0) {
+        const SplitTile &next = choose_mixed_tile(split, split_count, M, bits);
+        double wgs, least = 0.0;
+        const double more_us = 1.5 * split_work(split, split_count, next, M, bits, wgs) / cus;      // (next to wide tiles: 1.5 times what they take in a round of their own)
+        for (int form = kHalves128; form <= kHalves256; ++form)
+            for (int b = 4; b >= 3; --b) {
+                const WideTiles t = wide_columns(form, token_blocks, (token_blocks + b - 1) / b);
+                if (!mixed_has(t)) continue;
+                const double us = wide_time(t, halves, halves_count, bits, cus, more_us);
+                if (!l.together || us < least) { l = MatrixLaunches{t, &next, true}; least = us; }
+            }
+        if (l.together) return l;
+    }
+    if (halves_count > 0) l.halves = choose_wide(false, halves, halves_count, token_blocks, bits, cus);
+    if (split_count > 0) l.split = &choose_split_tile(split, split_count, M, bits, cus);
+    return l;
 }
 
 }  // namespace lcd

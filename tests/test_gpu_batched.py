@@ -94,7 +94,7 @@ def test_gemm_split_tile_edges(bits, shape):
 
 
 def _narrow_takes(M, N, K, bits):
-    """Layers of the narrow kernel, by the rule of lcd_gemm.hip."""
+    """Layers of the narrow kernel, by the rule of lcd_gemm_plan.h."""
     if M <= 16 or M > 96:
         return False
     if N > 4096:
@@ -139,10 +139,10 @@ def test_narrow_kernel_grouped_and_quantised(bits, M):
 
 
 def _split_tile_of(N, K, M, bits):
-    """(32-row pairs, 32-token blocks) of the split kernel's tile for one layer, by the rule and the table of lcd_gemm.hip."""
+    """(32-row pairs, 32-token blocks) of the split kernel's tile for one layer, by the rule and the table of lcd_gemm_plan.h."""
     import math, re, torch
     from pathlib import Path
-    table = re.findall(r"\{(\d), (\d), ([\d.]+), \{([\d., ]+)\}\}", (Path(lcd.__file__).parent / "csrc" / "lcd_gemm.hip").read_text())
+    table = re.findall(r"\{(\d), (\d), ([\d.]+), \{([\d., ]+)\}\}", (Path(lcd.__file__).parent / "csrc" / "lcd_gemm_plan.h").read_text())
     assert len(table) == 6
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     times = []

@@ -2,9 +2,6 @@
 on the GPU against the oracle."""
 import functools
 import random
-import shutil
-import subprocess
-from pathlib import Path
 
 import numpy as np
 import pytest
@@ -12,57 +9,8 @@ import pytest
 import synth
 import oracle
 import paper_2506_12038_amd as lcd
+from gemm_plan import choices, numbering
 from gpu_common import assert_parity, to_dev
-
-CSRC = Path(lcd.__file__).parent / "csrc"
-INCLUDE = CSRC.parent.parent / "include"
-MAIN = r"""
-#include <cstdio>
-#include "lcd_gemm_plan.h"
-// the numbering: a layer's tiles in either set of columns, then every workgroup's tile
-static int tiles()
-{
-    struct { struct { uint32_t tiles[2]; } p[16]; int count; } batch;
-    unsigned blocks;
-    while (scanf("%d %u", &batch.count, &blocks) == 2) {
-        for (int i = 0; i < batch.count; ++i) if (scanf("%u %u", &batch.p[i].tiles[0], &batch.p[i].tiles[1]) != 2) return 1;
-        for (unsigned b = 0; b < blocks; ++b) {
-            const lcd::WideTileAt at = lcd::wide_tile_of(batch, b);
-            printf("%d %d %d\n", at.layer, at.second, at.tile);
-        }
-    }
-    return 0;
-}
-int main(int argc, char **)
-{
-    if (argc > 1) return tiles();
-    int whole, bits, M, count;
-    while (scanf("%d %d %d %d", &whole, &bits, &M, &count) == 4) {
-        lcd::WideLayer l[16];
-        for (int i = 0; i < count; ++i) if (scanf("%d %d", &l[i].N, &l[i].K) != 2) return 1;
-        const lcd::WideTiles t = lcd::choose_wide(whole < 0 ? lcd::whole_takes(M, l[0].N, l[0].K, bits) : whole, l, count, (M + 31) / 32, bits, 256);
-        printf("%d %d %d %d\n", t.form, t.blocks, t.big, t.columns);
-    }
-}
-"""
-
-
-@functools.lru_cache(None)
-def _program():
-    if shutil.which("g++") is None:
-        pytest.skip("no g++")
-    import tempfile
-    d = Path(tempfile.mkdtemp())
-    (d / "plan.cpp").write_text(MAIN)
-    subprocess.run(["g++", "-O1", "-std=c++17", f"-I{CSRC}", f"-I{INCLUDE}", str(d / "plan.cpp"), "-o", str(d / "plan")], check=True)
-    return d / "plan"
-
-
-def _choices(cases):
-    """(form, blocks, big, columns) of every (whole or -1: as the rule has it, bits, M, [(N, K), ...])."""
-    text = "\n".join(f"{w} {b} {M} {len(ls)} " + " ".join(f"{n} {k}" for n, k in ls) for w, b, M, ls in cases)
-    out = subprocess.run([str(_program())], input=text, capture_output=True, text=True, check=True).stdout
-    return [tuple(map(int, line.split())) for line in out.splitlines()]
 
 
 def _case(rng):
@@ -73,7 +21,7 @@ def _case(rng):
 def test_columns_hold_every_block_once():
     rng = random.Random(7)
     cases = [_case(rng) for _ in range(2000)]
-    for (whole, bits, M, layers), (form, blocks, big, columns) in zip(cases, _choices(cases)):
+    for (whole, bits, M, layers), (form, blocks, big, columns) in zip(cases, choices(cases)):
         token_blocks = -(-M // 32)
         if whole and token_blocks < 5:
             assert columns == 0           # (no such tile: the rule never asks for one)
@@ -86,7 +34,7 @@ def test_columns_hold_every_block_once():
 def test_whole_layers_have_whole_tiles():
     rng = random.Random(8)
     cases = [(-1, b, M, ls[:1]) for _, b, M, ls in (_case(rng) for _ in range(2000))]
-    assert all(columns > 0 for _, _, _, columns in _choices(cases))
+    assert all(columns > 0 for _, _, _, columns in choices(cases))
 
 
 @pytest.mark.parametrize("seed", range(20))
@@ -94,9 +42,7 @@ def test_every_tile_has_one_workgroup(seed):
     rng = random.Random(seed)
     tiles = [[rng.choice([0, rng.randint(1, 20), rng.randint(1, 400)]) for _ in range(2)] for _ in range(rng.choice([1, 1, 2, 3, 7, 16]))]
     queue = -(-sum(map(sum, tiles)) // 8)        # the launch: as many workgroups on every XCD
-    text = f"{len(tiles)} {8 * queue}\n" + "\n".join(f"{a} {b}" for a, b in tiles)
-    out = subprocess.run([str(_program()), "tiles"], input=text, capture_output=True, text=True, check=True).stdout
-    got = [tuple(map(int, line.split())) for line in out.splitlines()]
+    got = numbering(tiles, 8 * queue)
     assert len(got) == 8 * queue
     assert sorted(t for t in got if t[0] >= 0) == [(i, s, t) for i, sets in enumerate(tiles) for s in (0, 1) for t in range(sets[s])]
     # an XCD's workgroups go through the wider columns of all layers first, a layer's tiles in rising order
@@ -110,7 +56,7 @@ def _shapes(bits):
     """A layer for every (form, blocks, whether there are columns of one block less) that a single call takes."""
     sizes = [(N, K, M) for K in (512, 768) for N in (4112, 8208, 16400, 20496) for M in range(130, 2049, 61) if -(-N // 64) * -(-M // 128) > 256]
     found = {}
-    for (N, K, M), (form, blocks, big, columns) in zip(sizes, _choices([(-1, bits, M, [(N, K)]) for N, K, M in sizes])):
+    for (N, K, M), (form, blocks, big, columns) in zip(sizes, choices([(-1, bits, M, [(N, K)]) for N, K, M in sizes])):
         found.setdefault((form, blocks, big < columns), (N, K, M))
     return found
 
