@@ -9,8 +9,8 @@ import pytest
 import synth
 import oracle
 import paper_2506_12038_amd as lcd
-from gemm_plan import choices, numbering
-from gpu_common import assert_parity, to_dev
+from gemm_plan import HALVES, WHOLE, choices, launches, numbering
+from gpu_common import TOL, assert_parity, to_dev
 
 
 def _case(rng):
@@ -51,30 +51,53 @@ def test_every_tile_has_one_workgroup(seed):
         assert own == sorted(own)
 
 
+# (form, blocks, whether there are columns of one block less) that single calls take
+TILES = [(form, blocks, narrower) for form, most in ((0, range(2, 5)), (1, range(2, 5)), (2, range(5, 9))) for blocks in most for narrower in (False, True)]
+
+
 @functools.lru_cache(None)
 def _shapes(bits):
-    """A layer for every (form, blocks, whether there are columns of one block less) that a single call takes."""
-    sizes = [(N, K, M) for K in (512, 768) for N in (4112, 8208, 16400, 20496) for M in range(130, 2049, 61) if -(-N // 64) * -(-M // 128) > 256]
+    """Layers with the least work for every tile: rows that end inside a tile, the last token block not full, an even and (halves) an odd number of chunks."""
+    rng = random.Random(bits)
+    sizes = [(16 * int(2 ** rng.uniform(6, 11)), 256 * int(2 ** rng.uniform(0, 3.5)), int(2 ** rng.uniform(6.1, 11.2))) for _ in range(60000)]
+    sizes = [(N, K, M) for N, K, M in sizes if N % 256 and M % 32]
     found = {}
-    for (N, K, M), (form, blocks, big, columns) in zip(sizes, choices([(-1, bits, M, [(N, K)]) for N, K, M in sizes])):
-        found.setdefault((form, blocks, big < columns), (N, K, M))
+    for (N, K, M), (kernels, *_), (form, blocks, big, columns) in zip(sizes, launches([(bits, M, [(N, K)]) for N, K, M in sizes]),
+                                                                        choices([(-1, bits, M, [(N, K)]) for N, K, M in sizes])):
+        if kernels[0] in (HALVES, WHOLE):
+            key = (form, blocks, big < columns), K // 256 % 2 if form < 2 else 0
+            if key not in found or N * K * M < np.prod(found[key]):
+                found[key] = N, K, M
     return found
 
 
-# Rows that end inside a tile (N = 16 more than a multiple of 256), two and three chunks of K, the last token block not full, columns of
-# one width and of two.  Sampled rows (the first, the last, tile edges) against the oracle.
-@pytest.mark.gpu
 @pytest.mark.parametrize("bits", [2, 3, 4])
-def test_every_wide_tile(bits):
+def test_layers_for_every_wide_tile(bits):
+    assert sorted(_shapes(bits)) == sorted((tile, odd) for tile in TILES for odd in ((0, 1) if tile[0] < 2 else (0,)))
+
+
+# Sampled rows (the first, the last, tile edges) against the oracle, fp16 activations and INT8 codes; every output written.
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_every_wide_tile(bits, tile):
     import torch
-    found = _shapes(bits)
-    assert {f for f, _, _ in found} == {0, 1, 2}
-    for key, (N, K, M) in sorted(found.items()):
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256       # (the plan's)
+    for key, (N, K, M) in sorted(_shapes(bits).items()):
+        if key[0] != tile:
+            continue
+        print(bits, key, N, K, M, flush=True)
         layer = synth.make_layer_uniform(N, K, bits, M, seed=N + K + M)
-        packed, lut = lcd.lcd_pack_indices(to_dev(layer["idx"]), bits), lcd.lcd_build_lut(to_dev(layer["codebook"]), bits)
-        y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
-        lcd.lcd_lut_gemm(packed, lut, to_dev(layer["x"]), to_dev(layer["s"]), N, bits, y=y)
-        y = y.cpu().numpy()
-        assert np.isfinite(y).all(), key
+        dev = lcd.lcd_pack_indices(to_dev(layer["idx"]), bits), lcd.lcd_build_lut(to_dev(layer["codebook"]), bits), to_dev(layer["x"]), to_dev(layer["s"])
         rows = np.unique(np.r_[0, 31, 32, 63, 64, 127, 128, 255, 256, N - 17, N - 16, N - 1, np.linspace(0, N - 1, 24).astype(int)])
-        assert_parity(y[:, rows], oracle.lut_matmul(layer["codebook"][rows], layer["idx"][rows], layer["x"], layer["s"], bits))
+        args = layer["codebook"][rows], layer["idx"][rows], layer["x"], layer["s"]
+        s_q = float(np.float32(np.quantile(np.abs(layer["x"].astype(np.float64) / layer["s"]), 0.99) / 127.0))
+        for quantised in (False, True):
+            y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+            if quantised:
+                lcd.lcd_lut_gemm_q8(*dev, s_q, N, bits, y=y)
+            else:
+                lcd.lcd_lut_gemm(*dev, N, bits, y=y)
+            assert torch.isfinite(y).all(), (key, quantised)
+            Y = oracle.quantised_lut_matmul(*args, s_q, bits) if quantised else oracle.lut_matmul(*args, bits)
+            assert_parity(y[:, torch.from_numpy(rows).cuda()].cpu().numpy(), Y, 1e-3 if quantised else TOL, (key, quantised))
