@@ -5,6 +5,7 @@ import pytest
 import oracle
 import synth
 import paper_2506_12038_amd as lcd
+from gemm_plan import HALVES, NARROW, SPLIT, WHOLE, choices, launches
 from gpu_common import TOL, assert_parity, check_layer, config_layers, run_hip, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -82,8 +83,8 @@ def test_bucket_passes(bits, M, quantised, tiles, K):
 
 
 # the split kernel behind lcd_lut_gemm: one token either side of a tile, rows that fill half a pair, fewer 128-column units than
-# waves (K = 256), units that do not divide by the waves (K = 1280, 2304), and the first token count of the same
-# layer that the large tiles take
+# waves (K = 256), units that do not divide by the waves (K = 1280, 2304); and layers around the ends of its range, which the narrow (few
+# tokens) or the wide kernel takes (at 2 bits, whose range is shorter, some that are its own at 3 and 4)
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("shape", [(48, 1280, 33), (48, 1280, 64), (48, 2304, 33), (48, 2304, 64), (5136, 256, 65), (1040, 512, 300), (5136, 256, 34), (5136, 1280, 65), (5136, 256, 97), (5136, 256, 200),
                                    (5136, 2304, 300), (8016, 2304, 129), (4096, 4096, 17), (4112, 4096, 32), (28800, 256, 128), (28800, 256, 257), (16384, 256, 128), (16400, 256, 128),
@@ -93,24 +94,13 @@ def test_gemm_split_tile_edges(bits, shape):
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
 
 
-def _narrow_takes(M, N, K, bits):
-    """Layers of the narrow kernel, by the rule of lcd_gemm_plan.h."""
-    if M <= 16 or M > 96:
-        return False
-    if N > 4096:
-        return M <= 64 or 6144 <= N <= 12288
-    if M <= 48:
-        return M <= 32 or K <= 2048 or (N > 2048 and (K <= 4096 or bits > 2))
-    return M <= 64 and N >= 2048 and K <= 2048
-
-
 # the narrow kernel: one token either side of a block of 16, every number of blocks; row tiles per workgroup up to, at and past what a
 # variant holds (6, 4, 3) and in more than one pass; fewer chunks than waves, one and several per wave
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("N,K,M", [(4096, 4096, 17), (4096, 4352, 32), (48, 1280, 33), (4112, 256, 33), (4112, 2304, 48), (2064, 512, 49), (12288, 256, 64), (20496, 512, 64), (16400, 2304, 50),
                                    (24592, 256, 47), (32800, 512, 20), (6144, 2304, 65), (6160, 256, 80), (12288, 512, 81), (8208, 4352, 96)])
 def test_gemm_narrow_kernel_edges(bits, N, K, M):
-    assert _narrow_takes(M, N, K, bits) and not (M <= 32 and N * K < 1 << 24)
+    assert launches([(bits, M, [(N, K)])])[0][0] == (NARROW,)
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
 
 
@@ -138,20 +128,6 @@ def test_narrow_kernel_grouped_and_quantised(bits, M):
             assert torch.equal(y, single), (N, q8)
 
 
-def _split_tile_of(N, K, M, bits):
-    """(32-row pairs, 32-token blocks) of the split kernel's tile for one layer, by the rule and the table of lcd_gemm_plan.h."""
-    import math, re, torch
-    from pathlib import Path
-    table = re.findall(r"\{(\d), (\d), ([\d.]+), \{([\d., ]+)\}\}", (Path(lcd.__file__).parent / "csrc" / "lcd_gemm_plan.h").read_text())
-    assert len(table) == 6
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    times = []
-    for pairs, blocks, fixed_us, column_ns in ((int(a), int(b), float(c), [float(v) for v in d.split(",")]) for a, b, c, d in table):
-        wgs = -(-N // (32 * pairs)) * -(-M // (32 * blocks))
-        times.append((math.ceil(wgs / cus) * (fixed_us + 1e-3 * column_ns[bits - 2] * K), pairs, blocks))
-    return min(times, key=lambda t: t[0])[1:]         # (the first of equal times)
-
-
 # every tile of the split kernel at every width, with an uneven number of 128-column units per wave (K = 2304: 18 units on 8
 # waves; K = 1792, for 64 x 32 at 4 bits, which longer rows do not take: 14), so that a wave refills its ring, its packed words
 # and its operands across units; a last row tile in half a pair, a last token block that is not full
@@ -159,25 +135,29 @@ def _split_tile_of(N, K, M, bits):
 @pytest.mark.parametrize("tile", [(1, 1), (1, 2), (2, 1), (2, 2), (2, 3), (2, 4)])
 def test_gemm_every_split_tile(bits, tile):
     rows = [48 + 928 * i for i in range(37)] + [2704]
-    found = [(N, K, M) for K in (2304, 1792) for M in (45, 77, 109, 141, 173, 237) for N in rows
-             if -(-N // 256) * -(-M // 128) <= 64 and not _narrow_takes(M, N, K, bits) and _split_tile_of(N, K, M, bits) == tile]
+    sizes = [(N, K, M) for K in (2304, 1792) for M in (45, 77, 109, 141, 173, 237) for N in rows]
+    plans = launches([(bits, M, [(N, K)]) for N, K, M in sizes])
+    found = [size for size, (kernels, _, _, split) in zip(sizes, plans) if kernels == (SPLIT,) and split == tile]
     assert found
     N, K, M = found[0]
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
 
 
-# the large-tile kernel's last tiles cut in two: the last 2, 6, 16 of an XCD's queue, rows that end in the first
-# half, in the second half and at the end of a tile, and (M = 1, last block) one token in a half's first token blocks
+# the wide kernel on many token blocks: rows that end in a tile's first rows, in its middle and with it, a last token block of 24, 32 and one token
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("shape", [(4112, 256, 2040), (4240, 512, 2048), (8336, 512, 1025), (6144, 256, 1985)])
-def test_gemm_last_tiles_cut_in_two(bits, shape):
+def test_gemm_wide_long_prompts(bits, shape):
     N, K, M = shape
     check_layer(synth.make_layer_uniform(N, K, bits, M, seed=N + K + M), bits, "gemm")
 
 
-def test_gemm_tiles_cut_in_two_on_their_own_only():
-    # tiles that a single call cuts in two and a group does not: the same bits
-    _check_grouped_prefill(3, 2000, [(4112, 256), (4352, 512)])
+# wide layers that take other tiles in a group than on their own, in halves and whole: the same bits
+@pytest.mark.parametrize("M,shapes,kernel", [(387, [(9424, 768), (4784, 768)], HALVES), (579, [(10400, 768), (9888, 768)], WHOLE)])
+def test_gemm_tiles_that_depend_on_the_group(M, shapes, kernel):
+    assert launches([(3, M, shapes)])[0][0] == (kernel, kernel)
+    together, *alone = choices([(int(kernel == WHOLE), 3, M, layers) for layers in (shapes, shapes[:1], shapes[1:])])
+    assert all(tile[:2] != together[:2] for tile in alone)
+    _check_grouped_prefill(3, M, shapes)
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
@@ -343,8 +323,8 @@ def test_grouped_prefill_matches_single_calls_and_oracle(bits, M):
     _check_grouped_prefill(bits, M, [(272, 1024), (1040, 512), (48, 2816), (4112, 256), (16, 4352)])
 
 
-# layers of one call on different kernels: decode and split; split and large tiles (one launch: split tiles of 96 and 128
-# tokens, the large tiles' last round whole and cut in two, layers that end inside a tile of either kind)
+# layers of one call on different kernels: decode and narrow; split and wide, in a launch of their own (129 tokens: five blocks have no tiles for both) and in
+# one (every variant of that launch: test_gpu_mixed_launch.py), layers that end inside a tile of either kind
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("M,shapes", [(20, [(64, 512), (8192, 2048), (4096, 4096), (48, 2816)]),
                                       (129, [(16912, 256), (256, 512), (17040, 256), (4112, 256)]),

@@ -83,7 +83,7 @@ def _hard_columns(K, seed):
 @pytest.mark.parametrize("M", [1, 2, 3, 4, 7, 16, 40, 200, 2100])
 def test_gpu_codes_next_to_half_integers(M):
     # row n reads column n: y = s_q * q, s_q a power of two.  1 to 4 tokens: the bucket kernel's codes; 7: the tokens kernel's (16 at K = 4096: made
-    # ahead); 40: ahead of the narrow kernel; 200 and 2100: ahead of the split and the large tiles.
+    # ahead); 40: ahead of the narrow kernel; 200 and 2100: ahead of the split and the wide tiles.
     import torch
     bits, K = 2, 4096
     codebook = np.zeros((K, 4), dtype=np.float16)
