@@ -23,14 +23,13 @@ FLAGS = [
 ]
 
 
-# The prefill kernels (lcd_gemm*.hip) keep their accumulators in fixed AGPRs through inline assembly: the compiler
+# The prefill kernels (lcd_gemm_*.hip) keep their accumulators in fixed AGPRs through inline assembly: the compiler
 # must not use AGPRs as spill space there.
 # lcd_pack.hip, lcd_gemv.hip: the same for the transformation of one input.
 # lcd_bucket.hip, lcd_tokens.hip, lcd_tokens_mixed.hip: the decode kernels' eleven (twelve) leading arguments (the table of first
 # workgroups or a single layer, the input the layers share, the widths' first workgroups) are preloaded into scalar registers at wave start
 # instead of being read from the argument segment.
-EXTRA = {"lcd_gemm.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
-         "lcd_gemm_split.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
+EXTRA = {"lcd_gemm_split.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_gemm_wide.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_gemm_mixed.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"],
          "lcd_pack.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=10"],

@@ -1,5 +1,5 @@
-// What the two prefill kernels (lcd_gemm.hip, lcd_gemm_split.hip) share: accumulators in fixed registers,
-// codebook tables, LDS helpers.
+// What the wide and the split prefill kernel (lcd_gemm_wide.h, lcd_gemm_split.h) share: accumulators in fixed registers,
+// codebook tables, packed words, LDS helpers.
 #pragma once
 #include <hip/hip_runtime.h>
 #include "lcd_internal.h"
@@ -8,13 +8,11 @@
 
 namespace lcd {
 
-
 // packed weights are read by every token block of the layer: default cache policy (the non-temporal
 // hint of the decode kernels costs 2 % here)
 constexpr int kGemmWeightPolicy = 0;
 
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
-typedef __attribute__((address_space(1))) const uint32_t glb_u32;
 
 // ---- accumulators in fixed accumulation registers ------------------------------------------------
 // The accumulators of a wave (up to 16 of 16 registers each) live in a[0:255] and are touched only by the
@@ -107,6 +105,19 @@ __device__ __forceinline__ void lds_wait()
 {
     asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(N) : "memory");
 }
+template <int N>
+__device__ __forceinline__ void vmem_wait()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+// 16 bytes per lane from LDS, not waited for
+template <int OFFSET>
+__device__ __forceinline__ uint4v lds_read(uint32_t base)
+{
+    uint4v v;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(base), "n"(OFFSET) : "memory");
+    return v;
+}
 __device__ __forceinline__ uint32_t lds_address(const uint8_t *p)
 {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t *)p;
@@ -121,21 +132,32 @@ struct GemmTileRegs {
     uint4v hi4[PAIRS];   // 4 bits: the second plane
 };
 
+// Where a lane's packed words of each pair stand: its row and slot never change (rows past the layer out of range: zeros), the 128-column half
+// travels as the scalar offset.
+template <int PAIRS> struct GemmRows { uint32_t at[PAIRS], slot; };
 template <int BITS, int PAIRS>
-__device__ __forceinline__ void load_gemm_tiles(GemmTileRegs<BITS, PAIRS> &r, __amdgpu_buffer_rsrc_t packed, int t0, int nt,
-                                                int kc, int c, int h, int lane)
+__device__ __forceinline__ GemmRows<PAIRS> gemm_rows(int t0, int nt, int kc, int lane)
 {
     constexpr uint32_t TB = kTileRows * kTileCols * BITS / 8;
-    const int sub = (lane >> 4) & 1, kh = lane >> 5, i = lane & 15;
+    GemmRows<PAIRS> rows;
+    rows.slot = 16 * (lane >> 5) + (lane & 15);
 #pragma unroll
     for (int p = 0; p < PAIRS; ++p) {
-        const int tile = t0 + 2 * p + sub;
-        const uint32_t base = ((uint32_t)tile * (uint32_t)kc + (uint32_t)c) * TB;
-        const int slot = 16 * (2 * h + kh) + i;          // lane slot inside the 16 x 256 tile
-        const bool v = tile < nt;
-        r.lo[p] = __builtin_amdgcn_raw_buffer_load_b128(packed, v ? base + 16 * slot : 0xFFFFFFF0u, 0, kGemmWeightPolicy);
-        if (BITS == 3) r.hi[p] = __builtin_amdgcn_raw_buffer_load_b64(packed, v ? base + 1024 + 8 * slot : 0xFFFFFFF0u, 0, kGemmWeightPolicy);
-        if (BITS == 4) r.hi4[p] = __builtin_amdgcn_raw_buffer_load_b128(packed, v ? base + 1024 + 16 * slot : 0xFFFFFFF0u, 0, kGemmWeightPolicy);
+        const uint32_t tile = t0 + 2 * p + ((lane >> 4) & 1);
+        rows.at[p] = tile < (uint32_t)nt ? tile * (uint32_t)kc * TB + 16 * rows.slot : 0xFFFFFFF0u;
+    }
+    return rows;
+}
+// half h of chunk c
+template <int BITS, int PAIRS>
+__device__ __forceinline__ void load_gemm_words(GemmTileRegs<BITS, PAIRS> &r, __amdgpu_buffer_rsrc_t packed, const GemmRows<PAIRS> &rows, uint32_t c, uint32_t h)
+{
+    const uint32_t o = c * (kTileRows * kTileCols * BITS / 8);
+#pragma unroll
+    for (int p = 0; p < PAIRS; ++p) {
+        r.lo[p] = __builtin_amdgcn_raw_buffer_load_b128(packed, rows.at[p], o + h * 512, kGemmWeightPolicy);
+        if (BITS == 3) r.hi[p] = __builtin_amdgcn_raw_buffer_load_b64(packed, rows.at[p] < 0xFFFFFFF0u ? rows.at[p] - 8 * rows.slot : 0xFFFFFFF0u, o + h * 256 + 1024, kGemmWeightPolicy);
+        if (BITS == 4) r.hi4[p] = __builtin_amdgcn_raw_buffer_load_b128(packed, rows.at[p], o + h * 512 + 1024, kGemmWeightPolicy);
     }
 }
 

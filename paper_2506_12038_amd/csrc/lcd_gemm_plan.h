@@ -63,7 +63,7 @@ inline bool split_takes(int M, int N, int K, int bits)
 }
 
 
-// ---- wide tiles -------------------------------------------------------------------------------------------
+// ---- wide tiles --------------------------------------------------------------------------------------
 // A tile of the wide kernel (lcd_gemm_wide.h) is 256 rows (or 128) x up to 8 blocks of 32 tokens.  The blocks of a call are dealt out to columns of tiles as
 // evenly as they go: `big` columns of `blocks`, then columns of one block less.
 struct WideTiles {
@@ -170,7 +170,14 @@ inline WideTiles choose_wide(bool whole, const LayerSize *layers, int count, int
     return best;
 }
 
-// Which form takes a layer.  They add in different orders, so this looks at the layer and the tokens alone.
+// Which form takes a layer.  They add in different orders, so this looks at the layer and the tokens alone: whole where the model has one such layer
+// and two of them in a launch faster in the product of both, and one layer no more than a tenth slower.  Time over the better form's for a layer on its own
+// / three alike in a call, smoothing included, mean of 324 sizes (129 to 2048 tokens, 1024 to 28672 rows, K = 1024 to 11008, 2, 3 and 4 bits): this rule 1.002 / 1.035 (at
+// most 1.10 / 1.29), without the tenth 1.001 / 1.040, halves always 1.022 / 1.060, whole wherever there are five blocks 1.30 / 1.033.  Whole / halves, us:
+//   4096 x 4096    2048 tokens, 3 bits  68.6/66.8, three 173/180      1500 tokens, 4 bits  66.8/62.1, three 153/169
+//   11008 x 4096    333 tokens, 2 bits  58.7/36.3, three 116/93       2048 tokens, 3 bits 160/168, three 456/497
+//   4096 x 11008   1500 tokens, 4 bits 164/150, three 390/427         2048 tokens, 3 bits 172/165, three 446/454
+//   8192 x 8192     333 tokens, 4 bits 129/60, three 151/172          2048 tokens, 4 bits 232/267, three 659/765
 inline bool whole_takes(int M, int N, int K, int bits)
 {
     const LayerSize pair[2] = {{N, K}, {N, K}};

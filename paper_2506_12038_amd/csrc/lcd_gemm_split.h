@@ -1,5 +1,4 @@
-// The split prefill kernel's workgroup: token counts whose 256 x 128 output tiles would leave compute units idle (gfx950):
-// the split kernel.
+// The split prefill kernel's workgroup (gfx950): layers of so few outputs that larger tiles would leave compute units idle.
 //
 // Output tile per workgroup: 32 or 64 rows x 32..128 tokens; its 8 waves all own the whole tile and
 // split K: wave w takes the 128-column halves w, w + 8, ... of the chunks.  As in the wide kernel the
@@ -13,7 +12,7 @@
 // What bounds it: the activations' way from L2 into LDS (every wave reads its own: 2 bytes per token and
 // column and workgroup, 75..98 GB/s per compute unit), with 32 tokens x 64 rows the dequantiser; around it about 2 us
 // of start-up and epilogue per workgroup and about 4 us of smoothing launch per call.  That is why the tile is
-// as small as fills the compute units.  Measured against 256 x 128 tiles (16..86 workgroups on these), per call: 11008 x 4096,
+// as small as fills the compute units.  Measured against tiles of 256 x 128 (16..86 workgroups on these; another kernel), per call: 11008 x 4096,
 // 4 bits, 100 tokens 57 -> 22 us; 7B block (q, k, v | o | gate, up | down), 2 bits and INT8 codes, 333 tokens
 // 298 -> 185 us.  Rings of 5 or 6 k-steps instead of 4 and tiles of 128 rows x 64..128 tokens whose activations all waves share gained nothing
 // over the range (the latter 1.2 to 1.3 on some groups, 0.66 to 1 on the others and on single layers).
@@ -36,19 +35,6 @@ constexpr size_t split_lds_bytes()
     const size_t ring = (size_t)kSplitWaves * split_ring<PAIRS, TBLK>() * TBLK * 1024;
     const size_t parts = (size_t)2 * kSplitWaves * split_part_bytes<PAIRS>();
     return ring > parts ? ring : parts;
-}
-
-template <int N>
-__device__ __forceinline__ void vmem_wait()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-template <int OFFSET>
-__device__ __forceinline__ uint4v ring_read(uint32_t base)
-{
-    uint4v v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(base), "n"(OFFSET) : "memory");
-    return v;
 }
 
 // 1 KiB (16 bytes per lane) from byte `offset` + OFFSET of a buffer to the LDS bytes at `to`.  The instruction adds its own
@@ -104,24 +90,8 @@ __device__ __forceinline__ void split_workgroup(const GemmBatch &batch, uint32_t
             copy_block<(j & 3) * 1024>(xs, to + ((j % RING) * TBLK + b) * 1024, lane * 16, src + block_at[b] + (j & 4) * 1024);
     };
 
-    // Packed words of unit u: the lane's row and slot never change (kept, with rows past the layer out of range: zeros), the unit
-    // travels as the scalar offset.
-    uint32_t row_at[PAIRS];
-    const uint32_t slot = 16 * (lane >> 5) + (lane & 15);
-#pragma unroll
-    for (int p = 0; p < PAIRS; ++p) {
-        const uint32_t tile = t0 + 2 * p + ((lane >> 4) & 1);
-        row_at[p] = tile < (uint32_t)nt ? tile * (uint32_t)kc * TB + 16 * slot : 0xFFFFFFF0u;
-    }
-    auto load_words = [&](GemmTileRegs<BITS, PAIRS> &r, int u) __attribute__((always_inline)) {
-        const uint32_t o = (uint32_t)(u >> 1) * TB, half = u & 1;
-#pragma unroll
-        for (int p = 0; p < PAIRS; ++p) {
-            r.lo[p] = __builtin_amdgcn_raw_buffer_load_b128(packed, row_at[p], o + half * 512, kGemmWeightPolicy);
-            if (BITS == 3) r.hi[p] = __builtin_amdgcn_raw_buffer_load_b64(packed, row_at[p] < 0xFFFFFFF0u ? row_at[p] - 8 * slot : 0xFFFFFFF0u, o + half * 256 + 1024, kGemmWeightPolicy);
-            if (BITS == 4) r.hi4[p] = __builtin_amdgcn_raw_buffer_load_b128(packed, row_at[p], o + half * 512 + 1024, kGemmWeightPolicy);
-        }
-    };
+    const GemmRows<PAIRS> rows = gemm_rows<BITS, PAIRS>(t0, nt, kc, lane);
+    auto load_words = [&](GemmTileRegs<BITS, PAIRS> &r, int u) __attribute__((always_inline)) { load_gemm_words<BITS>(r, packed, rows, (uint32_t)(u >> 1), u & 1); };
 
     // 4 bits, 64 rows: no registers for two units' words; words 0, 1 and words 2, 3 of the next unit are loaded when
     // the present unit's have been decoded
@@ -131,8 +101,8 @@ __device__ __forceinline__ void split_workgroup(const GemmBatch &batch, uint32_t
         const uint32_t o = (uint32_t)(u >> 1) * TB + (u & 1) * 512 + 8 * H;
 #pragma unroll
         for (int p = 0; p < PAIRS; ++p) {
-            const uint2v a = __builtin_amdgcn_raw_buffer_load_b64(packed, row_at[p], o, kGemmWeightPolicy);
-            const uint2v b = __builtin_amdgcn_raw_buffer_load_b64(packed, row_at[p], o + 1024, kGemmWeightPolicy);
+            const uint2v a = __builtin_amdgcn_raw_buffer_load_b64(packed, rows.at[p], o, kGemmWeightPolicy);
+            const uint2v b = __builtin_amdgcn_raw_buffer_load_b64(packed, rows.at[p], o + 1024, kGemmWeightPolicy);
             r.lo[p][2 * H] = a[0]; r.lo[p][2 * H + 1] = a[1];
             r.hi4[p][2 * H] = b[0]; r.hi4[p][2 * H + 1] = b[1];
         }
@@ -167,7 +137,7 @@ __device__ __forceinline__ void split_workgroup(const GemmBatch &batch, uint32_t
                 // the first read of k-step ja: its copy must have landed (copies land in order; loads of packed words that
                 // were issued in between only make the wait stricter)
                 if constexpr (ahead % TBLK == 0) vmem_wait<(issued - ja) * TBLK>();
-                window[ahead & 3] = ring_read<((ja % RING) * TBLK + ahead % TBLK) * 1024>(ring_base);
+                window[ahead & 3] = lds_read<((ja % RING) * TBLK + ahead % TBLK) * 1024>(ring_base);
             }
             lds_wait<(LAST && STEPS - 1 - f < 3) ? STEPS - 1 - f : 3>();
             __builtin_amdgcn_sched_barrier(0);
@@ -228,9 +198,9 @@ __device__ __forceinline__ void split_workgroup(const GemmBatch &batch, uint32_t
             else decode_word<BITS, 0>(r0.lo[p][0], hb[p], tb[p], wa.op[p][0], wa.op[p][1]);
         }
         vmem_wait<(RING - 1 - 2 / TBLK) * TBLK>();
-        window[0] = ring_read<0>(ring_base);
-        window[1] = ring_read<1024>(ring_base);
-        window[2] = ring_read<2048>(ring_base);
+        window[0] = lds_read<0>(ring_base);
+        window[1] = lds_read<1024>(ring_base);
+        window[2] = lds_read<2048>(ring_base);
         int u = wave;
         if constexpr (HALVES) {
             for (; u + kSplitWaves < units; u += kSplitWaves) unit(std::false_type{}, r0, r0, u);

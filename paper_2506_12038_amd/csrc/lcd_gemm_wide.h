@@ -13,7 +13,8 @@
 //
 // Ring: 16 k-steps (two units of 8) of T KiB per half.  A quarter is 4 k-steps; while quarter i is multiplied, quarter i + 2 is copied into the
 // place of quarter i - 2.  One barrier per quarter, AHEAD steps before its first read, so that no wave runs out of operands at it; copies have two quarters to
-// land and the wait in front of the barrier leaves the newer quarter's under way.  (The copies are buffer loads: behind global loads to LDS
+// land and the wait in front of the barrier leaves the newest T loads under way: the newer quarter's copies, or, at the second barrier of a unit, the next packed
+// words' loads (1 to 4, asked for after those copies) and as many fewer of the copies.  (The copies are buffer loads: behind global loads to LDS
 // the compiler waits for every load under way wherever packed words are used.)  Every matrix instruction is followed by a share of the next packed
 // word's dequantisation.
 //
@@ -28,19 +29,6 @@
 
 namespace lcd {
 
-template <int N>
-__device__ __forceinline__ void wide_vmem_wait()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-template <int OFFSET>
-__device__ __forceinline__ uint4v wide_read(uint32_t base)
-{
-    uint4v v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(base), "n"(OFFSET) : "memory");
-    return v;
-}
-
 // 1 KiB (16 bytes per lane) from byte lane_offset + offset of a buffer to LDS
 __device__ __forceinline__ void copy_kib(__amdgpu_buffer_rsrc_t from, uint32_t to, uint32_t lane_offset, uint32_t offset)
 {
@@ -50,8 +38,9 @@ __device__ __forceinline__ void copy_kib(__amdgpu_buffer_rsrc_t from, uint32_t t
 constexpr int kWideOutStride = 64 * 2 + 16;     // bytes of a token's 64 rows in the output stage (16-byte aligned, spreads the banks)
 template <int T, int SPLIT, int PAIRS> constexpr size_t wide_lds_bytes()
 {
-    const size_t ring = (size_t)SPLIT * 16 * T * 1024, out = (size_t)4 * SPLIT * 2 * 32 * kWideOutStride, sums = SPLIT == 2 ? (size_t)4 * PAIRS * T * 4096 : 0;
-    return ring > out ? (ring > sums ? ring : sums) : (out > sums ? out : sums);
+    // whole: the output stage, two blocks per wave; halves: the sums that the waves of a row group hand over, which the output is staged in
+    const size_t ring = (size_t)SPLIT * 16 * T * 1024, after = SPLIT == 1 ? (size_t)4 * 2 * 32 * kWideOutStride : (size_t)4 * 2 * (PAIRS == 2 ? T : (T + 1) / 2) * 4096;
+    return ring > after ? ring : after;
 }
 
 // One output tile: tokens [32 tb0, 32 (tb0 + T)), rows [128 PAIRS bx, + 128 PAIRS).  SPLIT 2: K in halves.  The blocks all lie inside the padded tokens.
@@ -86,22 +75,8 @@ __device__ __forceinline__ void wide_tile(const uint8_t *__restrict__ packed_, c
         copy_kib(src, copy_to + decltype(SLOT_)::value * (4 * T * 1024) + b * 1024, copy_from, decltype(AT_)::value + b * (16 * 1024));
     };
 
-    uint32_t row_at[PAIRS];
-    const uint32_t slot = 16 * (lane >> 5) + (lane & 15);
-#pragma unroll
-    for (int p = 0; p < PAIRS; ++p) {
-        const uint32_t tile = t0 + 2 * p + ((lane >> 4) & 1);
-        row_at[p] = tile < (uint32_t)nt ? tile * (uint32_t)kc * TB + 16 * slot : 0xFFFFFFF0u;
-    }
-    auto load_words = [&](GemmTileRegs<BITS, PAIRS> &r, int c, int h) __attribute__((always_inline)) {
-        const uint32_t o = (uint32_t)c * TB;
-#pragma unroll
-        for (int p = 0; p < PAIRS; ++p) {
-            r.lo[p] = __builtin_amdgcn_raw_buffer_load_b128(packed, row_at[p], o + h * 512, kGemmWeightPolicy);
-            if (BITS == 3) r.hi[p] = __builtin_amdgcn_raw_buffer_load_b64(packed, row_at[p] < 0xFFFFFFF0u ? row_at[p] - 8 * slot : 0xFFFFFFF0u, o + h * 256 + 1024, kGemmWeightPolicy);
-            if (BITS == 4) r.hi4[p] = __builtin_amdgcn_raw_buffer_load_b128(packed, row_at[p], o + h * 512 + 1024, kGemmWeightPolicy);
-        }
-    };
+    const GemmRows<PAIRS> rows = gemm_rows<BITS, PAIRS>(t0, nt, kc, lane);
+    auto load_words = [&](GemmTileRegs<BITS, PAIRS> &r, int c, int h) __attribute__((always_inline)) { load_gemm_words<BITS>(r, packed, rows, (uint32_t)c, h); };
     using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>; using I3 = std::integral_constant<int, 3>;
 
@@ -133,12 +108,12 @@ __device__ __forceinline__ void wide_tile(const uint8_t *__restrict__ packed_, c
         if constexpr (BITS == 4) decode_word4(r0.lo[p][0], r0.hi4[p][0], tb[p], wa.op[p][0], wa.op[p][1]);
         else decode_word<BITS, 0>(r0.lo[p][0], hb[p], tb[p], wa.op[p][0], wa.op[p][1]);
     }
-    wide_vmem_wait<T>();
+    vmem_wait<T>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     uint4v window[WIN];
     const uint32_t base[2] = {ring + lane * 16, ring + lane * 16 + 8 * T * 1024};
-    unrolled<AHEAD>([&](auto i) __attribute__((always_inline)) { window[decltype(i)::value] = wide_read<decltype(i)::value * 1024>(base[0]); });
+    unrolled<AHEAD>([&](auto i) __attribute__((always_inline)) { window[decltype(i)::value] = lds_read<decltype(i)::value * 1024>(base[0]); });
 
     // One packed word per pair: two k-steps.  U: parity of the unit (buffer half), D: word, DN: the word of rn decoded meanwhile.
     // The first and the third word copy the first and second half of the next unit's activations, which stand in chunk `src`.
@@ -173,11 +148,11 @@ __device__ __forceinline__ void wide_tile(const uint8_t *__restrict__ packed_, c
         unrolled<WSTEPS>([&](auto st_) __attribute__((always_inline)) {
             constexpr int st = decltype(st_)::value, f = D * WSTEPS + st, j = f / T, blk = f % T, fa = f + AHEAD;
             if constexpr (fa == 4 * T || fa == 8 * T) {
-                wide_vmem_wait<T>();                  // this wave's copies of the next quarter have landed ...
+                vmem_wait<T>();                  // this wave's copies of the next quarter have landed ...
                 __builtin_amdgcn_s_barrier();      // ... and everybody else's
                 asm volatile("" ::: "memory");
             }
-            window[fa % WIN] = fa < 8 * T ? wide_read<(fa < 8 * T ? fa : 0) * 1024>(base[U]) : wide_read<(fa < 8 * T ? 0 : fa - 8 * T) * 1024>(base[U ^ 1]);
+            window[fa % WIN] = fa < 8 * T ? lds_read<(fa < 8 * T ? fa : 0) * 1024>(base[U]) : lds_read<(fa < 8 * T ? 0 : fa - 8 * T) * 1024>(base[U ^ 1]);
             lds_wait<AHEAD>();
             __builtin_amdgcn_sched_barrier(0);
             mfma_acc<blk, false>(cur.op[0][j & 1], window[f % WIN]);
