@@ -160,7 +160,7 @@ class LayerSet:
             return "gemm_narrow_kernel or gemm_split_kernel, by layer (beyond %d such tiles gemm_wide_kernel)" % most
         if min(tiles) > most:
             return "gemm_wide_kernel"
-        return "gemm_split_kernel" if max(tiles) <= most else "gemm_split_kernel or gemm_wide_kernel, by layer (one gemm_mixed_kernel launch for both)"
+        return "gemm_split_kernel" if max(tiles) <= most else "gemm_split_kernel or gemm_wide_kernel, by layer (gemm_mixed_kernel where one launch takes both)"
 
     def block_step(self, replica):
         """One decode step in dependency order: one grouped launch per stage."""

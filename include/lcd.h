@@ -244,7 +244,8 @@ lcd_status lcd_lut_gemv_q8_grouped(const lcd_gemv_problem *problems /*HOST*/, co
 /* ---- grouped prefill: several independent layers in few launches --------------------------- *
  *
  * The same product as lcd_lut_gemm for `count` (1..16) layers with one token count M >= 1 and one
- * index width: one smoothing launch for all layers, then one matrix launch whose workgroups take
+ * index width: one smoothing launch for all layers, then one to three matrix launches, by the kernels that
+ * lcd_lut_gemm gives the layers to, whose workgroups take
  * the layers' output tiles one layer after the other (those with the largest K first), so that
  * the compute units the tail of one layer leaves idle start on the next.  Layers that lcd_lut_gemm gives to the
  * decode kernel (all with up to 16 tokens, small ones with up to 32) go out ahead as one decode call, of one or two

@@ -18,11 +18,11 @@
 // the compiler waits for every load under way wherever packed words are used.)  Every matrix instruction is followed by a share of the next packed
 // word's dequantisation.
 //
-// What bounds it: the power management.  8192 x 8192, 8192 tokens, T = 8: matrix pipe busy 85 to 87 % of a workgroup's cycles at 1.53 GHz; with two wait states per matrix
-// instruction and the dequantiser in one place per step 77 % at 1.68 GHz, the same time.  So fewer instructions per product count: 3 bits, 8192 tokens, tiles
+// What bounds it: the power management.  8192 x 8192, 8192 tokens, T = 8: matrix pipe busy 85 % of the cycles, at 1.40 GHz (counter run, 878 us); with two wait states per
+// matrix instruction and the dequantiser in one place per step less of them at a higher clock, the same time.  So fewer instructions per product count: 3 bits, 8192 tokens, tiles
 // of 256 x 128 with two waves of 64 x 128 per SIMD as before 945 us, whole, T = 4, 6, 8 978, 930, 840 us (1.31 PFLOP/s); 2 bits 875 -> 800, 4 bits 1065 -> 868.
-// Tiles of 128 x 256 in halves (same registers, twice the copies) 946 us.  Whole calls against the large-tile and the split kernel before it, 7B block, 2048
-// tokens, 3 bits 802 -> 743 us; 333 tokens of codes, 2 bits 183 -> 170; by layer: beside split_takes and in lcd_gemm_plan.h.
+// Tiles of 128 x 256 in halves (same registers, twice the copies) 946 us.  Whole calls against the large-tile and the split kernel before it, 7B block in four
+// calls, 2048 tokens, 3 bits 806 -> 746 us; 333 tokens of codes, 2 bits 193 -> 177 (both sides on one box); by layer: beside split_takes and in lcd_gemm_plan.h.
 #pragma once
 #include <type_traits>
 #include "lcd_gemm_common.h"
